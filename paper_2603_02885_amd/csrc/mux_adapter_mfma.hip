@@ -2,8 +2,7 @@
 // activation matrix once from HBM and are bound by that stream; the MFMA only keeps the
 // arithmetic (r FLOP per byte) off the vector ALUs.
 //
-//   down:  Out[T,RP] = s_t * In[T,C] P_t^T      S1: In = X,  P_t^T = A_t as it is ([K][r], ranks that are multiples
-//                                               of 8) or P_t = A_t^T from the transposed region ([r][K])
+//   down:  Out[T,RP] = s_t * In[T,C] A_t        S1: In = X; rows of A_t in whole 16-byte pieces (see rank_pieces)
 //   s4:    one pass over dY for both of its products (the adapter's backward is computed "in a fused manner",
 //          section 3.2): per (row group, 512-column slab) the slab's share of dY B_t^T (summed over the slabs and scaled
 //          by gs_reduce -> Gs[T,RP]) and the row group's share of Hs^T dY (summed over the row groups by reduce -> dB_t)
@@ -65,13 +64,12 @@ __device__ __forceinline__ uint32_t step_bits(const GroupBits& g, int s) {
 // loads that cover whole 128-byte lines (8 rows x 128 B per wave instruction: rows of 64 B move at half the rate
 // on this memory system), two slabs ahead in registers, pass through a wave-private LDS region in their natural
 // layout and come back in the 16x16x32 MFMA operand layout.  No workgroup barrier in the loop.  The partial sums
-// of the waves are combined through LDS in a fixed order.
-//   DOWN_X     LoRA items: Out = s_t X A_t; rows of other kinds: zero.  NAT: A_t is read as it is, [K][r] with r a
-//              multiple of 8 -- the 64 rows of a slab are one contiguous run of 128 r bytes, laid into LDS row by row
-//              and read back with the contraction index contiguous through ds_read_b64_tr_b16; else P_t = A_t^T from
-//              the transposed region.
-//   DOWN_TUNE  TUNING items only (other rows are left alone): u = z D_t with z from the saved compact rows and
-//              P_t = D_t^T from the transposed region; U2 = u, Out = s_t gelu(u)
+// of the waves are combined through LDS in a fixed order.  A_t [C][r] is read in rows of rank_pieces(r) 16-byte
+// pieces: the 64 rows of a slab are one contiguous run, laid into LDS row by row and read back with the contraction
+// index contiguous through ds_read_b64_tr_b16.
+//   DOWN_X     LoRA items: Out = s_t X A_t; rows of other kinds: zero.
+//   DOWN_TUNE  TUNING items only (other rows are left alone): u = z D_t with z from the saved compact rows;
+//              U2 = u, Out = s_t gelu(u)
 // The work item and the validity bits of its rows come from two lists whose offsets are launch arguments, so the
 // first loads of X wait for one memory latency, not for a chain of them.
 enum : int { DOWN_X = 0, DOWN_TUNE = 2 };
@@ -79,7 +77,6 @@ struct DownParams {
   const int32_t* dtab;
   const bf16_t* In;    // [T, C]  (DOWN_TUNE: [z_rows, C], rows numbered like the saved x W)
   bf16_t* Out;         // [T, RP]
-  const bf16_t* AT;    // base of the transposed region (null with NAT)
   bf16_t* U2;          // [T, RP] pre-activations of the TUNING rows: written by DOWN_TUNE
   int C, RP, mode;
   int items_off, bits_off;   // word offsets in dtab: 64-row items, and two words of row-validity bits per item
@@ -93,11 +90,11 @@ __device__ __forceinline__ float gelu_slope_f(float u) {
 
 constexpr int GP = 72;   // LDS row pitch in elements (144 B): 16 consecutive rows of one 16-byte piece hit 64 different banks
 
-template <int NJM, int NWV, int DEPTH, bool NAT>
+template <int NJM, int NWV, int DEPTH>
 __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
   constexpr int ROWS = 32, NTHR = 64 * NWV;
-  constexpr int PP = NJM * 16 + 8;                              // NAT: LDS pitch of the [64][r] slab of A_t (elements)
-  constexpr int PSLAB = NAT ? 64 * PP : NJM * 16 * GP;
+  constexpr int PP = NJM * 16 + 8;                              // LDS pitch of the [64][r] slab of A_t (elements)
+  constexpr int PSLAB = 64 * PP;
   constexpr int SLAB = ROWS * GP + PSLAB;                      // elements per wave: In slab, then P slab
   constexpr int REDW = NJM * 16 * (ROWS + 4) * 2;              // the same region later holds the partial sums (floats)
   constexpr int REGION = SLAB > REDW ? SLAB : REDW;
@@ -124,9 +121,7 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
   }
   const DevTask tk = get_task(p.tasks, it.task);
   const int rank = tk.rank, NJ = (rank + 15) >> 4;
-  const bf16_t* P = NAT ? (const bf16_t*)tk.A : p.AT + tk.at_off;
-  const int prow = NJ * 16;                          // rows that exist in a transposed P
-
+  const int ppr = rank_pieces(rank);                 // 16-byte pieces in a row of A_t
   const int per = ((p.C + NWV - 1) / NWV + 63) & ~63;
   const int cbeg = wave * per, cend = cbeg + per < p.C ? cbeg + per : p.C;
   bf16_t* sX = lds[wave];
@@ -134,7 +129,7 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
 
   const size_t in_row0 = p.mode == DOWN_TUNE ? (size_t)(tk.zrow0 + row0 - tk.row_begin) : (size_t)row0;
   const rsrc_t rIn = make_rsrc(p.In + in_row0 * p.C, (uint32_t)nr * (uint32_t)p.C * 2u);
-  const rsrc_t rP = make_rsrc(P, (NAT ? (uint32_t)p.C * (uint32_t)rank : (uint32_t)prow * (uint32_t)p.C) * 2u);
+  const rsrc_t rP = make_rsrc(tk.A, (uint32_t)p.C * (uint32_t)ppr * 16u);
   // one wave instruction: 8 rows x 128 B; lane -> row lane/8 (+ 8 q), 16-byte piece lane%8
   const int b_row = lane >> 3, b_pc = (lane & 7) * 8;
   uint32_t x_off[4], p_off[2 * NJM];
@@ -144,25 +139,15 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
     const int m = b_row + 8 * q;
     x_off[q] = (m < nr && ((vbits >> m) & 1u)) ? ((uint32_t)m * (uint32_t)p.C + (uint32_t)b_pc) * 2u : OOB;
   }
-  if (NAT) {
-    // the [64][rank] slab is 8 rank 16-byte pieces in a row; piece -> (row, piece of the row)
-    const int ppr = rank >> 3;
+  // the slab is 64 ppr 16-byte pieces in a row; piece -> (row, piece of the row)
 #pragma unroll
-    for (int q = 0; q < 2 * NJM; ++q) {
-      const int piece = q * 64 + lane;
-      p_off[q] = q < ppr ? (uint32_t)piece * 16u : OOB;
-      p_lds[q] = (piece / ppr) * PP + (piece % ppr) * 8;
-    }
-    // columns of the LDS slab beyond the rank are never written: they read as zero
-    for (int e = lane; e < 64 * (PP / 8); e += 64) *(u32x4*)(sP + (e / (PP / 8)) * PP + (e % (PP / 8)) * 8) = (u32x4){0u, 0u, 0u, 0u};
-  } else {
-#pragma unroll
-    for (int q = 0; q < 2 * NJM; ++q) {
-      const int j = b_row + 8 * q;
-      p_off[q] = (q < 2 * NJ && j < prow) ? ((uint32_t)j * (uint32_t)p.C + (uint32_t)b_pc) * 2u : OOB;
-      p_lds[q] = j * GP + b_pc;
-    }
+  for (int q = 0; q < 2 * NJM; ++q) {
+    const int piece = q * 64 + lane;
+    p_off[q] = q < ppr ? (uint32_t)piece * 16u : OOB;
+    p_lds[q] = (piece / ppr) * PP + (piece % ppr) * 8;
   }
+  // columns of the LDS slab beyond the last piece are never written: they read as zero
+  for (int e = lane; e < 64 * (PP / 8); e += 64) *(u32x4*)(sP + (e / (PP / 8)) * PP + (e % (PP / 8)) * 8) = (u32x4){0u, 0u, 0u, 0u};
 
   f32x4 acc[2][NJM];
 #pragma unroll
@@ -177,17 +162,17 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
   auto load = [&](int c, int buf) {          // a slab that starts past the end of this wave's share reads as zeros
     const bool in = c < cend;                 // the share ends on a multiple of 64 or at C, where the buffer ends
     const uint32_t kx = (c + b_pc < cend) ? (uint32_t)c * 2u : OOB;     // OOB + OOB wraps into range: mask on k only
-    const uint32_t kp = in ? (NAT ? (uint32_t)c * (uint32_t)rank * 2u : (uint32_t)c * 2u) : OOB;
+    const uint32_t kp = in ? (uint32_t)c * (uint32_t)ppr * 16u : OOB;
 #pragma unroll
     for (int q = 0; q < 4; ++q) gx[buf][q] = buf_load16(rIn, (x_off[q] == OOB || kx == OOB) ? OOB : x_off[q] + kx);
 #pragma unroll
     for (int q = 0; q < 2 * NJM; ++q) {
-      const bool ok = p_off[q] != OOB && kp != OOB && (NAT || c + b_pc < cend);
+      const bool ok = p_off[q] != OOB && kp != OOB;
       gp[buf][q] = buf_load16(rP, ok ? p_off[q] + kp : OOB);
     }
   };
   const int i = lane & 15, g = lane >> 4;
-  const int tr_off = (8 * g + (i >> 2)) * PP + 4 * (i & 3);     // NAT: transposed reads of the [k][j] slab
+  const int tr_off = (8 * g + (i >> 2)) * PP + 4 * (i & 3);     // transposed reads of the [k][j] slab
   // DEPTH slabs in flight while one is multiplied
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) {
@@ -202,7 +187,7 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
         for (int q = 0; q < 4; ++q) *(u32x4*)(sX + (b_row + 8 * q) * GP + b_pc) = gx[buf][q];
 #pragma unroll
         for (int q = 0; q < 2 * NJM; ++q)
-          if (NAT ? (q * 8 < rank) : (q < 2 * NJ)) *(u32x4*)(sP + p_lds[q]) = gp[buf][q];
+          if (q < ppr) *(u32x4*)(sP + p_lds[q]) = gp[buf][q];
         load(c + 64 * buf + 64 * DEPTH, buf);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -214,13 +199,9 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
 #pragma unroll
           for (int jt = 0; jt < NJM; ++jt)
             if (jt < NJ) {
-              if (NAT) {
-                const bf16x4 lo = lds_read_tr(sP + s * 32 * PP + tr_off + jt * 16);
-                const bf16x4 hi = lds_read_tr(sP + s * 32 * PP + tr_off + 4 * PP + jt * 16);
-                b[jt][s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-              } else {
-                b[jt][s] = *(const bf16x8*)(sP + (jt * 16 + i) * GP + s * 32 + 8 * g);
-              }
+              const bf16x4 lo = lds_read_tr(sP + s * 32 * PP + tr_off + jt * 16);
+              const bf16x4 hi = lds_read_tr(sP + s * 32 * PP + tr_off + 4 * PP + jt * 16);
+              b[jt][s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             }
         }
 #pragma unroll
@@ -263,20 +244,15 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
   }
 }
 
-template <bool NAT>
-void launch_down_t(const CallCtx& c, const char* name, const DownParams& p) {
-  const unsigned items = (unsigned)c.st->items[TS64].size();
-  // eight waves split the contraction (four for ranks above 32, whose LDS regions are larger); two slabs in flight
-  if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2, NAT>), dim3(items * 2), dim3(512), 0, c.stream, p);
-  else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2, NAT>), dim3(items * 2), dim3(512), 0, c.stream, p);
-  else MUX_LAUNCH(name, (k_down<4, 4, 2, NAT>), dim3(items * 2), dim3(256), 0, c.stream, p);
-}
-void launch_down(const CallCtx& c, const char* name, DownParams p, bool natural) {
+void launch_down(const CallCtx& c, const char* name, DownParams p) {
   p.items_off = c.st->dev_image[DH_NITEMS0 + 3 * TS64 + 1];
   p.bits_off = c.st->dev_image[DH_OFF_ITEM_BITS];
   p.tasks = *c.tref;
-  if (natural) launch_down_t<true>(c, name, p);
-  else launch_down_t<false>(c, name, p);
+  const unsigned items = (unsigned)c.st->items[TS64].size();
+  // eight waves split the contraction (four for ranks above 32, whose LDS regions are larger); two slabs in flight
+  if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2>), dim3(items * 2), dim3(512), 0, c.stream, p);
+  else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2>), dim3(items * 2), dim3(512), 0, c.stream, p);
+  else MUX_LAUNCH(name, (k_down<4, 4, 2>), dim3(items * 2), dim3(256), 0, c.stream, p);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -658,19 +634,17 @@ __global__ __launch_bounds__(256) void k_grad(const GradParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Adapter-Tuning: Out = In + Small P for the rows of TUNING items, P = [r][N] as stored (forward: U_t, Y = z + Hs U_t,
-// In = the saved compact z rows, Out = Y; backward: D_t^T from the transposed region, dYs = dY + Gs D_t^T, In = dY,
-// Out = the compact dYs rows).  grid = (64-row items, ceil(N/256)); each wave owns 64 columns: its [r][64] slab of P
-// goes through a wave-private LDS region in natural layout and comes back k-major with ds_read_b64_tr_b16; the
-// products are staged 16 rows at a time in fp32 so that In is read and Out is written in whole 128-byte lines.
+// Adapter-Tuning: Out = In + Small P for the rows of TUNING items (forward: P = U_t [r][N] as stored, Y = z + Hs U_t,
+// In = the saved compact z rows, Out = Y; backward: P = D_t^T, dYs = dY + Gs D_t^T, In = dY, Out = the compact dYs
+// rows).  grid = (64-row items, ceil(N/256)); each wave owns 64 columns: its [r][64] slab of U_t goes through a
+// wave-private LDS region in natural layout and comes back k-major with ds_read_b64_tr_b16; of D_t [N][r] a lane
+// loads the eight consecutive r of one column (a 16-byte piece of a row) straight from memory; the products are staged 16 rows at a time in fp32 so that In is read and Out is written in whole 128-byte lines.
 struct TuneAddParams {
   const int32_t* dtab;
   const bf16_t* In;
   const bf16_t* Small;   // [T, RP]
   bf16_t* Out;
-  const bf16_t* AT;      // backward: base of the transposed region (D_t^T); forward: null (U_t = tk.B)
   int N, RP, backward;
-  int natural;           // backward: D_t [N][r] is read as it is (every rank a multiple of 8), nothing was transposed
   TaskRef tasks;
 };
 
@@ -686,20 +660,17 @@ __global__ __launch_bounds__(256) void k_tune_add(const TuneAddParams p) {
   const int cw0 = blockIdx.y * 256 + wave * 64;
   if (cw0 >= p.N) return;
   const int rank = tk.rank;
-  const bf16_t* P = p.backward ? p.AT + tk.at_off : (const bf16_t*)tk.B;
-  const int prow = p.backward ? ((rank + 15) & ~15) : rank;
   bf16_t* sp = sP[wave];
   float* sc = sC[wave];
 
-  // P slab [NKS*32][64] -> LDS, natural layout; rows beyond the rank read as zero
-  const bool direct = p.backward && p.natural;      // D_t [N][r]: a lane's eight k of one column lie together in memory
-  const rsrc_t rP = make_rsrc(P, (uint32_t)prow * (uint32_t)p.N * 2u);
+  // slab [NKS*32][64] of U_t -> LDS, natural layout; rows beyond the rank read as zero
   const int b_row = lane >> 3, b_pc = (lane & 7) * 8;
-  if (!direct) {
+  if (!p.backward) {
+    const rsrc_t rP = make_rsrc(tk.B, (uint32_t)rank * (uint32_t)p.N * 2u);
 #pragma unroll
     for (int q = 0; q < NKS * 4; ++q) {
       const int j = b_row + 8 * q;
-      const bool ok = j < prow && cw0 + b_pc < p.N;
+      const bool ok = j < rank && cw0 + b_pc < p.N;
       const u32x4 v = buf_load16(rP, ok ? (uint32_t)(((size_t)j * p.N + cw0 + b_pc) * 2) : OOB);
       *(u32x4*)(sp + j * GP + b_pc) = v;
     }
@@ -719,14 +690,15 @@ __global__ __launch_bounds__(256) void k_tune_add(const TuneAddParams p) {
   __builtin_amdgcn_wave_barrier();
   const int tr_off = (8 * g + (i >> 2)) * GP + 4 * (i & 3);
   bf16x8 b[4][NKS];
-  if (direct) {
-    const rsrc_t rD = make_rsrc(tk.A, (uint32_t)p.N * (uint32_t)rank * 2u);
+  if (p.backward) {
+    const uint32_t pitch = 16u * (uint32_t)rank_pieces(rank);       // bytes in a row of D_t
+    const rsrc_t rD = make_rsrc(tk.A, (uint32_t)p.N * pitch);
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) {
         const int col = cw0 + ct * 16 + i, k = ks * 32 + 8 * g;
-        b[ct][ks] = as_bf16x8(buf_load16(rD, (col < p.N && k < rank) ? (uint32_t)(((size_t)col * rank + k) * 2) : OOB));
+        b[ct][ks] = as_bf16x8(buf_load16(rD, (col < p.N && k < rank) ? (uint32_t)col * pitch + (uint32_t)k * 2u : OOB));
       }
   } else {
 #pragma unroll
@@ -962,9 +934,8 @@ size_t adapter_partial_bytes(int K, int N, const mux_segtab* st) { return part_l
 
 mux_status adapter_down_x(const CallCtx& c, const void* X, void* Hs) {
   if (c.st->n_lora == 0) return MUX_OK;
-  // A_t is read as it is when every LoRA rank allows it; else A_t^T was laid into c.AT by the packing kernel of this call
-  DownParams p{c.dtab, (const bf16_t*)X, (bf16_t*)Hs, c.lora_natural ? nullptr : (const bf16_t*)c.AT, nullptr, c.K, c.RP, DOWN_X};
-  launch_down(c, "down_x", p, c.lora_natural);
+  DownParams p{c.dtab, (const bf16_t*)X, (bf16_t*)Hs, nullptr, c.K, c.RP, DOWN_X};
+  launch_down(c, "down_x", p);
   return MUX_OK;
 }
 
@@ -995,11 +966,10 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, voi
   return MUX_OK;
 }
 
-// Adapter-Tuning: Y = z + Hs U_t (forward) or dYs = dY + Gs D_t^T (backward, D_t^T from the transposed region)
+// Adapter-Tuning: Y = z + Hs U_t (forward) or dYs = dY + Gs D_t^T (backward)
 mux_status adapter_tune_add(const CallCtx& c, const void* In, const void* Small, void* Out, int backward) {
   if (c.st->n_tuning == 0) return MUX_OK;
-  TuneAddParams p{c.dtab, (const bf16_t*)In, (const bf16_t*)Small, (bf16_t*)Out, (const bf16_t*)c.AT, c.N, c.RP, backward,
-                  c.tune_natural ? 1 : 0};
+  TuneAddParams p{c.dtab, (const bf16_t*)In, (const bf16_t*)Small, (bf16_t*)Out, c.N, c.RP, backward};
   p.tasks = *c.tref;
   const dim3 grid((unsigned)c.st->items[TS64].size(), (c.N + 255) / 256);
   if (c.RP <= 32) MUX_LAUNCH(backward ? "tune_dz" : "tune_up", (k_tune_add<1>), grid, dim3(256), 0, c.stream, p);
@@ -1007,12 +977,11 @@ mux_status adapter_tune_add(const CallCtx& c, const void* In, const void* Small,
   return MUX_OK;
 }
 
-// Adapter-Tuning forward, after the backbone GEMM saved z = x W: u = z D_t, Hs = s_t gelu(u).  D_t [N, r] is read as it
-// is when every such rank is a multiple of 8; else D_t^T was laid into c.AT by the packing kernel of this call.
+// Adapter-Tuning forward, after the backbone GEMM saved z = x W: u = z D_t, Hs = s_t gelu(u).
 mux_status adapter_down_tune(const CallCtx& c, const void* Z, void* Hs) {
   if (c.st->n_tuning == 0) return MUX_OK;
-  DownParams p{c.dtab, (const bf16_t*)Z, (bf16_t*)Hs, c.tune_natural ? nullptr : (const bf16_t*)c.AT, (bf16_t*)c.U2, c.N, c.RP, DOWN_TUNE};
-  launch_down(c, "tune_down", p, c.tune_natural);
+  DownParams p{c.dtab, (const bf16_t*)Z, (bf16_t*)Hs, (bf16_t*)c.U2, c.N, c.RP, DOWN_TUNE};
+  launch_down(c, "tune_down", p);
   return MUX_OK;
 }
 

@@ -14,33 +14,27 @@ __global__ __launch_bounds__(64) void k_write_tasks(DevTask* __restrict__ out, c
   if (i < count) out[base + i] = tb.t[i];
 }
 
-// A_t^T [round_up(r,16)][K] (zero rows beyond r) of the LoRA tasks whose rank is not a multiple of 8, and D_t^T
-// [round_up(r,16)][N] of the Adapter-Tuning tasks, into the transposed region of the workspace: the down-projection
-// reads these operands with the contraction index contiguous.  Block b handles 64 rows of task b / nkb.
-__global__ __launch_bounds__(256) void k_pack_at(const TaskRef tasks, uint16_t* __restrict__ pack_at, int Kin, int Nout,
-                                                  int only_tuning) {
-  __shared__ uint16_t t[64][66];
-  const int nkb = ((Kin > Nout ? Kin : Nout) + 63) / 64;
-  const int i = blockIdx.x / nkb, k0 = (blockIdx.x % nkb) * 64;
-  const DevTask tk = get_task(tasks, i);
-  // LORA: A_t [K, r]; TUNING: D_t [N, r] (in the same slot); both go out as [round_up(r,16)][rows]
-  if (tk.kind != MUX_ADAPTER_LORA && tk.kind != MUX_ADAPTER_TUNING) return;
-  if (only_tuning && tk.kind != MUX_ADAPTER_TUNING) return;     // the backward pass needs D_t^T only
-  if (tk.at_off < 0) return;                                     // a LoRA task whose A_t is read as it is
-  const int K = tk.kind == MUX_ADAPTER_LORA ? Kin : Nout;
-  if (k0 >= K) return;
-  const int r = tk.rank, rp = (r + 15) & ~15;
-  const uint16_t* A = (const uint16_t*)tk.A;
-  for (int e = threadIdx.x; e < 64 * rp; e += 256) {
-    const int kk = e / rp, j = e % rp;
-    t[j][kk] = (j < r && k0 + kk < K) ? A[(size_t)(k0 + kk) * r + j] : (uint16_t)0;
+// Ranks that are not multiples of 8: A_t [K, r] (Adapter-Tuning: D_t [N, r]) once more with its rows padded to
+// round_up(r, 8) elements (zeros), so that every kernel of the matrix-core path reads rows of whole 16-byte pieces.
+// tk.L is the caller's matrix, tk.A the padded copy in the workspace; one thread per 16-byte piece.  A copy of a few
+// hundred KB, bound by its launch (4 us at 1608 x 12); before it, such ranks sent the whole backward product to a
+// register-staged GEMM at a third of the pipelined one's rate.
+__global__ __launch_bounds__(256) void k_pad_rank(const TaskRef tasks, int K, int N) {
+  const DevTask tk = get_task(tasks, blockIdx.x);
+  if ((tk.kind != MUX_ADAPTER_LORA && tk.kind != MUX_ADAPTER_TUNING) || tk.L == nullptr) return;
+  const int rows = tk.kind == MUX_ADAPTER_LORA ? K : N;
+  const int pieces = rank_pieces(tk.rank);
+  const int e = blockIdx.y * 256 + threadIdx.x;
+  if (e >= rows * pieces) return;
+  const int row = e / pieces, j0 = (e % pieces) * 8;
+  const uint16_t* src = (const uint16_t*)tk.L + (size_t)row * tk.rank;
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int j = j0 + 2 * i;
+    w[i] = (j < tk.rank ? (uint32_t)src[j] : 0u) | (j + 1 < tk.rank ? (uint32_t)src[j + 1] << 16 : 0u);
   }
-  __syncthreads();
-  uint16_t* dst = pack_at + tk.at_off;
-  for (int e = threadIdx.x; e < 64 * rp; e += 256) {
-    const int j = e >> 6, kk = e & 63;
-    if (k0 + kk < K) dst[(size_t)j * K + k0 + kk] = t[j][kk];
-  }
+  *(uint4*)((uint16_t*)tk.A + (size_t)e * 8) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // A table without rows: every task's gradient is zero.  grid = (tasks, blocks over the largest gradient).
@@ -58,6 +52,11 @@ __global__ __launch_bounds__(256) void k_zero_grads(const TaskRef tasks, int K, 
 }
 
 namespace {
+
+// A ranked task whose A_t (D_t) has rows that are no whole number of 16-byte pieces
+inline bool rank_is_padded(const HostTask& ht) {
+  return (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) && (ht.rank & 7) != 0;
+}
 
 struct Layout {
   size_t esz;          // bytes per stored element
@@ -79,8 +78,7 @@ Layout make_layout(const mux_layer_desc* L, const mux_segtab* st) {
   o.g_bytes = o.h_bytes;
   size_t at_elems = 0;
   for (const HostTask& ht : st->tasks)
-    if (ht.kind == MUX_ADAPTER_LORA) at_elems += (size_t)round_up(ht.rank, 16) * L->K;
-    else if (ht.kind == MUX_ADAPTER_TUNING) at_elems += (size_t)round_up(ht.rank, 16) * L->N;
+    if (rank_is_padded(ht)) at_elems += (size_t)round_up(ht.rank, 8) * (ht.kind == MUX_ADAPTER_LORA ? L->K : L->N);
   o.at_bytes = L->dtype == MUX_DT_BF16 ? align256(at_elems * 2) : 0;
   o.part_bytes = L->dtype == MUX_DT_BF16 ? fast_partial_bytes(L->K, L->N, st) : 0;
   o.dys_bytes = (L->dtype == MUX_DT_BF16 || st->n_tuning > 0) ? o.z_bytes : 0;
@@ -161,15 +159,11 @@ mux_status check_hip(const char* fn) {
   return MUX_OK;
 }
 
-// Does the down-projection read this LoRA task's A_t [K, r] as it is (rows of 16-byte pieces), or a transposed copy?
-inline bool lora_a_natural(const HostTask& ht) { return (ht.rank & 7) == 0; }
-
-// The per-call task parameters, laid out on the host.  at_off: element offset of the task's transposed operand in the
-// workspace region, -1 for a LoRA task whose A_t is read as it is.
+// The per-call task parameters, laid out on the host.  `padded` (matrix-core path): where the padded copies of the
+// A_t whose rank is not a multiple of 8 go; null on the plain path, which takes any rank as it is.
 void build_tasks(const mux_layer_desc* L, const mux_segtab* st, void* const* dA, void* const* dB, void* const* dL,
-                 bool fast, int diff_route, bool backward, std::vector<DevTask>& out) {
+                 uint16_t* padded, int diff_route, bool backward, std::vector<DevTask>& out) {
   out.assign((size_t)st->n_tasks, DevTask{});
-  int64_t at_off = 0;
   int slot = 0;         // diff_route 1: index of the next merged weight; 2: element offset of the next packed list
   for (int t = 0; t < st->n_tasks; ++t) {
     const HostTask& ht = st->tasks[t];
@@ -184,7 +178,11 @@ void build_tasks(const mux_layer_desc* L, const mux_segtab* st, void* const* dA,
     d.dL = (kind == MUX_ADAPTER_IA3_OUT && dL) ? (float*)dL[t] : nullptr;
     d.scale = ht.scale; d.kind = kind; d.rank = ht.rank;
     d.row_begin = ht.row_begin; d.row_count = ht.row_count; d.zrow0 = ht.zrow0;
-    d.at_off = at_off;
+    if (padded && rank_is_padded(ht)) {
+      d.L = d.A;                                  // the caller's matrix; k_pad_rank lays its copy out
+      d.A = padded;
+      padded += (size_t)round_up(ht.rank, 8) * (kind == MUX_ADAPTER_LORA ? L->K : L->N);
+    }
     if (kind == MUX_ADAPTER_DIFF) {
       const mux_sparse_mask* m = L->masks[t];
       d.A = m->nnz > 0 ? L->A[t] : nullptr;
@@ -200,20 +198,14 @@ void build_tasks(const mux_layer_desc* L, const mux_segtab* st, void* const* dA,
         d.dL = (float*)(backward ? m->bwd_ent : m->fwd_ent);
       }
     }
-    if (kind == MUX_ADAPTER_LORA) {
-      if (fast && lora_a_natural(ht)) d.at_off = -1;
-      at_off += (int64_t)round_up(ht.rank, 16) * L->K;
-    } else if (kind == MUX_ADAPTER_TUNING) {
-      at_off += (int64_t)round_up(ht.rank, 16) * L->N;
-    }
   }
 }
 
 // Makes the tasks visible to the kernels of the call: by value in `ref` when they fit and no kernel of the call needs
-// the table in memory, else written into the workspace by a small kernel; and lays out the transposed operands when
-// a kernel of the call reads them (pack: 0 no, 1 all of them, 2 only those of the Adapter-Tuning tasks).
+// the table in memory, else written into the workspace by a small kernel; and pads the rows of the A_t that need it
+// (matrix-core path).
 void publish_tasks(const mux_layer_desc* L, const mux_segtab* st, const std::vector<DevTask>& tasks, bool need_table,
-                   DevTask* dtasks, TaskRef& ref, int pack, void* pack_at, hipStream_t stream) {
+                   DevTask* dtasks, TaskRef& ref, bool fast, hipStream_t stream) {
   std::memset(&ref, 0, sizeof(ref));
   if (!need_table && st->n_tasks <= kArgTasks) {
     for (int t = 0; t < st->n_tasks; ++t) ref.arg.t[t] = tasks[t];
@@ -227,22 +219,16 @@ void publish_tasks(const mux_layer_desc* L, const mux_segtab* st, const std::vec
     }
     ref.mem = dtasks;
   }
-  if (pack && pack_at) {
-    const int rows_max = L->K > L->N ? L->K : L->N;
-    MUX_LAUNCH("pack_at", k_pack_at, dim3((unsigned)st->n_tasks * (unsigned)((rows_max + 63) / 64)), dim3(256), 0, stream,
-               ref, (uint16_t*)pack_at, L->K, L->N, pack == 2 ? 1 : 0);
-  }
-}
-
-bool any_packed_lora(const mux_segtab* st) {
-  for (const HostTask& ht : st->tasks)
-    if (ht.kind == MUX_ADAPTER_LORA && !lora_a_natural(ht)) return true;
-  return false;
-}
-bool any_packed_tuning(const mux_segtab* st) {
-  for (const HostTask& ht : st->tasks)
-    if (ht.kind == MUX_ADAPTER_TUNING && (ht.rank & 7) != 0) return true;
-  return false;
+  size_t most = 0;                    // 16-byte pieces of the largest padded copy
+  if (fast)
+    for (const HostTask& ht : st->tasks)
+      if (rank_is_padded(ht)) {
+        const size_t n = (size_t)rank_pieces(ht.rank) * (ht.kind == MUX_ADAPTER_LORA ? L->K : L->N);
+        if (n > most) most = n;
+      }
+  if (most > 0)
+    MUX_LAUNCH("pad_rank", k_pad_rank, dim3((unsigned)st->n_tasks, (unsigned)((most + 255) / 256)), dim3(256), 0, stream,
+               ref, L->K, L->N);
 }
 
 }  // namespace
@@ -269,7 +255,6 @@ CallCtx make_ctx(const mux_layer_desc* layer, const mux_segtab* st, const void* 
   c.st = st;
   c.dtab = (const int32_t*)dev_segtab;
   c.K = layer->K; c.N = layer->N; c.ldw = layer->ldw; c.RP = lo.RP;
-  c.AT = (char*)ws + lo.tasks_bytes + lo.g_bytes;
   c.dYs = (char*)ws + lo.tasks_bytes + lo.g_bytes + lo.at_bytes;
   c.W = layer->W;
   c.stream = stream;
@@ -303,15 +288,13 @@ extern "C" mux_status mux_lora_forward(const mux_layer_desc* layer, const mux_se
   // the matrix-core kernels, unless the storage type, the flag, a shape or a pointer rules them out: then the plain ones
   const bool fast = layer->dtype == MUX_DT_BF16 && !(layer->flags & MUX_LAYER_REFERENCE_KERNELS) &&
                     fast_supported(c, X, Y, H, Z, nullptr, nullptr);
-  c.lora_natural = fast && !any_packed_lora(st);
   if (fast && lo.dp_bytes > 0 && fast_gemm_patches_diff(c, false)) c.diffPack = (char*)ws + lo.ws_bytes - lo.dp_bytes;
   else if (fast && lo.dw_bytes > 0) c.diffW = (char*)ws + lo.ws_bytes - lo.dp_bytes - lo.dw_bytes;
   std::vector<DevTask> tasks;
-  build_tasks(layer, st, nullptr, nullptr, nullptr, c.lora_natural, c.diffPack ? 2 : (c.diffW ? 1 : 0), false, tasks);
+  uint16_t* const padded = fast ? (uint16_t*)((char*)ws + lo.tasks_bytes + lo.g_bytes) : nullptr;
+  build_tasks(layer, st, nullptr, nullptr, nullptr, padded, c.diffPack ? 2 : (c.diffW ? 1 : 0), false, tasks);
   TaskRef tref;
-  c.tune_natural = fast && !any_packed_tuning(st);
-  const int pack = !fast ? 0 : ((st->n_lora > 0 && !c.lora_natural) ? 1 : ((st->n_tuning > 0 && !c.tune_natural) ? 2 : 0));
-  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, pack, c.AT, stream);
+  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, fast && st->T > 0, stream);
   c.tref = &tref;
   c.dtasks = tref.mem;
   mux_status s;
@@ -344,14 +327,13 @@ static mux_status backward_impl(const char* fn, const mux_layer_desc* layer, con
   void* G = (char*)ws + lo.tasks_bytes;
   const bool fast = layer->dtype == MUX_DT_BF16 && !(layer->flags & MUX_LAYER_REFERENCE_KERNELS) &&
                     fast_supported(c, X, dY, dX, G, H, Z);
-  c.lora_natural = fast && !any_packed_lora(st);
   if (fast && lo.dp_bytes > 0 && dX && fast_gemm_patches_diff(c, true)) c.diffPack = (char*)ws + lo.ws_bytes - lo.dp_bytes;
   else if (fast && lo.dw_bytes > 0 && dX) c.diffW = (char*)ws + lo.ws_bytes - lo.dp_bytes - lo.dw_bytes;
   std::vector<DevTask> tasks;
-  build_tasks(layer, st, dA, dB, dL, c.lora_natural, c.diffPack ? 2 : (c.diffW ? 1 : 0), true, tasks);
+  uint16_t* const padded = fast ? (uint16_t*)((char*)ws + lo.tasks_bytes + lo.g_bytes) : nullptr;
+  build_tasks(layer, st, dA, dB, dL, padded, c.diffPack ? 2 : (c.diffW ? 1 : 0), true, tasks);
   TaskRef tref;
-  c.tune_natural = fast && !any_packed_tuning(st);
-  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, (fast && st->n_tuning > 0 && !c.tune_natural) ? 2 : 0, c.AT, stream);
+  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, fast && st->T > 0, stream);
   c.tref = &tref;
   c.dtasks = tref.mem;
   if (st->T == 0) {                 // no rows at all: zero gradients (or leave the accumulators as they are)

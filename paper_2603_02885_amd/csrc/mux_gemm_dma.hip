@@ -8,14 +8,16 @@
 // v_mfma_f32_32x32x16_bf16.
 //   * `buffer_load_dwordx4 ... lds` writes each lane's 16 bytes at LDS base + 16*lane, so a wave
 //     instruction fills 1 KB of a stage.  A masked piece gets an out-of-range offset and lands as zeros.
-//   * K-tiles are 64 deep whenever the contraction length allows: a row of a [rows][64] tile is one whole
-//     128-byte line of X, dY or W.  Measured on this part, the L2 -> LDS path moves half-lines (the 64-byte rows
-//     of a 32-deep tile) at half the rate of whole lines, at every level of the hierarchy, and that rate, not the
-//     matrix cores, was the limit of the 32-deep version.  Two stages of 64 KB; the loads of tile kt+2 go out
-//     right after the barrier that frees the stage of tile kt.  The 32-deep version (four stages, three tiles
-//     in flight) remains for contraction lengths that are multiples of 32 only.
+//   * K-tiles are 64 deep: a row of a [rows][64] tile is one whole 128-byte line of X, dY or W.  Measured on this
+//     part, the L2 -> LDS path moves half-lines (the 64-byte rows of a 32-deep tile) at half the rate of whole
+//     lines, at every level of the hierarchy, and that rate, not the matrix cores, was the limit of a 32-deep
+//     version.  Two stages of 64 KB; the loads of tile kt+2 go out right after the barrier that frees the stage of
+//     tile kt.  A contraction length that is no multiple of 64 ends in a tile whose 16-byte pieces past the end are
+//     parked out of range (zeros land): 1608 x 6424 on 2378 rows took 173 us forward and 282 us backward in a
+//     register-staged kernel that masked its loads, 83 and 123 us here (a template flag: the test for the last tile in the
+//     loop of launches without one cost them 1 %).
 //   * LDS rows cannot be padded under the DMA rule, so 16-byte pieces are XOR-swizzled instead:
-//     [rows][BK] tiles by row bits, the forward's [BK][256] tile of W by k bits.
+//     [rows][64] tiles by row bits, the forward's [64][256] tile of W by k bits.
 //   * one workgroup barrier per K-tile, placed before the last MFMA step: by then every read of
 //     the current stage is done (it may be refilled) and the next tile has landed (it may be read).
 //   * one workgroup per compute unit at a time; the tiles left over after the last full round of workgroups are
@@ -38,6 +40,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
 constexpr int BM = 256;
+constexpr int BK = 64;                          // depth of a K-tile
 constexpr int TILE_N = 256;                     // width of a tile in the launch's tile index space
 constexpr int TS256 = 2;
 constexpr uint32_t OOB = 0x80000000u;
@@ -98,17 +101,13 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 __device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
-// Swizzle of the 16-byte piece index inside a row of a [rows][BK] tile: sixteen consecutive rows read the same
-// logical piece with one ds_read_b128 and must land in sixteen different 16-byte bank groups.
-template <int BK>
-__device__ __forceinline__ int swz_row(int r) {
-  if (BK == 32) return (((r >> 1) ^ (r >> 3)) & 1) | (((r >> 2) & 1) << 1);   // 64-byte rows: 4 pieces
-  return (r >> 1) & 7;                                                          // 128-byte rows: 8 pieces
-}
+// Swizzle of the 16-byte piece index inside a 128-byte row of a [rows][64] tile: sixteen consecutive rows read the
+// same logical piece with one ds_read_b128 and must land in sixteen different 16-byte bank groups.
+__device__ __forceinline__ int swz_row(int r) { return (r >> 1) & 7; }
 
-// Up to four A stages, four B stages and the per-row validity flags of one workgroup.
+// Two A and two B arrays (a stage each, two stages each for quarter tiles) and the per-row validity flags of a workgroup.
 struct Smem {
-  bf16_t *a0, *a1, *a2, *a3, *b0, *b1, *b2, *b3;
+  bf16_t *a0, *a1, *b0, *b1;
   int* row;
   bf16_t *e0, *e1, *e2, *e3;     // FUSE: stages of the [64][rank] slabs of A_t
   uint32_t pk_lds;               // DIFFP: LDS byte address of the stages' slots for 256 packed entries of the masks each
@@ -121,36 +120,34 @@ struct Smem {
 //   <4,4,1> eight waves, 128x32 per wave, a 256x128 half of a tile,
 //   <2,2,2> four waves (one per SIMD), 64x64 per wave, a 128x128 quarter: for what is left after the last full
 //           round of workgroups.
-// BK = 64 with two stages, or BK = 32 with four.
 // `xcd_slot` = (per-XCD tile slot) * 8 + XCD; `half` selects the 128 columns of a half-width tile, `mhalf` the
 // 128 rows of a quarter.
-// FUSE (forward, 64-deep stages, half and quarter tiles): the down-projection Hs = s_t X A_t of the tile's rows is
+// FUSE (forward, half and quarter tiles): the down-projection Hs = s_t X A_t of the tile's rows is
 // computed in the same K loop -- the [64][rank] slab of A_t of every K-tile is staged beside the tile of W, wave
 // (wm, wn) multiplies it with the X fragment of its row block wn (one more MFMA per step) -- and goes, scaled and
 // rounded to bf16, straight into the A side of the adapter K-tile (and, from the tiles of the first column, to
 // memory for the backward): no separate pass over X, no launch for it.  Every column tile redoes the product for
 // its rows, which is why this is for launches that do not fill the compute units anyway.
-// DIFFP (64-deep stages): the rows of a Diff-Pruning task meet W + M_t * delta_t without a copy of W: once a tile of W
+// DIFFP: the rows of a Diff-Pruning task meet W + M_t * delta_t without a copy of W: once a tile of W
 // has landed in LDS, the masked entries that fall into it are added in place (one bf16 read-modify-write each) and a
 // second barrier follows before the tile is read.  The mask lists its entries by tiles -- buckets of 64 of the
 // contraction index by 128 lines of the W side, numbered so that the one or two buckets of a tile are neighbours --
 // and the launch brings them packed, (contraction index % 64) << 23 | (line % 128) << 16 | bf16 value.  The entries
 // of a K-tile travel with it: every loading wave fetches 64 of them straight into LDS with the tile's other loads
 // (256 a tile; a bucket pair with more reads the rest from memory when the tile is patched).
-template <bool NT, int WNW, int MI, int NI, int BK, bool FUSE = false, bool DIFFP = false>
+template <bool NT, int WNW, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slot, const int half, const int mhalf,
                                           const Smem sm) {
-  static_assert(!FUSE || (!NT && BK == 64 && WNW == MI && !(MI == 4 && NI == 2)), "FUSE: forward, 64-deep, half or quarter tiles");
-  static_assert(!DIFFP || (BK == 64 && !FUSE), "DIFFP: 64-deep stages");
+  static_assert(!FUSE || (!NT && WNW == MI && !(MI == 4 && NI == 2)), "FUSE: forward, half or quarter tiles");
+  static_assert(!DIFFP || !FUSE, "DIFFP: not with FUSE");
   constexpr int BN = WNW * NI * 32;
   constexpr int BMT = 2 * MI * 32;
   static_assert(BN == 256 || BN == 128, "tile width");
   static_assert(BMT == 256 || BMT == 128, "tile height");
-  static_assert(BK == 32 || BK == 64, "K-tile depth");
-  // LDS stages.  A 64-deep stage of a full or half tile takes 64 or 48 KB: two fit.  A quarter's takes 32 KB and
-  // half the MFMA time, which is less than the latency of the loads: four stages, three tiles in flight.
-  constexpr int NST = (BK == 64 && MI == 4) ? 2 : 4;
-  constexpr bool SPLIT = BK == 64 && NST == 4;    // four stages in the two arrays per operand that 64-deep stages have
+  // LDS stages.  A stage of a full or half tile takes 64 or 48 KB: two fit.  A quarter's takes 32 KB and half the
+  // MFMA time, which is less than the latency of the loads: four stages, three tiles in flight.
+  constexpr int NST = MI == 4 ? 2 : 4;
+  constexpr bool SPLIT = NST == 4;                // four stages in two arrays per operand
   constexpr int NW = 2 * WNW, NTHR = 64 * NW;
   constexpr int A_ELEMS = BMT * BK;               // elements of one A stage
   // The loads are issued by the first half of the waves only.  Each SIMD hosts waves w and w + NW/2 and serves the
@@ -170,8 +167,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   constexpr int RPCB = 64 / PPRB;                 // forward: k-rows per 1 KB chunk
   constexpr int WCOLS = NI * 32;                  // columns of the wave tile
   constexpr int EPW = WCOLS + 8;                  // epilogue staging pitch (elements)
-  bf16_t* const sA0 = sm.a0; bf16_t* const sA1 = sm.a1; bf16_t* const sA2 = sm.a2; bf16_t* const sA3 = sm.a3;
-  bf16_t* const sB0 = sm.b0; bf16_t* const sB1 = sm.b1; bf16_t* const sB2 = sm.b2; bf16_t* const sB3 = sm.b3;
+  bf16_t* const sA0 = sm.a0; bf16_t* const sA1 = sm.a1;
+  bf16_t* const sB0 = sm.b0; bf16_t* const sB1 = sm.b1;
   bf16_t* const sE0 = sm.e0; bf16_t* const sE1 = sm.e1; bf16_t* const sE2 = sm.e2; bf16_t* const sE3 = sm.e3;
   int* const sRow = sm.row;
 
@@ -225,7 +222,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   const bf16_t* adapterB = NT ? (const bf16_t*)tk.A : (const bf16_t*)tk.B;
   const bf16_t* Lvec = (const bf16_t*)tk.L;
 
-  const int KT = p.Kc / BK;                         // the contraction length is a multiple of BK
+  const int KT = (p.Kc + BK - 1) / BK;
+  const int k_tail = p.Kc - (KT - 1) * BK;          // TAIL: contraction indices in the last backbone tile (a multiple of 8)
   const int KT_ext = lora ? (rank + BK - 1) / BK : 0;
   const int KT_total = KT + KT_ext;
   const bool fuse_h = FUSE && lora;                 // this tile forms Hs of its rows in the K loop
@@ -273,19 +271,20 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   const rsrc_t rA = make_rsrc(a_base, a_rows_bytes);
   const rsrc_t rW = make_rsrc(task_weight(tk, p.W, p.Wdiff, p.wdiff_stride), (uint32_t)((size_t)(NT ? p.Nc : p.Kc) * p.ldw * 2));
   const rsrc_t rE = make_rsrc(lora ? p.Ext + (size_t)row0 * p.RP : p.Ain, lora ? (uint32_t)nrows * (uint32_t)p.RP * 2u : 0u);
-  const rsrc_t rP = make_rsrc(lora ? adapterB : p.Ain, lora ? (uint32_t)(NT ? (size_t)p.Nc * rank : (size_t)rank * p.Nc) * 2u : 0u);
+  const int a_pitch = 8 * rank_pieces(rank);         // elements in a row of A_t
+  const rsrc_t rP = make_rsrc(lora ? adapterB : p.Ain, lora ? (uint32_t)(NT ? (size_t)p.Nc * a_pitch : (size_t)rank * p.Nc) * 2u : 0u);
 
-  // FUSE: A_t [K][rank] as it is; the slab of K-tile kt is the 128 rank bytes from byte kt * 128 rank on, loading wave
-  // w brings its w-th KB (lane l the 16 bytes at 1024 w + 16 l), so the slab lies in LDS as in memory, [64][rank]
-  const rsrc_t rAt = make_rsrc(fuse_h ? tk.A : (const void*)p.Ain, fuse_h ? (uint32_t)p.Kc * (uint32_t)rank * 2u : 0u);
-  const uint32_t offE = (fuse_h && (uint32_t)(lw * 1024 + lane * 16) < 128u * (uint32_t)rank) ? (uint32_t)(lw * 1024 + lane * 16) : OOB;
+  // FUSE: A_t [K][a_pitch]; the slab of K-tile kt is the 128 a_pitch bytes from byte kt * 128 a_pitch on, loading wave
+  // w brings its w-th KB (lane l the 16 bytes at 1024 w + 16 l), so the slab lies in LDS as in memory, [64][a_pitch]
+  const rsrc_t rAt = make_rsrc(fuse_h ? tk.A : (const void*)p.Ain, fuse_h ? (uint32_t)p.Kc * (uint32_t)a_pitch * 2u : 0u);
+  const uint32_t offE = (fuse_h && (uint32_t)(lw * 1024 + lane * 16) < 128u * (uint32_t)a_pitch) ? (uint32_t)(lw * 1024 + lane * 16) : OOB;
   uint32_t kE = 0;
-  const uint32_t stepE = 128u * (uint32_t)rank;
+  const uint32_t stepE = 128u * (uint32_t)a_pitch;
 
   // row of the [rows][BK] tile chunk q of this wave puts this lane on, and the logical k-piece it fetches there
   auto a_row_of = [&](int q) { return lw * (RPC * ACH) + RPC * q + r_in; };
   auto b_row_of = [&](int q) { return lw * (RPC * BCH) + RPC * q + r_in; };   // backward: row of W inside the tile
-  auto piece_of = [&](int row) { return (lane % LPR) ^ swz_row<BK>(row); };
+  auto piece_of = [&](int row) { return (lane % LPR) ^ swz_row(row); };
   // forward W tile: k-row = (lw*BCH + q)*RPCB + lane/PPRB, physical piece lane%PPRB -> logical n
   const int nk_in = lane / PPRB;
   const int n_pp = lane % PPRB;
@@ -315,8 +314,19 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   int next_tile = 0;                                          // index of the tile the next issue() fetches
 
   // uniform, rarely taken: everything that changes at a tile-kind boundary
+  const int special = TAIL ? KT - 1 : KT;                     // the first tile that is not like the ones before it
   auto prepare = [&]() {
-    if (next_tile >= KT) {
+    if (next_tile < special) return;
+    if (TAIL && next_tile == KT - 1) {                                // the last backbone tile is not full: pieces past the end
+#pragma unroll
+      for (int q = 0; q < ACH; ++q)
+        if (piece_of(a_row_of(q)) * 8 >= k_tail) offA[q] = OOB;
+      if (NT) {                                               // (the forward's rows of W past the end lie behind its buffer)
+#pragma unroll
+        for (int q = 0; q < BCH; ++q)
+          if (piece_of(b_row_of(q)) * 8 >= k_tail) offB[q] = OOB;
+      }
+    } else {
       if (FUSE) kE = OOB;                                     // no slab of A_t past the backbone tiles
       if (next_tile >= KT_total) {
         kA = OOB; kB = OOB;
@@ -338,7 +348,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
           if (NT) {
             const int c = c0 + b_row_of(q);
             const int j = j0 + piece_of(b_row_of(q)) * 8;
-            offB[q] = (c < p.Nc && j < rank) ? (uint32_t)(((size_t)c * rank + j) * 2) : OOB;
+            offB[q] = (c < p.Nc && j < a_pitch) ? (uint32_t)(((size_t)c * a_pitch + j) * 2) : OOB;
           } else {
             const int kk = (lw * BCH + q) * RPCB + nk_in;
             const int seg = (n_pp >> 1) ^ ((kk & 3) << 1);
@@ -369,7 +379,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   const int li = lane & 31, lg = lane >> 5;
   const int l16 = lane & 15, lhalf = (lane >> 4) & 1;
   // [rows][BK] tiles: row = (wm|wn)*128 + t*32 + li; logical piece 2*ks + lg (the swizzle depends on li only)
-  const int swz = swz_row<BK>(li);
+  const int swz = swz_row(li);
   const int a_rd = (wm * (32 * MI) + li) * BK;  // elements; + t*32*BK + ((2ks+lg)^swz)*8
   const int bt_rd = (wn * WCOLS + li) * BK;
   // forward W tile: k = ks*16 + 8 lg + 4 h + l16/4 ; logical seg = wn*8 + 2 t + lhalf ; + 4*(l16%4) elements
@@ -418,19 +428,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
     const int mi = m / NI, ni = m % NI;
     acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ni], a[mi], acc[mi][ni], 0, 0, 0);
   };
-  // one MFMA step with the loads of one tile (all ACH+BCH of them) spread between its MFMA pairs
-  auto mma_with_loads = [&](const bf16x8 (&a)[MI], const bf16x8 (&b)[NI], bf16_t* dA, bf16_t* dB) {
-    constexpr int PAIRS = MI * NI / 2;
-#pragma unroll
-    for (int i = 0; i < PAIRS; ++i) {
-      mma_one(a, b, 2 * i);
-      mma_one(a, b, 2 * i + 1);
-#pragma unroll
-      for (int d = (i * (ACH + BCH)) / PAIRS; d < ((i + 1) * (ACH + BCH)) / PAIRS; ++d) issue_one(dA, dB, nullptr, d);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
   // One operand fragment of step ks: r = 0, 1 .. in the order the next step's MFMAs first need them
   // (A0, B0 .. B(NI-1), A1 .. A(MI-1)).
   auto read_one = [&](const bf16_t* cA, const bf16_t* cB, int ks, int r, bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
@@ -459,8 +456,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   for (int v = 0; v < 16; ++v) hacc[v] = 0.f;
   auto read_e = [&](const bf16_t* cE, int ks) -> bf16x8 {
     const int krow = ks * 16 + 8 * lg + kq;
-    const bf16x4 lo = lds_read_tr(cE + krow * rank + lhalf * 16 + bn_col);
-    const bf16x4 hi = lds_read_tr(cE + (krow + 4) * rank + lhalf * 16 + bn_col);
+    const bf16x4 lo = lds_read_tr(cE + krow * a_pitch + lhalf * 16 + bn_col);
+    const bf16x4 hi = lds_read_tr(cE + (krow + 4) * a_pitch + lhalf * 16 + bn_col);
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
   // the product of this step's slab fragment with the X fragment of row block wn, picked by selects on the (uniform)
@@ -513,11 +510,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   static_assert(!SPLIT || (2 * A_ELEMS <= BM * BK && 2 * BN * BK <= BM * BK), "two stages per array");
   auto stA = [&](int s) -> bf16_t* {
     if (SPLIT) return (s < 2 ? sA0 : sA1) + (s & 1) * A_ELEMS;
-    return s == 0 ? sA0 : (s == 1 ? sA1 : (s == 2 ? sA2 : sA3));
+    return s == 0 ? sA0 : sA1;
   };
   auto stB = [&](int s) -> bf16_t* {
     if (SPLIT) return (s < 2 ? sB0 : sB1) + (s & 1) * (BN * BK);
-    return s == 0 ? sB0 : (s == 1 ? sB1 : (s == 2 ? sB2 : sB3));
+    return s == 0 ? sB0 : sB1;
   };
   auto stE = [&](int s) -> bf16_t* { return s == 0 ? sE0 : (s == 1 ? sE1 : (s == 2 ? sE2 : sE3)); };
   auto tile_barrier = [&]() {
@@ -533,7 +530,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   auto patch_tile = [&](bf16_t* cB, uint32_t cP, int o0, int o1, int o2) {
     auto add_entry = [&](uint32_t w, int pos) {
       const int j = (int)(w >> 23), line = (int)((w >> 16) & 127u) + ((SPAN == 2 && o0 + pos >= o1) ? 128 : 0);
-      bf16_t* e = NT ? cB + line * BK + (((j >> 3) ^ swz_row<BK>(line)) * 8) + (j & 7)
+      bf16_t* e = NT ? cB + line * BK + (((j >> 3) ^ swz_row(line)) * 8) + (j & 7)
                      : cB + j * BN + (((line >> 4) ^ ((j & 3) << 1)) * 16) + (line & 15);
       // (the packed bf16 add of the LDS atomic unit in place of this read-modify-write was 5 % slower)
       *e = f32_to_bf16(bf16_to_f32(*e) + __uint_as_float(w << 16));
@@ -546,7 +543,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
       for (int pos = 256 + tid; pos < o2 - o0; pos += NTHR) add_entry(dlist[o0 + pos], pos);
   };
   // ---- prologue: tiles 0 .. PRE-1 in flight; tile 0 landed and visible; its first operands in registers
-  constexpr int PRE = BK == 64 ? NST : NST - 1;
+  constexpr int PRE = NST;
 #pragma unroll
   for (int s0 = 0; s0 < PRE; ++s0) {
     prepare();
@@ -570,76 +567,44 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   // FUSE: the K loop ends with the backbone; the adapter tile (its B_t side is fetched like any tile) follows below
   const int KT_loop = fuse_h ? KT : KT_total;
 
-  if (BK == 64) {
-    // Steps 0..2 run from registers read one step ahead; before the last step every wave has read all of this
-    // stage and tile kt+1 has landed (the loads of the NST-2 tiles after it may stay in flight): barrier; then,
-    // under the last step's MFMAs, the first operands of tile kt+1 are read and all loads of tile kt+NST are
-    // issued into the stage just freed.
-    for (int kt2 = 0; kt2 < KT_loop; kt2 += NST) {
+  // Steps 0..2 run from registers read one step ahead; before the last step every wave has read all of this
+  // stage and tile kt+1 has landed (the loads of the NST-2 tiles after it may stay in flight): barrier; then,
+  // under the last step's MFMAs, the first operands of tile kt+1 are read and all loads of tile kt+NST are
+  // issued into the stage just freed.
+  for (int kt2 = 0; kt2 < KT_loop; kt2 += NST) {
 #pragma unroll
-      for (int u = 0; u < NST; ++u) {
-        const int kt = kt2 + u;
-        if (kt < KT_loop) {
-          bf16_t* cA = stA(u);
-          bf16_t* cB = stB(u);
-          bf16_t* cE = stE(u);
-          prepare();
-          __builtin_amdgcn_sched_barrier(0);
-          fused_step(a0, b0, cA, cB, 1, a1, b1, true, std::false_type{}, nullptr, nullptr, e0, e1, cE, nullptr);
-          fused_step(a1, b1, cA, cB, 2, a0, b0, true, std::false_type{}, nullptr, nullptr, e1, e0, cE, nullptr);
-          fused_step(a0, b0, cA, cB, 3, a1, b1, true, std::false_type{}, nullptr, nullptr, e0, e1, cE, nullptr);
-          wait_vmcnt<(NST - 2) * NLD>();
-          wait_lgkm0();
-          tile_barrier();
-          __builtin_amdgcn_sched_barrier(0);
-          if (DIFFP) {
-            // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.  (Waiting for the
-            // tile one step earlier and adding the entries under the MFMAs of the third step was slower.)
-            const int un = (u + 1) % NST;
-            if (patch && ps2[un] > ps0[un]) {
-              patch_tile(stB(un), ldsP(un), ps0[un], ps1[un], ps2[un]);
-              wait_lgkm0();
-              tile_barrier();
-            }
-            // this stage is refilled with tile kt + NST (PRE == NST here): its entries, and the offsets of the tile after
-            ps0[u] = nx0; ps1[u] = nx1; ps2[u] = nx2;
-            bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
-            __builtin_amdgcn_sched_barrier(0);
+    for (int u = 0; u < NST; ++u) {
+      const int kt = kt2 + u;
+      if (kt < KT_loop) {
+        bf16_t* cA = stA(u);
+        bf16_t* cB = stB(u);
+        bf16_t* cE = stE(u);
+        prepare();
+        __builtin_amdgcn_sched_barrier(0);
+        fused_step(a0, b0, cA, cB, 1, a1, b1, true, std::false_type{}, nullptr, nullptr, e0, e1, cE, nullptr);
+        fused_step(a1, b1, cA, cB, 2, a0, b0, true, std::false_type{}, nullptr, nullptr, e1, e0, cE, nullptr);
+        fused_step(a0, b0, cA, cB, 3, a1, b1, true, std::false_type{}, nullptr, nullptr, e0, e1, cE, nullptr);
+        wait_vmcnt<(NST - 2) * NLD>();
+        wait_lgkm0();
+        tile_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (DIFFP) {
+          // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.  (Waiting for the
+          // tile one step earlier and adding the entries under the MFMAs of the third step was slower.)
+          const int un = (u + 1) % NST;
+          if (patch && ps2[un] > ps0[un]) {
+            patch_tile(stB(un), ldsP(un), ps0[un], ps1[un], ps2[un]);
+            wait_lgkm0();
+            tile_barrier();
           }
-          fused_step(a1, b1, stA((u + 1) % NST), stB((u + 1) % NST), 0, a0, b0, true, std::true_type{}, cA, cB, e1, e0,
-                     stE((u + 1) % NST), cE, ldsP(u), ps0[u], ps2[u]);   // past the last tile: read, unused
-          issue_done();
-        }
-      }
-    }
-  } else {
-    for (int kt4 = 0; kt4 < KT_total; kt4 += NST) {
-#pragma unroll
-      for (int u = 0; u < NST; ++u) {
-        const int kt = kt4 + u;
-        if (kt < KT_total) {
-          bf16_t* cA = stA(u);
-          bf16_t* cB = stB(u);
-          prepare();
-          __builtin_amdgcn_sched_barrier(0);
-          // first MFMA step.  The operand reads of the second step go out first (their latency hides under the
-          // MFMAs); the refill of the stage computed from in the previous iteration with tile kt+3 (past the last
-          // tile: zeros nobody reads) is spread between the MFMA pairs.
-          read_ops(cA, cB, 1, a1, b1);
-          __builtin_amdgcn_sched_barrier(0);
-          mma_with_loads(a0, b0, stA((u + NST - 1) % NST), stB((u + NST - 1) % NST));
-          issue_done();
-          // tile kt+1 must have landed (the two newer ones may stay in flight) and every read of this stage be done
-          wait_vmcnt<(NST - 2) * NLD>();
-          wait_lgkm0();
-          tile_barrier();
-          __builtin_amdgcn_sched_barrier(0);
-          // second MFMA step, with the first operands of the next tile read under it
-          if (kt + 1 < KT_total) read_ops(stA((u + 1) % NST), stB((u + 1) % NST), 0, a0, b0);
-          __builtin_amdgcn_sched_barrier(0);
-          mma(a1, b1);
+          // this stage is refilled with tile kt + NST (PRE == NST here): its entries, and the offsets of the tile after
+          ps0[u] = nx0; ps1[u] = nx1; ps2[u] = nx2;
+          bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
           __builtin_amdgcn_sched_barrier(0);
         }
+        fused_step(a1, b1, stA((u + 1) % NST), stB((u + 1) % NST), 0, a0, b0, true, std::true_type{}, cA, cB, e1, e0,
+                   stE((u + 1) % NST), cE, ldsP(u), ps0[u], ps2[u]);   // past the last tile: read, unused
+        issue_done();
       }
     }
   }
@@ -753,17 +718,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
 // The workgroups after them compute the remaining tiles in pieces (tail_split = 2: two half-width tiles each;
 // 4: four 128 x 128 quarters each); all pieces of a tile run on the same XCD.  The dispatcher hands out workgroups
 // in index order, so the pieces start as the compute units finish their last full tile.
-template <bool NT, int BK, bool FUSE, bool DIFFP>
+template <bool NT, bool FUSE, bool DIFFP, bool TAIL>
 __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
-  constexpr int STAGE_ELEMS = BM * BK;            // 16 KB (BK = 32, four stages) or 32 KB (BK = 64, two) per operand
+  constexpr int STAGE_ELEMS = BM * BK;            // 32 KB per operand and stage
   __shared__ __attribute__((aligned(1024))) bf16_t sA0[STAGE_ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16_t sA1[STAGE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t sA2[BK == 32 ? STAGE_ELEMS : 8];
-  __shared__ __attribute__((aligned(1024))) bf16_t sA3[BK == 32 ? STAGE_ELEMS : 8];
   __shared__ __attribute__((aligned(1024))) bf16_t sB0[STAGE_ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16_t sB1[STAGE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t sB2[BK == 32 ? STAGE_ELEMS : 8];
-  __shared__ __attribute__((aligned(1024))) bf16_t sB3[BK == 32 ? STAGE_ELEMS : 8];
   __shared__ __attribute__((aligned(1024))) bf16_t sE0[FUSE ? 2048 : 8];   // FUSE: [64][rank <= 32] slabs of A_t, 4 KB a stage
   __shared__ __attribute__((aligned(1024))) bf16_t sE1[FUSE ? 2048 : 8];
   __shared__ __attribute__((aligned(1024))) bf16_t sE2[FUSE ? 2048 : 8];
@@ -771,18 +732,18 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   __shared__ __attribute__((aligned(1024))) uint32_t sP[DIFFP ? 4 * 256 : 2];   // DIFFP: 256 packed entries a stage
   __shared__ int sOff[DIFFP ? 3 * 1024 : 2];                                      // DIFFP: K < 65536, so at most 1023 K-tiles
   __shared__ int sRow[256];
-  const Smem sm = {sA0, sA1, sA2, sA3, sB0, sB1, sB2, sB3, sRow, sE0, sE1, sE2, sE3, (uint32_t)(uintptr_t)(lds_void_ptr)sP, sOff};
+  const Smem sm = {sA0, sA1, sB0, sB1, sRow, sE0, sE1, sE2, sE3, (uint32_t)(uintptr_t)(lds_void_ptr)sP, sOff};
   const int b = blockIdx.x;
   // the start stamps wait in the buffer itself (words 2, 3), so that nothing stays live across the tile
   if (p.clk != nullptr && b == 0 && threadIdx.x == 0) { p.clk[2] = clock64(); p.clk[3] = wall_clock64(); }
   if (!FUSE && b < p.n_full) {                    // a launch with the down-projection in the loop has pieces only
-    gemm_tile<NT, 4, 4, 2, BK, false, DIFFP>(p, b, 0, 0, sm);
+    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, b, 0, 0, sm);
   } else if (p.tail_split == 2) {
     const int t = b - p.n_full;                                       // n_full is a multiple of 8
-    gemm_tile<NT, 4, 4, 1, BK, FUSE, DIFFP>(p, p.n_full + (((t >> 4) << 3) | (t & 7)), (t >> 3) & 1, 0, sm);
+    gemm_tile<NT, 4, 4, 1, FUSE, DIFFP, TAIL>(p, p.n_full + (((t >> 4) << 3) | (t & 7)), (t >> 3) & 1, 0, sm);
   } else {
     const int t = b - p.n_full;
-    gemm_tile<NT, 2, 2, 2, BK, FUSE, DIFFP>(p, p.n_full + (((t >> 5) << 3) | (t & 7)), (t >> 3) & 1, (t >> 4) & 1, sm);
+    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, TAIL>(p, p.n_full + (((t >> 5) << 3) | (t & 7)), (t >> 3) & 1, (t >> 4) & 1, sm);
   }
   if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
     atomicAdd(p.clk, (unsigned long long)clock64() - p.clk[2]);
@@ -802,8 +763,8 @@ int compute_units() {
 }
 
 // The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters.
-struct TilePlan { int n_m, n_n, per_xcd, n_full, tail_split, grid; bool narrow; };
-TilePlan plan_tiles(const CallCtx& c, int Kc, int Nc) {
+struct TilePlan { int n_m, n_n, per_xcd, n_full, tail_split, grid; };
+TilePlan plan_tiles(const CallCtx& c, int Nc) {
   TilePlan t{};
   t.n_m = (int)c.st->items[TS256].size();
   t.n_n = (Nc + TILE_N - 1) / TILE_N;
@@ -814,7 +775,6 @@ TilePlan plan_tiles(const CallCtx& c, int Kc, int Nc) {
   // half-width tiles.
   static const bool no_halves = getenv("MUX_GEMM_NO_HALF_TILES") != nullptr;
   static const bool no_quarters = getenv("MUX_GEMM_NO_QUARTER_TILES") != nullptr;
-  static const bool narrow = getenv("MUX_GEMM_BK32") != nullptr;
   const int ncu = compute_units();
   const int full_slots = (total / ncu) * (ncu / 8);          // per-XCD slots covered by whole rounds
   const int rem = total - full_slots * 8;
@@ -823,7 +783,6 @@ TilePlan plan_tiles(const CallCtx& c, int Kc, int Nc) {
   t.tail_split = (!no_quarters && 4 * rem <= ncu) ? 4 : 2;
   t.n_full = 8 * (t.per_xcd - tail_slots);
   t.grid = t.n_full + 8 * t.tail_split * tail_slots;
-  t.narrow = narrow || Kc % 64 != 0;
   return t;
 }
 
@@ -834,50 +793,48 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.dtab = c.dtab; p.tasks = *c.tref; p.Ain = Ain; p.W = (const bf16_t*)c.W; p.ldw = c.ldw; p.Ext = Ext; p.Out = Out;
   p.Zsave = Zsave; p.Kc = Kc; p.Nc = Nc; p.RP = c.RP;
   p.HsOut = fuse_down ? (bf16_t*)Ext : nullptr;
-  const TilePlan t = plan_tiles(c, Kc, Nc);
+  const TilePlan t = plan_tiles(c, Nc);
   p.n_m = t.n_m; p.n_n = t.n_n; p.per_xcd = t.per_xcd; p.n_full = t.n_full; p.tail_split = t.tail_split;
   p.AinScaled = (const bf16_t*)c.dYs;
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
   p.DiffPack = (const uint32_t*)c.diffPack;
   p.clk = diag_clock_buffer();
   if (t.n_m * t.n_n == 0) return MUX_OK;
-  if (fuse_down && (NT || t.narrow || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
-  if (p.DiffPack != nullptr && (t.narrow || fuse_down)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
-  if (!t.narrow) {
-    if (!NT && fuse_down) MUX_LAUNCH("gemm_nn", (k_gemm_dma<false, 64, true, false>), dim3(t.grid), dim3(512), 0, c.stream, p);
-    else if (p.DiffPack != nullptr) MUX_LAUNCH(NT ? "gemm_nt" : "gemm_nn", (k_gemm_dma<NT, 64, false, true>), dim3(t.grid), dim3(512), 0, c.stream, p);
-    else MUX_LAUNCH(NT ? "gemm_nt" : "gemm_nn", (k_gemm_dma<NT, 64, false, false>), dim3(t.grid), dim3(512), 0, c.stream, p);
-  } else {
-    MUX_LAUNCH(NT ? "gemm_nt" : "gemm_nn", (k_gemm_dma<NT, 32, false, false>), dim3(t.grid), dim3(512), 0, c.stream, p);
-  }
+  if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
+  if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
+  const char* name = NT ? "gemm_nt" : "gemm_nn";
+  const dim3 grid(t.grid), block(512);
+  const bool tail = Kc % BK != 0;                 // (masked entries are added only where there is none)
+  if (!NT && fuse_down && tail) MUX_LAUNCH(name, (k_gemm_dma<false, true, false, true>), grid, block, 0, c.stream, p);
+  else if (!NT && fuse_down) MUX_LAUNCH(name, (k_gemm_dma<false, true, false, false>), grid, block, 0, c.stream, p);
+  else if (p.DiffPack != nullptr) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true, false>), grid, block, 0, c.stream, p);
+  else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true>), grid, block, 0, c.stream, p);
+  else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, false>), grid, block, 0, c.stream, p);
   return MUX_OK;
 }
 
 }  // namespace
 
-// The pipelined kernel needs what the register-staged one needs, a contraction length that is a multiple of 32,
-// and in the backward every LoRA rank a multiple of 8 (rows of A_t are read in 16-byte pieces).
-bool gemm_dma_supported(const CallCtx& c, bool backward) {
-  if (!gemm_mfma_supported(c)) return false;
-  if ((backward ? c.N : c.K) % 32 != 0) return false;      // no K-tail masks in the pipelined loop
-  if (backward)
-    for (const HostTask& ht : c.st->tasks)
-      if (ht.kind == MUX_ADAPTER_LORA && (ht.rank & 7) != 0) return false;
-  return true;
+// 16-byte loads need rows of X, dY, W, Hs and B_t to start 16-byte aligned (rows of A_t: see rank_pieces), and the
+// 32-bit buffer offsets need W and the largest row group a kernel builds one descriptor over (1024 rows of
+// activations; rows parked at offset 2^31 must stay out of range) below 2 GiB.
+bool gemm_dma_supported(const CallCtx& c) {
+  const int64_t big = (int64_t)1 << 31;
+  return (c.K % 8 == 0) && (c.N % 8 == 0) && (c.ldw % 8 == 0) && (((uintptr_t)c.W & 15) == 0) &&
+         ((int64_t)c.K * c.ldw * 2 < big) && ((int64_t)1024 * (c.K > c.N ? c.K : c.N) * 2 < big);
 }
 
 // Can the forward of this call form Hs = s_t X A_t inside the backbone tile loop?  The kernel can when the launch is
-// made of half or quarter tiles only, with 64-deep stages, LoRA ranks up to 32 that are multiples of 8 (A_t is read in
-// place) and no Adapter-Tuning task.  It is chosen for launches of quarter tiles (at most a quarter of the compute
+// made of half or quarter tiles only, with LoRA ranks up to 32 and no Adapter-Tuning task.  It is chosen for launches of quarter tiles (at most a quarter of the compute
 // units' worth of 256 x 256 tiles): there the loop waits on loads, the extra product per step costs about 0.13 us per
 // 64 of K, and the launch it saves costs 9 to 25 us; in launches of half tiles the extra product costs more than the
 // launch (measured 4 to 13 % slower).  MUX_GEMM_FUSE_DOWN (read once): 0 never, 2 in launches of half tiles as well.
 bool gemm_dma_fuses_down(const CallCtx& c) {
   static const int mode = [] { const char* e = getenv("MUX_GEMM_FUSE_DOWN"); return e == nullptr ? 1 : atoi(e); }();
-  if (mode == 0 || !gemm_dma_supported(c, false)) return false;
-  if (c.st->n_lora == 0 || c.st->n_tuning > 0 || !c.lora_natural || c.st->r_max > 32 || c.diffPack != nullptr) return false;
-  const TilePlan t = plan_tiles(c, c.K, c.N);
-  if (t.narrow || t.n_full != 0 || t.n_m * t.n_n == 0) return false;
+  if (mode == 0) return false;
+  if (c.st->n_lora == 0 || c.st->n_tuning > 0 || c.st->r_max > 32 || c.diffPack != nullptr) return false;
+  const TilePlan t = plan_tiles(c, c.N);
+  if (t.n_full != 0 || t.n_m * t.n_n == 0) return false;
   return t.tail_split == 4 || mode == 2;
 }
 

@@ -50,7 +50,8 @@ struct DevTask {
   int32_t row_count;
   int32_t zrow0;      // first row of this task inside the saved x W region (IA3_OUT, TUNING) or inside the
                       // block-transposed copies (DIFF, a multiple of 64), else -1
-  int64_t at_off;     // element offset of this task's transposed A_t inside the workspace region
+  int64_t at_off;     // LORA, TUNING with a rank that is no multiple of 8, matrix-core path: A = the copy of A_t with rows
+                      // padded to rank_pieces(rank) 16-byte pieces, L = the caller's A_t
                       // DIFF tasks: A = values, dA = their gradient, B = row_ptr, L = col_idx, dB = col_ptr, dL = col_ent
                       // (all int32 arrays), at_off = number of masked entries; rank = index of the task's merged
                       // weight W + M_t * delta_t in the workspace when the call builds them, or the element offset of
@@ -118,6 +119,8 @@ unsigned long long* diag_clock_buffer();
   } while (0)
 
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
+// 16-byte pieces in a row of A_t (D_t) as the matrix-core kernels read it
+__host__ __device__ inline int rank_pieces(int rank) { return (rank + 7) >> 3; }
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Everything a kernel launcher needs about one call.
@@ -129,14 +132,11 @@ struct CallCtx {
   int K, N;
   int64_t ldw;
   int RP;                  // row pitch (elements) of the H / G buffers
-  void* AT;                // workspace: per-task A_t^T [round_up(r_t,16)][K] bf16 (forward, fast path)
   void* dYs;               // workspace [z_rows][N]: the backbone backward's input rows of the kinds that change it
                            // (IA3_OUT: dY * l_t, fast path only; TUNING: dY + p D_t^T)
   const void* W;
   hipStream_t stream;
   void* U2;                // saved: pre-activations z D_t of the TUNING rows, [T][RP] (null without such tasks)
-  bool lora_natural;       // every LoRA rank is a multiple of 8: the down-projection reads A_t [K, r] as it is
-  bool tune_natural;       // likewise every Adapter-Tuning rank: D_t [N, r] is read as it is, forward and backward
   int diff_max_nnz;        // largest mask of the DIFF tasks of this call
   void* diffT[2];          // workspace: block-transposed copies of the DIFF rows of X ([0]) and of dY ([1])
   void* diffW;             // workspace: per DIFF task with entries, W + M_t * delta_t [K][ldw] bf16 (matrix-core path;
@@ -176,11 +176,7 @@ void diff_forward(const CallCtx& c, int dtype, const void* X, void* Y);         
 void diff_backward(const CallCtx& c, int dtype, const void* X, const void* dY, void* dX, int accumulate);     // dX, d delta_t
 
 // matrix-core backbone GEMM (bf16)
-bool gemm_mfma_supported(const CallCtx& c);
-mux_status gemm_mfma_forward(const CallCtx& c, const void* X, const void* Hs, void* Y, void* Z);
-mux_status gemm_mfma_backward(const CallCtx& c, const void* dY, const void* Gs, void* dX, int only_ia3);
-// pipelined variant (direct-to-LDS loads, 4 stages)
-bool gemm_dma_supported(const CallCtx& c, bool backward);
+bool gemm_dma_supported(const CallCtx& c);
 bool fast_gemm_patches_diff(const CallCtx& c, bool backward);   // the backbone product of this call can add masked entries in LDS
 bool gemm_dma_fuses_down(const CallCtx& c);   // the forward launch would be half / quarter tiles only: Hs is formed in its K loop
 mux_status gemm_dma_forward(const CallCtx& c, const void* X, const void* Hs, void* Y, void* Z, bool fuse_down);

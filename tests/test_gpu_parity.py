@@ -98,6 +98,27 @@ def test_kernel_choice_by_shape(env):
     run_case(env, wl, seed=4)
 
 
+@pytest.mark.parametrize("K,N", [(8, 72), (72, 8), (136, 200), (568, 1096), (1160, 2376)])
+def test_contraction_tails_and_odd_ranks(env, K, N):
+    """Contraction lengths that are no multiple of the 64-deep K-tile (a last tile of 8, 16, 24 .. elements, a tile that
+    is all there is) and ranks that are no multiple of 8, on launches of quarter, half and whole tiles.  W lies in wider
+    rows whose gap is NaN: nothing past the contraction may be read."""
+    mx, torch = env
+    toks = (70, 300, 129, 260, 90) if K < 1000 else (1500, 2100, 1030, 2900, 600)
+    kinds = [(wlm.KIND_LORA, 4), (wlm.KIND_LORA, 12), (wlm.KIND_IA3, 0), (wlm.KIND_LORA, 33), (wlm.KIND_ADAPTER, 20)]
+    for some in (kinds, [(wlm.KIND_LORA, 1), (wlm.KIND_LORA, 20), (wlm.KIND_NONE, 0), (wlm.KIND_LORA, 31), (wlm.KIND_LORA, 8)]):
+        wl = wlm.Workload(name=f"tail{K}", layers=[("w", K, N)], chunk=64, sigma_w=0.05, sigma_ab=0.05,
+                          tasks=[wlm.Task(k, r, 2.0, [n]) for (k, r), n in zip(some, toks)])
+        g, got, ref, errs = run_case(env, wl, seed=K + N)
+        wide = torch.full((K, N + 24), float("nan"), dtype=g.W.dtype, device=g.W.device)
+        wide[:, :N] = g.W
+        g.layer = mx.LayerDesc(K, N, mx.MUX_DT_BF16, wide, len(wl.tasks), g.A, g.B, g.L, ldw=N + 24)
+        y, dx = g.Y.clone(), g.dX.clone()
+        g.forward(); g.backward()
+        torch.cuda.synchronize()
+        assert torch.equal(g.Y, y) and torch.equal(g.dX, dx)
+
+
 @pytest.mark.parametrize("n_items", [16, 20, 23, 28])
 def test_gemm_last_round_pieces(env, n_items):
     """The backbone GEMM cuts the tiles left after the last full round of workgroups (one per compute unit) into
