@@ -49,6 +49,9 @@ struct AttnParams {
   float* delta;       // [H][T]
   int64_t ldq, ldk, ldv, ldo;
   int T, H, Hkv;      // query heads, key/value heads (H = group * Hkv: query head h reads key/value head h / group)
+  int short_map;      // forward: the pairs are dealt to the XCDs as in the kernel of the short sequences
+  int list_off;       // word offset of the launch's block list in dtab
+  int block0, n_blocks;   // the launch covers the entries block0 .. block0 + n_blocks - 1 of its list
   float scale;
 };
 
@@ -96,15 +99,33 @@ __device__ __forceinline__ void work_item(int n_blocks, int n_heads, int& block,
   }
 }
 
+// The same for launches of short sequences: with a multiple of eight heads every XCD takes its own run of neighbouring
+// heads of every block, the head running fastest, else a contiguous run of the (block, head) pairs: the heads of a
+// sequence, whose row segments share cache lines (160 bytes at D = 80), meet in one L2.
+// The grid is rounded up to a multiple of eight; false = nothing to do.
+__device__ __forceinline__ bool short_item(int n_blocks, int n_heads, int& block, int& head) {
+  const unsigned total = (unsigned)n_blocks * (unsigned)n_heads, xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  if ((n_heads & 7) == 0) {
+    const unsigned hx = (unsigned)n_heads >> 3;
+    block = (int)(j / hx);
+    head = (int)(xcd * hx + j % hx);
+    return true;
+  }
+  const unsigned per = (total + 7) >> 3, id = xcd * per + j;
+  block = (int)(id / (unsigned)n_heads);
+  head = (int)(id % (unsigned)n_heads);
+  return id < total;
+}
+
 // ROWS rows x D columns of one head from global memory (rows past `limit` read as zero) into registers, then LDS.
-// The tile is cut into 16-byte pieces, D / 8 a row.  Where the pieces of a row divide evenly among the 256 / ROWS
+// The tile is cut into 16-byte pieces, D / 8 a row.  Where the pieces of a row divide evenly among the NTHR / ROWS
 // threads that a row can have, a thread takes consecutive pieces of one row (one address, constant offsets);
-// otherwise the 256 threads take the pieces of the tile in order, 256 at a time.
-template <int ROWS, int D>
+// otherwise the NTHR threads take the pieces of the tile in order, NTHR at a time.
+template <int ROWS, int D, int NTHR = 256>
 struct TileLoadT {
-  static constexpr int PPR = D / 8, NP = ROWS * PPR, TPR = 256 / ROWS;
+  static constexpr int PPR = D / 8, NP = ROWS * PPR, TPR = NTHR / ROWS;
   static constexpr bool RUNS = PPR % TPR == 0;
-  static constexpr int N = RUNS ? PPR / TPR : (NP + 255) / 256;
+  static constexpr int N = RUNS ? PPR / TPR : (NP + NTHR - 1) / NTHR;
   uint4 r[N];
   __device__ __forceinline__ void load(const bf16_t* base, int64_t ld, int first, int row0, int limit, int hc, int tid) {
     if (RUNS) {
@@ -115,8 +136,8 @@ struct TileLoadT {
     } else {
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const int e = tid + 256 * i, row = row0 + e / PPR, pc = e % PPR;
-        const bool ok = (NP % 256 == 0 || e < NP) && row < limit;
+        const int e = tid + NTHR * i, row = row0 + e / PPR, pc = e % PPR;
+        const bool ok = (NP % NTHR == 0 || e < NP) && row < limit;
         r[i] = ok ? *(const uint4*)(base + (size_t)(first + row) * ld + hc + pc * 8) : uint4{0u, 0u, 0u, 0u};
       }
     }
@@ -129,18 +150,18 @@ struct TileLoadT {
     } else {
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const int e = tid + 256 * i;
-        if (NP % 256 == 0 || e < NP) *(uint4*)(tile + (e / PPR) * pitch + (e % PPR) * 8) = r[i];
+        const int e = tid + NTHR * i;
+        if (NP % NTHR == 0 || e < NP) *(uint4*)(tile + (e / PPR) * pitch + (e % PPR) * 8) = r[i];
       }
     }
   }
 };
 // Zero in the columns D .. DP-1 of a staged tile of `rows` rows (nothing is ever stored there afterwards).
-template <int D, int DP>
+template <int D, int DP, int NTHR = 256>
 __device__ __forceinline__ void zero_pad_columns(bf16_t* tile, int rows, int pitch, int tid) {
   if constexpr (DP > D) {
     constexpr int PIECES = (DP - D) / 8;       // 16-byte pieces a row
-    for (int e = tid; e < rows * PIECES; e += 256)
+    for (int e = tid; e < rows * PIECES; e += NTHR)
       *(uint4*)(tile + (e / PIECES) * pitch + D + (e % PIECES) * 8) = uint4{0u, 0u, 0u, 0u};
   }
 }
@@ -152,8 +173,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd(AttnParams p) {
   __shared__ __align__(16) bf16_t sK[TILE * KP];
   __shared__ __align__(16) bf16_t sV[TILE * TP];
   int wi_block, wi_head;
-  work_item(p.dtab[DH_ATT_NBLK], p.H, wi_block, wi_head);
-  const int32_t* blk = p.dtab + p.dtab[DH_ATT_OFF_FWD] + wi_block * DA_WORDS;
+  if (p.short_map) { if (!short_item(p.n_blocks, p.H, wi_block, wi_head)) return; }
+  else work_item(p.n_blocks, p.H, wi_block, wi_head);
+  const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN], q0 = blk[DA_BLOCK0];
   const int hc = wi_head * D;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, half = lane >> 5;
@@ -356,8 +378,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_q(AttnParams p) {
   __shared__ __align__(16) bf16_t sK[TILE * TP];
   __shared__ __align__(16) bf16_t sV[TILE * KP];
   int wi_block, wi_head;
-  work_item(p.dtab[DH_ATT_NBLK], p.H, wi_block, wi_head);
-  const int32_t* blk = p.dtab + p.dtab[DH_ATT_OFF_FWD] + wi_block * DA_WORDS;
+  work_item(p.n_blocks, p.H, wi_block, wi_head);
+  const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN], q0 = blk[DA_BLOCK0];
   const int hc = wi_head * D;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, half = lane >> 5;
@@ -456,8 +478,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(AttnParams p) {
   __shared__ __align__(16) bf16_t sVf[BLK * KP];   // the block's own V rows (B operand of dO V^T), kept here to save registers
   __shared__ float sLse[QT], sDelta[QT];
   int wi_block, wi_head;                       // wi_head: a key/value head
-  work_item(p.dtab[DH_ATT_NBLK], p.Hkv, wi_block, wi_head);
-  const int32_t* blk = p.dtab + p.dtab[DH_ATT_OFF_BWD] + wi_block * DA_WORDS;
+  work_item(p.n_blocks, p.Hkv, wi_block, wi_head);
+  const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN], k0 = blk[DA_BLOCK0];
   const int hc = wi_head * D;
   const int group = p.H / p.Hkv;
@@ -566,6 +588,185 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(AttnParams p) {
   }
 }
 
+// ------------------------------------------------------------------------------------------------ short sequences
+// The whole backward of a sequence of at most R tokens (R = 64 or 128) in one workgroup: R / 32 waves, wave w owns the
+// keys 32 w .. as in k_attn_bwd_kv, and since every key of a query is here, dQ needs no second pass over the scores and
+// dO . O no pass of its own.  Such calls are bound by memory traffic and latency, not by the matrix cores: eight
+// tensors cross the memory once (the two-kernel way reads Q, K, V, dO twice and dO, O a third time, with four launches
+// in a row for it).  Per 32 queries: S, dP and dS by the waves whose keys they see; dS [keys][queries] goes through LDS, and
+// the waves share dQ^T = K^T dS^T by 32-column tiles.  Two barriers a step; the next 32 queries are in flight meanwhile.
+// The lane's V row stays in registers, K only in LDS (it is needed there for dQ): 68 KB of LDS at R = 128, D = 128, two
+// workgroups a compute unit.  Measured, forward and backward of a call: 32 heads of 80, sequences of 64 and 128 tokens
+// (2944 in all) 94 -> 72 us; 46 sequences of 64 and 32 heads of 128, 126 -> 94 us (3.9 TB/s over what has to move).
+template <int D, int R>
+__global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
+  constexpr int KS = Dim<D>::KS, DT = Dim<D>::DT, DP = Dim<D>::DP, TP = Dim<D>::TP;
+  constexpr int NW = R / 32, NTHR = 64 * NW, QT = 32, SP = QT + 16;   // SP: pitch of the dS tile
+  constexpr bool LATE = D > 96;                // loads of the next tile behind the products: their registers are not free before
+  __shared__ __align__(16) bf16_t sK[R * TP];
+  __shared__ __align__(16) bf16_t sQ[QT * TP];
+  __shared__ __align__(16) bf16_t sD[QT * TP];
+  __shared__ __align__(16) bf16_t sS[R * SP];
+  __shared__ float sLse[R], sDelta[R];
+  int wi_block, wi_head;                       // wi_head: a key/value head
+  if (!short_item(p.n_blocks, p.Hkv, wi_block, wi_head)) return;
+  const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
+  const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN];
+  const int hc = wi_head * D;
+  const int group = p.H / p.Hkv;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, half = lane >> 5;
+  const int kl = 32 * wave + li;               // this lane's key (and, for the statistics, its query) in the sequence
+  const bool kok = kl < len;
+  // dO . O (the two half-waves take alternate 16-byte pieces of the rows of query kl) and the log-sum-exp, into LDS
+  auto dot = [](float s, const uint4& x, const uint4& y) {
+    const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      s = fmaf(__uint_as_float(xs[q] << 16), __uint_as_float(ys[q] << 16), s);
+      s = fmaf(__uint_as_float(xs[q] & 0xffff0000u), __uint_as_float(ys[q] & 0xffff0000u), s);
+    }
+    return s;
+  };
+  auto piece = [&](const bf16_t* base, int hq, int st) {
+    return kok ? *(const uint4*)(base + (size_t)(first + kl) * p.ldo + hq * D + 8 * half + 16 * st) : uint4{0u, 0u, 0u, 0u};
+  };
+  auto load_lse = [&](int hq) {
+    return kok ? p.lse[(size_t)hq * p.T + first + kl] * LOG2E : INFINITY;            // exp2(x - inf) = 0
+  };
+  auto store_stats = [&](float s, float lse2) {
+    s += __shfl_xor(s, 32);
+    if (half == 0) { sDelta[kl] = s; sLse[kl] = lse2; }
+  };
+  TileLoadT<QT, D, NTHR> tq, td;
+  bf16x8 vf[KS];
+  {
+    TileLoadT<R, D, NTHR> t;
+    t.load(p.K, p.ldk, first, 0, len, hc, tid);
+    uint4 xd[KS], xo[KS];                      // every load of the prologue is on its way before the first wait
+#pragma unroll
+    for (int st = 0; st < KS; ++st) { xd[st] = piece(p.dO, wi_head * group, st); xo[st] = piece(p.O, wi_head * group, st); }
+    const float lse2 = load_lse(wi_head * group);
+    tq.load(p.Q, p.ldq, first, 0, len, wi_head * group * D, tid);
+    td.load(p.dO, p.ldo, first, 0, len, wi_head * group * D, tid);
+    const bf16_t* vrow = p.V + (size_t)(first + kl) * p.ldv + hc + 8 * half;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) vf[s] = kok ? *(const bf16x8*)(vrow + 16 * s) : zero8();
+    zero_pad_columns<D, DP, NTHR>(sK, R, TP, tid);
+    zero_pad_columns<D, DP, NTHR>(sQ, QT, TP, tid);
+    zero_pad_columns<D, DP, NTHR>(sD, QT, TP, tid);
+    t.store(sK, TP, tid);
+    float sum = 0.f;
+#pragma unroll
+    for (int st = 0; st < KS; ++st) sum = dot(sum, xd[st], xo[st]);
+    store_stats(sum, lse2);
+  }
+  const bf16_t* kfrag = sK + kl * TP + 8 * half;
+  const float c = p.scale * LOG2E;
+  f32x16 dk[DT], dv[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) { dk[dt][j] = 0.f; dv[dt][j] = 0.f; }
+  for (int g = 0; g < group; ++g) {            // every query head that reads this key/value head
+    const int hq = wi_head * group + g, hcq = hq * D;
+    if (g > 0) {                               // (every read of the last head's statistics lies before its last barrier)
+      float sum = 0.f;
+#pragma unroll 2
+      for (int st = 0; st < KS; ++st) sum = dot(sum, piece(p.dO, hq, st), piece(p.O, hq, st));
+      store_stats(sum, load_lse(hq));
+    }
+    for (int qb = 0; qb < len; qb += QT) {
+      tq.store(sQ, TP, tid);                   // (every wave is past its reads of the last tile: the second barrier below)
+      td.store(sD, TP, tid);
+      __syncthreads();
+      // the next 32 queries, of this head or of the next one
+      auto load_next = [&]() {
+        const bool more = qb + QT < len;
+        const int gn = more ? g : g + 1, qn = more ? qb + QT : 0;
+        if (gn < group) {
+          tq.load(p.Q, p.ldq, first, qn, len, (wi_head * group + gn) * D, tid);
+          td.load(p.dO, p.ldo, first, qn, len, (wi_head * group + gn) * D, tid);
+        }
+      };
+      if (!LATE) load_next();
+      if (qb + QT - 1 >= 32 * wave) {          // some query of the tile sees a key of this wave
+        f32x16 s, dp;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) { s[j] = 0.f; dp[j] = 0.f; }
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+          s = mma(*(const bf16x8*)(sQ + li * TP + 16 * st + 8 * half), *(const bf16x8*)(kfrag + 16 * st), s);
+          dp = mma(*(const bf16x8*)(sD + li * TP + 16 * st + 8 * half), vf[st], dp);
+          if (D > 96 && st % 2 == 1) __builtin_amdgcn_sched_barrier(0);     // (the operand reads would pile up in registers)
+        }
+        // P (keys past the sequence come after every query: the mask takes them)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s[j] = fast_exp2(fmaf(s[j], c, -sLse[qb + tok(j, half)]));
+        if (qb < 32 * wave + 32) {             // only the tile on the diagonal pays for the mask
+          const int rel = kl - qb - 4 * half;  // query 8 (j / 4) + j % 4 sees the key iff it is >= rel
+#pragma unroll
+          for (int j = 0; j < 16; ++j)
+            if (8 * (j >> 2) + (j & 3) < rel) s[j] = 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) dp[j] = s[j] * (dp[j] - sDelta[qb + tok(j, half)]);   // dS
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const bf16x8 pb = pack8(s, u), ds = pack8(dp, u);
+          // the same eight values of dS, queries 16 u + 4 half + {0..3, 8..11} of this lane's key
+          const uint4 w = __builtin_bit_cast(uint4, ds);
+          *(uint2*)(sS + kl * SP + 16 * u + 4 * half) = uint2{w.x, w.y};
+          *(uint2*)(sS + kl * SP + 16 * u + 4 * half + 8) = uint2{w.z, w.w};
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) {
+            dv[dt] = mma(read_across<TP>(sD, 16 * u, 32 * dt, lane), pb, dv[dt]);
+            dk[dt] = mma(read_across<TP>(sQ, 16 * u, 32 * dt, lane), ds, dk[dt]);
+          }
+          if (D > 96) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (LATE) load_next();
+      __syncthreads();
+      // dQ of the tile: keys 0 .. qb + 31, this wave's 32-column tiles of the head dimension
+      for (int dt = wave; dt < DT; dt += NW) {
+        f32x16 dq;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) dq[j] = 0.f;
+        for (int k16 = 0; k16 < qb + QT; k16 += 16)
+          dq = mma(read_across<TP>(sK, k16, 32 * dt, lane), read_across<SP>(sS, k16, 0, lane), dq);
+        if (qb + li < len) {
+          bf16_t* orow = p.dQ + (size_t)(first + qb + li) * p.ldq + hcq + 32 * dt + 4 * half;
+#pragma unroll
+          for (int jg = 0; jg < 4; ++jg) {
+            if (32 * dt + 8 * jg >= D) continue;
+            uint2 v;
+            v.x = pack_bf16x2(dq[4 * jg + 0] * p.scale, dq[4 * jg + 1] * p.scale);
+            v.y = pack_bf16x2(dq[4 * jg + 2] * p.scale, dq[4 * jg + 3] * p.scale);
+            *(uint2*)(orow + 8 * jg) = v;
+          }
+        }
+      }
+    }
+  }                                             // next query head of the group
+  if (kok) {
+    bf16_t* krow = p.dK + (size_t)(first + kl) * p.ldk + hc;
+    bf16_t* vrow = p.dV + (size_t)(first + kl) * p.ldv + hc;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int jg = 0; jg < 4; ++jg) {
+        if (32 * dt + 8 * jg >= D) continue;
+        uint2 a, b;
+        a.x = pack_bf16x2(dk[dt][4 * jg + 0] * p.scale, dk[dt][4 * jg + 1] * p.scale);
+        a.y = pack_bf16x2(dk[dt][4 * jg + 2] * p.scale, dk[dt][4 * jg + 3] * p.scale);
+        b.x = pack_bf16x2(dv[dt][4 * jg + 0], dv[dt][4 * jg + 1]);
+        b.y = pack_bf16x2(dv[dt][4 * jg + 2], dv[dt][4 * jg + 3]);
+        *(uint2*)(krow + 32 * dt + 8 * jg + 4 * half) = a;
+        *(uint2*)(vrow + 32 * dt + 8 * jg + 4 * half) = b;
+      }
+  }
+}
+
 mux_status check(const char* fn, const mux_attn_desc* d, const mux_segtab* st) {
   if (!d || !st) return fail(MUX_ERR_INVALID_ARG, std::string(fn) + ": null descriptor or table");
   if (d->n_heads < 1 || d->n_kv_heads < 1 || d->head_dim < 1) return fail(MUX_ERR_INVALID_ARG, std::string(fn) + ": bad head counts");
@@ -596,6 +797,15 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
     else if ((D) == 80) MUX_LAUNCH(name, K<80>, grid, dim3(256), 0, stream, p);            \
     else MUX_LAUNCH(name, K<64>, grid, dim3(256), 0, stream, p);                           \
   } while (0)
+#define ATTN_LAUNCH_SHORT(name, R, D, grid, stream, p)                                                     \
+  do {                                                                                                     \
+    if ((D) == 128) MUX_LAUNCH(name, (k_attn_bwd_short<128, R>), grid, dim3(2 * R), 0, stream, p);          \
+    else if ((D) == 96) MUX_LAUNCH(name, (k_attn_bwd_short<96, R>), grid, dim3(2 * R), 0, stream, p);       \
+    else if ((D) == 80) MUX_LAUNCH(name, (k_attn_bwd_short<80, R>), grid, dim3(2 * R), 0, stream, p);       \
+    else MUX_LAUNCH(name, (k_attn_bwd_short<64, R>), grid, dim3(2 * R), 0, stream, p);                      \
+  } while (0)
+
+unsigned short_grid(int n_blocks, int n_heads) { return ((unsigned)n_blocks * (unsigned)n_heads + 7) / 8 * 8; }
 
 mux_status last_hip(const char* fn) {
   hipError_t e = hipGetLastError();
@@ -635,11 +845,15 @@ extern "C" mux_status mux_attn_forward(const mux_attn_desc* desc, const mux_segt
   p.ldq = desc->ldq; p.ldk = desc->ldk; p.ldv = desc->ldv; p.ldo = desc->ldo;
   p.T = st->T; p.H = desc->n_heads; p.Hkv = desc->n_kv_heads;
   p.scale = desc->scale > 0.f ? desc->scale : 1.f / sqrtf((float)D);
+  p.n_blocks = st->n_attn_blocks;
+  p.list_off = st->dev_image[DH_ATT_OFF_FWD];
   ZeroParams z{};
   z.dtab = p.dtab; z.out[0] = (bf16_t*)O; z.ld[0] = desc->ldo; z.n_out = 1; z.width[0] = desc->n_heads * D;
-  MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
+  if (st->valid_total < st->T)                // a table without padding rows has nothing to clear
+    MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
+  p.short_map = st->n_attn_blocks64 + st->n_attn_blocks128 == st->n_attn_blocks;
   if (st->n_attn_blocks > 0)
-    ATTN_LAUNCH("attn_fwd", k_attn_fwd, D, dim3((unsigned)st->n_attn_blocks * (unsigned)desc->n_heads), stream, p);
+    ATTN_LAUNCH("attn_fwd", k_attn_fwd, D, dim3(p.short_map ? short_grid(st->n_attn_blocks, desc->n_heads) : (unsigned)st->n_attn_blocks * (unsigned)desc->n_heads), stream, p);
   return last_hip(fn);
 }
 
@@ -670,12 +884,35 @@ extern "C" mux_status mux_attn_backward(const mux_attn_desc* desc, const mux_seg
   z.dtab = p.dtab; z.n_out = 3;
   z.width[0] = desc->n_heads * D; z.width[1] = z.width[2] = desc->n_kv_heads * D;
   z.out[0] = p.dQ; z.ld[0] = desc->ldq; z.out[1] = p.dK; z.ld[1] = desc->ldk; z.out[2] = p.dV; z.ld[2] = desc->ldv;
-  MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
-  const size_t n = (size_t)st->T * desc->n_heads;
-  ATTN_LAUNCH("attn_delta", k_attn_delta, D, dim3((unsigned)(((n + 3) / 4 * 16 + 255) / 256)), stream, p);
-  if (st->n_attn_blocks > 0) {
-    ATTN_LAUNCH("attn_bwd_kv", k_attn_bwd_kv, D, dim3((unsigned)st->n_attn_blocks * (unsigned)desc->n_kv_heads), stream, p);
-    ATTN_LAUNCH("attn_bwd_q", k_attn_bwd_q, D, dim3((unsigned)st->n_attn_blocks * (unsigned)desc->n_heads), stream, p);
+  if (st->valid_total < st->T)
+    MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
+  // Sequences of at most 128 tokens (the end of the list, which runs from the longest sequence to the shortest) have a
+  // kernel of their own for the whole pass, where they are all there is or fill the chip by themselves (512 workgroups: two a
+  // compute unit); fewer beside longer ones ride in the launches those need anyway.  Likewise sequences of at most 64
+  // tokens take a launch of narrower workgroups only where they fill the chip.
+  int n64 = st->n_attn_blocks64, n128 = st->n_attn_blocks128, n_long = st->n_attn_blocks - n64 - n128;
+  const int64_t fill = 512, hkv = desc->n_kv_heads;
+  if (n_long > 0 && (n64 + n128) * hkv < fill) { n_long += n64 + n128; n64 = n128 = 0; }
+  if (n128 > 0 && n64 * hkv < fill) { n128 += n64; n64 = 0; }
+  p.list_off = st->dev_image[DH_ATT_OFF_BWD];
+  if (n_long > 0) {
+    const size_t n = (size_t)st->T * desc->n_heads;
+    p.n_blocks = n_long;
+    ATTN_LAUNCH("attn_delta", k_attn_delta, D, dim3((unsigned)(((n + 3) / 4 * 16 + 255) / 256)), stream, p);
+    ATTN_LAUNCH("attn_bwd_kv", k_attn_bwd_kv, D, dim3((unsigned)n_long * (unsigned)desc->n_kv_heads), stream, p);
+    AttnParams q = p;
+    q.list_off = st->dev_image[DH_ATT_OFF_FWD];
+    ATTN_LAUNCH("attn_bwd_q", k_attn_bwd_q, D, dim3((unsigned)n_long * (unsigned)desc->n_heads), stream, q);
+  }
+  if (n128 > 0) {
+    p.block0 = n_long;
+    p.n_blocks = n128;
+    ATTN_LAUNCH_SHORT("attn_bwd_128", 128, D, dim3(short_grid(n128, desc->n_kv_heads)), stream, p);
+  }
+  if (n64 > 0) {
+    p.block0 = n_long + n128;
+    p.n_blocks = n64;
+    ATTN_LAUNCH_SHORT("attn_bwd_64", 64, D, dim3(short_grid(n64, desc->n_kv_heads)), stream, p);
   }
   return last_hip(fn);
 }

@@ -270,6 +270,8 @@ extern "C" mux_status mux_segtab_build(const mux_task_desc* tasks, int32_t n_tas
         const int32_t nb = (sq.len + kAttnBlockRows - 1) / kAttnBlockRows;
         for (int32_t b = nb - 1; b >= 0; --b) fwd.push_back({sq.first_row, sq.len, b * kAttnBlockRows});
         for (int32_t b = 0; b < nb; ++b) bwd.push_back({sq.first_row, sq.len, b * kAttnBlockRows});
+        if (sq.len <= kAttnBlockRows / 2) st->n_attn_blocks64 += nb;
+        else if (sq.len <= kAttnBlockRows) st->n_attn_blocks128 += nb;
       }
       st->n_attn_blocks = (int32_t)fwd.size();
       dv[DH_ATT_NBLK] = st->n_attn_blocks;

@@ -134,6 +134,17 @@ def test_grouped_query_heads(env):
     run(env, [[1000]], chunk=128, H=8, Hkv=8, seed=12)                    # eight heads: the XCD-wise work mapping
 
 
+@pytest.mark.parametrize("d", [64, 80, 96, 128])
+def test_backward_of_short_sequences(env, d):
+    """Sequences of at most 64 and of at most 128 tokens, whose backward is one kernel: alone and beside longer ones,
+    every 32-token step of it full, ragged or one token long, grouped heads, fused buffer, large scores, a table without
+    padding rows."""
+    edges = [[1, 32, 33], [63, 64], [65, 95, 96, 97], [127, 128]]
+    run(env, edges, chunk=32, H=4, Hkv=2, seed=40 + d, d=d, fused=True, check_repeat=True)
+    run(env, edges + [[129], [260, 2]], chunk=32, H=8, Hkv=8, seed=41 + d, d=d, flags=1)
+    run(env, [[64, 128, 64], [128], [64]], chunk=64, H=3, seed=42 + d, d=d, sigma=3.0)
+
+
 def test_llama_heads_one_block(env):
     """32 heads of 128 (the q/k/v width of the 4096-wide projections), ragged lengths."""
     run(env, [[384, 100], [77]], chunk=128, H=32, seed=7)
