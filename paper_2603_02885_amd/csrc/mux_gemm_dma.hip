@@ -24,6 +24,11 @@
 //     cut into two 256x128 halves or four 128x128 quarters (four waves, four 32 KB stages) at the end of the
 //     same launch, so that they occupy the compute units once more instead of a fraction of them for a whole
 //     tile time.
+//   * padding costs no products: the tiles are those of row groups with real tokens (a list on the host's side of the
+//     table), dealt to the XCDs by their number; a row group with tokens in its first 128 rows only runs as two quarters, and
+//     the groups without any are cleared by workgroups at the end of the launch.  32 tasks of about 1024 rows, aligned to
+//     1024 (a quarter of the row groups is padding, and fell on the XCDs unevenly), 8192 x 1024 and 1024 x 8192, both
+//     directions: 3015 -> 2741 us for the whole pass; 18 k rows aligned to 512, 5120-wide: 6171 -> 5945 us.
 // Every stage is its own __shared__ array so that the compiler's wait-count insertion can tell
 // the stage being filled from the stage being read.
 #include <cstdlib>
@@ -42,7 +47,6 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 constexpr int BM = 256;
 constexpr int BK = 64;                          // depth of a K-tile
 constexpr int TILE_N = 256;                     // width of a tile in the launch's tile index space
-constexpr int TS256 = 2;
 constexpr uint32_t OOB = 0x80000000u;
 
 struct GemmParams {
@@ -55,7 +59,11 @@ struct GemmParams {
   bf16_t* Zsave;       // forward: x W of IA3_OUT rows (may be null)
   bf16_t* HsOut;       // forward with the down-projection in the tile loop: Hs [T, RP] is written here (else null)
   int Kc, Nc, RP;
-  int n_m, n_n, per_xcd;   // tile grid in units of 256 x TILE_N tiles; workgroups per XCD over the whole grid
+  int items_off;           // word offset in dtab of the row groups' list (DH_OFF_GEMM_ITEMS)
+  int n_n;                 // column tiles
+  int n_m, per_xcd;        // row groups with tokens past their first 128 rows; their tiles an XCD takes
+  int n_mh, per_xcd_h;     // the same of the groups with tokens in their first 128 rows only
+  int half0, clear0;       // first workgroups of the pieces of such groups, and of those that clear the groups without tokens
   int n_full;              // workgroups that compute full tiles (a multiple of 8); the rest compute pieces of tiles
   int tail_split;          // pieces per tile after the full ones: 2 (halves) or 4 (quarters)
   unsigned long long* clk;  // diagnostic: counters workgroup 0 adds its elapsed cycles and 100 MHz ticks to (null: off)
@@ -114,6 +122,35 @@ struct Smem {
   int* off;                      //        per K-tile, where the entries of this tile's buckets begin, split and end
 };
 
+// Tile (row group tm, column tile tn) of slot xcd_slot = (per-XCD slot) * 8 + XCD: an XCD takes a contiguous range of the
+// tiles, in groups of four row groups.  False: the slot is past the end.
+__device__ __forceinline__ bool tile_of_slot(int n_m, int n_n, int per_xcd, int xcd_slot, int& tm, int& tn) {
+  const int jslot = xcd_slot >> 3;
+  const int L = (xcd_slot & 7) * per_xcd + jslot;
+  if (jslot >= per_xcd || L >= n_m * n_n) return false;
+  constexpr int GROUP = 4;
+  const int width = GROUP * n_n;
+  const int first_m = (L / width) * GROUP;
+  const int gsize = n_m - first_m < GROUP ? n_m - first_m : GROUP;
+  tm = first_m + (L % width) % gsize;
+  tn = (L % width) / gsize;
+  return true;
+}
+
+// Zeros on the rows past the first 128 of a row group that has tokens in those only (threads 256 .. 511): 128 columns of
+// the output, and with the first of them the rows of Hs.
+__device__ __forceinline__ void clear_below(const GemmParams& p, int xcd_slot, int half) {
+  int tm, tn;
+  if (!tile_of_slot(p.n_mh, p.n_n, p.per_xcd_h, xcd_slot, tm, tn)) return;
+  const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + tm) * DI_WORDS);
+  const int c0 = tn * TILE_N + half * 128, tid = threadIdx.x & 255, c = c0 + (tid & 15) * 8;
+  if (c < p.Nc)
+    for (int m = 128 + (tid >> 4); m < iw.z; m += 16) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
+  if (c0 == 0 && p.HsOut != nullptr)
+    for (int e = tid; e < (iw.z - 128) * (p.RP / 8); e += 256)
+      *(uint4*)(p.HsOut + (size_t)(iw.y + 128 + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
+}
+
 // One output tile.  WNW = waves along N, MI x NI = 32x32 MFMA tiles per wave; 2*WNW waves on a
 // BMT x BN tile with BMT = 2*MI*32 and BN = WNW*NI*32:
 //   <4,4,2> eight waves (two per SIMD), 128x64 per wave, the full 256x256 tile;
@@ -136,8 +173,8 @@ struct Smem {
 // of a K-tile travel with it: every loading wave fetches 64 of them straight into LDS with the tile's other loads
 // (256 a tile; a bucket pair with more reads the rest from memory when the tile is patched).
 template <bool NT, int WNW, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false>
-__device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slot, const int half, const int mhalf,
-                                          const Smem sm) {
+__device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int per_xcd,
+                                          const int xcd_slot, const int half, const int mhalf, const Smem sm) {
   static_assert(!FUSE || (!NT && WNW == MI && !(MI == 4 && NI == 2)), "FUSE: forward, half or quarter tiles");
   static_assert(!DIFFP || !FUSE, "DIFFP: not with FUSE");
   constexpr int BN = WNW * NI * 32;
@@ -172,19 +209,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   bf16_t* const sE0 = sm.e0; bf16_t* const sE1 = sm.e1; bf16_t* const sE2 = sm.e2; bf16_t* const sE3 = sm.e3;
   int* const sRow = sm.row;
 
-  const int total = p.n_m * p.n_n;
-  const int jslot = xcd_slot >> 3;
-  if (jslot >= p.per_xcd) return;
-  const int L = (xcd_slot & 7) * p.per_xcd + jslot;
-  if (L >= total) return;
-  constexpr int GROUP = 4;
-  const int width = GROUP * p.n_n;
-  const int first_m = (L / width) * GROUP;
-  const int gsize = p.n_m - first_m < GROUP ? p.n_m - first_m : GROUP;
-  const int tm = first_m + (L % width) % gsize;
-  const int tn = (L % width) / gsize;
-
-  const ItemView it = load_item(p.dtab, TS256, tm);
+  int tm, tn;
+  if (!tile_of_slot(n_m, p.n_n, per_xcd, xcd_slot, tm, tn)) return;
+  const int4 iw = *(const int4*)(p.dtab + p.items_off + (item0 + tm) * DI_WORDS);
+  const ItemView it = {iw.x, iw.y, iw.z, iw.w};   // (nvalid: rows up to the last real token)
   const int mrow0 = mhalf * BMT;                  // first row of the item this tile covers
   const int nrows = it.nrows - mrow0 < BMT ? it.nrows - mrow0 : BMT;   // rows of the item inside this tile
   if (nrows <= 0) return;
@@ -205,7 +233,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
       for (int e = tid; e < nrows * (p.RP / 8); e += NTHR)
         *(uint4*)(p.HsOut + (size_t)(row0 + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
   };
-  if (it.task < 0 || it.nvalid == 0) {             // rows of no task, or padding only: zeros out
+  const int nlive = it.nvalid - mrow0 < nrows ? it.nvalid - mrow0 : nrows;   // rows of the tile up to its last token
+  if (nlive <= 0) {                                // padding only: zeros out
     for (int e = tid; e < nrows * (BN / 8); e += NTHR) {
       const int m = e / (BN / 8), c = c0 + (e % (BN / 8)) * 8;
       if (c < p.Nc) *(uint4*)(p.Out + (size_t)(row0 + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
@@ -265,7 +294,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int xcd_slo
   // (lane -> row lane/LPR, physical piece lane%LPR), or RPCB k-rows of the forward's [BK][BN] tile of W
   // (lane -> k-row lane/PPRB, physical piece lane%PPRB).  Loading wave w owns chunks w*ACH .. of A and w*BCH .. of B.
   const int r_in = lane / LPR;                                  // row inside the chunk
-  const uint32_t a_rows_bytes = (uint32_t)nrows * (uint32_t)p.Kc * 2u;
+  const uint32_t a_rows_bytes = (uint32_t)nlive * (uint32_t)p.Kc * 2u;     // (rows past the last token are not fetched)
   const bf16_t* a_base = (NT && (ia3 || tuning)) ? p.AinScaled + (size_t)(tk.zrow0 + row0 - tk.row_begin) * p.Kc
                                      : p.Ain + (size_t)row0 * p.Kc;
   const rsrc_t rA = make_rsrc(a_base, a_rows_bytes);
@@ -734,16 +763,37 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   __shared__ int sRow[256];
   const Smem sm = {sA0, sA1, sB0, sB1, sRow, sE0, sE1, sE2, sE3, (uint32_t)(uintptr_t)(lds_void_ptr)sP, sOff};
   const int b = blockIdx.x;
+  if (b >= p.clear0) {                            // a row group without tokens: 2048 columns of its output rows
+    const int slabs = (p.Nc + 2047) / 2048, d = b - p.clear0;
+    const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + p.n_mh + d / slabs) * DI_WORDS);
+    const int c = (d % slabs) * 2048 + (threadIdx.x & 255) * 8;
+    if (c < p.Nc)
+      for (int m = threadIdx.x >> 8; m < iw.z; m += 2) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
+    if (FUSE && d % slabs == 0 && p.HsOut != nullptr)
+      for (int e = threadIdx.x; e < iw.z * (p.RP / 8); e += 512)
+        *(uint4*)(p.HsOut + (size_t)(iw.y + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
+    return;
+  }
   // the start stamps wait in the buffer itself (words 2, 3), so that nothing stays live across the tile
   if (p.clk != nullptr && b == 0 && threadIdx.x == 0) { p.clk[2] = clock64(); p.clk[3] = wall_clock64(); }
   if (!FUSE && b < p.n_full) {                    // a launch with the down-projection in the loop has pieces only
-    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, b, 0, 0, sm);
-  } else if (p.tail_split == 2) {
+    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, 0, p.n_m, p.per_xcd, b, 0, 0, sm);
+  } else if (b < p.half0 && p.tail_split == 2) {
     const int t = b - p.n_full;                                       // n_full is a multiple of 8
-    gemm_tile<NT, 4, 4, 1, FUSE, DIFFP, TAIL>(p, p.n_full + (((t >> 4) << 3) | (t & 7)), (t >> 3) & 1, 0, sm);
+    gemm_tile<NT, 4, 4, 1, FUSE, DIFFP, TAIL>(p, 0, p.n_m, p.per_xcd, p.n_full + (((t >> 4) << 3) | (t & 7)), (t >> 3) & 1,
+                                              0, sm);
   } else {
-    const int t = b - p.n_full;
-    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, TAIL>(p, p.n_full + (((t >> 5) << 3) | (t & 7)), (t >> 3) & 1, (t >> 4) & 1, sm);
+    // a quarter of a tile left over, or of one whose row group has tokens in its first 128 rows only
+    const bool hg = b >= p.half0;
+    const int t = b - (hg ? p.half0 : p.n_full);
+    const int mhalf = hg ? 0 : (t >> 4) & 1;
+    if (hg && threadIdx.x >= 256) {                // the four waves that a quarter does not need clear the padding below it
+      clear_below(p, ((t >> 4) << 3) | (t & 7), (t >> 3) & 1);
+      return;
+    }
+    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, TAIL>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, hg ? p.per_xcd_h : p.per_xcd,
+                                              hg ? (((t >> 4) << 3) | (t & 7)) : p.n_full + (((t >> 5) << 3) | (t & 7)),
+                                              (t >> 3) & 1, mhalf, sm);
   }
   if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
     atomicAdd(p.clk, (unsigned long long)clock64() - p.clk[2]);
@@ -762,27 +812,32 @@ int compute_units() {
   return n;
 }
 
-// The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters.
-struct TilePlan { int n_m, n_n, per_xcd, n_full, tail_split, grid; };
+// The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters, then the
+// quarters of the row groups with tokens in their first 128 rows only, then the clearing of those without any.
+struct TilePlan { int n_m, n_mh, n_n, per_xcd, per_xcd_h, n_full, tail_split, half0, clear0, grid; };
 TilePlan plan_tiles(const CallCtx& c, int Nc) {
   TilePlan t{};
-  t.n_m = (int)c.st->items[TS256].size();
+  t.n_m = c.st->n_gemm[0];
+  t.n_mh = c.st->n_gemm[1];
   t.n_n = (Nc + TILE_N - 1) / TILE_N;
   const int total = t.n_m * t.n_n;
   t.per_xcd = (total + 7) / 8;
+  t.per_xcd_h = (t.n_mh * t.n_n + 7) / 8;
   // One workgroup per compute unit at a time: the tiles left after the last full round would keep a fraction of
-  // the units busy for a whole tile time.  When they fit four times, they run as quarters, when twice, as
-  // half-width tiles.
+  // the units busy for a whole tile time.  When they fit four times (beside the quarters that follow), they run as
+  // quarters, when twice, as half-width tiles.
   static const bool no_halves = getenv("MUX_GEMM_NO_HALF_TILES") != nullptr;
   static const bool no_quarters = getenv("MUX_GEMM_NO_QUARTER_TILES") != nullptr;
   const int ncu = compute_units();
   const int full_slots = (total / ncu) * (ncu / 8);          // per-XCD slots covered by whole rounds
-  const int rem = total - full_slots * 8;
+  const int rem = total - full_slots * 8, more = 2 * t.n_mh * t.n_n;
   int tail_slots = 0;
-  if (!no_halves && ncu % 8 == 0 && rem > 0 && 2 * rem <= ncu) tail_slots = t.per_xcd - full_slots;
-  t.tail_split = (!no_quarters && 4 * rem <= ncu) ? 4 : 2;
+  if (!no_halves && ncu % 8 == 0 && rem > 0 && 2 * rem + more <= ncu) tail_slots = t.per_xcd - full_slots;
+  t.tail_split = (!no_quarters && 4 * rem + more <= ncu) ? 4 : 2;
   t.n_full = 8 * (t.per_xcd - tail_slots);
-  t.grid = t.n_full + 8 * t.tail_split * tail_slots;
+  t.half0 = t.n_full + 8 * t.tail_split * tail_slots;
+  t.clear0 = t.half0 + 16 * t.per_xcd_h;
+  t.grid = t.clear0 + c.st->n_gemm[2] * ((Nc + 2047) / 2048);
   return t;
 }
 
@@ -794,12 +849,14 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.Zsave = Zsave; p.Kc = Kc; p.Nc = Nc; p.RP = c.RP;
   p.HsOut = fuse_down ? (bf16_t*)Ext : nullptr;
   const TilePlan t = plan_tiles(c, Nc);
+  p.items_off = c.st->dev_image[DH_OFF_GEMM_ITEMS];
   p.n_m = t.n_m; p.n_n = t.n_n; p.per_xcd = t.per_xcd; p.n_full = t.n_full; p.tail_split = t.tail_split;
+  p.n_mh = t.n_mh; p.per_xcd_h = t.per_xcd_h; p.half0 = t.half0; p.clear0 = t.clear0;
   p.AinScaled = (const bf16_t*)c.dYs;
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
   p.DiffPack = (const uint32_t*)c.diffPack;
   p.clk = diag_clock_buffer();
-  if (t.n_m * t.n_n == 0) return MUX_OK;
+  if (t.grid == 0) return MUX_OK;
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
   const char* name = NT ? "gemm_nt" : "gemm_nn";
@@ -834,7 +891,7 @@ bool gemm_dma_fuses_down(const CallCtx& c) {
   if (mode == 0) return false;
   if (c.st->n_lora == 0 || c.st->n_tuning > 0 || c.st->r_max > 32 || c.diffPack != nullptr) return false;
   const TilePlan t = plan_tiles(c, c.N);
-  if (t.n_full != 0 || t.n_m * t.n_n == 0) return false;
+  if (t.n_full != 0 || (t.n_m + t.n_mh) * t.n_n == 0) return false;
   return t.tail_split == 4 || mode == 2;
 }
 

@@ -21,6 +21,8 @@ enum : int {
   DH_ATT_OFF_BWD,        // list ordered for the pass that walks the queries after a block; 4 words an entry (DA_*)
   DH_OFF_ITEM_TOK0,      // per 64-row work item: how many tokens of its task lie on the rows before it
   DH_OFF_ITEM_BITS,      // per 64-row work item: two words, bit r = row row0 + r of the item is a real token
+  DH_OFF_GEMM_ITEMS,     // the 256-row work items ordered for the backbone product (see mux_segtab::n_gemm), DI_WORDS each,
+                         // with the rows up to the last real token in the place of DI_NVALID
   DH_HDR_WORDS = 32
 };
 constexpr int kNumTileSizes = 4;
@@ -93,6 +95,9 @@ struct mux_segtab {
   int32_t n_attn_blocks128 = 0, n_attn_blocks64 = 0;   // those of sequences of 65..128 and of at most 64 tokens (one each)
   std::vector<mux::Item> items[mux::kNumTileSizes];
   std::vector<int32_t> task_item_begin[mux::kNumTileSizes], task_item_count[mux::kNumTileSizes];
+  // 256-row work items by what the backbone product has to compute of them: those with a real token past their first
+  // 128 rows, those with real tokens in the first 128 rows only, those without any
+  int32_t n_gemm[3] = {0, 0, 0};
 };
 
 namespace mux {

@@ -248,6 +248,20 @@ extern "C" mux_status mux_segtab_build(const mux_task_desc* tasks, int32_t n_tas
         dv.push_back((int32_t)w[1]);
       }
     }
+    // the 256-row items in the order of n_gemm, inside a class as they lie in the batch
+    {
+      while (dv.size() % 4) dv.push_back(0);
+      dv[DH_OFF_GEMM_ITEMS] = (int32_t)dv.size();
+      for (int cls = 0; cls < 3; ++cls)
+        for (const Item& it : st->items[2]) {
+          int32_t live = it.task >= 0 ? it.nrows : 0;
+          while (live > 0 && st->row_task[it.row0 + live - 1] < 0) --live;
+          if ((live > 128 ? 0 : live > 0 ? 1 : 2) != cls) continue;
+          st->n_gemm[cls]++;
+          const int32_t w[DI_WORDS] = {it.task, it.row0, it.nrows, live};
+          dv.insert(dv.end(), w, w + DI_WORDS);
+        }
+    }
     // Dispatch: the packed position of a task's token = the number of the task's tokens on the rows before it
     {
       dv[DH_OFF_ITEM_TOK0] = (int32_t)dv.size();

@@ -145,6 +145,21 @@ def test_gemm_last_round_pieces(env, n_items):
     run_case(env, wl, seed=n_items, cols=np.unique(cols), kcols=np.unique(kcols))
 
 
+@pytest.mark.parametrize("K,N", [(512, 768), (4096, 4096)])
+def test_gemm_row_groups_with_padding(env, K, N):
+    """Row groups of 256 by what the backbone GEMM computes of them: tokens past the first 128 rows, in the first 128 only
+    (1, 127 and 128 tokens, and two short chunks), none at all (in the middle of a task, at its end, after the last one):
+    pieces with the down-projection in the loop, and whole tiles beside quarters."""
+    rep = 1 if K == 512 else 5                           # 75 groups of 16 column tiles: more than four full rounds
+    kinds = [(wlm.KIND_LORA, 16, 2.0), (wlm.KIND_IA3, 0, 1.0), (wlm.KIND_LORA, 8, 0.5), (wlm.KIND_NONE, 0, 1.0)]
+    lens = [[1], [1024 + 127], [512 + 128], [700 * rep, 129]]
+    tasks = [wlm.Task(k, r, sc, [n * (rep if i == 1 else 1) for n in lens[i]]) for i, (k, r, sc) in enumerate(kinds)]
+    wl = wlm.Workload(name=f"groups{K}", layers=[("w", K, N)], tasks=tasks, chunk=1024, sigma_w=0.05, sigma_ab=0.05)
+    rng = np.random.default_rng(K)
+    cols, kcols = (np.unique(np.concatenate([rng.choice(n, 120, replace=False), [0, 127, 128, n - 1]])) for n in (N, K))
+    run_case(env, wl, seed=K, cols=cols, kcols=kcols)
+
+
 def test_mfma_probe_runs(env):
     """The diagnostic MFMA loop: launches, reports its FLOP count, leaves finite sums (operands 1 and 0.5: every
     accumulator element of a loop turn grows by 8 products of 16 terms of 0.5), rejects bad arguments."""
