@@ -249,10 +249,14 @@ void launch_down(const CallCtx& c, const char* name, DownParams p) {
   p.bits_off = c.st->dev_image[DH_OFF_ITEM_BITS];
   p.tasks = *c.tref;
   const unsigned items = (unsigned)c.st->items[TS64].size();
-  // eight waves split the contraction (four for ranks above 32, whose LDS regions are larger); two slabs in flight
-  if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2>), dim3(items * 2), dim3(512), 0, c.stream, p);
-  else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2>), dim3(items * 2), dim3(512), 0, c.stream, p);
-  else MUX_LAUNCH(name, (k_down<4, 4, 2>), dim3(items * 2), dim3(256), 0, c.stream, p);
+  // Eight waves split the contraction; two slabs in flight.  Ranks above 32 need LDS regions of 14 KB a wave: eight waves
+  // leave room for one workgroup a compute unit, four for two.  So they take eight where a unit has one workgroup or none
+  // (84 items at 4096: 18.6 -> 15.1 us) and four beyond (324 items: 61.7 us, eight waves 63.6).
+  const dim3 grid(items * 2);
+  if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2>), grid, dim3(512), 0, c.stream, p);
+  else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2>), grid, dim3(512), 0, c.stream, p);
+  else if (items * 2 <= 256) MUX_LAUNCH(name, (k_down<4, 8, 2>), grid, dim3(512), 0, c.stream, p);
+  else MUX_LAUNCH(name, (k_down<4, 4, 2>), grid, dim3(256), 0, c.stream, p);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -832,67 +836,95 @@ __global__ __launch_bounds__(512) void k_dl(const int32_t* __restrict__ dtab, co
 }
 
 // ------------------------------------------------------------------------------------------------
-// out_t = (accumulate ? out_t : 0) + sum over the task's items, ascending.  grid = (tasks, blocks over the elements).
-// LoRA and Adapter-Tuning tasks: elements [0, r*N) are dB_t [r][N] from part0, elements [r*N, r*(N+K)) are dA_t from
-// part1, stored transposed as [K][r].  IA3_OUT tasks: dl_t [N] from part_ia3 (one row per 64-row item).
-__global__ __launch_bounds__(256) void k_reduce(const int32_t* __restrict__ dtab, const TaskRef tasks,
-                                               const float* __restrict__ part0, const float* __restrict__ part1,
-                                               const float* __restrict__ part_ia3, int N, int K,
-                                               int RP, int ts0, int ts1, int accumulate, size_t slot0, size_t slot1) {
+// out_t = (accumulate ? out_t : 0) + sum over the task's items, ascending.  grid = (tasks, blocks).
+// LoRA and Adapter-Tuning tasks: the first blocks take 1024 elements of dB_t [r][N] each, from part0; the blocks after
+// them dA_t, whose partials in part1 are [r][K] and which is stored [K][r]: such a block takes all r of
+// reduce_cols(r) columns, so that it writes one contiguous run of dA_t.  IA3_OUT tasks: dl_t [N] from part_ia3 (one row
+// per 64-row item).
+// Bound by the latency of a few dependent loads and, before blocks wrote whole runs of dA_t, by stores of 4 bytes at a
+// stride of r floats: 32 tasks of rank 16, 8192 x 1024 and 1024 x 8192, 29.2 -> 14.7 us a launch; 16 tasks of rank 8 to
+// 64 at 4096 x 4096, 31.4 -> 18.4 us; two tasks at 256 x 256, 4.1 -> 2.9 us.
+__host__ __device__ __forceinline__ int reduce_cols(int rank) {     // columns of dA_t a block takes: rank * columns <= 1024
+  const int n = (1024 / rank) & ~3;
+  return n < 4 ? 4 : n;
+}
+struct ReduceParams {
+  const int32_t* dtab;
+  const float *part0, *part1, *part_ia3;
+  int N, K, accumulate;
+  int items_off[3], task_items_off[3];       // word offsets in dtab of the row groups of part0, part1 and part_ia3
+  size_t slot0, slot1;                       // elements per row group in part0, part1
+  TaskRef tasks;
+};
+__global__ __launch_bounds__(256) void k_reduce(const ReduceParams p) {
+  __shared__ float sT[2048];                 // the block's piece of dA_t, [columns][r + 1]
   const int t = blockIdx.x;
-  const DevTask tk = get_task(tasks, t);
+  const DevTask tk = get_task(p.tasks, t);
   const bool ranked = tk.kind == MUX_ADAPTER_LORA || tk.kind == MUX_ADAPTER_TUNING;
   if (!ranked && tk.kind != MUX_ADAPTER_IA3_OUT) return;
-  const int mode = ranked ? 0 : 1;
-  if (mode == 1) { part0 = part_ia3; slot0 = (size_t)N; ts0 = TS64; }
-  if (tk.kind == MUX_ADAPTER_TUNING) K = N;    // its first gradient is dD_t [N][r]
-  const int rows = mode == 1 ? 1 : tk.rank;
-  size_t e = ((size_t)blockIdx.y * 256 + threadIdx.x) * 4;     // four consecutive elements of one row (N, K multiples of 4)
-  const float* part = part0;
-  int C = N;
-  float* out = mode == 1 ? tk.dL : tk.dB;
-  bool transposed = false;
-  size_t slot = slot0;
-  int ts = ts0;                                // row-group size of the partials: the two passes choose their own
-  if (mode == 0 && e >= (size_t)rows * N) {
-    e -= (size_t)rows * N;
-    part = part1; C = K; out = tk.dA; transposed = true; slot = slot1; ts = ts1;
-  }
-  if (!out || e >= (size_t)rows * C) return;
-  const int j = (int)(e / C), c = (int)(e % C);
-  const int32_t* ti = dtab + dtab[DH_NITEMS0 + 3 * ts + 2] + 2 * t;
+  const int rows = ranked ? tk.rank : 1, N = p.N;
+  const int nb0 = (int)(((size_t)rows * N + 1023) / 1024);
+  const bool transposed = (int)blockIdx.y >= nb0;
+  if (transposed && !ranked) return;
+  const int which = !ranked ? 2 : (transposed ? 1 : 0);
+  const int C = (transposed && tk.kind != MUX_ADAPTER_TUNING) ? p.K : N;    // the first gradient of Adapter-Tuning is dD_t [N][r]
+  float* out = !ranked ? tk.dL : (transposed ? tk.dA : tk.dB);
+  const float* part = which == 0 ? p.part0 : (which == 1 ? p.part1 : p.part_ia3);
+  const size_t slot = which == 0 ? p.slot0 : (which == 1 ? p.slot1 : (size_t)N);
+  const int cols = transposed ? reduce_cols(rows) : 0, c0 = transposed ? ((int)blockIdx.y - nb0) * cols : 0;
+  if (!out || (transposed && c0 >= C)) return;
+  // four consecutive elements of one row of the partials a thread (N, K multiples of 4)
+  const int tid = threadIdx.x;
+  const size_t e = ((size_t)blockIdx.y * 256 + tid) * 4;                    // in dB_t or dl_t
+  const int j_t = transposed ? tid / (cols >> 2) : 0, ct = transposed ? (tid % (cols >> 2)) * 4 : 0;
+  const bool mine = transposed ? (j_t < rows && c0 + ct < C) : e < (size_t)rows * C;
+  const size_t at = transposed ? (size_t)j_t * C + c0 + ct : e;             // in a row group's partials
+  const int32_t* ti = p.dtab + p.task_items_off[which] + 2 * t;
   const int ib = ti[0], ic = ti[1];
-  const int32_t* items = dtab + dtab[DH_NITEMS0 + 3 * ts + 1];
+  const int32_t* items = p.dtab + p.items_off[which];
   // four items in flight (a thread that fetched them one by one would wait a memory latency per item); an item
   // without valid rows holds no partial and adds an exact zero; the sum runs in ascending item order
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int q = 0; q < ic; q += 4) {
-    float4 v[4];
+  if (mine)
+    for (int q = 0; q < ic; q += 4) {
+      float4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const bool has = q + u < ic && items[(ib + q + u) * DI_WORDS + DI_NVALID] != 0;
-      v[u] = has ? *(const float4*)(part + (size_t)(ib + q + u) * slot + (size_t)j * C + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int u = 0; u < 4; ++u) {
+        const bool has = q + u < ic && items[(ib + q + u) * DI_WORDS + DI_NVALID] != 0;
+        v[u] = has ? *(const float4*)(part + (size_t)(ib + q + u) * slot + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
-  }
   if (transposed) {
-    float* dst = out + (size_t)c * rows + j;
-    dst[0] = accumulate ? dst[0] + s.x : s.x;
-    dst[rows] = accumulate ? dst[rows] + s.y : s.y;
-    dst[2 * (size_t)rows] = accumulate ? dst[2 * (size_t)rows] + s.z : s.z;
-    dst[3 * (size_t)rows] = accumulate ? dst[3 * (size_t)rows] + s.w : s.w;
-  } else if (((uintptr_t)out & 15) == 0) {
+    const int pitch = rows + 1;
+    if (mine) {
+      sT[ct * pitch + j_t] = s.x;
+      sT[(ct + 1) * pitch + j_t] = s.y;
+      sT[(ct + 2) * pitch + j_t] = s.z;
+      sT[(ct + 3) * pitch + j_t] = s.w;
+    }
+    __syncthreads();
+    const int n = (C - c0 < cols ? C - c0 : cols) * rows;
+    float* dst = out + (size_t)c0 * rows;
+    for (int i = tid; i < n; i += 256) {
+      const float v = sT[(i / rows) * pitch + i % rows];
+      dst[i] = p.accumulate ? dst[i] + v : v;
+    }
+    return;
+  }
+  if (!mine) return;
+  if (((uintptr_t)out & 15) == 0) {
     float4* dst = (float4*)(out + e);
     float4 o = s;
-    if (accumulate) { const float4 d = *dst; o.x += d.x; o.y += d.y; o.z += d.z; o.w += d.w; }
+    if (p.accumulate) { const float4 d = *dst; o.x += d.x; o.y += d.y; o.z += d.z; o.w += d.w; }
     *dst = o;
   } else {                                     // a gradient buffer of the caller that is only 4-byte aligned
     float* dst = out + e;
-    dst[0] = accumulate ? dst[0] + s.x : s.x;
-    dst[1] = accumulate ? dst[1] + s.y : s.y;
-    dst[2] = accumulate ? dst[2] + s.z : s.z;
-    dst[3] = accumulate ? dst[3] + s.w : s.w;
+    dst[0] = p.accumulate ? dst[0] + s.x : s.x;
+    dst[1] = p.accumulate ? dst[1] + s.y : s.y;
+    dst[2] = p.accumulate ? dst[2] + s.z : s.z;
+    dst[3] = p.accumulate ? dst[3] + s.w : s.w;
   }
 }
 
@@ -999,35 +1031,41 @@ mux_status adapter_grads(const CallCtx& c, const void* X, const void* dY, const 
   float* part_ia3 = (float*)((char*)part + pl.gpart + pl.part0 + pl.part1);
   const size_t slot0 = (size_t)c.RP * c.N, slot1 = (size_t)c.RP * K1;
   double moved = 0.0;       // what the reduction moves: every row group's partials once in, the gradients once out
-  size_t elems = 0;
+  int blocks = 0;           // of the reduction, the most a task has
   if (ranked) {
     GradParams p{c.dtab, {(const bf16_t*)Hs, (const bf16_t*)Gs}, {(const bf16_t*)dY, (const bf16_t*)X}, {part0, part1},
                  {c.N, c.K}, c.RP, ts_a, (const bf16_t*)Z, {slot0, slot1}, 1,
                  c.st->dev_image[DH_NITEMS0 + 3 * ts_a + 1], c.st->dev_image[DH_OFF_ROWBITS], c.st->T};
     p.tasks = *c.tref;
     launch_grad(c, "grad_da", p, dim3((unsigned)c.st->items[ts_a].size(), (K1 + 255) / 256, 1));
-    elems = (size_t)c.st->r_max * ((size_t)c.N + K1);
     for (const HostTask& ht : c.st->tasks)
       if (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) {
-        const double kk = ht.kind == MUX_ADAPTER_TUNING ? c.N : c.K;
+        const int kk = ht.kind == MUX_ADAPTER_TUNING ? c.N : c.K;
+        const int nb = (int)(((size_t)ht.rank * c.N + 1023) / 1024) + (kk + reduce_cols(ht.rank) - 1) / reduce_cols(ht.rank);
+        if (nb > blocks) blocks = nb;
         const double gb = (ht.row_count + kTileRows[ts_b] - 1) / kTileRows[ts_b], ga = (ht.row_count + kTileRows[ts_a] - 1) / kTileRows[ts_a];
-        moved += 4.0 * ht.rank * (gb * c.N + ga * kk) + 4.0 * ht.rank * (c.N + kk) * (accumulate ? 2 : 1);
+        moved += 4.0 * ht.rank * (gb * c.N + ga * kk) + 4.0 * ht.rank * ((double)c.N + kk) * (accumulate ? 2 : 1);
       }
   }
   if (c.st->n_ia3 > 0) {
     MUX_LAUNCH("grad_dl", k_dl, dim3((unsigned)c.st->items[TS64].size(), (c.N + 1023) / 1024), dim3(512), 0, c.stream,
                c.dtab, *c.tref, (const bf16_t*)dY, (const bf16_t*)Z, part_ia3, (bf16_t*)c.dYs, c.N,
                c.st->dev_image[DH_NITEMS0 + 3 * TS64 + 1], c.st->dev_image[DH_OFF_ITEM_BITS]);
-    if ((size_t)c.N > elems) elems = (size_t)c.N;
+    if ((c.N + 1023) / 1024 > blocks) blocks = (c.N + 1023) / 1024;
     for (const HostTask& ht : c.st->tasks)
       if (ht.kind == MUX_ADAPTER_IA3_OUT) moved += 4.0 * c.N * ((ht.row_count + 63) / 64) + 4.0 * c.N * (accumulate ? 2 : 1);
   }
-  if (elems > 0) {
+  if (blocks > 0) {
     // one reduction for every kind: a task's workgroups take the sums its kind has
+    ReduceParams p{c.dtab, part0, part1, part_ia3, c.N, c.K, accumulate, {}, {}, slot0, slot1};
+    const int ts[3] = {ts_b, ts_a, TS64};
+    for (int i = 0; i < 3; ++i) {
+      p.items_off[i] = c.st->dev_image[DH_NITEMS0 + 3 * ts[i] + 1];
+      p.task_items_off[i] = c.st->dev_image[DH_NITEMS0 + 3 * ts[i] + 2];
+    }
+    p.tasks = *c.tref;
     prof_note_bytes(moved);
-    MUX_LAUNCH("reduce_grads", k_reduce, dim3(M, (unsigned)((elems + 1023) / 1024)), dim3(256), 0, c.stream, c.dtab, *c.tref,
-               (const float*)part0, (const float*)part1, (const float*)part_ia3, c.N, c.K, c.RP, ts_b, ts_a, accumulate,
-               slot0, slot1);
+    MUX_LAUNCH("reduce_grads", k_reduce, dim3(M, (unsigned)blocks), dim3(256), 0, c.stream, p);
   }
   return MUX_OK;
 }

@@ -119,6 +119,29 @@ def test_contraction_tails_and_odd_ranks(env, K, N):
         assert torch.equal(g.Y, y) and torch.equal(g.dX, dx)
 
 
+@pytest.mark.parametrize("K,N", [(264, 136), (1032, 520)])
+def test_gradient_reduction_blocks(env, K, N):
+    """The blocks that bring the partial gradients together: as many columns of dA_t as a rank leaves room for (ranks 1 to
+    64, column counts that leave the last block ragged), gradient buffers that are 4-byte aligned only, overwritten and
+    added to."""
+    mx, torch = env
+    kinds = [(wlm.KIND_LORA, r) for r in (1, 3, 12, 63, 64, 16)] + [(wlm.KIND_ADAPTER, 7), (wlm.KIND_IA3, 0)]
+    wl = wlm.Workload(name=f"reduce{K}", layers=[("w", K, N)], chunk=64, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(k, r, 2.0, [40 + 150 * i]) for i, (k, r) in enumerate(kinds)])
+    g, got, ref, errs = run_case(env, wl, seed=K)
+    for k in ("dA", "dB", "dL"):
+        first = getattr(g, k)
+        odd = [None if t is None else torch.ones(t.numel() + 1, device=t.device)[1:] for t in first]
+        setattr(g, k, odd)
+        g.backward(accumulate=1)
+        g.backward(accumulate=1)
+        torch.cuda.synchronize()
+        for a, b in zip(first, odd):
+            assert a is None or torch.equal(b, (a.flatten() + 1.0) + a.flatten()), k
+        setattr(g, k, first)
+        g.backward()
+
+
 @pytest.mark.parametrize("n_items", [16, 20, 23, 28])
 def test_gemm_last_round_pieces(env, n_items):
     """The backbone GEMM cuts the tiles left after the last full round of workgroups (one per compute unit) into
