@@ -63,6 +63,7 @@ struct Layout {
   int RP;              // H / G row pitch in elements
   size_t h_bytes, z_bytes, u2_bytes, saved_bytes;
   size_t tasks_bytes, g_bytes, at_bytes, dys_bytes, part_bytes, dt_bytes, dw_bytes, dp_bytes, ws_bytes;
+  size_t split_bytes;  // beyond ws_bytes: partial tiles of split backbone products; a call without this room splits none
   int dw_slots;        // DIFF tasks with entries: each gets room for its merged weight (matrix-core path)
 };
 
@@ -115,6 +116,11 @@ Layout make_layout(const mux_layer_desc* L, const mux_segtab* st) {
   }
   o.dw_bytes = (size_t)o.dw_slots * diff_merged_bytes(L->K, L->ldw);
   o.ws_bytes = o.tasks_bytes + o.g_bytes + o.at_bytes + o.dys_bytes + o.part_bytes + 2 * o.dt_bytes + o.dw_bytes + o.dp_bytes;
+  // (not past the size of the library's static workspace, which has to serve the calls it served without them, and alike)
+  const bool fast = L->dtype == MUX_DT_BF16 && !(L->flags & MUX_LAYER_REFERENCE_KERNELS) && L->K % 8 == 0 && L->N % 8 == 0;
+  o.split_bytes = fast ? gemm_split_bytes(L->K, L->N, st) : 0;
+  const size_t room = o.ws_bytes < MUX_STATIC_WS_BYTES ? (MUX_STATIC_WS_BYTES - o.ws_bytes) & ~size_t(255) : 0;
+  if (o.split_bytes > room) o.split_bytes = room;
   return o;
 }
 
@@ -243,14 +249,15 @@ extern "C" size_t mux_lora_saved_bytes(const mux_layer_desc* layer, const mux_se
 
 extern "C" size_t mux_lora_workspace_bytes(const mux_layer_desc* layer, const mux_segtab* st) {
   if (!layer || !st || layer->N <= 0 || layer->K <= 0) return 0;
-  return make_layout(layer, st).ws_bytes;
+  const Layout lo = make_layout(layer, st);
+  return lo.ws_bytes + lo.split_bytes;
 }
 
 namespace {
 
 // Everything a call's kernels share, from the layer, the table and the carved workspace.
 CallCtx make_ctx(const mux_layer_desc* layer, const mux_segtab* st, const void* dev_segtab, const Layout& lo, void* ws,
-                 const void* saved, hipStream_t stream) {
+                 size_t ws_bytes, const void* saved, hipStream_t stream) {
   CallCtx c{};
   c.st = st;
   c.dtab = (const int32_t*)dev_segtab;
@@ -266,6 +273,8 @@ CallCtx make_ctx(const mux_layer_desc* layer, const mux_segtab* st, const void* 
   c.diffPack = nullptr;
   c.diffW_stride = (int64_t)(diff_merged_bytes(layer->K, layer->ldw) / 2);
   c.diffW_slots = lo.dw_slots;
+  c.split = (char*)ws + lo.ws_bytes;
+  c.split_room = ws_bytes >= lo.ws_bytes + lo.split_bytes ? lo.split_bytes : 0;
   return c;
 }
 
@@ -282,7 +291,7 @@ extern "C" mux_status mux_lora_forward(const mux_layer_desc* layer, const mux_se
   if (!saved && (st->n_lora > 0 || st->n_tuning > 0))
     return fail(MUX_ERR_INVALID_ARG, std::string(fn) + ": saved is null but a task is LoRA or Adapter-Tuning");
   hipStream_t stream = (hipStream_t)hip_stream;
-  CallCtx c = make_ctx(layer, st, dev_segtab, lo, ws, saved, stream);
+  CallCtx c = make_ctx(layer, st, dev_segtab, lo, ws, ws_bytes, saved, stream);
   void* H = saved;
   void* Z = (saved && st->z_rows > 0) ? (char*)saved + lo.h_bytes : nullptr;
   // the matrix-core kernels, unless the storage type, the flag, a shape or a pointer rules them out: then the plain ones
@@ -321,7 +330,7 @@ static mux_status backward_impl(const char* fn, const mux_layer_desc* layer, con
   const Layout lo = make_layout(layer, st);
   if (ws_bytes < lo.ws_bytes) return fail(MUX_ERR_WORKSPACE, std::string(fn) + ": workspace too small");
   hipStream_t stream = (hipStream_t)hip_stream;
-  CallCtx c = make_ctx(layer, st, dev_segtab, lo, ws, saved, stream);
+  CallCtx c = make_ctx(layer, st, dev_segtab, lo, ws, ws_bytes, saved, stream);
   const void* H = saved;
   const void* Z = (saved && st->z_rows > 0) ? (const char*)saved + lo.h_bytes : nullptr;
   void* G = (char*)ws + lo.tasks_bytes;

@@ -66,6 +66,8 @@ struct GemmParams {
   int half0, clear0;       // first workgroups of the pieces of such groups, and of those that clear the groups without tokens
   int n_full;              // workgroups that compute full tiles (a multiple of 8); the rest compute pieces of tiles
   int tail_split;          // pieces per tile after the full ones: 2 (halves) or 4 (quarters)
+  float* Part;             // partial tiles of a split contraction: [splits][quarters][128 * 128] fp32, in accumulator order
+  int splits, quarters;    // pieces of the contraction, each a workgroup of its own (1: none); quarters of the launch then
   unsigned long long* clk;  // diagnostic: counters workgroup 0 adds its elapsed cycles and 100 MHz ticks to (null: off)
   const uint32_t* DiffPack; // entries of the Diff-Pruning masks packed for this launch (index << 16 | bf16 value), or null
   const bf16_t* Wdiff;      // merged weights W + M_t * delta_t of the Diff-Pruning tasks, `wdiff_stride` elements apart (or null)
@@ -151,6 +153,16 @@ __device__ __forceinline__ void clear_below(const GemmParams& p, int xcd_slot, i
       *(uint4*)(p.HsOut + (size_t)(iw.y + 128 + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
 }
 
+// Quarter q of a split launch (whose parameters put all tiles in one run: tile L is slot 8 L): true: of a row group with tokens in its first 128 rows only.
+__device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, int& half, int& mhalf) {
+  const int q0 = 4 * p.n_m * p.n_n;
+  const bool hg = q >= q0;
+  half = q & 1;
+  mhalf = hg ? 0 : (q >> 1) & 1;
+  L = hg ? (q - q0) >> 1 : q >> 2;
+  return hg;
+}
+
 // One output tile.  WNW = waves along N, MI x NI = 32x32 MFMA tiles per wave; 2*WNW waves on a
 // BMT x BN tile with BMT = 2*MI*32 and BN = WNW*NI*32:
 //   <4,4,2> eight waves (two per SIMD), 128x64 per wave, the full 256x256 tile;
@@ -172,9 +184,13 @@ __device__ __forceinline__ void clear_below(const GemmParams& p, int xcd_slot, i
 // and the launch brings them packed, (contraction index % 64) << 23 | (line % 128) << 16 | bf16 value.  The entries
 // of a K-tile travel with it: every loading wave fetches 64 of them straight into LDS with the tile's other loads
 // (256 a tile; a bucket pair with more reads the rest from memory when the tile is patched).
-template <bool NT, int WNW, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false>
+// SPLITK (quarters): the tile's `split`-th share of its K-tiles only; the accumulators go to p.Part as they lie in the
+// registers (slot: the quarter's number), for k_gemm_sum.
+template <bool NT, int WNW, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int per_xcd,
-                                          const int xcd_slot, const int half, const int mhalf, const Smem sm) {
+                                          const int xcd_slot, const int half, const int mhalf, const Smem sm,
+                                          const int split = 0, const int slot = 0) {
+  static_assert(!SPLITK || (!FUSE && !DIFFP && MI == 2 && NI == 2), "SPLITK: quarters, the plain loop");
   static_assert(!FUSE || (!NT && WNW == MI && !(MI == 4 && NI == 2)), "FUSE: forward, half or quarter tiles");
   static_assert(!DIFFP || !FUSE, "DIFFP: not with FUSE");
   constexpr int BN = WNW * NI * 32;
@@ -255,6 +271,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const int k_tail = p.Kc - (KT - 1) * BK;          // TAIL: contraction indices in the last backbone tile (a multiple of 8)
   const int KT_ext = lora ? (rank + BK - 1) / BK : 0;
   const int KT_total = KT + KT_ext;
+  const int kt_first = SPLITK ? (int)((unsigned)(split * KT_total) / (unsigned)p.splits) : 0;
+  const int kt_end = SPLITK ? (int)((unsigned)((split + 1) * KT_total) / (unsigned)p.splits) : KT_total;
   const bool fuse_h = FUSE && lora;                 // this tile forms Hs of its rows in the K loop
   // DIFFP: the bucket offsets of this task's listing for this direction, the buckets of this tile in a K-tile's row
   // of buckets, and per stage the entries of the tile it holds: first, first of the second bucket, end
@@ -339,14 +357,18 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   // to the adapter operands (Ext rows and B_t / A_t), whose offsets restart from zero; past the last tile
   // everything is parked out of range (zeros land in a stage nobody reads).
   rsrc_t curA = rA, curB = rW;
-  uint32_t kA = 0, kB = 0, stepA = BK * 2u, stepB = NT ? BK * 2u : (uint32_t)((size_t)BK * p.ldw * 2);
-  int next_tile = 0;                                          // index of the tile the next issue() fetches
+  uint32_t stepA = BK * 2u, stepB = NT ? BK * 2u : (uint32_t)((size_t)BK * p.ldw * 2);
+  uint32_t kA = (uint32_t)kt_first * stepA, kB = (uint32_t)kt_first * stepB;
+  int next_tile = kt_first;                                          // index of the tile the next issue() fetches
 
   // uniform, rarely taken: everything that changes at a tile-kind boundary
-  const int special = TAIL ? KT - 1 : KT;                     // the first tile that is not like the ones before it
+  const int odd_tile = TAIL ? KT - 1 : KT;                    // the first tile that is not like the ones before it
+  const int special = SPLITK && kt_end < odd_tile ? kt_end : odd_tile;
   auto prepare = [&]() {
     if (next_tile < special) return;
-    if (TAIL && next_tile == KT - 1) {                                // the last backbone tile is not full: pieces past the end
+    if (SPLITK && next_tile >= kt_end) {                      // the next share's: nothing to fetch
+      kA = OOB; kB = OOB;
+    } else if (TAIL && next_tile == KT - 1) {                                // the last backbone tile is not full: pieces past the end
 #pragma unroll
       for (int q = 0; q < ACH; ++q)
         if (piece_of(a_row_of(q)) * 8 >= k_tail) offA[q] = OOB;
@@ -594,7 +616,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   read_ops(sA0, sB0, 0, a0, b0);
   if (FUSE && fuse_h) e0 = read_e(sE0, 0);
   // FUSE: the K loop ends with the backbone; the adapter tile (its B_t side is fetched like any tile) follows below
-  const int KT_loop = fuse_h ? KT : KT_total;
+  const int KT_loop = fuse_h ? KT : kt_end - kt_first;
 
   // Steps 0..2 run from registers read one step ahead; before the last step every wave has read all of this
   // stage and tile kt+1 has landed (the loads of the NST-2 tiles after it may stay in flight): barrier; then,
@@ -643,6 +665,17 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
+  if (SPLITK) {                                     // 16 bytes a lane, 1 KB a store
+    float4* part = (float4*)(p.Part + ((size_t)split * p.quarters + slot) * (BMT * BN)) + wave * (MI * NI * 4 * 64) + lane;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          part[((mi * NI + ni) * 4 + j) * 64] = make_float4(acc[mi][ni][4 * j], acc[mi][ni][4 * j + 1], acc[mi][ni][4 * j + 2], acc[mi][ni][4 * j + 3]);
+    return;
+  }
   if (FUSE && fuse_h) {
     // The adapter tile.  Its W-side operand (rows of B_t) was fetched like any K-tile into the stage after the last
     // backbone tile's; its A side is Hs = s_t (X A_t) of the tile's rows, which the waves hold in hacc: this lane has
@@ -747,7 +780,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
 // The workgroups after them compute the remaining tiles in pieces (tail_split = 2: two half-width tiles each;
 // 4: four 128 x 128 quarters each); all pieces of a tile run on the same XCD.  The dispatcher hands out workgroups
 // in index order, so the pieces start as the compute units finish their last full tile.
-template <bool NT, bool FUSE, bool DIFFP, bool TAIL>
+// SPLITK: all tiles are quarters, and p.splits workgroups share the contraction of each; the (share, quarter) pairs, share by
+// share, go to the XCDs in eight equal runs (dealt by whole tiles, 10 tiles of 6 quarters left three XCDs idle and gave
+// the others two rounds: 20.8 us, 14.8 so, for 60 quarters of 2560 x 2560 in four shares).
+template <bool NT, bool FUSE, bool DIFFP, bool TAIL, bool SPLITK = false>
 __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   constexpr int STAGE_ELEMS = BM * BK;            // 32 KB per operand and stage
   __shared__ __attribute__((aligned(1024))) bf16_t sA0[STAGE_ELEMS];
@@ -775,8 +811,19 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
     return;
   }
   // the start stamps wait in the buffer itself (words 2, 3), so that nothing stays live across the tile
-  if (p.clk != nullptr && b == 0 && threadIdx.x == 0) { p.clk[2] = clock64(); p.clk[3] = wall_clock64(); }
-  if (!FUSE && b < p.n_full) {                    // a launch with the down-projection in the loop has pieces only
+  if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) { p.clk[2] = clock64(); p.clk[3] = wall_clock64(); }
+  if constexpr (SPLITK) {
+    const int id = (b & 7) * (p.clear0 >> 3) + (b >> 3), split = id / p.quarters, q = id % p.quarters;
+    int L, half, mhalf;
+    if (split >= p.splits) return;
+    const bool hg = quarter_of(p, q, L, half, mhalf);
+    if (hg && threadIdx.x >= 256) {
+      if (split == 0) clear_below(p, 8 * L, half);
+      return;
+    }
+    gemm_tile<NT, 2, 2, 2, false, false, TAIL, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, hg ? p.per_xcd_h : p.per_xcd, 8 * L,
+                                                     half, mhalf, sm, split, q);
+  } else if (!FUSE && b < p.n_full) {                    // a launch with the down-projection in the loop has pieces only
     gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, 0, p.n_m, p.per_xcd, b, 0, 0, sm);
   } else if (b < p.half0 && p.tail_split == 2) {
     const int t = b - p.n_full;                                       // n_full is a multiple of 8
@@ -801,6 +848,72 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   }
 }
 
+// The shares of a split contraction, summed in ascending order, then the epilogue of gemm_tile (scale, mask, round, store).
+// Bound by latency: there are few outputs, and a wave's time is its chain of loads.  So a workgroup takes one 32 x 64 block of
+// a wave tile, eight a quarter, a wave a quarter of the block's accumulator registers (1 KB a wave instruction, as the tiles
+// stored them), four shares in flight; the block turns in LDS into rows, one 16-byte piece a thread.
+template <bool NT>
+__global__ __launch_bounds__(256) void k_gemm_sum(const GemmParams p) {
+  constexpr int EPW = 72;
+  __shared__ __attribute__((aligned(16))) bf16_t stage[32 * EPW];
+  const int b = blockIdx.x >> 3, wave_t = (blockIdx.x >> 1) & 3, mi = blockIdx.x & 1;    // quarter, its wave tile, row block
+  int L, half, mhalf, tm, tn;
+  const bool hg = quarter_of(p, b, L, half, mhalf);
+  if (!tile_of_slot(hg ? p.n_mh : p.n_m, p.n_n, hg ? p.per_xcd_h : p.per_xcd, 8 * L, tm, tn)) return;
+  const int4 iw = *(const int4*)(p.dtab + p.items_off + ((hg ? p.n_m : 0) + tm) * DI_WORDS);
+  const ItemView it = {iw.x, iw.y, iw.z, iw.w};
+  const int mrow0 = mhalf * 128, row0 = it.row0 + mrow0;
+  const int cw0 = tn * TILE_N + half * 128 + (wave_t & 1) * 64;
+  const int nrows = it.nrows - mrow0 < 128 ? it.nrows - mrow0 : 128;
+  const int m0 = (wave_t >> 1) * 64 + mi * 32;                         // first row of the block inside the quarter
+  if (m0 >= nrows || it.nvalid - mrow0 <= 0 || cw0 >= p.Nc) return;    // (a quarter of padding only: zeros are out already)
+  const DevTask tk = get_task(p.tasks, it.task);
+  const bool ia3 = !NT && tk.kind == MUX_ADAPTER_IA3_OUT, z_only = !NT && tk.kind == MUX_ADAPTER_TUNING && p.Zsave;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 31, lg = lane >> 5;
+  const size_t share = (size_t)p.quarters * (128 * 128 / 4);
+  const float4* part = (const float4*)(p.Part + (size_t)b * (128 * 128)) + (wave_t * 16 + mi * 8 + wave * 2) * 64 + lane;
+  float4 s[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+  for (int k = 0; k < p.splits; k += 4) {
+    float4 v[4][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) v[u][i] = k + u < p.splits ? part[(k + u) * share + i * 64] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) { s[i].x += v[u][i].x; s[i].y += v[u][i].y; s[i].z += v[u][i].z; s[i].w += v[u][i].w; }
+  }
+  const int m = m0 + (int)(threadIdx.x >> 3), c = cw0 + (int)(threadIdx.x & 7) * 8;      // the piece this thread stores
+  const bool out = m < nrows && c < p.Nc, keep = out && row_is_valid(p.dtab, row0 + m);
+  const int passes = (ia3 && p.Zsave) ? 2 : 1;
+  for (int pass = 0; pass < passes; ++pass) {
+    const bool to_z = z_only || pass + 1 < passes;
+    bf16_t* dst = to_z ? p.Zsave + (size_t)(tk.zrow0 - tk.row_begin) * p.Nc : p.Out;
+    // s[i], with 2 wave + i = 4 ni + j: row li of the block, columns 32 ni + 8 j + 4 lg .. + 3
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = 2 * wave + i, col = 32 * (r >> 2) + 8 * (r & 3) + 4 * lg;
+      if (ia3 && !to_z && cw0 + col < p.Nc) {
+        const bf16_t* l = (const bf16_t*)tk.L + cw0 + col;
+        s[i].x *= bf16_to_f32(l[0]); s[i].y *= bf16_to_f32(l[1]); s[i].z *= bf16_to_f32(l[2]); s[i].w *= bf16_to_f32(l[3]);
+      }
+      uint2 v;
+      v.x = pack_bf16x2(s[i].x, s[i].y);
+      v.y = pack_bf16x2(s[i].z, s[i].w);
+      *(uint2*)(stage + li * EPW + col) = v;
+    }
+    __syncthreads();
+    if (out) {
+      uint4 v = *(const uint4*)(stage + (threadIdx.x >> 3) * EPW + (threadIdx.x & 7) * 8);
+      if (!keep) v = make_uint4(0, 0, 0, 0);
+      *(uint4*)(dst + (size_t)(row0 + m) * p.Nc + c) = v;
+    }
+    __syncthreads();
+  }
+}
+
 // Number of compute units, asked once.
 int compute_units() {
   static int n = 0;
@@ -815,10 +928,10 @@ int compute_units() {
 // The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters, then the
 // quarters of the row groups with tokens in their first 128 rows only, then the clearing of those without any.
 struct TilePlan { int n_m, n_mh, n_n, per_xcd, per_xcd_h, n_full, tail_split, half0, clear0, grid; };
-TilePlan plan_tiles(const CallCtx& c, int Nc) {
+TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   TilePlan t{};
-  t.n_m = c.st->n_gemm[0];
-  t.n_mh = c.st->n_gemm[1];
+  t.n_m = st->n_gemm[0];
+  t.n_mh = st->n_gemm[1];
   t.n_n = (Nc + TILE_N - 1) / TILE_N;
   const int total = t.n_m * t.n_n;
   t.per_xcd = (total + 7) / 8;
@@ -837,8 +950,40 @@ TilePlan plan_tiles(const CallCtx& c, int Nc) {
   t.n_full = 8 * (t.per_xcd - tail_slots);
   t.half0 = t.n_full + 8 * t.tail_split * tail_slots;
   t.clear0 = t.half0 + 16 * t.per_xcd_h;
-  t.grid = t.clear0 + c.st->n_gemm[2] * ((Nc + 2047) / 2048);
+  t.grid = t.clear0 + st->n_gemm[2] * ((Nc + 2047) / 2048);
   return t;
+}
+
+// How many workgroups share the contraction of a quarter.  Launches whose quarters leave half of the compute units or
+// more without one spend their time walking all of K on the rest; with S shares the walk is 1 / S as long.  Estimate, in us,
+// from launches of 16 to 256 workgroups: 0.46 a K-tile (0.57 with the down-projection in the loop, which a split launch
+// leaves to a launch of its own: 9), 12 for the second launch and the shares' stores, 0.01 a share of a quarter.  A share
+// keeps eight K-tiles, twice what is in flight.
+// Whole pass, whole contraction -> split, rank 16: 4096 x 4096, 100 tokens, forward 39.3 -> 26.4 us, training 88.9 -> 64.4;
+// 8000 x 1000, 300 tokens, 70.3 -> 30.2 and 109.6 -> 69.4; 11008 x 4096, 64 tokens, 92.4 -> 40.0 and 139.4 -> 81.0; near the
+// line 2048 x 3000, 300 tokens, training 77.8 -> 67.5, and 4096 x 4096, 500 tokens of rank 64, 47.3 -> 46.0 forward.  Split
+// against the estimate, 1024 x 1024 with 200 tokens took 15.8 us in the place of 11.0.  MUX_GEMM_NO_SPLIT (read once): never.
+int plan_splits(const mux_segtab* st, int Kc, int Nc, bool nt, size_t room) {
+  static const bool off = getenv("MUX_GEMM_NO_SPLIT") != nullptr;
+  const TilePlan t = plan_tiles(st, Nc);
+  const int quarters = (4 * t.n_m + 2 * t.n_mh) * t.n_n, kt = (Kc + BK - 1) / BK;
+  if (off || quarters == 0 || t.n_full != 0 || t.tail_split != 4 || st->n_diff > 0) return 1;
+  const bool fused = !nt && st->n_lora > 0 && st->n_tuning == 0 && st->r_max <= 32;
+  const size_t share = (size_t)quarters * (128 * 128 * 4);
+  int most = compute_units() / quarters < kt / 8 ? compute_units() / quarters : kt / 8;
+  if ((size_t)most * share > room) most = (int)(room / share);
+  int best = 1;
+  double best_us = kt * (fused ? 0.57 : 0.46);
+  for (int s = 2; s <= most; ++s) {
+    const double us = (kt + s - 1) / s * 0.46 + 0.01 * s * quarters + 12.0 + (fused ? 9.0 : 0.0);
+    if (us < best_us) { best_us = us; best = s; }
+  }
+  return best;
+}
+size_t split_bytes(const mux_segtab* st, int Kc, int Nc, bool nt) {
+  const int s = plan_splits(st, Kc, Nc, nt, ~(size_t)0);
+  const TilePlan t = plan_tiles(st, Nc);
+  return s > 1 ? (size_t)s * (4 * t.n_m + 2 * t.n_mh) * t.n_n * (128 * 128 * 4) : 0;
 }
 
 template <bool NT>
@@ -848,7 +993,7 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.dtab = c.dtab; p.tasks = *c.tref; p.Ain = Ain; p.W = (const bf16_t*)c.W; p.ldw = c.ldw; p.Ext = Ext; p.Out = Out;
   p.Zsave = Zsave; p.Kc = Kc; p.Nc = Nc; p.RP = c.RP;
   p.HsOut = fuse_down ? (bf16_t*)Ext : nullptr;
-  const TilePlan t = plan_tiles(c, Nc);
+  const TilePlan t = plan_tiles(c.st, Nc);
   p.items_off = c.st->dev_image[DH_OFF_GEMM_ITEMS];
   p.n_m = t.n_m; p.n_n = t.n_n; p.per_xcd = t.per_xcd; p.n_full = t.n_full; p.tail_split = t.tail_split;
   p.n_mh = t.n_mh; p.per_xcd_h = t.per_xcd_h; p.half0 = t.half0; p.clear0 = t.clear0;
@@ -857,11 +1002,24 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.DiffPack = (const uint32_t*)c.diffPack;
   p.clk = diag_clock_buffer();
   if (t.grid == 0) return MUX_OK;
+  p.Part = (float*)c.split;
+  p.splits = plan_splits(c.st, Kc, Nc, NT, c.split_room);
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
   const char* name = NT ? "gemm_nt" : "gemm_nn";
   const dim3 grid(t.grid), block(512);
   const bool tail = Kc % BK != 0;                 // (masked entries are added only where there is none)
+  if (p.splits > 1) {
+    p.quarters = (4 * t.n_m + 2 * t.n_mh) * t.n_n;
+    p.per_xcd = t.n_m * t.n_n; p.per_xcd_h = t.n_mh * t.n_n;        // tiles in one run, see quarter_of
+    p.clear0 = (p.splits * p.quarters + 7) / 8 * 8;
+    const dim3 sgrid(t.grid - t.clear0 + p.clear0);
+    if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true, true>), sgrid, block, 0, c.stream, p);
+    else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, false, true>), sgrid, block, 0, c.stream, p);
+    prof_note_bytes(((double)p.splits * 4 + 2) * c.st->valid_total * Nc);
+    MUX_LAUNCH("gemm_sum", k_gemm_sum<NT>, dim3(8 * p.quarters), dim3(256), 0, c.stream, p);
+    return MUX_OK;
+  }
   if (!NT && fuse_down && tail) MUX_LAUNCH(name, (k_gemm_dma<false, true, false, true>), grid, block, 0, c.stream, p);
   else if (!NT && fuse_down) MUX_LAUNCH(name, (k_gemm_dma<false, true, false, false>), grid, block, 0, c.stream, p);
   else if (p.DiffPack != nullptr) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true, false>), grid, block, 0, c.stream, p);
@@ -871,6 +1029,11 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
 }
 
 }  // namespace
+
+size_t gemm_split_bytes(int K, int N, const mux_segtab* st) {
+  const size_t f = split_bytes(st, K, N, false), b = split_bytes(st, N, K, true);
+  return align256(f > b ? f : b);
+}
 
 // 16-byte loads need rows of X, dY, W, Hs and B_t to start 16-byte aligned (rows of A_t: see rank_pieces), and the
 // 32-bit buffer offsets need W and the largest row group a kernel builds one descriptor over (1024 rows of
@@ -890,7 +1053,8 @@ bool gemm_dma_fuses_down(const CallCtx& c) {
   static const int mode = [] { const char* e = getenv("MUX_GEMM_FUSE_DOWN"); return e == nullptr ? 1 : atoi(e); }();
   if (mode == 0) return false;
   if (c.st->n_lora == 0 || c.st->n_tuning > 0 || c.st->r_max > 32 || c.diffPack != nullptr) return false;
-  const TilePlan t = plan_tiles(c, c.N);
+  if (plan_splits(c.st, c.K, c.N, false, c.split_room) > 1) return false;
+  const TilePlan t = plan_tiles(c.st, c.N);
   if (t.n_full != 0 || (t.n_m + t.n_mh) * t.n_n == 0) return false;
   return t.tail_split == 4 || mode == 2;
 }

@@ -151,6 +151,8 @@ struct CallCtx {
   int diffW_slots;         // how many tasks have one
   void* diffPack;          // workspace: the masks' entries packed for the backbone product of this call, which adds
                            // them to the tiles of W in LDS (index << 16 | bf16 value; null: another route is taken)
+  void* split;             // workspace: `split_room` bytes for the partial tiles of backbone products whose contraction is split
+  size_t split_room;
 };
 
 // H / G row pitch in elements
@@ -185,6 +187,7 @@ void diff_backward(const CallCtx& c, int dtype, const void* X, const void* dY, v
 bool gemm_dma_supported(const CallCtx& c);
 bool fast_gemm_patches_diff(const CallCtx& c, bool backward);   // the backbone product of this call can add masked entries in LDS
 bool gemm_dma_fuses_down(const CallCtx& c);   // the forward launch would be half / quarter tiles only: Hs is formed in its K loop
+size_t gemm_split_bytes(int K, int N, const mux_segtab* st);   // what CallCtx::split can use
 mux_status gemm_dma_forward(const CallCtx& c, const void* X, const void* Hs, void* Y, void* Z, bool fuse_down);
 mux_status gemm_dma_backward(const CallCtx& c, const void* dY, const void* Gs, void* dX);
 

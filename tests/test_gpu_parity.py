@@ -485,6 +485,40 @@ def test_task_table_by_value_and_in_memory(env):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("K,N", [(4096, 640), (640, 4096), (5512, 1032), (3400, 264)])
+@pytest.mark.parametrize("toks", [(1,), (300, 127, 129, 20, 70), (128, 200, 64)])
+def test_split_contraction(env, K, N, toks):
+    """Backbone products of a few tiles with a long contraction: their K-tiles are shared out and k_gemm_sum brings the
+    shares together.  Contraction tails, ragged last columns, row groups with tokens in their first 128 rows only and
+    groups without any, every kind's epilogue, ranks that need the down-projection apart; a workspace without room for
+    the shares gives the same to rounding."""
+    mx, torch = env
+    kinds = [(wlm.KIND_LORA, 16), (wlm.KIND_IA3, 0), (wlm.KIND_LORA, 64 if len(toks) == 3 else 12),
+             (wlm.KIND_NONE, 0), (wlm.KIND_ADAPTER, 20)]
+    for chunk in (64, 512):
+        wl = wlm.Workload(name=f"split{K}", layers=[("w", K, N)], chunk=chunk, sigma_w=0.05, sigma_ab=0.05,
+                          tasks=[wlm.Task(k, r, 2.0, [n]) for (k, r), n in zip(kinds, toks)])
+        g, got, ref, errs = run_case(env, wl, seed=K + len(toks))
+        y, dx = g.Y.clone(), g.dX.clone()
+        mx.mux_profile_enable(1)
+        mx.mux_profile_collect()
+        g.forward(); g.backward()
+        torch.cuda.synchronize()
+        names = [e["name"] for e in mx.mux_profile_collect()]
+        assert "gemm_sum" in names or chunk > 64, names      # (the larger batch may leave the workspace no room for shares)
+        assert torch.equal(g.Y, y) and torch.equal(g.dX, dx)
+        whole, g.ws_bytes = g.ws_bytes, g.ws_bytes - 256
+        g.forward(); g.backward()
+        torch.cuda.synchronize()
+        names = [e["name"] for e in mx.mux_profile_collect()]
+        mx.mux_profile_enable(0)
+        g.ws_bytes = whole
+        assert "gemm_sum" not in names, names
+        # the same products summed in another order: an ulp of bf16 (2^-7 of a value at most) apart
+        for a, b in ((y, g.Y), (dx, g.dX)):
+            assert (a.float() - b.float()).abs().max() <= 2.0 ** -7 * a.float().abs().max()
+
+
 def fuse_workload(K, N, toks):
     tasks = [wlm.Task(wlm.KIND_LORA, 16, 2.0, [toks[0]]), wlm.Task(wlm.KIND_IA3, 0, 1.0, [70]),
              wlm.Task(wlm.KIND_LORA, 32, 0.5, [toks[1], 21]), wlm.Task(wlm.KIND_NONE, 0, 1.0, [64]),
