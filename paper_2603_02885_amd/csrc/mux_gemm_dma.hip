@@ -231,7 +231,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const ItemView it = {iw.x, iw.y, iw.z, iw.w};   // (nvalid: rows up to the last real token)
   const int mrow0 = mhalf * BMT;                  // first row of the item this tile covers
   const int nrows = it.nrows - mrow0 < BMT ? it.nrows - mrow0 : BMT;   // rows of the item inside this tile
-  if (nrows <= 0) return;
   const int row0 = it.row0 + mrow0;
   const int c0 = tn * TILE_N + half * BN;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -241,23 +240,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const bool loader = wave < LW;
   const int lw = wave % LW;                       // chunk owner index (meaningful for loading waves)
 
-  if (tid < BMT) sRow[tid] = (it.task >= 0 && tid < nrows && row_is_valid(p.dtab, row0 + tid)) ? 1 : 0;
+  if (tid < BMT) sRow[tid] = (tid < nrows && row_is_valid(p.dtab, row0 + tid)) ? 1 : 0;
 
-  // FUSE: the tiles of the first column also write Hs of their rows; zeros where no LoRA product is formed
-  auto zero_hs_rows = [&]() {
-    if (FUSE && c0 == 0 && p.HsOut != nullptr)
-      for (int e = tid; e < nrows * (p.RP / 8); e += NTHR)
-        *(uint4*)(p.HsOut + (size_t)(row0 + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
-  };
-  const int nlive = it.nvalid - mrow0 < nrows ? it.nvalid - mrow0 : nrows;   // rows of the tile up to its last token
-  if (nlive <= 0) {                                // padding only: zeros out
-    for (int e = tid; e < nrows * (BN / 8); e += NTHR) {
-      const int m = e / (BN / 8), c = c0 + (e % (BN / 8)) * 8;
-      if (c < p.Nc) *(uint4*)(p.Out + (size_t)(row0 + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
-    }
-    zero_hs_rows();
-    return;
-  }
+  // Rows of the tile up to its last token: at least one.  A group with tokens past its first 128 rows has some in each of
+  // its pieces, one without them runs its upper pieces only, and a group without any token makes no tile.
+  const int nlive = it.nvalid - mrow0 < nrows ? it.nvalid - mrow0 : nrows;
 
   const DevTask tk = get_task(p.tasks, it.task);
   const bool lora = tk.kind == MUX_ADAPTER_LORA;
@@ -866,7 +853,7 @@ __global__ __launch_bounds__(256) void k_gemm_sum(const GemmParams p) {
   const int cw0 = tn * TILE_N + half * 128 + (wave_t & 1) * 64;
   const int nrows = it.nrows - mrow0 < 128 ? it.nrows - mrow0 : 128;
   const int m0 = (wave_t >> 1) * 64 + mi * 32;                         // first row of the block inside the quarter
-  if (m0 >= nrows || it.nvalid - mrow0 <= 0 || cw0 >= p.Nc) return;    // (a quarter of padding only: zeros are out already)
+  if (m0 >= nrows || cw0 >= p.Nc) return;
   const DevTask tk = get_task(p.tasks, it.task);
   const bool ia3 = !NT && tk.kind == MUX_ADAPTER_IA3_OUT, z_only = !NT && tk.kind == MUX_ADAPTER_TUNING && p.Zsave;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
