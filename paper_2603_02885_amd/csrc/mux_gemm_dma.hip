@@ -61,8 +61,8 @@ struct GemmParams {
   int Kc, Nc, RP;
   int items_off;           // word offset in dtab of the row groups' list (DH_OFF_GEMM_ITEMS)
   int n_n;                 // column tiles
-  int n_m, per_xcd;        // row groups with tokens past their first 128 rows; their tiles an XCD takes
-  int n_mh, per_xcd_h;     // the same of the groups with tokens in their first 128 rows only
+  int n_m;                 // row groups with tokens past their first 128 rows
+  int n_mh;                // those with tokens in their first 128 rows only
   int half0, clear0;       // first workgroups of the pieces of such groups, and of those that clear the groups without tokens
   int n_full;              // workgroups that compute full tiles (a multiple of 8); the rest compute pieces of tiles
   int tail_split;          // pieces per tile after the full ones: 2 (halves) or 4 (quarters)
@@ -124,26 +124,33 @@ struct Smem {
   int* off;                      //        per K-tile, where the entries of this tile's buckets begin, split and end
 };
 
-// Tile (row group tm, column tile tn) of slot xcd_slot = (per-XCD slot) * 8 + XCD: an XCD takes a contiguous range of the
-// tiles, in groups of four row groups.  False: the slot is past the end.
-__device__ __forceinline__ bool tile_of_slot(int n_m, int n_n, int per_xcd, int xcd_slot, int& tm, int& tn) {
-  const int jslot = xcd_slot >> 3;
-  const int L = (xcd_slot & 7) * per_xcd + jslot;
-  if (jslot >= per_xcd || L >= n_m * n_n) return false;
+// Number of the tile in slot `j` of an XCD, of `total` tiles; -1: the XCD has no such slot.  An XCD takes a contiguous
+// range of the tiles, and the first `total % 8` XCDs one tile more than the others.
+__host__ __device__ __forceinline__ int tile_of_slot(int total, int xcd, int j) {
+  const int q = total >> 3, r = total & 7;
+  return j < q + (xcd < r ? 1 : 0) ? xcd * q + (xcd < r ? xcd : r) + j : -1;
+}
+// The tiles of the row groups with tokens in their first 128 rows only are dealt from the XCD on that has no tile more of
+// the others, so that the XCDs have as many pieces as each other to within one tile.  Ranges of ceil(total / 8) tiles for
+// both left the last XCDs idle and gave the others a second round: 35 tiles as quarters and 49 pairs of quarters are 238
+// pieces for 256 units, but were 34 on each of seven XCDs of 32 units (1280 x 1792, forward: 33.1 us so, 18.8 now).
+__host__ __device__ __forceinline__ int xcd_of_half(int n_full_tiles, int xcd) { return (xcd - n_full_tiles) & 7; }
+
+// Row group tm and column tile tn of tile L: groups of four row groups, the row group running fastest.
+__device__ __forceinline__ void tile_at(int n_m, int n_n, int L, int& tm, int& tn) {
   constexpr int GROUP = 4;
   const int width = GROUP * n_n;
   const int first_m = (L / width) * GROUP;
   const int gsize = n_m - first_m < GROUP ? n_m - first_m : GROUP;
   tm = first_m + (L % width) % gsize;
   tn = (L % width) / gsize;
-  return true;
 }
 
 // Zeros on the rows past the first 128 of a row group that has tokens in those only (threads 256 .. 511): 128 columns of
 // the output, and with the first of them the rows of Hs.
-__device__ __forceinline__ void clear_below(const GemmParams& p, int xcd_slot, int half) {
+__device__ __forceinline__ void clear_below(const GemmParams& p, int L, int half) {
   int tm, tn;
-  if (!tile_of_slot(p.n_mh, p.n_n, p.per_xcd_h, xcd_slot, tm, tn)) return;
+  tile_at(p.n_mh, p.n_n, L, tm, tn);
   const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + tm) * DI_WORDS);
   const int c0 = tn * TILE_N + half * 128, tid = threadIdx.x & 255, c = c0 + (tid & 15) * 8;
   if (c < p.Nc)
@@ -153,7 +160,7 @@ __device__ __forceinline__ void clear_below(const GemmParams& p, int xcd_slot, i
       *(uint4*)(p.HsOut + (size_t)(iw.y + 128 + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
 }
 
-// Quarter q of a split launch (whose parameters put all tiles in one run: tile L is slot 8 L): true: of a row group with tokens in its first 128 rows only.
+// Quarter q of a split launch: true: of a row group with tokens in its first 128 rows only.
 __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, int& half, int& mhalf) {
   const int q0 = 4 * p.n_m * p.n_n;
   const bool hg = q >= q0;
@@ -169,8 +176,8 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 //   <4,4,1> eight waves, 128x32 per wave, a 256x128 half of a tile,
 //   <2,2,2> four waves (one per SIMD), 64x64 per wave, a 128x128 quarter: for what is left after the last full
 //           round of workgroups.
-// `xcd_slot` = (per-XCD tile slot) * 8 + XCD; `half` selects the 128 columns of a half-width tile, `mhalf` the
-// 128 rows of a quarter.
+// L = number of the tile among those of the `n_m` row groups from `item0` on; `half` selects the 128 columns of a
+// half-width tile, `mhalf` the 128 rows of a quarter.
 // FUSE (forward, half and quarter tiles): the down-projection Hs = s_t X A_t of the tile's rows is
 // computed in the same K loop -- the [64][rank] slab of A_t of every K-tile is staged beside the tile of W, wave
 // (wm, wn) multiplies it with the X fragment of its row block wn (one more MFMA per step) -- and goes, scaled and
@@ -187,9 +194,9 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 // SPLITK (quarters): the tile's `split`-th share of its K-tiles only; the accumulators go to p.Part as they lie in the
 // registers (slot: the quarter's number), for k_gemm_sum.
 template <bool NT, int WNW, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false>
-__device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int per_xcd,
-                                          const int xcd_slot, const int half, const int mhalf, const Smem sm,
-                                          const int split = 0, const int slot = 0) {
+__device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int L,
+                                          const int half, const int mhalf, const Smem sm, const int split = 0,
+                                          const int slot = 0) {
   static_assert(!SPLITK || (!FUSE && !DIFFP && MI == 2 && NI == 2), "SPLITK: quarters, the plain loop");
   static_assert(!FUSE || (!NT && WNW == MI && !(MI == 4 && NI == 2)), "FUSE: forward, half or quarter tiles");
   static_assert(!DIFFP || !FUSE, "DIFFP: not with FUSE");
@@ -226,7 +233,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   int* const sRow = sm.row;
 
   int tm, tn;
-  if (!tile_of_slot(n_m, p.n_n, per_xcd, xcd_slot, tm, tn)) return;
+  tile_at(n_m, p.n_n, L, tm, tn);
   const int4 iw = *(const int4*)(p.dtab + p.items_off + (item0 + tm) * DI_WORDS);
   const ItemView it = {iw.x, iw.y, iw.z, iw.w};   // (nvalid: rows up to the last real token)
   const int mrow0 = mhalf * BMT;                  // first row of the item this tile covers
@@ -805,29 +812,32 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
     if (split >= p.splits) return;
     const bool hg = quarter_of(p, q, L, half, mhalf);
     if (hg && threadIdx.x >= 256) {
-      if (split == 0) clear_below(p, 8 * L, half);
+      if (split == 0) clear_below(p, L, half);
       return;
     }
-    gemm_tile<NT, 2, 2, 2, false, false, TAIL, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, hg ? p.per_xcd_h : p.per_xcd, 8 * L,
-                                                     half, mhalf, sm, split, q);
+    gemm_tile<NT, 2, 2, 2, false, false, TAIL, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q);
   } else if (!FUSE && b < p.n_full) {                    // a launch with the down-projection in the loop has pieces only
-    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, 0, p.n_m, p.per_xcd, b, 0, 0, sm);
+    const int L = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 3);
+    if (L < 0) return;
+    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, 0, p.n_m, L, 0, 0, sm);
   } else if (b < p.half0 && p.tail_split == 2) {
     const int t = b - p.n_full;                                       // n_full is a multiple of 8
-    gemm_tile<NT, 4, 4, 1, FUSE, DIFFP, TAIL>(p, 0, p.n_m, p.per_xcd, p.n_full + (((t >> 4) << 3) | (t & 7)), (t >> 3) & 1,
-                                              0, sm);
+    const int L = tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 4));
+    if (L < 0) return;
+    gemm_tile<NT, 4, 4, 1, FUSE, DIFFP, TAIL>(p, 0, p.n_m, L, (t >> 3) & 1, 0, sm);
   } else {
     // a quarter of a tile left over, or of one whose row group has tokens in its first 128 rows only
     const bool hg = b >= p.half0;
     const int t = b - (hg ? p.half0 : p.n_full);
-    const int mhalf = hg ? 0 : (t >> 4) & 1;
+    const int half = (t >> 3) & 1, mhalf = hg ? 0 : (t >> 4) & 1;
+    const int L = hg ? tile_of_slot(p.n_mh * p.n_n, xcd_of_half(p.n_m * p.n_n, t & 7), t >> 4)
+                     : tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 5));
+    if (L < 0) return;
     if (hg && threadIdx.x >= 256) {                // the four waves that a quarter does not need clear the padding below it
-      clear_below(p, ((t >> 4) << 3) | (t & 7), (t >> 3) & 1);
+      clear_below(p, L, half);
       return;
     }
-    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, TAIL>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, hg ? p.per_xcd_h : p.per_xcd,
-                                              hg ? (((t >> 4) << 3) | (t & 7)) : p.n_full + (((t >> 5) << 3) | (t & 7)),
-                                              (t >> 3) & 1, mhalf, sm);
+    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, TAIL>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm);
   }
   if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
     atomicAdd(p.clk, (unsigned long long)clock64() - p.clk[2]);
@@ -846,7 +856,7 @@ __global__ __launch_bounds__(256) void k_gemm_sum(const GemmParams p) {
   const int b = blockIdx.x >> 3, wave_t = (blockIdx.x >> 1) & 3, mi = blockIdx.x & 1;    // quarter, its wave tile, row block
   int L, half, mhalf, tm, tn;
   const bool hg = quarter_of(p, b, L, half, mhalf);
-  if (!tile_of_slot(hg ? p.n_mh : p.n_m, p.n_n, hg ? p.per_xcd_h : p.per_xcd, 8 * L, tm, tn)) return;
+  tile_at(hg ? p.n_mh : p.n_m, p.n_n, L, tm, tn);
   const int4 iw = *(const int4*)(p.dtab + p.items_off + ((hg ? p.n_m : 0) + tm) * DI_WORDS);
   const ItemView it = {iw.x, iw.y, iw.z, iw.w};
   const int mrow0 = mhalf * 128, row0 = it.row0 + mrow0;
@@ -914,29 +924,35 @@ int compute_units() {
 
 // The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters, then the
 // quarters of the row groups with tokens in their first 128 rows only, then the clearing of those without any.
-struct TilePlan { int n_m, n_mh, n_n, per_xcd, per_xcd_h, n_full, tail_split, half0, clear0, grid; };
+struct TilePlan { int n_m, n_mh, n_n, n_full, tail_split, half0, clear0, grid; };
 TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   TilePlan t{};
   t.n_m = st->n_gemm[0];
   t.n_mh = st->n_gemm[1];
   t.n_n = (Nc + TILE_N - 1) / TILE_N;
-  const int total = t.n_m * t.n_n;
-  t.per_xcd = (total + 7) / 8;
-  t.per_xcd_h = (t.n_mh * t.n_n + 7) / 8;
+  const int total = t.n_m * t.n_n, total_h = t.n_mh * t.n_n;
+  const int slots = (total + 7) / 8, slots_h = (total_h + 7) / 8;              // of the XCD with most tiles
   // One workgroup per compute unit at a time: the tiles left after the last full round would keep a fraction of
-  // the units busy for a whole tile time.  When they fit four times (beside the quarters that follow), they run as
-  // quarters, when twice, as half-width tiles.
+  // the units busy for a whole tile time.  When they fit four times (beside the quarters that follow) on every XCD, they
+  // run as quarters, when twice, as half-width tiles (which the XCDs have equal numbers of, to within one).  42 tiles and
+  // 42 pairs are 252 pieces as quarters, 34 of them on two XCDs (1280 x 5376, 576 tokens, forward: 28.3 us with halves).
   static const bool no_halves = getenv("MUX_GEMM_NO_HALF_TILES") != nullptr;
   static const bool no_quarters = getenv("MUX_GEMM_NO_QUARTER_TILES") != nullptr;
   const int ncu = compute_units();
   const int full_slots = (total / ncu) * (ncu / 8);          // per-XCD slots covered by whole rounds
-  const int rem = total - full_slots * 8, more = 2 * t.n_mh * t.n_n;
+  const int rem = total - full_slots * 8, more = 2 * total_h;
   int tail_slots = 0;
-  if (!no_halves && ncu % 8 == 0 && rem > 0 && 2 * rem + more <= ncu) tail_slots = t.per_xcd - full_slots;
-  t.tail_split = (!no_quarters && 4 * rem + more <= ncu) ? 4 : 2;
-  t.n_full = 8 * (t.per_xcd - tail_slots);
+  if (!no_halves && ncu % 8 == 0 && rem > 0 && 2 * rem + more <= ncu) tail_slots = slots - full_slots;
+  bool quarters = !no_quarters;
+  for (int x = 0; x < 8 && quarters; ++x) {
+    const int tail = total / 8 + (x < total % 8 ? 1 : 0) - full_slots;
+    const int pairs = total_h / 8 + (xcd_of_half(total, x) < total_h % 8 ? 1 : 0);
+    quarters = 4 * tail + 2 * pairs <= ncu / 8;
+  }
+  t.tail_split = quarters ? 4 : 2;
+  t.n_full = 8 * (slots - tail_slots);
   t.half0 = t.n_full + 8 * t.tail_split * tail_slots;
-  t.clear0 = t.half0 + 16 * t.per_xcd_h;
+  t.clear0 = t.half0 + 16 * slots_h;
   t.grid = t.clear0 + st->n_gemm[2] * ((Nc + 2047) / 2048);
   return t;
 }
@@ -982,8 +998,8 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.HsOut = fuse_down ? (bf16_t*)Ext : nullptr;
   const TilePlan t = plan_tiles(c.st, Nc);
   p.items_off = c.st->dev_image[DH_OFF_GEMM_ITEMS];
-  p.n_m = t.n_m; p.n_n = t.n_n; p.per_xcd = t.per_xcd; p.n_full = t.n_full; p.tail_split = t.tail_split;
-  p.n_mh = t.n_mh; p.per_xcd_h = t.per_xcd_h; p.half0 = t.half0; p.clear0 = t.clear0;
+  p.n_m = t.n_m; p.n_n = t.n_n; p.n_full = t.n_full; p.tail_split = t.tail_split;
+  p.n_mh = t.n_mh; p.half0 = t.half0; p.clear0 = t.clear0;
   p.AinScaled = (const bf16_t*)c.dYs;
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
   p.DiffPack = (const uint32_t*)c.diffPack;
@@ -998,7 +1014,6 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   const bool tail = Kc % BK != 0;                 // (masked entries are added only where there is none)
   if (p.splits > 1) {
     p.quarters = (4 * t.n_m + 2 * t.n_mh) * t.n_n;
-    p.per_xcd = t.n_m * t.n_n; p.per_xcd_h = t.n_mh * t.n_n;        // tiles in one run, see quarter_of
     p.clear0 = (p.splits * p.quarters + 7) / 8 * 8;
     const dim3 sgrid(t.grid - t.clear0 + p.clear0);
     if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true, true>), sgrid, block, 0, c.stream, p);

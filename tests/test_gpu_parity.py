@@ -183,6 +183,29 @@ def test_gemm_row_groups_with_padding(env, K, N):
     run_case(env, wl, seed=K, cols=cols, kcols=kcols)
 
 
+@pytest.mark.parametrize("n_upper,n_lower,N,quarters", [(2, 2, 5376, False), (5, 7, 1792, True), (3, 11, 2304, False)])
+def test_gemm_pieces_on_every_xcd(env, n_upper, n_lower, N, quarters):
+    """Tiles and pairs of quarters that fill the compute units to within a few: the XCDs (32 units each) get as many pieces
+    as each other, and a launch is cut into quarters only where they fit every XCD, not just the 256 units together -- the
+    kernel list tells, since launches of quarters form Hs in the tile loop.  42 tiles and 42 pairs: 252 pieces, but 34 on two
+    XCDs; 35 and 49: at most 32; 27 and 99: only halves fit at all."""
+    mx, torch = env
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the counts are those of 256 compute units")
+    tasks = [wlm.Task(wlm.KIND_LORA, 16, 2.0, [256 - 13 * i]) for i in range(n_upper)]
+    tasks += [wlm.Task(wlm.KIND_LORA if i else wlm.KIND_IA3, 8, 2.0, [128 - 11 * i]) for i in range(n_lower)]
+    wl = wlm.Workload(name="pieces", layers=[("w", 192, N)], tasks=tasks, chunk=64, sigma_w=0.05, sigma_ab=0.05)
+    cols = np.unique(np.concatenate([np.random.default_rng(N).choice(N, 150, replace=False), [0, 127, 128, N - 1]]))
+    g, got, ref, errs = run_case(env, wl, seed=N, cols=cols)
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    g.forward()
+    torch.cuda.synchronize()
+    names = [e["name"] for e in mx.mux_profile_collect()]
+    mx.mux_profile_enable(0)
+    assert ("down_x" not in names) == quarters, names
+
+
 def test_mfma_probe_runs(env):
     """The diagnostic MFMA loop: launches, reports its FLOP count, leaves finite sums (operands 1 and 0.5: every
     accumulator element of a loop turn grows by 8 products of 16 terms of 0.5), rejects bad arguments."""
