@@ -807,6 +807,42 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 unsigned short_grid(int n_blocks, int n_heads) { return ((unsigned)n_blocks * (unsigned)n_heads + 7) / 8 * 8; }
 
+// Which blocks of the list (it runs from the longest sequence to the shortest) the backward takes how: n_long in the
+// kernels of any length, then n128 in the one-kernel backward of up to 128 tokens, then n64 in that of up to 64.
+void plan_backward(const mux_segtab* st, const mux_attn_desc* desc, int& n_long, int& n128, int& n64) {
+  n64 = st->n_attn_blocks64; n128 = st->n_attn_blocks128;
+  n_long = st->n_attn_blocks - n64 - n128;
+  const int64_t hkv = desc->n_kv_heads, group = desc->n_heads / desc->n_kv_heads;
+  // A workgroup of the one-kernel backward walks the query heads of its key/value head one after the other and forms dQ
+  // for each, which the kernels of any length spread over a workgroup a query head.  So it pays with short groups of short
+  // rows, or with enough workgroups (128, 256 of the narrow ones) that the chip has work meanwhile.  Forward and backward,
+  // kernels of any length -> one kernel, D = 128: group 2, 4 x 128 tokens (64 workgroups) 48.9 -> 41.3 us; group 3, 1 x 128 (4)
+  // 51.7 -> 54.3; group 8, 16 x 128 tokens (64) 118.6 -> 126.9, 32 x 128 (128) 147 -> 139, 64 x 128 (256) 212 -> 174; group 32,
+  // 64 x 128 (64) 402 -> 484, 128 x 128 (128) 609 -> 549; 64 tokens: group 4, 8 x 64 (64) 41.9 -> 43.8, group 8, 32 x 64 (128)
+  // 86.4 -> 95.6, 64 x 64 (256) 121 -> 108.  D = 96: group 3, 4 x 128 (32) 42.3 -> 40.5.  D = 80: group 4, 4 x 128 (16)
+  // 44.8 -> 48.1.  D = 64: group 4, 2 x 64 (8) 25.3 -> 23.6, 4 x 128 (16) 38.2 -> 40.0; group 16, 64 x 128 (64) 121 -> 141.
+  auto pays = [&](int n, int tokens) {
+    return (group * desc->head_dim <= 288 && (group <= 3 || tokens == 64)) || n * hkv >= (tokens == 128 ? 128 : 256);
+  };
+  const int64_t fill = 512;                    // two workgroups a compute unit
+  // Beside longer sequences the short ones fill the gaps of the launches those need anyway.  Launches of their own pay
+  // where they are many and the longer ones are soon done: 64 x 128 tokens beside one sequence of 256, 1024, 4096 tokens, 32
+  // heads of 128: riding 377, 408, 1140 us, apart 307, 386, 1166; 32 heads of 64, 100 x 100 tokens beside 512: 216 and 235;
+  // 20 heads of 64, 204 x 128 beside 1024: 380 and 350, 102 x 128 beside 3 x 2048: 425 and 488.  With groups, which gain
+  // least at 64 tokens: 8 groups of 4 heads of 128, 256 x 128 tokens beside 256, 1024, 4096: riding 909, 924, 1910, apart
+  // 809, 997, 2041; 200 x 50 beside 4 x 200: 365 and 411.
+  const int64_t weight = (group == 1 ? n64 + n128 : n128) * hkv * desc->head_dim / 128;      // workgroups, in those of 128 columns
+  if (n_long > 0 && weight < (group == 1 && st->attn_longest <= 1024 ? 1792 : 4 * (int64_t)st->attn_longest)) {
+    n_long += n64 + n128;
+    n64 = n128 = 0;
+  }
+  // The launch of narrower workgroups for at most 64 tokens fills the chip, and so does what it leaves to the other
+  // (128 x 64 tokens and 128, 8 groups of 4 heads: 263 us in two launches, 185 in one; 51 x 64 tokens and 12 x 128, 20 heads of 64:
+  // 53 and 65).
+  if (n128 > 0 && (n64 * hkv < fill || !pays(n128, 128))) { n128 += n64; n64 = 0; }
+  if ((n128 > 0 && !pays(n128, 128)) || (n64 > 0 && !pays(n64, 64))) { n_long += n64 + n128; n64 = n128 = 0; }
+}
+
 mux_status last_hip(const char* fn) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MUX_ERR_DEVICE, std::string(fn) + ": " + hipGetErrorString(e));
@@ -886,14 +922,8 @@ extern "C" mux_status mux_attn_backward(const mux_attn_desc* desc, const mux_seg
   z.out[0] = p.dQ; z.ld[0] = desc->ldq; z.out[1] = p.dK; z.ld[1] = desc->ldk; z.out[2] = p.dV; z.ld[2] = desc->ldv;
   if (st->valid_total < st->T)
     MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
-  // Sequences of at most 128 tokens (the end of the list, which runs from the longest sequence to the shortest) have a
-  // kernel of their own for the whole pass, where they are all there is or fill the chip by themselves (512 workgroups: two a
-  // compute unit); fewer beside longer ones ride in the launches those need anyway.  Likewise sequences of at most 64
-  // tokens take a launch of narrower workgroups only where they fill the chip.
-  int n64 = st->n_attn_blocks64, n128 = st->n_attn_blocks128, n_long = st->n_attn_blocks - n64 - n128;
-  const int64_t fill = 512, hkv = desc->n_kv_heads;
-  if (n_long > 0 && (n64 + n128) * hkv < fill) { n_long += n64 + n128; n64 = n128 = 0; }
-  if (n128 > 0 && n64 * hkv < fill) { n128 += n64; n64 = 0; }
+  int n64 = 0, n128 = 0, n_long = 0;
+  plan_backward(st, desc, n_long, n128, n64);
   p.list_off = st->dev_image[DH_ATT_OFF_BWD];
   if (n_long > 0) {
     const size_t n = (size_t)st->T * desc->n_heads;

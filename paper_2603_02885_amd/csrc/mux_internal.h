@@ -93,6 +93,7 @@ struct mux_segtab {
   std::vector<mux::HostTask> tasks;
   int32_t n_attn_blocks = 0;        // 128-row blocks of sequences (attention work items)
   int32_t n_attn_blocks128 = 0, n_attn_blocks64 = 0;   // those of sequences of 65..128 and of at most 64 tokens (one each)
+  int32_t attn_longest = 0;         // tokens of the longest sequence
   std::vector<mux::Item> items[mux::kNumTileSizes];
   std::vector<int32_t> task_item_begin[mux::kNumTileSizes], task_item_count[mux::kNumTileSizes];
   // 256-row work items by what the backbone product has to compute of them: those with a real token past their first

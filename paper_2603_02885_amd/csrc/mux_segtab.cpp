@@ -288,6 +288,7 @@ extern "C" mux_status mux_segtab_build(const mux_task_desc* tasks, int32_t n_tas
         else if (sq.len <= kAttnBlockRows) st->n_attn_blocks128 += nb;
       }
       st->n_attn_blocks = (int32_t)fwd.size();
+      if (!order.empty()) st->attn_longest = order.front().len;
       dv[DH_ATT_NBLK] = st->n_attn_blocks;
       dv[DH_ATT_OFF_FWD] = (int32_t)dv.size();
       for (const Blk& b : fwd) { const int32_t w[DA_WORDS] = {b.first_row, b.len, b.b0, 0}; dv.insert(dv.end(), w, w + DA_WORDS); }

@@ -145,6 +145,30 @@ def test_backward_of_short_sequences(env, d):
     run(env, [[64, 128, 64], [128], [64]], chunk=64, H=3, seed=42 + d, d=d, sigma=3.0)
 
 
+@pytest.mark.parametrize("lens,H,Hkv,d,kernels", [
+    ([[128]], 8, 1, 128, {"kv"}),                                   # one workgroup would walk eight query heads
+    ([[64], [40, 9]], 4, 2, 64, {"64"}),                            # short groups
+    ([[100] * 65, [65] * 63], 4, 1, 64, {"128"}),                   # enough workgroups
+    ([[100] * 65, [65] * 62], 4, 1, 64, {"kv"}),
+    ([[7] * 256, [128]], 8, 2, 96, {"128"}),                        # the one longer sequence would be a launch of its own
+    ([[300], [10] * 600], 1, 1, 64, {"kv"}),                        # beside a longer sequence
+    ([[130], [3] * 1800], 1, 1, 128, {"kv", "64"}),
+    ([[130], [3] * 1800], 2, 1, 128, {"kv"}),
+    ([[130], [66] * 520], 2, 1, 128, {"kv", "128"}),
+])
+def test_which_kernels_take_the_backward_of_short_sequences(env, lens, H, Hkv, d, kernels):
+    """Sequences of at most 128 tokens go through the one-kernel backward where its workgroups (one a key/value head) are
+    many or their groups short, beside longer ones only where they are most of the work; else through the kernels of any
+    length."""
+    mx, _ = env
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    run(env, lens, chunk=64, H=H, Hkv=Hkv, seed=50 + H + d, d=d)
+    names = {e["name"] for e in mx.mux_profile_collect()}
+    mx.mux_profile_enable(0)
+    assert {n[len("attn_bwd_"):] for n in names if n.startswith("attn_bwd_")} - {"q"} == kernels, names
+
+
 def test_llama_heads_one_block(env):
     """32 heads of 128 (the q/k/v width of the 4096-wide projections), ragged lengths."""
     run(env, [[384, 100], [77]], chunk=128, H=32, seed=7)
