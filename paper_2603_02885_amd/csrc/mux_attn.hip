@@ -99,22 +99,29 @@ __device__ __forceinline__ void work_item(int n_blocks, int n_heads, int& block,
   }
 }
 
-// The same for launches of short sequences: with a multiple of eight heads every XCD takes its own run of neighbouring
-// heads of every block, the head running fastest, else a contiguous run of the (block, head) pairs: the heads of a
-// sequence, whose row segments share cache lines (160 bytes at D = 80), meet in one L2.
-// The grid is rounded up to a multiple of eight; false = nothing to do.
+__host__ __device__ __forceinline__ bool short_deals_blocks(int D, int n_blocks) { return D % 64 != 0 && n_blocks >= 32; }
+// The same for launches of short sequences.  With a multiple of eight heads every XCD takes its own run of neighbouring
+// heads of every block, the head running fastest.  Other numbers of heads: where the row segments of neighbouring heads
+// share cache lines (160 bytes at D = 80) the blocks are dealt to the XCDs in turn, each with all of its heads, so that these
+// meet in one L2; else, and with few blocks, the block runs fastest.  (A contiguous run of the pairs an XCD gives the first
+// XCDs the long sequences: 53 heads of 96, 20 x 128 and 20 x 70 tokens, backward 131 us so, 116 now; 28 heads of 128, 200 x 50
+// and 200 x 10, 427 and 317; 53 heads of 96, 128 x 128, dealt in turn 380, the block fastest 404.)
+// false = nothing to do.
+template <int D>
 __device__ __forceinline__ bool short_item(int n_blocks, int n_heads, int& block, int& head) {
-  const unsigned total = (unsigned)n_blocks * (unsigned)n_heads, xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const unsigned xcd = blockIdx.x & 7, j = blockIdx.x >> 3, nb = (unsigned)n_blocks, nh = (unsigned)n_heads;
   if ((n_heads & 7) == 0) {
-    const unsigned hx = (unsigned)n_heads >> 3;
+    const unsigned hx = nh >> 3;
     block = (int)(j / hx);
     head = (int)(xcd * hx + j % hx);
-    return true;
+  } else if (short_deals_blocks(D, n_blocks)) {
+    block = (int)(xcd + 8 * (j / nh));
+    head = (int)(j % nh);
+  } else {
+    block = (int)(blockIdx.x % nb);
+    head = (int)(blockIdx.x / nb);
   }
-  const unsigned per = (total + 7) >> 3, id = xcd * per + j;
-  block = (int)(id / (unsigned)n_heads);
-  head = (int)(id % (unsigned)n_heads);
-  return id < total;
+  return block < n_blocks && head < n_heads;
 }
 
 // ROWS rows x D columns of one head from global memory (rows past `limit` read as zero) into registers, then LDS.
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd(AttnParams p) {
   __shared__ __align__(16) bf16_t sK[TILE * KP];
   __shared__ __align__(16) bf16_t sV[TILE * TP];
   int wi_block, wi_head;
-  if (p.short_map) { if (!short_item(p.n_blocks, p.H, wi_block, wi_head)) return; }
+  if (p.short_map) { if (!short_item<D>(p.n_blocks, p.H, wi_block, wi_head)) return; }
   else work_item(p.n_blocks, p.H, wi_block, wi_head);
   const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN], q0 = blk[DA_BLOCK0];
@@ -609,7 +616,7 @@ __global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
   __shared__ __align__(16) bf16_t sS[R * SP];
   __shared__ float sLse[R], sDelta[R];
   int wi_block, wi_head;                       // wi_head: a key/value head
-  if (!short_item(p.n_blocks, p.Hkv, wi_block, wi_head)) return;
+  if (!short_item<D>(p.n_blocks, p.Hkv, wi_block, wi_head)) return;
   const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN];
   const int hc = wi_head * D;
@@ -805,7 +812,11 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
     else MUX_LAUNCH(name, (k_attn_bwd_short<64, R>), grid, dim3(2 * R), 0, stream, p);                      \
   } while (0)
 
-unsigned short_grid(int n_blocks, int n_heads) { return ((unsigned)n_blocks * (unsigned)n_heads + 7) / 8 * 8; }
+// Workgroups of a launch whose pairs short_item hands out
+unsigned short_grid(int n_blocks, int n_heads, int D) {
+  const bool dealt = n_heads % 8 != 0 && short_deals_blocks(D, n_blocks);
+  return (unsigned)(dealt ? (n_blocks + 7) / 8 * 8 : n_blocks) * (unsigned)n_heads;
+}
 
 // Which blocks of the list (it runs from the longest sequence to the shortest) the backward takes how: n_long in the
 // kernels of any length, then n128 in the one-kernel backward of up to 128 tokens, then n64 in that of up to 64.
@@ -887,9 +898,15 @@ extern "C" mux_status mux_attn_forward(const mux_attn_desc* desc, const mux_segt
   z.dtab = p.dtab; z.out[0] = (bf16_t*)O; z.ld[0] = desc->ldo; z.n_out = 1; z.width[0] = desc->n_heads * D;
   if (st->valid_total < st->T)                // a table without padding rows has nothing to clear
     MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
-  p.short_map = st->n_attn_blocks64 + st->n_attn_blocks128 == st->n_attn_blocks;
+  // Only short sequences and a multiple of eight heads: dealt as in the backward where neighbouring heads share cache lines,
+  // heads share keys and values, or the pairs are many (32 heads of 80, 16 x 64 tokens 10.2 -> 9.5 us; 8 groups of 4 heads of
+  // 128, 64 x 64, 30.3 -> 25.8; 32 heads of 128, 128 x 128, 145 -> 130, but 24 x 128 22.1 -> 24.2; with 28 heads of 128 or 53
+  // of 96 no way of keeping the heads of a sequence together beat the block running fastest: 60 x 100 and 60 x 30 tokens 56.5 us,
+  // contiguous runs 75.8, blocks dealt in turn 60.0).
+  p.short_map = st->n_attn_blocks64 + st->n_attn_blocks128 == st->n_attn_blocks && p.H % 8 == 0 &&
+                (D % 64 != 0 || p.H > p.Hkv || (int64_t)st->n_attn_blocks * p.H >= 2048);
   if (st->n_attn_blocks > 0)
-    ATTN_LAUNCH("attn_fwd", k_attn_fwd, D, dim3(p.short_map ? short_grid(st->n_attn_blocks, desc->n_heads) : (unsigned)st->n_attn_blocks * (unsigned)desc->n_heads), stream, p);
+    ATTN_LAUNCH("attn_fwd", k_attn_fwd, D, dim3((unsigned)st->n_attn_blocks * (unsigned)desc->n_heads), stream, p);
   return last_hip(fn);
 }
 
@@ -937,12 +954,12 @@ extern "C" mux_status mux_attn_backward(const mux_attn_desc* desc, const mux_seg
   if (n128 > 0) {
     p.block0 = n_long;
     p.n_blocks = n128;
-    ATTN_LAUNCH_SHORT("attn_bwd_128", 128, D, dim3(short_grid(n128, desc->n_kv_heads)), stream, p);
+    ATTN_LAUNCH_SHORT("attn_bwd_128", 128, D, dim3(short_grid(n128, desc->n_kv_heads, D)), stream, p);
   }
   if (n64 > 0) {
     p.block0 = n_long + n128;
     p.n_blocks = n64;
-    ATTN_LAUNCH_SHORT("attn_bwd_64", 64, D, dim3(short_grid(n64, desc->n_kv_heads)), stream, p);
+    ATTN_LAUNCH_SHORT("attn_bwd_64", 64, D, dim3(short_grid(n64, desc->n_kv_heads, D)), stream, p);
   }
   return last_hip(fn);
 }

@@ -169,6 +169,14 @@ def test_which_kernels_take_the_backward_of_short_sequences(env, lens, H, Hkv, d
     assert {n[len("attn_bwd_"):] for n in names if n.startswith("attn_bwd_")} - {"q"} == kernels, names
 
 
+@pytest.mark.parametrize("H,Hkv,d", [(5, 5, 80), (7, 7, 64), (3, 1, 96), (8, 8, 80), (24, 8, 64)])
+def test_short_sequences_over_the_xcds(env, H, Hkv, d):
+    """The ways in which (block, head) pairs of short sequences are dealt to the XCDs, forward and backward: numbers of heads
+    that are and are not multiples of eight, fewer and more than 32 blocks, a last block that not every XCD has."""
+    for lens in ([[100, 7] * 3], [[100, 70, 65] * 13], [[90, 30] * 34, [64] * 50]):
+        run(env, lens, chunk=64, H=H, Hkv=Hkv, seed=60 + H + d, d=d)
+
+
 def test_llama_heads_one_block(env):
     """32 heads of 128 (the q/k/v width of the 4096-wide projections), ragged lengths."""
     run(env, [[384, 100], [77]], chunk=128, H=32, seed=7)
