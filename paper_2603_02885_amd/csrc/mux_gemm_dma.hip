@@ -31,6 +31,7 @@
 //     directions: 3015 -> 2741 us for the whole pass; 18 k rows aligned to 512, 5120-wide: 6171 -> 5945 us.
 // Every stage is its own __shared__ array so that the compiler's wait-count insertion can tell
 // the stage being filled from the stage being read.
+#include <atomic>
 #include <cstdlib>
 #include <type_traits>
 
@@ -911,15 +912,15 @@ __global__ __launch_bounds__(256) void k_gemm_sum(const GemmParams p) {
   }
 }
 
-// Number of compute units, asked once.
+// Number of compute units of the current device, asked once; while it cannot be told, that of the part the kernels are made for.
 int compute_units() {
-  static int n = 0;
-  if (n == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n = v;
-    else n = 256;
-  }
-  return n;
+  static std::atomic<int> n{0};
+  if (const int known = n.load(std::memory_order_relaxed)) return known;
+  int dev = 0, v = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
+    return kComputeUnits;
+  n.store(v, std::memory_order_relaxed);
+  return v;
 }
 
 // The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters, then the
@@ -965,15 +966,17 @@ TilePlan plan_tiles(const mux_segtab* st, int Nc) {
 // Whole pass, whole contraction -> split, rank 16: 4096 x 4096, 100 tokens, forward 39.3 -> 26.4 us, training 88.9 -> 64.4;
 // 8000 x 1000, 300 tokens, 70.3 -> 30.2 and 109.6 -> 69.4; 11008 x 4096, 64 tokens, 92.4 -> 40.0 and 139.4 -> 81.0; near the
 // line 2048 x 3000, 300 tokens, training 77.8 -> 67.5, and 4096 x 4096, 500 tokens of rank 64, 47.3 -> 46.0 forward.  Split
-// against the estimate, 1024 x 1024 with 200 tokens took 15.8 us in the place of 11.0.  MUX_GEMM_NO_SPLIT (read once): never.
-int plan_splits(const mux_segtab* st, int Kc, int Nc, bool nt, size_t room) {
-  static const bool off = getenv("MUX_GEMM_NO_SPLIT") != nullptr;
-  const TilePlan t = plan_tiles(st, Nc);
-  const int quarters = (4 * t.n_m + 2 * t.n_mh) * t.n_n, kt = (Kc + BK - 1) / BK;
-  if (off || quarters == 0 || t.n_full != 0 || t.tail_split != 4 || st->n_diff > 0) return 1;
+// against the estimate, 1024 x 1024 with 200 tokens took 15.8 us in the place of 11.0.
+// Arithmetic on the host alone: sizes are asked for in processes without a device too.
+int count_quarters(const mux_segtab* st, int Nc) {
+  return (4 * st->n_gemm[0] + 2 * st->n_gemm[1]) * ((Nc + TILE_N - 1) / TILE_N);
+}
+int plan_splits(const mux_segtab* st, int Kc, int Nc, bool nt, size_t room, int units) {
+  const int quarters = count_quarters(st, Nc), kt = (Kc + BK - 1) / BK;
+  if (quarters == 0 || st->n_diff > 0) return 1;
   const bool fused = !nt && st->n_lora > 0 && st->n_tuning == 0 && st->r_max <= 32;
   const size_t share = (size_t)quarters * (128 * 128 * 4);
-  int most = compute_units() / quarters < kt / 8 ? compute_units() / quarters : kt / 8;
+  int most = units / quarters < kt / 8 ? units / quarters : kt / 8;
   if ((size_t)most * share > room) most = (int)(room / share);
   int best = 1;
   double best_us = kt * (fused ? 0.57 : 0.46);
@@ -983,10 +986,16 @@ int plan_splits(const mux_segtab* st, int Kc, int Nc, bool nt, size_t room) {
   }
   return best;
 }
+// The shares of a launch: only a launch of nothing but quarters is split.  MUX_GEMM_NO_SPLIT (read once): none is.
+int launch_splits(const CallCtx& c, int Kc, int Nc, bool nt) {
+  static const bool off = getenv("MUX_GEMM_NO_SPLIT") != nullptr;
+  const TilePlan t = plan_tiles(c.st, Nc);
+  if (off || t.n_full != 0 || t.tail_split != 4) return 1;
+  return plan_splits(c.st, Kc, Nc, nt, c.split_room, compute_units());
+}
 size_t split_bytes(const mux_segtab* st, int Kc, int Nc, bool nt) {
-  const int s = plan_splits(st, Kc, Nc, nt, ~(size_t)0);
-  const TilePlan t = plan_tiles(st, Nc);
-  return s > 1 ? (size_t)s * (4 * t.n_m + 2 * t.n_mh) * t.n_n * (128 * 128 * 4) : 0;
+  const int s = plan_splits(st, Kc, Nc, nt, ~(size_t)0, kComputeUnits);
+  return s > 1 ? (size_t)s * count_quarters(st, Nc) * (128 * 128 * 4) : 0;
 }
 
 template <bool NT>
@@ -1006,14 +1015,14 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.clk = diag_clock_buffer();
   if (t.grid == 0) return MUX_OK;
   p.Part = (float*)c.split;
-  p.splits = plan_splits(c.st, Kc, Nc, NT, c.split_room);
+  p.splits = launch_splits(c, Kc, Nc, NT);
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
   const char* name = NT ? "gemm_nt" : "gemm_nn";
   const dim3 grid(t.grid), block(512);
   const bool tail = Kc % BK != 0;                 // (masked entries are added only where there is none)
   if (p.splits > 1) {
-    p.quarters = (4 * t.n_m + 2 * t.n_mh) * t.n_n;
+    p.quarters = count_quarters(c.st, Nc);
     p.clear0 = (p.splits * p.quarters + 7) / 8 * 8;
     const dim3 sgrid(t.grid - t.clear0 + p.clear0);
     if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true, true>), sgrid, block, 0, c.stream, p);
@@ -1055,7 +1064,7 @@ bool gemm_dma_fuses_down(const CallCtx& c) {
   static const int mode = [] { const char* e = getenv("MUX_GEMM_FUSE_DOWN"); return e == nullptr ? 1 : atoi(e); }();
   if (mode == 0) return false;
   if (c.st->n_lora == 0 || c.st->n_tuning > 0 || c.st->r_max > 32 || c.diffPack != nullptr) return false;
-  if (plan_splits(c.st, c.K, c.N, false, c.split_room) > 1) return false;
+  if (launch_splits(c, c.K, c.N, false) > 1) return false;
   const TilePlan t = plan_tiles(c.st, c.N);
   if (t.n_full != 0 || (t.n_m + t.n_mh) * t.n_n == 0) return false;
   return t.tail_split == 4 || mode == 2;

@@ -125,6 +125,7 @@ unsigned long long* diag_clock_buffer();
     hipLaunchKernelGGL(kernel, grid, block, smem, stream, __VA_ARGS__);  \
   } while (0)
 
+constexpr int kComputeUnits = 256;  // of the part the kernels are made for (MI355X)
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 // 16-byte pieces in a row of A_t (D_t) as the matrix-core kernels read it
 __host__ __device__ inline int rank_pieces(int rank) { return (rank + 7) >> 3; }

@@ -107,6 +107,51 @@ def test_argument_errors(mx):
     assert e.value.status == 4
 
 
+SIZES = """
+import os
+import paper_2603_02885_amd as mx
+mx.load_library()
+for K, N in ((4096, 4096), (8000, 1000), (256, 256), (11008, 4096)):
+    for lens in ([[100]], [[300, 20], [64]], [[5000]]):
+        st = mx.mux_segtab_build([mx.TaskDesc(1, 16, 1.0, l) for l in lens], 64)
+        layer = mx.LayerDesc(K, N, mx.MUX_DT_BF16, 0x1000, len(lens), [0x1000] * len(lens), [0x1000] * len(lens), None)
+        print(K, N, mx.mux_lora_saved_bytes(layer, st), mx.mux_lora_workspace_bytes(layer, st))
+def target(fd):
+    try:
+        return os.readlink("/proc/self/fd/" + fd)
+    except OSError:
+        return ""
+print("device open:", any(target(fd) == "/dev/kfd" for fd in os.listdir("/proc/self/fd")))
+"""
+
+
+def sizes_in_a_fresh_process(**switches):
+    import subprocess
+    import sys
+    env = {k: v for k, v in os.environ.items() if not k.startswith("MUX_")}
+    r = subprocess.run([sys.executable, "-c", SIZES], cwd=ROOT, env=dict(env, **switches), capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return r.stdout
+
+
+def test_sizes_follow_from_the_layer_and_the_table():
+    """mux_lora_saved_bytes and mux_lora_workspace_bytes are arithmetic on their arguments: no switch of the environment
+    changes them, and asking opens no device -- a process that only plans, and may fork later, stays without one."""
+    plain = sizes_in_a_fresh_process()
+    assert "device open: False" in plain, plain
+    for switch in ("MUX_GEMM_NO_SPLIT", "MUX_GEMM_NO_QUARTER_TILES", "MUX_GEMM_NO_HALF_TILES"):
+        assert sizes_in_a_fresh_process(**{switch: "1"}) == plain, switch
+
+
+@pytest.mark.gpu
+def test_sizes_open_no_device():
+    """The same where there is a device to open, and the sizes are those given without one."""
+    assert os.path.exists("/dev/kfd")
+    out = sizes_in_a_fresh_process()
+    assert "device open: False" in out, out
+    assert out == sizes_in_a_fresh_process(HIP_VISIBLE_DEVICES="")
+
+
 def test_empty_table(mx):
     st = mx.mux_segtab_build([], 64)
     assert mx.mux_segtab_rows(st) == 0 and mx.mux_segtab_n_chunks(st) == 0
