@@ -17,7 +17,9 @@
  *   - All GPU work is enqueued on the given hipStream_t (passed as void*); no call
  *     synchronises.  Argument checks happen on the host before anything is launched; a call
  *     that returns an error has launched nothing.
- *   - Same inputs give bit-identical outputs (no floating-point atomics anywhere).
+ *   - Same inputs give bit-identical outputs (no floating-point atomics anywhere): the same layer, table and tensors, on the
+ *     same kind of device, with a workspace of at least the size asked for.  How many workgroups share a sum, and so the
+ *     order of its terms, follows from the whole batch: a task's results may differ in their last bits between two tables.
  *   - Tensors are row-major and dense unless a leading dimension is given.
  *     X[T,K], W[K,N] (Y = X W, the orientation of Eq. 1), Y[T,N], dY[T,N], dX[T,K],
  *     A_t[K,r_t], B_t[r_t,N], l_t[N].  T = mux_segtab_rows().
@@ -186,7 +188,9 @@ typedef struct {
  * contents undefined between calls).  Both follow from the layer description and the table alone
  * (for DIFF tasks also from what their masks bring: with the listing by tiles the call packs the
  * entries, 4 bytes each; without it, it may hold a copy of W per such task).  For products of a few tiles with a long
- * contraction `ws` includes room for partial tiles (never past MUX_STATIC_WS_BYTES in all). */
+ * contraction the size of `ws` includes room for partial tiles (never past MUX_STATIC_WS_BYTES in all).  A `ws` too small for
+ * these alone is accepted too: such a product is then summed without them, in another order, slower and with other last
+ * bits.  A `ws` too small for the rest is refused (MUX_ERR_WORKSPACE). */
 size_t mux_lora_saved_bytes(const mux_layer_desc* layer, const mux_segtab* st);
 size_t mux_lora_workspace_bytes(const mux_layer_desc* layer, const mux_segtab* st);
 
