@@ -87,12 +87,12 @@ def test_long_contraction_mixed_ranks(env):
 
 
 def test_kernel_choice_by_shape(env):
-    """Shapes that select the other kernels: contraction lengths that are multiples of 32 but not of 64 (the 32-deep
-    pipelined GEMM, forward and backward), and rows that are not 16-byte aligned (the plain kernels)."""
+    """Contraction lengths that are multiples of 32 but not of 64 (a last K-tile that is half full, forward and backward),
+    and rows that are not 16-byte aligned (the plain kernels)."""
     tasks = [wlm.Task(wlm.KIND_LORA, 8, 2.0, [90, 40]), wlm.Task(wlm.KIND_IA3, 0, 1.0, [130]),
              wlm.Task(wlm.KIND_LORA, 40, 0.5, [300]), wlm.Task(wlm.KIND_NONE, 0, 1.0, [33]),
              wlm.Task(wlm.KIND_LORA, 16, 1.0, [257])]
-    wl = wlm.Workload(name="bk32", layers=[("w", 416, 352)], tasks=tasks, chunk=32, sigma_w=0.05, sigma_ab=0.05)
+    wl = wlm.Workload(name="halftile", layers=[("w", 416, 352)], tasks=tasks, chunk=32, sigma_w=0.05, sigma_ab=0.05)
     run_case(env, wl, seed=3)
     wl = wlm.Workload(name="unaligned", layers=[("w", 100, 52)], tasks=tasks, chunk=16, sigma_w=0.05, sigma_ab=0.05)
     run_case(env, wl, seed=4)
@@ -313,8 +313,8 @@ def test_diff_pruning_routes(env):
 
 
 def test_diff_pruning_routes_differ_by_direction(env):
-    """A LoRA rank that is not a multiple of 8 sends the backward to the register-staged GEMM: the forward still adds
-    the masked entries in its tile loop, the backward runs the sparse update after its product."""
+    """Beside a LoRA rank that is not a multiple of 8 the forward adds the masked entries in its tile loop, the backward keeps
+    the sparse update after its product, which adds delta_t unrounded."""
     mx, torch = env
     tasks = [wlm.Task(wlm.KIND_LORA, 12, 2.0, [100]), wlm.Task(wlm.KIND_DIFF, 0, 1.0, [70, 45], density=0.02),
              wlm.Task(wlm.KIND_DIFF, 0, 1.0, [150, 21], density=0.08), wlm.Task(wlm.KIND_IA3, 0, 1.0, [33])]
@@ -684,25 +684,43 @@ def test_graph_capture_and_replay(env, which):
         torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("var", ["MUX_GEMM_BK32", "MUX_GEMM_NO_HALF_TILES", "MUX_GEMM_NO_QUARTER_TILES", "MUX_GEMM_REGSTAGED",
+def check_split(env, shared):
+    """Parity of products of a few tiles with a long contraction and, from the kernel list, whether they were shared out."""
+    mx, torch = env
+    tasks = [wlm.Task(wlm.KIND_LORA, 16, 2.0, [70]), wlm.Task(wlm.KIND_IA3, 0, 1.0, [33]), wlm.Task(wlm.KIND_ADAPTER, 8, 1.0, [20])]
+    for K, N in ((4096, 640), (640, 4096)):
+        wl = wlm.Workload(name=f"few{K}", layers=[("w", K, N)], tasks=tasks, chunk=64, sigma_w=0.05, sigma_ab=0.05)
+        g, got, ref, errs = run_case(env, wl, seed=K)
+        mx.mux_profile_enable(1)
+        mx.mux_profile_collect()
+        g.forward(); g.backward()
+        torch.cuda.synchronize()
+        names = [e["name"] for e in mx.mux_profile_collect()]
+        mx.mux_profile_enable(0)
+        assert ("gemm_sum" in names) == shared, names
+
+
+@pytest.mark.parametrize("var", ["MUX_GEMM_NO_HALF_TILES", "MUX_GEMM_NO_QUARTER_TILES", "MUX_GEMM_NO_SPLIT",
                                  "MUX_GEMM_FUSE_DOWN=0", "MUX_GEMM_FUSE_DOWN=2"])
 def test_gemm_variants_in_a_fresh_process(env, var):
-    """The switches that are read once per process (32-deep stages where 64-deep ones would be taken; full tiles
-    only; half-width tiles where quarters would be taken for the last round; the register-staged kernel, which
-    otherwise only sees the shapes the pipelined kernel does not take, on shapes both can run; the down-projection
-    never inside the tile loop, or in launches of half tiles as well): a parity case in a child process with the
-    switch set."""
+    """The switches that are read once per process (full tiles only; half-width tiles where quarters would be taken for
+    the last round; no contraction shared out to several workgroups; the down-projection never inside the tile loop, or in
+    launches of half tiles as well): parity cases in a child process with the switch set, and what the kernel list can
+    show of the switch."""
     import os
     import subprocess
     import sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     code = ("import torch, paper_2603_02885_amd as mx; mx.load_library(); import mux_workloads as wlm;"
-            "from tests.test_gpu_parity import run_case, mixed_workload, tuning_workload, check_fused_down;"
+            "from tests.test_gpu_parity import run_case, mixed_workload, tuning_workload, check_fused_down, check_split;"
             "tasks = [wlm.Task(wlm.KIND_LORA, 16, 2.0, [700]), wlm.Task(wlm.KIND_IA3, 0, 1.0, [300]), wlm.Task(wlm.KIND_LORA, 40, 1.0, [900])];"
             "wl = wlm.Workload(name='v', layers=[('w', 512, 1280)], tasks=tasks, chunk=64, sigma_w=0.04, sigma_ab=0.05);"
             "run_case((mx, torch), wl, seed=5); run_case((mx, torch), mixed_workload(K=320, N=256), seed=6); run_case((mx, torch), tuning_workload(K=192, N=160), seed=22);")
     if var == "MUX_GEMM_FUSE_DOWN=2":
         code += "check_fused_down((mx, torch), True);"
+    if var == "MUX_GEMM_NO_SPLIT":
+        check_split(env, True)
+        code += "check_split((mx, torch), False);"
     code += "print('variant ok')"
     envv = dict(os.environ)
     name, _, value = var.partition("=")
