@@ -255,7 +255,7 @@ void launch_down(const CallCtx& c, const char* name, DownParams p) {
   const dim3 grid(items * 2);
   if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2>), grid, dim3(512), 0, c.stream, p);
   else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2>), grid, dim3(512), 0, c.stream, p);
-  else if (items * 2 <= 256) MUX_LAUNCH(name, (k_down<4, 8, 2>), grid, dim3(512), 0, c.stream, p);
+  else if (items * 2 <= (unsigned)kComputeUnits) MUX_LAUNCH(name, (k_down<4, 8, 2>), grid, dim3(512), 0, c.stream, p);
   else MUX_LAUNCH(name, (k_down<4, 4, 2>), grid, dim3(256), 0, c.stream, p);
 }
 
@@ -844,10 +844,8 @@ __global__ __launch_bounds__(512) void k_dl(const int32_t* __restrict__ dtab, co
 // Bound by the latency of a few dependent loads and, before blocks wrote whole runs of dA_t, by stores of 4 bytes at a
 // stride of r floats: 32 tasks of rank 16, 8192 x 1024 and 1024 x 8192, 29.2 -> 14.7 us a launch; 16 tasks of rank 8 to
 // 64 at 4096 x 4096, 31.4 -> 18.4 us; two tasks at 256 x 256, 4.1 -> 2.9 us.
-__host__ __device__ __forceinline__ int reduce_cols(int rank) {     // columns of dA_t a block takes: rank * columns <= 1024
-  const int n = (1024 / rank) & ~3;
-  return n < 4 ? 4 : n;
-}
+static_assert(MUX_MAX_RANK <= 256, "reduce_cols: a block takes four columns at least");
+__host__ __device__ __forceinline__ int reduce_cols(int rank) { return (1024 / rank) & ~3; }   // columns of dA_t a block takes
 struct ReduceParams {
   const int32_t* dtab;
   const float *part0, *part1, *part_ia3;

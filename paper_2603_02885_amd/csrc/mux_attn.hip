@@ -826,16 +826,17 @@ void plan_backward(const mux_segtab* st, const mux_attn_desc* desc, int& n_long,
   const int64_t hkv = desc->n_kv_heads, group = desc->n_heads / desc->n_kv_heads;
   // A workgroup of the one-kernel backward walks the query heads of its key/value head one after the other and forms dQ
   // for each, which the kernels of any length spread over a workgroup a query head.  So it pays with short groups of short
-  // rows, or with enough workgroups (128, 256 of the narrow ones) that the chip has work meanwhile.  Forward and backward,
-  // kernels of any length -> one kernel, D = 128: group 2, 4 x 128 tokens (64 workgroups) 48.9 -> 41.3 us; group 3, 1 x 128 (4)
-  // 51.7 -> 54.3; group 8, 16 x 128 tokens (64) 118.6 -> 126.9, 32 x 128 (128) 147 -> 139, 64 x 128 (256) 212 -> 174; group 32,
+  // rows, or with enough workgroups (one for two compute units, of the narrow ones one for each) that the chip has work
+  // meanwhile.  Forward and backward, kernels of any length -> one kernel, D = 128: group 2, 4 x 128 tokens (64 workgroups)
+  // 48.9 -> 41.3 us; group 3, 1 x 128 (4) 51.7 -> 54.3; group 8, 16 x 128 tokens (64) 118.6 -> 126.9, 32 x 128 (128) 147 -> 139, 64 x 128 (256) 212 -> 174; group 32,
   // 64 x 128 (64) 402 -> 484, 128 x 128 (128) 609 -> 549; 64 tokens: group 4, 8 x 64 (64) 41.9 -> 43.8, group 8, 32 x 64 (128)
   // 86.4 -> 95.6, 64 x 64 (256) 121 -> 108.  D = 96: group 3, 4 x 128 (32) 42.3 -> 40.5.  D = 80: group 4, 4 x 128 (16)
   // 44.8 -> 48.1.  D = 64: group 4, 2 x 64 (8) 25.3 -> 23.6, 4 x 128 (16) 38.2 -> 40.0; group 16, 64 x 128 (64) 121 -> 141.
   auto pays = [&](int n, int tokens) {
-    return (group * desc->head_dim <= 288 && (group <= 3 || tokens == 64)) || n * hkv >= (tokens == 128 ? 128 : 256);
+    return (group * desc->head_dim <= 288 && (group <= 3 || tokens == 64)) ||
+           n * hkv >= (tokens == 128 ? kComputeUnits / 2 : kComputeUnits);
   };
-  const int64_t fill = 512;                    // two workgroups a compute unit
+  const int64_t fill = 2 * kComputeUnits;      // two workgroups a compute unit
   // Beside longer sequences the short ones fill the gaps of the launches those need anyway.  Launches of their own pay
   // where they are many and the longer ones are soon done: 64 x 128 tokens beside one sequence of 256, 1024, 4096 tokens, 32
   // heads of 128: riding 377, 408, 1140 us, apart 307, 386, 1166; 32 heads of 64, 100 x 100 tokens beside 512: 216 and 235;
@@ -843,7 +844,7 @@ void plan_backward(const mux_segtab* st, const mux_attn_desc* desc, int& n_long,
   // least at 64 tokens: 8 groups of 4 heads of 128, 256 x 128 tokens beside 256, 1024, 4096: riding 909, 924, 1910, apart
   // 809, 997, 2041; 200 x 50 beside 4 x 200: 365 and 411.
   const int64_t weight = (group == 1 ? n64 + n128 : n128) * hkv * desc->head_dim / 128;      // workgroups, in those of 128 columns
-  if (n_long > 0 && weight < (group == 1 && st->attn_longest <= 1024 ? 1792 : 4 * (int64_t)st->attn_longest)) {
+  if (n_long > 0 && weight < (group == 1 && st->attn_longest <= 1024 ? 7 * kComputeUnits : 4 * (int64_t)st->attn_longest)) {
     n_long += n64 + n128;
     n64 = n128 = 0;
   }
@@ -899,12 +900,12 @@ extern "C" mux_status mux_attn_forward(const mux_attn_desc* desc, const mux_segt
   if (st->valid_total < st->T)                // a table without padding rows has nothing to clear
     MUX_LAUNCH("attn_zero_pad", k_attn_zero_pad, dim3((unsigned)st->items[0].size(), (unsigned)((z.width[0] + 2047) / 2048)), dim3(256), 0, stream, z);
   // Only short sequences and a multiple of eight heads: dealt as in the backward where neighbouring heads share cache lines,
-  // heads share keys and values, or the pairs are many (32 heads of 80, 16 x 64 tokens 10.2 -> 9.5 us; 8 groups of 4 heads of
-  // 128, 64 x 64, 30.3 -> 25.8; 32 heads of 128, 128 x 128, 145 -> 130, but 24 x 128 22.1 -> 24.2; with 28 heads of 128 or 53
+  // heads share keys and values, or the pairs are many, eight a compute unit (40 heads of 80, 16 x 64 tokens 10.2 -> 9.5 us;
+  // 8 groups of 4 heads of 128, 64 x 64, 30.3 -> 25.8; 32 heads of 128, 128 x 128, 145 -> 130, but 24 x 128 22.1 -> 24.2; with 28 heads of 128 or 53
   // of 96 no way of keeping the heads of a sequence together beat the block running fastest: 60 x 100 and 60 x 30 tokens 56.5 us,
   // contiguous runs 75.8, blocks dealt in turn 60.0).
   p.short_map = st->n_attn_blocks64 + st->n_attn_blocks128 == st->n_attn_blocks && p.H % 8 == 0 &&
-                (D % 64 != 0 || p.H > p.Hkv || (int64_t)st->n_attn_blocks * p.H >= 2048);
+                (D % 64 != 0 || p.H > p.Hkv || (int64_t)st->n_attn_blocks * p.H >= 8 * kComputeUnits);
   if (st->n_attn_blocks > 0)
     ATTN_LAUNCH("attn_fwd", k_attn_fwd, D, dim3((unsigned)st->n_attn_blocks * (unsigned)desc->n_heads), stream, p);
   return last_hip(fn);
