@@ -64,6 +64,7 @@ struct GemmParams {
   int n_n;                 // column tiles
   int n_m;                 // row groups with tokens past their first 128 rows
   int n_mh;                // those with tokens in their first 128 rows only
+  int start_h[9];          // of their tiles, the first one of every XCD (start_h[8]: how many there are)
   int half0, clear0;       // first workgroups of the pieces of such groups, and of those that clear the groups without tokens
   int n_full;              // workgroups that compute full tiles (a multiple of 8); the rest compute pieces of tiles
   int tail_split;          // pieces per tile after the full ones: 2 (halves) or 4 (quarters)
@@ -127,15 +128,10 @@ struct Smem {
 
 // Number of the tile in slot `j` of an XCD, of `total` tiles; -1: the XCD has no such slot.  An XCD takes a contiguous
 // range of the tiles, and the first `total % 8` XCDs one tile more than the others.
-__host__ __device__ __forceinline__ int tile_of_slot(int total, int xcd, int j) {
+__device__ __forceinline__ int tile_of_slot(int total, int xcd, int j) {
   const int q = total >> 3, r = total & 7;
   return j < q + (xcd < r ? 1 : 0) ? xcd * q + (xcd < r ? xcd : r) + j : -1;
 }
-// The tiles of the row groups with tokens in their first 128 rows only are dealt from the XCD on that has no tile more of
-// the others, so that the XCDs have as many pieces as each other to within one tile.  Ranges of ceil(total / 8) tiles for
-// both left the last XCDs idle and gave the others a second round: 35 tiles as quarters and 49 pairs of quarters are 238
-// pieces for 256 units, but were 34 on each of seven XCDs of 32 units (1280 x 1792, forward: 33.1 us so, 18.8 now).
-__host__ __device__ __forceinline__ int xcd_of_half(int n_full_tiles, int xcd) { return (xcd - n_full_tiles) & 7; }
 
 // Row group tm and column tile tn of tile L: groups of four row groups, the row group running fastest.
 __device__ __forceinline__ void tile_at(int n_m, int n_n, int L, int& tm, int& tn) {
@@ -831,9 +827,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
     const bool hg = b >= p.half0;
     const int t = b - (hg ? p.half0 : p.n_full);
     const int half = (t >> 3) & 1, mhalf = hg ? 0 : (t >> 4) & 1;
-    const int L = hg ? tile_of_slot(p.n_mh * p.n_n, xcd_of_half(p.n_m * p.n_n, t & 7), t >> 4)
-                     : tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 5));
-    if (L < 0) return;
+    int L;
+    if (hg) {
+      L = p.start_h[t & 7] + (t >> 4);
+      if (L >= p.start_h[(t & 7) + 1]) return;
+    } else {
+      L = tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 5));
+      if (L < 0) return;
+    }
     if (hg && threadIdx.x >= 256) {                // the four waves that a quarter does not need clear the padding below it
       clear_below(p, L, half);
       return;
@@ -925,18 +926,17 @@ int compute_units() {
 
 // The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters, then the
 // quarters of the row groups with tokens in their first 128 rows only, then the clearing of those without any.
-struct TilePlan { int n_m, n_mh, n_n, n_full, tail_split, half0, clear0, grid; };
+struct TilePlan { int n_m, n_mh, n_n, n_full, tail_split, start_h[9], half0, clear0, grid; };
 TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   TilePlan t{};
   t.n_m = st->n_gemm[0];
   t.n_mh = st->n_gemm[1];
   t.n_n = (Nc + TILE_N - 1) / TILE_N;
   const int total = t.n_m * t.n_n, total_h = t.n_mh * t.n_n;
-  const int slots = (total + 7) / 8, slots_h = (total_h + 7) / 8;              // of the XCD with most tiles
+  const int slots = (total + 7) / 8;                         // of the XCDs with most tiles
   // One workgroup per compute unit at a time: the tiles left after the last full round would keep a fraction of
-  // the units busy for a whole tile time.  When they fit four times (beside the quarters that follow) on every XCD, they
-  // run as quarters, when twice, as half-width tiles (which the XCDs have equal numbers of, to within one).  42 tiles and
-  // 42 pairs are 252 pieces as quarters, 34 of them on two XCDs (1280 x 5376, 576 tokens, forward: 28.3 us with halves).
+  // the units busy for a whole tile time.  When they fit four times (beside the quarters that follow), they run as
+  // quarters, when twice, as half-width tiles.
   static const bool no_halves = getenv("MUX_GEMM_NO_HALF_TILES") != nullptr;
   static const bool no_quarters = getenv("MUX_GEMM_NO_QUARTER_TILES") != nullptr;
   const int ncu = compute_units();
@@ -944,14 +944,22 @@ TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   const int rem = total - full_slots * 8, more = 2 * total_h;
   int tail_slots = 0;
   if (!no_halves && ncu % 8 == 0 && rem > 0 && 2 * rem + more <= ncu) tail_slots = slots - full_slots;
-  bool quarters = !no_quarters;
-  for (int x = 0; x < 8 && quarters; ++x) {
-    const int tail = total / 8 + (x < total % 8 ? 1 : 0) - full_slots;
-    const int pairs = total_h / 8 + (xcd_of_half(total, x) < total_h % 8 ? 1 : 0);
-    quarters = 4 * tail + 2 * pairs <= ncu / 8;
-  }
-  t.tail_split = quarters ? 4 : 2;
+  t.tail_split = (!no_quarters && 4 * rem + more <= ncu) ? 4 : 2;
   t.n_full = 8 * (slots - tail_slots);
+  // The pairs of quarters go to the XCDs so that these have as many pieces as each other, to within one pair: the XCDs
+  // without a tile more of the others (from `odd` on) first get as many pairs as such a tile has pairs of pieces, then all of
+  // them equal shares.  So pieces that fit the compute units fit those of every XCD.  Ranges of ceil(tiles / 8) for both left
+  // the last XCDs idle and gave the others a second round: 35 tiles and 49 pairs, 238 pieces for 256 units, were 34 on each of
+  // seven XCDs of 32 units (1280 x 1792, forward: 33.1 us so, 19.0 now; 42 tiles and 42 pairs, 1280 x 5376: 33.0 and 20.4).
+  const int odd = total % 8, ahead = tail_slots > 0 ? t.tail_split / 2 * (8 - odd) : 0;
+  const int lead = odd == 0 ? 0 : (total_h < ahead ? total_h : ahead), rest = total_h - lead;
+  int slots_h = 0;
+  for (int x = 0; x < 8; ++x) {
+    int n = rest / 8 + (((x - odd) & 7) < rest % 8 ? 1 : 0);
+    if (x >= odd) n += lead / (8 - odd) + (x - odd < lead % (8 - odd) ? 1 : 0);
+    t.start_h[x + 1] = t.start_h[x] + n;
+    if (n > slots_h) slots_h = n;
+  }
   t.half0 = t.n_full + 8 * t.tail_split * tail_slots;
   t.clear0 = t.half0 + 16 * slots_h;
   t.grid = t.clear0 + st->n_gemm[2] * ((Nc + 2047) / 2048);
@@ -1009,6 +1017,7 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.items_off = c.st->dev_image[DH_OFF_GEMM_ITEMS];
   p.n_m = t.n_m; p.n_n = t.n_n; p.n_full = t.n_full; p.tail_split = t.tail_split;
   p.n_mh = t.n_mh; p.half0 = t.half0; p.clear0 = t.clear0;
+  for (int x = 0; x < 9; ++x) p.start_h[x] = t.start_h[x];
   p.AinScaled = (const bf16_t*)c.dYs;
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
   p.DiffPack = (const uint32_t*)c.diffPack;

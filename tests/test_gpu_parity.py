@@ -183,12 +183,12 @@ def test_gemm_row_groups_with_padding(env, K, N):
     run_case(env, wl, seed=K, cols=cols, kcols=kcols)
 
 
-@pytest.mark.parametrize("n_upper,n_lower,N,quarters", [(2, 2, 5376, False), (5, 7, 1792, True), (3, 11, 2304, False)])
+@pytest.mark.parametrize("n_upper,n_lower,N,quarters", [(2, 2, 5376, True), (5, 7, 1792, True), (13, 6, 1024, True),
+                                                        (3, 11, 2304, False)])
 def test_gemm_pieces_on_every_xcd(env, n_upper, n_lower, N, quarters):
-    """Tiles and pairs of quarters that fill the compute units to within a few: the XCDs (32 units each) get as many pieces
-    as each other, and a launch is cut into quarters only where they fit every XCD, not just the 256 units together -- the
-    kernel list tells, since launches of quarters form Hs in the tile loop.  42 tiles and 42 pairs: 252 pieces, but 34 on two
-    XCDs; 35 and 49: at most 32; 27 and 99: only halves fit at all."""
+    """Tiles and pairs of quarters that fill the compute units to within a few, dealt so that the XCDs have as many pieces as
+    each other: 42 tiles and 42 pairs, 35 and 49, 52 and 24 (no unit left over, two pairs on some XCDs and four on others); 27
+    and 99, of which only halves fit.  The kernel list tells, since launches of quarters form Hs in the tile loop."""
     mx, torch = env
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the counts are those of 256 compute units")
