@@ -184,11 +184,12 @@ def test_gemm_row_groups_with_padding(env, K, N):
 
 
 @pytest.mark.parametrize("n_upper,n_lower,N,quarters", [(2, 2, 5376, True), (5, 7, 1792, True), (13, 6, 1024, True),
-                                                        (3, 11, 2304, False)])
+                                                        (3, 11, 2304, False), (22, 5, 2304, False)])
 def test_gemm_pieces_on_every_xcd(env, n_upper, n_lower, N, quarters):
     """Tiles and pairs of quarters that fill the compute units to within a few, dealt so that the XCDs have as many pieces as
     each other: 42 tiles and 42 pairs, 35 and 49, 52 and 24 (no unit left over, two pairs on some XCDs and four on others); 27
-    and 99, of which only halves fit.  The kernel list tells, since launches of quarters form Hs in the tile loop."""
+    and 99, of which only halves fit; 198 and 45, which run as whole tiles.  The kernel list tells, since launches of quarters
+    form Hs in the tile loop."""
     mx, torch = env
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the counts are those of 256 compute units")
