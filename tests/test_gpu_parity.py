@@ -193,7 +193,7 @@ def test_gemm_pieces_on_every_xcd(env, n_upper, n_lower, N, quarters):
     mx, torch = env
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the counts are those of 256 compute units")
-    tasks = [wlm.Task(wlm.KIND_LORA, 16, 2.0, [256 - 13 * i]) for i in range(n_upper)]
+    tasks = [wlm.Task(wlm.KIND_LORA, 16, 2.0, [256 - 9 * (i % 14)]) for i in range(n_upper)]
     tasks += [wlm.Task(wlm.KIND_LORA if i else wlm.KIND_IA3, 8, 2.0, [128 - 11 * i]) for i in range(n_lower)]
     wl = wlm.Workload(name="pieces", layers=[("w", 192, N)], tasks=tasks, chunk=64, sigma_w=0.05, sigma_ab=0.05)
     cols = np.unique(np.concatenate([np.random.default_rng(N).choice(N, 150, replace=False), [0, 127, 128, N - 1]]))
