@@ -48,6 +48,10 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 constexpr int BM = 256;
 constexpr int BK = 64;                          // depth of a K-tile
 constexpr int TILE_N = 256;                     // width of a tile in the launch's tile index space
+// Columns of a row group without tokens that a workgroup clears.  In a launch of a few pieces the clearing must not outlast
+// them: 2048 columns, 1 MB a workgroup, did (704 x 2496, two tasks of 88 and 62 tokens aligned to 512, forward 13.0 us so, 12.7
+// now).
+constexpr int CLEAR_N = 512;
 constexpr uint32_t OOB = 0x80000000u;
 
 struct GemmParams {
@@ -790,12 +794,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   __shared__ int sRow[256];
   const Smem sm = {sA0, sA1, sB0, sB1, sRow, sE0, sE1, sE2, sE3, (uint32_t)(uintptr_t)(lds_void_ptr)sP, sOff};
   const int b = blockIdx.x;
-  if (b >= p.clear0) {                            // a row group without tokens: 2048 columns of its output rows
-    const int slabs = (p.Nc + 2047) / 2048, d = b - p.clear0;
+  if (b >= p.clear0) {                            // a row group without tokens: CLEAR_N columns of its output rows, a wave a row
+    const int slabs = (p.Nc + CLEAR_N - 1) / CLEAR_N, d = b - p.clear0;
     const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + p.n_mh + d / slabs) * DI_WORDS);
-    const int c = (d % slabs) * 2048 + (threadIdx.x & 255) * 8;
+    const int c = (d % slabs) * CLEAR_N + (threadIdx.x & 63) * 8;
     if (c < p.Nc)
-      for (int m = threadIdx.x >> 8; m < iw.z; m += 2) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
+      for (int m = threadIdx.x >> 6; m < iw.z; m += 8) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
     if (FUSE && d % slabs == 0 && p.HsOut != nullptr)
       for (int e = threadIdx.x; e < iw.z * (p.RP / 8); e += 512)
         *(uint4*)(p.HsOut + (size_t)(iw.y + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
@@ -971,7 +975,7 @@ TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   }
   t.half0 = t.n_full + 8 * t.tail_split * tail_slots;
   t.clear0 = t.half0 + 16 * slots_h;
-  t.grid = t.clear0 + st->n_gemm[2] * ((Nc + 2047) / 2048);
+  t.grid = t.clear0 + st->n_gemm[2] * ((Nc + CLEAR_N - 1) / CLEAR_N);
   return t;
 }
 
