@@ -54,8 +54,23 @@ constexpr int TILE_N = 256;                     // width of a tile in the launch
 constexpr int CLEAR_N = 512;
 constexpr uint32_t OOB = 0x80000000u;
 
+// A workgroup reads these one after the other as it finds out what it computes, from lines of 64 bytes that are cold at the
+// start of a launch: what it needs first lies in the first line, what comes next in the second.  (Spread over three lines,
+// 4096 x 4096, four tasks of 37 to 129 tokens, forward 40.4 us, so 40.0; 40.2 before there were two kinds of row groups.)
 struct GemmParams {
   const int32_t* dtab;
+  unsigned long long* clk;  // diagnostic: counters workgroup 0 adds its elapsed cycles and 100 MHz ticks to (null: off)
+  int n_full;              // workgroups that compute full tiles (a multiple of 8); the rest compute pieces of tiles
+  int tail_split;          // pieces per tile after the full ones: 2 (halves) or 4 (quarters)
+  int n_m;                 // row groups with tokens past their first 128 rows
+  int n_mh;                // those with tokens in their first 128 rows only
+  int half0, clear0;       // first workgroups of the pieces of the latter, and of those that clear the groups without tokens
+  int n_n;                 // column tiles
+  int items_off;           // word offset in dtab of the row groups' list (DH_OFF_GEMM_ITEMS)
+  int Kc, Nc, RP;
+  int splits;              // pieces of the contraction, each a workgroup of its own (1: none)
+  int start_h[9];          // of the tiles of the n_mh groups, the first one of every XCD (start_h[8]: how many there are)
+  int quarters;            // of a launch whose contraction is split
   const bf16_t* Ain;   // [T, Kc]  activations (X or dY)
   const bf16_t* W;     // [K, ldw]
   int64_t ldw;
@@ -63,18 +78,7 @@ struct GemmParams {
   bf16_t* Out;         // [T, Nc]
   bf16_t* Zsave;       // forward: x W of IA3_OUT rows (may be null)
   bf16_t* HsOut;       // forward with the down-projection in the tile loop: Hs [T, RP] is written here (else null)
-  int Kc, Nc, RP;
-  int items_off;           // word offset in dtab of the row groups' list (DH_OFF_GEMM_ITEMS)
-  int n_n;                 // column tiles
-  int n_m;                 // row groups with tokens past their first 128 rows
-  int n_mh;                // those with tokens in their first 128 rows only
-  int start_h[9];          // of their tiles, the first one of every XCD (start_h[8]: how many there are)
-  int half0, clear0;       // first workgroups of the pieces of such groups, and of those that clear the groups without tokens
-  int n_full;              // workgroups that compute full tiles (a multiple of 8); the rest compute pieces of tiles
-  int tail_split;          // pieces per tile after the full ones: 2 (halves) or 4 (quarters)
   float* Part;             // partial tiles of a split contraction: [splits][quarters][128 * 128] fp32, in accumulator order
-  int splits, quarters;    // pieces of the contraction, each a workgroup of its own (1: none); quarters of the launch then
-  unsigned long long* clk;  // diagnostic: counters workgroup 0 adds its elapsed cycles and 100 MHz ticks to (null: off)
   const uint32_t* DiffPack; // entries of the Diff-Pruning masks packed for this launch (index << 16 | bf16 value), or null
   const bf16_t* Wdiff;      // merged weights W + M_t * delta_t of the Diff-Pruning tasks, `wdiff_stride` elements apart (or null)
   int64_t wdiff_stride;
