@@ -942,13 +942,14 @@ TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   t.n_n = (Nc + TILE_N - 1) / TILE_N;
   const int ncu = compute_units();
   // Where no pieces fit behind the last full round, its tiles run whole.  If those of the groups with tokens in their first 128
-  // rows fit that round as whole tiles too, but not as the pairs of quarters that they would be else, they run whole with the
-  // others, and save a round of their own (1984 x 2688, 16 k tokens, training in two micro-batches, backward 504 tiles and 8
-  // such: 771 us before the groups were sorted, 780 as pairs, 744 whole; 640 x 2304, 22 groups and 5, forward: 30.9, 35.9, 30.7).
-  // Elsewhere it costs up to 3 % against the pairs: 2560 x 1536, 36 groups and 5, forward, 80.9, 78.4, 80.6.
+  // rows fit that round as whole tiles too, but not as the pairs of quarters that they would be else, and are few beside the
+  // others, they run whole with them: next to whole tiles a quarter takes 0.6 of their time, so that a second round of
+  // quarters ends after them.  As pairs, whole, forward: 640 x 2304, 198 tiles and 45 such, 35.6 us, 30.3; 4096 x 1536, 240 and 12,
+  // 146, 122; 2560 x 1536, 216 and 30, 77.7, 79.7.  Where they are many the products saved count for more: 1280 x 1536, 186 and
+  // 54, 44.8, 46.3; 2560 x 3584, 70 and 154, 58.3, 67.1; but 2560 x 1536, 162 and 84, 79.1, 75.6.
   {
     const int total = t.n_m * t.n_n, rem = total % ncu, lower = t.n_mh * t.n_n;
-    if (rem > 0 && 2 * (rem + lower) > ncu && rem + 2 * lower > ncu && rem + lower <= ncu) { t.n_m += t.n_mh; t.n_mh = 0; }
+    if (rem + lower <= ncu && rem + 2 * lower > ncu && 2 * (rem + lower) > ncu && rem >= 4 * lower) { t.n_m += t.n_mh; t.n_mh = 0; }
   }
   const int total = t.n_m * t.n_n, total_h = t.n_mh * t.n_n;
   const int slots = (total + 7) / 8;                         // of the XCDs with most tiles
