@@ -757,11 +757,20 @@ def main():
     ia3_rows = sum(task_rows[t] for t in range(M) if wl.tasks[t].kind == 2)
     tune_rows = sum(task_rows[t] for t in range(M) if wl.tasks[t].kind == 3)
     sum_tune = sum(task_rows[t] * wl.tasks[t].rank for t in range(M) if wl.tasks[t].kind == 3)
-    flops_backbone = 4.0 * T * sumKN
+    # rows the backbone product computes: row groups of 256 without a token make no tile, those with tokens in their first
+    # 128 rows only make half a tile
+    row_task, done, begin = mx.mux_segtab_row_task(st), [], 0
+    for rows in task_rows:
+        groups = [row_task[a:min(a + 256, begin + rows)] for a in range(begin, begin + rows, 256)]
+        done.append(sum(min(len(g), 128) if (g[128:] < 0).all() else len(g) for g in groups if (g >= 0).any()))
+        begin += rows
+    T_done = sum(done)
+    done_tr = sum(done[t] * wl.tasks[t].rank for t in range(M) if wl.tasks[t].kind == 1)
+    flops_backbone = 4.0 * T_done * sumKN
     flops_adapter = 6.0 * sum_tr * sum(K + N for _, K, N in wl.layers) + 12.0 * sum_tune * sum(N for _, K, N in wl.layers)
-    gemm_flops = {  # per step, per kernel family (all layers): 2TKN + 2 sum T_t r_t N (fwd) / K (bwd)
-        "gemm_nn": 2.0 * T * sumKN + 2.0 * sum_tr * sum(N for _, K, N in wl.layers),
-        "gemm_nt": 2.0 * T * sumKN + 2.0 * sum_tr * sum(K for _, K, N in wl.layers),
+    gemm_flops = {  # per step, per kernel family (all layers): 2TKN + 2 sum T_t r_t N (fwd) / K (bwd) over those rows
+        "gemm_nn": 2.0 * T_done * sumKN + 2.0 * done_tr * sum(N for _, K, N in wl.layers),
+        "gemm_nt": 2.0 * T_done * sumKN + 2.0 * done_tr * sum(K for _, K, N in wl.layers),
     }
     kernels = {}
     for e in prof_all:      # every kernel, from the extra steps after the timed region
@@ -869,7 +878,8 @@ def main():
         "tflops": (flops_backbone + flops_adapter) / (ms_per_step * 1e-3) / 1e12,
         "frac_of_bf16_mfma_peak": (flops_backbone + flops_adapter) / (ms_per_step * 1e-3) / 1e12 / PEAK_BF16_MFMA,
         "padded_rows_per_s": T / (ms_per_step * 1e-3),
-        "valid_row_fraction": valid / max(T, 1),          # FLOP figures count every row of the aligned batch
+        "valid_row_fraction": valid / max(T, 1),
+        "computed_row_fraction": T_done / max(T, 1),      # FLOP figures count the rows the backbone product computes
         "roofline": roofline,
         "kernels": kernels,
     }
