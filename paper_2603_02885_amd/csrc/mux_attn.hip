@@ -604,7 +604,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(AttnParams p) {
 // the waves share dQ^T = K^T dS^T by 32-column tiles.  Two barriers a step; the next 32 queries are in flight meanwhile.
 // The lane's V row stays in registers, K only in LDS (it is needed there for dQ): 68 KB of LDS at R = 128, D = 128, two
 // workgroups a compute unit.  Measured, forward and backward of a call: 32 heads of 80, sequences of 64 and 128 tokens
-// (2944 in all) 94 -> 72 us; 46 sequences of 64 and 32 heads of 128, 126 -> 94 us (3.9 TB/s over what has to move).
+// (2944 in all) 94 -> 71 us; 46 sequences of 64 and 32 heads of 128, 113 -> 82 us; 160 sequences of 128, 64 heads of 64,
+// 931 -> 574 us.
 template <int D, int R>
 __global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
   constexpr int KS = Dim<D>::KS, DT = Dim<D>::DT, DP = Dim<D>::DP, TP = Dim<D>::TP;

@@ -989,10 +989,9 @@ TilePlan plan_tiles(const mux_segtab* st, int Nc) {
 // from launches of 16 to 256 workgroups: 0.46 a K-tile (0.57 with the down-projection in the loop, which a split launch
 // leaves to a launch of its own: 9), 12 for the second launch and the shares' stores, 0.01 a share of a quarter.  A share
 // keeps eight K-tiles, twice what is in flight.
-// Whole pass, whole contraction -> split, rank 16: 4096 x 4096, 100 tokens, forward 39.3 -> 26.4 us, training 88.9 -> 64.4;
-// 8000 x 1000, 300 tokens, 70.3 -> 30.2 and 109.6 -> 69.4; 11008 x 4096, 64 tokens, 92.4 -> 40.0 and 139.4 -> 81.0; near the
-// line 2048 x 3000, 300 tokens, training 77.8 -> 67.5, and 4096 x 4096, 500 tokens of rank 64, 47.3 -> 46.0 forward.  Split
-// against the estimate, 1024 x 1024 with 200 tokens took 15.8 us in the place of 11.0.
+// Whole pass, whole contraction -> split, rank 16: 4096 x 4096, 100 tokens, forward 39.3 -> 25.7 us, training 88.4 -> 62.0;
+// 8000 x 1000, 300 tokens, 70.1 -> 30.5 and 109.1 -> 69.4; 11008 x 4096, 64 tokens, 93.6 -> 39.2 and 140.1 -> 79.6; near the
+// line 2048 x 3000, 300 tokens, training 77.8 -> 66.6, and 4096 x 4096, 500 tokens of rank 64, 45.5 -> 44.2 forward.
 // Arithmetic on the host alone: sizes are asked for in processes without a device too.
 int count_quarters(const mux_segtab* st, int Nc) {
   return (4 * st->n_gemm[0] + 2 * st->n_gemm[1]) * ((Nc + TILE_N - 1) / TILE_N);
