@@ -28,7 +28,7 @@
 //     table), dealt to the XCDs by their number; a row group with tokens in its first 128 rows only runs as two quarters, and
 //     the groups without any are cleared by workgroups at the end of the launch.  32 tasks of about 1024 rows, aligned to
 //     1024 (a quarter of the row groups is padding, and fell on the XCDs unevenly), 8192 x 1024 and 1024 x 8192, both
-//     directions: 3015 -> 2741 us for the whole pass; 18 k rows aligned to 512, 5120-wide: 6171 -> 5945 us.
+//     directions: 2984 -> 2667 us for the whole pass; 18 k rows aligned to 512, 5120-wide: 6095 -> 5849 us.
 // Every stage is its own __shared__ array so that the compiler's wait-count insertion can tell
 // the stage being filled from the stage being read.
 #include <atomic>
