@@ -207,6 +207,44 @@ def test_gemm_pieces_on_every_xcd(env, n_upper, n_lower, N, quarters):
     assert ("down_x" not in names) == quarters, names
 
 
+@pytest.mark.parametrize("seed", range(4))
+def test_every_tile_of_random_row_groups(env, seed):
+    """Forty random batches a seed, from one row group of 256 to several rounds of tiles: groups with tokens past their
+    first 128 rows, in those only, and none, over one to twenty column tiles -- whole tiles, halves, quarters, pairs of
+    quarters beside them or as whole tiles, shared contractions.  Small integers, whose products are exact in every order of
+    the sums, so that a tile that is missing, done by another's rows or left uncleared shows."""
+    mx, torch = env
+    rng = np.random.default_rng(seed)
+    dev = "cuda:0"
+    for case in range(40):
+        chunk = int(rng.choice([64, 128, 256, 512]))
+        lens = [int(rng.integers(129, 257)) if rng.random() < 0.6 else int(rng.integers(1, 129)) for _ in range(int(rng.integers(0, 16)))]
+        lens += [int(rng.integers(1, 9000))] if rng.random() < 0.6 or not lens else []
+        K, N = (int(rng.choice([64, 72, 2048])), int(rng.integers(1, 41)) * 128 + int(rng.choice([0, 8, 120])))
+        if rng.random() < 0.3:
+            K, N = N, K
+        st = mx.mux_segtab_build([mx.TaskDesc(wlm.KIND_NONE, 0, 1.0, [n]) for n in lens], chunk)
+        nb, T = mx.mux_segtab_device_bytes(st), mx.mux_segtab_rows(st)
+        print(f"case {seed}.{case}: K={K} N={N} chunk={chunk} lens={lens}", flush=True)
+        dtab = torch.empty(nb, dtype=torch.uint8, device=dev)
+        mx.mux_segtab_upload(st, dtab, nb)
+        gen = torch.Generator(device=dev).manual_seed(seed * 100 + case)
+        ints = lambda *shape: torch.randint(-1, 2, shape, device=dev, generator=gen).to(torch.bfloat16)      # noqa: E731
+        X, W, dY = ints(T, K), ints(K, N), ints(T, N)
+        layer = mx.LayerDesc(K, N, mx.MUX_DT_BF16, W, len(lens))
+        ws_bytes = mx.mux_lora_workspace_bytes(layer, st)
+        ws = torch.full((max(ws_bytes, 256),), 0xFF, dtype=torch.uint8, device=dev)
+        Y, dX = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device=dev), torch.full((T, K), float("nan"), dtype=torch.bfloat16, device=dev)
+        none = [None] * len(lens)
+        stream = torch.cuda.current_stream()
+        mx.mux_lora_forward(layer, st, dtab, X, Y, None, ws, ws_bytes, stream)
+        mx.mux_lora_backward(layer, st, dtab, X, dY, None, dX, none, none, none, 0, ws, ws_bytes, stream)
+        valid = torch.from_numpy(np.ascontiguousarray(mx.mux_segtab_row_task(st) >= 0)).to(dev)[:, None]
+        for got, a, b in ((Y, X, W), (dX, dY, W.t().contiguous())):
+            want = torch.where(valid, a.float() @ b.float(), torch.zeros((), device=dev)).to(torch.bfloat16)
+            assert torch.equal(got, want), (case, (got != want).nonzero()[:4].tolist())
+
+
 def test_mfma_probe_runs(env):
     """The diagnostic MFMA loop: launches, reports its FLOP count, leaves finite sums (operands 1 and 0.5: every
     accumulator element of a loop turn grows by 8 products of 16 terms of 0.5), rejects bad arguments."""
