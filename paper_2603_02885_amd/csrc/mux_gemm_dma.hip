@@ -79,6 +79,7 @@ struct GemmParams {
   bf16_t* Zsave;       // forward: x W of IA3_OUT rows (may be null)
   bf16_t* HsOut;       // forward with the down-projection in the tile loop: Hs [T, RP] is written here (else null)
   float* Part;             // partial tiles of a split contraction: [splits][quarters][128 * 128] fp32, in accumulator order
+  float* PartH;            // and of X A_t with it (forward): [splits][rows of the quarters, 128 each][32] fp32
   const uint32_t* DiffPack; // entries of the Diff-Pruning masks packed for this launch (index << 16 | bf16 value), or null
   const bf16_t* Wdiff;      // merged weights W + M_t * delta_t of the Diff-Pruning tasks, `wdiff_stride` elements apart (or null)
   int64_t wdiff_stride;
@@ -124,15 +125,29 @@ __device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F
 // Swizzle of the 16-byte piece index inside a 128-byte row of a [rows][64] tile: sixteen consecutive rows read the
 // same logical piece with one ds_read_b128 and must land in sixteen different 16-byte bank groups.
 __device__ __forceinline__ int swz_row(int r) { return (r >> 1) & 7; }
+// Swizzle of the 32-byte segments of a k-row of the forward's [64][BN] tile of W: the four k-rows that sixteen lanes read
+// across, two segments wide, must land in 256 different bytes of the banks.  Rows of 128 bytes: two of them do as they lie.
+template <int BN>
+__device__ __forceinline__ int swz_k(int kk) { return BN >= 128 ? (kk & 3) << 1 : kk & 2; }
 
-// Two A and two B arrays (a stage each, two stages each for quarter tiles) and the per-row validity flags of a workgroup.
+// LDS of a workgroup: the stages (see gemm_tile), the per-row validity flags, and with DIFFP, per K-tile, where the entries
+// of this tile's buckets begin, split and end.
 struct Smem {
-  bf16_t *a0, *a1, *b0, *b1;
+  bf16_t* base;
   int* row;
-  bf16_t *e0, *e1, *e2, *e3;     // FUSE: stages of the [64][rank] slabs of A_t
-  uint32_t pk_lds;               // DIFFP: LDS byte address of the stages' slots for 256 packed entries of the masks each
-  int* off;                      //        per K-tile, where the entries of this tile's buckets begin, split and end
+  int* off;
 };
+
+// Stages of a piece of 64 MI x 64 NI: as many as the LDS holds, eight at most.
+constexpr int kSlabElems = 2048;                  // FUSE: [64][rank <= 32] slab of A_t, 4 KB a stage
+constexpr int kPackElems = 512;                   // DIFFP: 256 packed entries of the masks, 1 KB a stage
+constexpr int piece_elems(int MI, int NI, bool FUSE, bool DIFFP) {
+  return 64 * (MI + NI) * BK + (FUSE ? kSlabElems : 0) + (DIFFP ? kPackElems : 0);
+}
+constexpr int piece_stages(int MI, int NI, bool FUSE, bool DIFFP) {
+  const int room = (160 * 1024 - 1024 - (DIFFP ? 12288 : 0)) / 2, n = room / piece_elems(MI, NI, FUSE, DIFFP);
+  return n < 8 ? n : 8;
+}
 
 // Number of the tile in slot `j` of an XCD, of `total` tiles; -1: the XCD has no such slot.  An XCD takes a contiguous
 // range of the tiles, and the first `total % 8` XCDs one tile more than the others.
@@ -151,7 +166,7 @@ __device__ __forceinline__ void tile_at(int n_m, int n_n, int L, int& tm, int& t
   tn = (L % width) / gsize;
 }
 
-// Zeros on the rows past the first 128 of a row group that has tokens in those only (threads 256 .. 511): 128 columns of
+// Zeros on the rows past the first 128 of a row group that has tokens in those only (256 threads): 128 columns of
 // the output, and with the first of them the rows of Hs.
 __device__ __forceinline__ void clear_below(const GemmParams& p, int L, int half) {
   int tm, tn;
@@ -178,14 +193,17 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 // One output tile.  WNW = waves along N, MI x NI = 32x32 MFMA tiles per wave; 2*WNW waves on a
 // BMT x BN tile with BMT = 2*MI*32 and BN = WNW*NI*32:
 //   <4,4,2> eight waves (two per SIMD), 128x64 per wave, the full 256x256 tile;
-//   <4,4,1> eight waves, 128x32 per wave, a 256x128 half of a tile,
-//   <2,2,2> four waves (one per SIMD), 64x64 per wave, a 128x128 quarter: for what is left after the last full
-//           round of workgroups.
+//   <4,4,1> eight waves, 128x32 per wave, a 256x128 half of a tile beside full ones;
+//   <2,2,2> and <2,4,2> four waves (one per SIMD), 64x64 or 128x64 per wave: a 128x128 quarter beside full tiles, a half in
+//           a launch without them;
+//   <1,MI,NI> four waves, a piece of 64 MI x 64 NI in a launch without full tiles: each wave forms the whole piece from a
+//           quarter of the contraction, one of the four MFMA steps of every K-tile, and the four sums are added at the end.
 // L = number of the tile among those of the `n_m` row groups from `item0` on; `half` selects the 128 columns of a
-// half-width tile, `mhalf` the 128 rows of a quarter.
-// FUSE (forward, half and quarter tiles): the down-projection Hs = s_t X A_t of the tile's rows is
-// computed in the same K loop -- the [64][rank] slab of A_t of every K-tile is staged beside the tile of W, wave
-// (wm, wn) multiplies it with the X fragment of its row block wn (one more MFMA per step) -- and goes, scaled and
+// half-width tile, `mhalf` the 128 rows of a quarter.  MI = 1: the list holds groups of 64 rows, L is the group and `half`
+// the column piece.
+// FUSE (forward, pieces): the down-projection Hs = s_t X A_t of the tile's rows is
+// computed in the same K loop -- the [64][rank] slab of A_t of every K-tile is staged beside the tile of W, the two waves
+// of a row half multiply it with the X fragments of half of its row blocks each (of the one it has, both) -- and goes, scaled and
 // rounded to bf16, straight into the A side of the adapter K-tile (and, from the tiles of the first column, to
 // memory for the backward): no separate pass over X, no launch for it.  Every column tile redoes the product for
 // its rows, which is why this is for launches that do not fill the compute units anyway.
@@ -198,21 +216,22 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 // (256 a tile; a bucket pair with more reads the rest from memory when the tile is patched).
 // SPLITK (quarters): the tile's `split`-th share of its K-tiles only; the accumulators go to p.Part as they lie in the
 // registers (slot: the quarter's number), for k_gemm_sum.
-template <bool NT, int WNW, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false>
+template <bool NT, int WAVES_N, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int L,
                                           const int half, const int mhalf, const Smem sm, const int split = 0,
                                           const int slot = 0) {
-  static_assert(!SPLITK || (!FUSE && !DIFFP && MI == 2 && NI == 2), "SPLITK: quarters, the plain loop");
-  static_assert(!FUSE || (!NT && WNW == MI && !(MI == 4 && NI == 2)), "FUSE: forward, half or quarter tiles");
+  static_assert(!SPLITK || (!DIFFP && MI == 2 && NI == 2), "SPLITK: quarters, the plain loop");
+  static_assert(WAVES_N == 4 || WAVES_N == 2 || WAVES_N == 1, "eight waves or four");
+  static_assert(!FUSE || (!NT && WAVES_N <= 2), "FUSE: forward, pieces");
+  constexpr bool KS = WAVES_N == 1;               // the waves share out the contraction in the loop, the tile after it
+  constexpr int WNW = KS ? 2 : WAVES_N;
   static_assert(!DIFFP || !FUSE, "DIFFP: not with FUSE");
   constexpr int BN = WNW * NI * 32;
   constexpr int BMT = 2 * MI * 32;
-  static_assert(BN == 256 || BN == 128, "tile width");
-  static_assert(BMT == 256 || BMT == 128, "tile height");
-  // LDS stages.  A stage of a full or half tile takes 64 or 48 KB: two fit.  A quarter's takes 32 KB and half the
-  // MFMA time, which is less than the latency of the loads: four stages, three tiles in flight.
-  constexpr int NST = MI == 4 ? 2 : 4;
-  constexpr bool SPLIT = NST == 4;                // four stages in two arrays per operand
+  constexpr bool PIECE = WNW == 2, ROW64 = MI == 1;
+  // LDS stages.  A stage of a full or half tile takes 64 or 48 KB: two of 64 KB fit.  A piece's takes less and has less
+  // MFMA time, which is below the latency of the loads: as many stages as there is room for, so many tiles less one in flight.
+  constexpr int NST = PIECE ? piece_stages(MI, NI, FUSE, DIFFP) : 2;
   constexpr int NW = 2 * WNW, NTHR = 64 * NW;
   constexpr int A_ELEMS = BMT * BK;               // elements of one A stage
   // The loads are issued by the first half of the waves only.  Each SIMD hosts waves w and w + NW/2 and serves the
@@ -232,22 +251,20 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   constexpr int RPCB = 64 / PPRB;                 // forward: k-rows per 1 KB chunk
   constexpr int WCOLS = NI * 32;                  // columns of the wave tile
   constexpr int EPW = WCOLS + 8;                  // epilogue staging pitch (elements)
-  bf16_t* const sA0 = sm.a0; bf16_t* const sA1 = sm.a1;
-  bf16_t* const sB0 = sm.b0; bf16_t* const sB1 = sm.b1;
-  bf16_t* const sE0 = sm.e0; bf16_t* const sE1 = sm.e1; bf16_t* const sE2 = sm.e2; bf16_t* const sE3 = sm.e3;
+  constexpr int STAGE = PIECE ? piece_elems(MI, NI, FUSE, DIFFP) : 2 * BM * BK;      // elements
   int* const sRow = sm.row;
 
   int tm, tn;
-  tile_at(n_m, p.n_n, L, tm, tn);
+  if (ROW64) { tm = L; tn = half; } else tile_at(n_m, p.n_n, L, tm, tn);
   const int4 iw = *(const int4*)(p.dtab + p.items_off + (item0 + tm) * DI_WORDS);
   const ItemView it = {iw.x, iw.y, iw.z, iw.w};   // (nvalid: rows up to the last real token)
   const int mrow0 = mhalf * BMT;                  // first row of the item this tile covers
   const int nrows = it.nrows - mrow0 < BMT ? it.nrows - mrow0 : BMT;   // rows of the item inside this tile
   const int row0 = it.row0 + mrow0;
-  const int c0 = tn * TILE_N + half * BN;
+  const int c0 = ROW64 ? tn * BN : tn * TILE_N + half * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (wave >= NW) return;                         // a tile of four waves: the others end here, before any barrier
+  if (wave >= NW) return;                         // a piece beside full tiles: the other waves end here, before any barrier
   const int wm = wave / WNW, wn = wave % WNW;
   const bool loader = wave < LW;
   const int lw = wave % LW;                       // chunk owner index (meaningful for loading waves)
@@ -262,21 +279,26 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const bool lora = tk.kind == MUX_ADAPTER_LORA;
   const bool ia3 = tk.kind == MUX_ADAPTER_IA3_OUT;
   const bool tuning = tk.kind == MUX_ADAPTER_TUNING;   // forward: only x W is produced here (saved); backward: prepared rows
-  const int rank = tk.rank;
+  const int rank = lora ? tk.rank : 0;
   const bf16_t* adapterB = NT ? (const bf16_t*)tk.A : (const bf16_t*)tk.B;
   const bf16_t* Lvec = (const bf16_t*)tk.L;
 
   const int KT = (p.Kc + BK - 1) / BK;
   const int k_tail = p.Kc - (KT - 1) * BK;          // TAIL: contraction indices in the last backbone tile (a multiple of 8)
-  const int KT_ext = lora ? (rank + BK - 1) / BK : 0;
-  const int KT_total = KT + KT_ext;
+  const int KT_ext = lora && !(FUSE && SPLITK) ? (rank + BK - 1) / BK : 0;
+  // this tile forms Hs of its rows in the K loop (SPLITK: only those of the first column, whose share k_gemm_sum adds up)
+  const bool fuse_h = FUSE && lora && (!SPLITK || c0 == 0);
+  // The loops of pieces take two K-tiles a turn, and where a second way out between the two would make the compiler copy all
+  // accumulators at every turn (FUSE, and the pieces of 64 rows) an odd number of tiles is followed by one of zeros.
+  const int KT_pad = fuse_h && !SPLITK ? KT & 1 : 0;
+  const int KT_total = KT + KT_pad + KT_ext;
   const int kt_first = SPLITK ? (int)((unsigned)(split * KT_total) / (unsigned)p.splits) : 0;
   const int kt_end = SPLITK ? (int)((unsigned)((split + 1) * KT_total) / (unsigned)p.splits) : KT_total;
-  const bool fuse_h = FUSE && lora;                 // this tile forms Hs of its rows in the K loop
   // DIFFP: the bucket offsets of this task's listing for this direction, the buckets of this tile in a K-tile's row
   // of buckets, and per stage the entries of the tile it holds: first, first of the second bucket, end
   const bool patch = DIFFP && tk.kind == MUX_ADAPTER_DIFF && tk.rank >= 0 && p.DiffPack != nullptr && c0 < p.Nc;
-  constexpr int SPAN = BN / 128;
+  static_assert(!DIFFP || BN >= 128, "DIFFP: whole buckets");
+  constexpr int SPAN = BN >= 128 ? BN / 128 : 1;
   const int32_t* bptr = (const int32_t*)tk.dB;
   const int nbk = (p.Nc + 127) >> 7, bcol = c0 >> 7;
   const int bspan = bcol + SPAN <= nbk ? SPAN : nbk - bcol;      // a ragged last tile may hold one bucket only
@@ -324,8 +346,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   // w brings its w-th KB (lane l the 16 bytes at 1024 w + 16 l), so the slab lies in LDS as in memory, [64][a_pitch]
   const rsrc_t rAt = make_rsrc(fuse_h ? tk.A : (const void*)p.Ain, fuse_h ? (uint32_t)p.Kc * (uint32_t)a_pitch * 2u : 0u);
   const uint32_t offE = (fuse_h && (uint32_t)(lw * 1024 + lane * 16) < 128u * (uint32_t)a_pitch) ? (uint32_t)(lw * 1024 + lane * 16) : OOB;
-  uint32_t kE = 0;
   const uint32_t stepE = 128u * (uint32_t)a_pitch;
+  uint32_t kE = (uint32_t)kt_first * stepE;
 
   // row of the [rows][BK] tile chunk q of this wave puts this lane on, and the logical k-piece it fetches there
   auto a_row_of = [&](int q) { return lw * (RPC * ACH) + RPC * q + r_in; };
@@ -347,7 +369,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
       offB[q] = (uint32_t)(((size_t)(c0 + b_row_of(q)) * p.ldw + piece_of(b_row_of(q)) * 8) * 2);
     } else {
       const int kk = (lw * BCH + q) * RPCB + nk_in;          // k-row inside the tile
-      const int seg = (n_pp >> 1) ^ ((kk & 3) << 1);         // logical 32-byte segment
+      const int seg = (n_pp >> 1) ^ swz_k<BN>(kk);           // logical 32-byte segment
       const int n = seg * 16 + (n_pp & 1) * 8;
       offB[q] = (c0 + n < p.Nc) ? (uint32_t)(((size_t)kk * p.ldw + c0 + n) * 2) : OOB;
     }
@@ -365,8 +387,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const int special = SPLITK && kt_end < odd_tile ? kt_end : odd_tile;
   auto prepare = [&]() {
     if (next_tile < special) return;
-    if (SPLITK && next_tile >= kt_end) {                      // the next share's: nothing to fetch
-      kA = OOB; kB = OOB;
+    if (PIECE && (next_tile >= kt_end || (fuse_h && next_tile == KT && KT_pad))) {
+      curA[2] = 0; curB[2] = 0;                               // past the end, or the next share's: zeros, whatever the offset
+      if (FUSE) kE = OOB;
     } else if (TAIL && next_tile == KT - 1) {                                // the last backbone tile is not full: pieces past the end
 #pragma unroll
       for (int q = 0; q < ACH; ++q)
@@ -381,10 +404,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
       if (next_tile >= KT_total) {
         kA = OOB; kB = OOB;
       } else {
-        const int j0 = (next_tile - KT) * BK;                 // first contraction index of this adapter tile
+        const int j0 = (next_tile - KT - KT_pad) * BK;        // first contraction index of this adapter tile
         curB = rP; kB = 0; stepA = 0; stepB = 0;
         if (FUSE) {
-          kA = OOB;                                           // the A side of the adapter tile comes from the accumulators
+          curA[2] = 0;                                        // the A side of the adapter tile comes from the accumulators
         } else {
           curA = rE; kA = 0;
 #pragma unroll
@@ -401,7 +424,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
             offB[q] = (c < p.Nc && j < a_pitch) ? (uint32_t)(((size_t)c * a_pitch + j) * 2) : OOB;
           } else {
             const int kk = (lw * BCH + q) * RPCB + nk_in;
-            const int seg = (n_pp >> 1) ^ ((kk & 3) << 1);
+            const int seg = (n_pp >> 1) ^ swz_k<BN>(kk);
             const int n = seg * 16 + (n_pp & 1) * 8;
             offB[q] = (c0 + n < p.Nc && j0 + kk < rank) ? (uint32_t)(((size_t)(j0 + kk) * p.Nc + c0 + n) * 2) : OOB;
           }
@@ -447,11 +470,29 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
       const int krow = ks * 16 + 8 * lg + kq;
 #pragma unroll
       for (int t = 0; t < NI; ++t) {
-        const int seg = (wn * (2 * NI) + 2 * t + lhalf) ^ (kq << 1);
+        const int seg = (wn * (2 * NI) + 2 * t + lhalf) ^ swz_k<BN>(kq);
         const bf16x4 lo = lds_read_tr(cB + krow * BN + seg * 16 + bn_col);
         const bf16x4 hi = lds_read_tr(cB + (krow + 4) * BN + seg * 16 + bn_col);
         b[t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       }
+    }
+  };
+
+  // KS: step `wave` of a K-tile, all 2 MI + 2 NI fragments of the tile
+  auto read_step = [&](const bf16_t* cA, const bf16_t* cB, int r, bf16x8 (&a)[2 * MI], bf16x8 (&b)[2 * NI]) {
+    const int pa = ((2 * wave + lg) ^ swz) * 8;
+    if (r < 2 * NI) {
+      if (NT) {
+        b[r] = *(const bf16x8*)(cB + (r * 32 + li) * BK + pa);
+      } else {
+        const int krow = wave * 16 + 8 * lg + kq;
+        const int seg = (2 * r + lhalf) ^ swz_k<BN>(kq);
+        const bf16x4 lo = lds_read_tr(cB + krow * BN + seg * 16 + bn_col);
+        const bf16x4 hi = lds_read_tr(cB + (krow + 4) * BN + seg * 16 + bn_col);
+        b[r] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+    } else {
+      a[r - 2 * NI] = *(const bf16x8*)(cA + ((r - 2 * NI) * 32 + li) * BK + pa);
     }
   };
 
@@ -491,89 +532,79 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
         b[t] = *(const bf16x8*)(cB + bt_rd + t * 32 * BK + pa);
       } else {
         const int krow = ks * 16 + 8 * lg + kq;
-        const int seg = (wn * (2 * NI) + 2 * t + lhalf) ^ (kq << 1);
+        const int seg = (wn * (2 * NI) + 2 * t + lhalf) ^ swz_k<BN>(kq);
         const bf16x4 lo = lds_read_tr(cB + krow * BN + seg * 16 + bn_col);
         const bf16x4 hi = lds_read_tr(cB + (krow + 4) * BN + seg * 16 + bn_col);
         b[t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       }
     }
   };
-  // FUSE: the accumulator of this wave's 32 x 32 block of X A_t (row block wn of the wave's rows, transposed like acc),
-  // the fragment of the slab of A_t for step ks (lane (li, lg): column li of the slab, 8 consecutive k), and the X
-  // fragment of row block wn.
-  f32x16 hacc;
+  // FUSE: the accumulators of this wave's 32 x 32 blocks of X A_t (row blocks HB wn .. of the wave's rows, transposed like
+  // acc), and the fragment of the slab of A_t for step ks (lane (li, lg): column li of the slab, 8 consecutive k).
+  constexpr int HB = MI / 2 > 0 ? MI / 2 : 1;
+  f32x16 hacc[HB];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) hacc[v] = 0.f;
+  for (int i = 0; i < HB; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) hacc[i][v] = 0.f;
   auto read_e = [&](const bf16_t* cE, int ks) -> bf16x8 {
     const int krow = ks * 16 + 8 * lg + kq;
     const bf16x4 lo = lds_read_tr(cE + krow * a_pitch + lhalf * 16 + bn_col);
     const bf16x4 hi = lds_read_tr(cE + (krow + 4) * a_pitch + lhalf * 16 + bn_col);
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
-  // the product of this step's slab fragment with the X fragment of row block wn, picked by selects on the (uniform)
-  // wn: an index would send the fragments through scratch memory, and a branch per row block makes the compiler copy
-  // the accumulator behind each MFMA
+  // the products of this step's slab fragment with the X fragments of this wave's row blocks, picked by selects on the
+  // (uniform) wn: an index would send the fragments through scratch memory, and a branch per row block makes the compiler
+  // copy the accumulator behind each MFMA
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   auto mma_h = [&](const bf16x8& e, const bf16x8 (&a)[MI]) {
-    u32x4 x = __builtin_bit_cast(u32x4, a[0]);
 #pragma unroll
-    for (int t = 1; t < MI; ++t) {
-      const u32x4 y = __builtin_bit_cast(u32x4, a[t]);
+    for (int i = 0; i < HB; ++i) {
+      u32x4 x = __builtin_bit_cast(u32x4, a[i]);
+      if (MI > 1) {
+        const u32x4 y = __builtin_bit_cast(u32x4, a[MI > 1 ? HB + i : 0]);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) x[c] = wn == t ? y[c] : x[c];
+        for (int c = 0; c < 4; ++c) x[c] = wn == 1 ? y[c] : x[c];
+      }
+      hacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e, __builtin_bit_cast(bf16x8, x), hacc[i], 0, 0, 0);
     }
-    hacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e, __builtin_bit_cast(bf16x8, x), hacc, 0, 0, 0);
   };
   // One MFMA step from (a, b) with the operand reads of step ks_next of (cA, cB) into (an, bn) issued one per
-  // MFMA in its shadow (skipped when rd is false), and, when LOADS, the loads of one tile into (dA, dB, dE) spread
-  // over the MFMAs after them.  FUSE: one more product, e with the X fragment of row block wn, and the read of the
-  // next step's fragment en of the slab cE.
+  // MFMA in its shadow, and, when LOADS, the loads of one tile into (dA, dB) spread over the MFMAs after them.
   auto fused_step = [&](const bf16x8 (&a)[MI], const bf16x8 (&b)[NI], const bf16_t* cA, const bf16_t* cB, int ks_next,
-                        bf16x8 (&an)[MI], bf16x8 (&bn)[NI], bool rd, auto LOADS, bf16_t* dA, bf16_t* dB,
-                        const bf16x8& e, bf16x8& en, const bf16_t* cE, bf16_t* dE, uint32_t dP = 0, int o0 = 0,
-                        int o2 = 0) {
+                        bf16x8 (&an)[MI], bf16x8 (&bn)[NI], auto LOADS, bf16_t* dA, bf16_t* dB, uint32_t dP = 0,
+                        int o0 = 0, int o2 = 0) {
     constexpr bool loads = decltype(LOADS)::value;
     constexpr int NM = MI * NI, NR = MI + NI, NL = NLD;
-    if (FUSE && fuse_h) en = read_e(cE, ks_next);
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       mma_one(a, b, m);
-      if (rd) {
-        if (m < NR) read_one(cA, cB, ks_next, m, an, bn);
-        if (m == NM - 1) {                                   // a narrower tile has more fragments than MFMAs
+      if (m < NR) read_one(cA, cB, ks_next, m, an, bn);
+      if (m == NM - 1) {                                     // a narrower tile has more fragments than MFMAs
 #pragma unroll
-          for (int r = NM; r < NR; ++r) read_one(cA, cB, ks_next, r, an, bn);
-        }
+        for (int r = NM; r < NR; ++r) read_one(cA, cB, ks_next, r, an, bn);
       }
       if (loads) {
 #pragma unroll
-        for (int d = (m * NL) / NM; d < ((m + 1) * NL) / NM; ++d) issue_one(dA, dB, dE, d, dP, o0, o2);
+        for (int d = (m * NL) / NM; d < ((m + 1) * NL) / NM; ++d) issue_one(dA, dB, nullptr, d, dP, o0, o2);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (FUSE && fuse_h) {
-      mma_h(e, a);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 
-  static_assert(!SPLIT || (2 * A_ELEMS <= BM * BK && 2 * BN * BK <= BM * BK), "two stages per array");
-  auto stA = [&](int s) -> bf16_t* {
-    if (SPLIT) return (s < 2 ? sA0 : sA1) + (s & 1) * A_ELEMS;
-    return s == 0 ? sA0 : sA1;
-  };
-  auto stB = [&](int s) -> bf16_t* {
-    if (SPLIT) return (s < 2 ? sB0 : sB1) + (s & 1) * (BN * BK);
-    return s == 0 ? sB0 : sB1;
-  };
-  auto stE = [&](int s) -> bf16_t* { return s == 0 ? sE0 : (s == 1 ? sE1 : (s == 2 ? sE2 : sE3)); };
+  auto stA = [&](int st) -> bf16_t* { return sm.base + st * STAGE; };
+  auto stB = [&](int st) -> bf16_t* { return sm.base + st * STAGE + (PIECE ? A_ELEMS : BM * BK); };
+  auto stE = [&](int st) -> bf16_t* { return sm.base + st * STAGE + A_ELEMS + BN * BK; };
   auto tile_barrier = [&]() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
 
-  auto ldsP = [&](int st) -> uint32_t { return sm.pk_lds + (uint32_t)st * 1024u; };
+  // DIFFP: LDS byte address of a stage's packed entries (eight waves: behind the two stages)
+  auto ldsP = [&](int st) -> uint32_t {
+    return (uint32_t)(uintptr_t)(lds_void_ptr)(PIECE ? sm.base + st * STAGE + A_ELEMS + BN * BK : sm.base + 2 * STAGE + st * kPackElems);
+  };
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
   // DIFFP: the entries o0 .. o2 - 1 of a tile (o1: the first of its second bucket), the first 256 of them in cP, added to
   // the W side of the tile in stage cB (landed, visible to the workgroup)
@@ -581,7 +612,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     auto add_entry = [&](uint32_t w, int pos) {
       const int j = (int)(w >> 23), line = (int)((w >> 16) & 127u) + ((SPAN == 2 && o0 + pos >= o1) ? 128 : 0);
       bf16_t* e = NT ? cB + line * BK + (((j >> 3) ^ swz_row(line)) * 8) + (j & 7)
-                     : cB + j * BN + (((line >> 4) ^ ((j & 3) << 1)) * 16) + (line & 15);
+                     : cB + j * BN + (((line >> 4) ^ swz_k<BN>(j)) * 16) + (line & 15);
       // (the packed bf16 add of the LDS atomic unit in place of this read-modify-write was 5 % slower)
       *e = f32_to_bf16(bf16_to_f32(*e) + __uint_as_float(w << 16));
     };
@@ -605,64 +636,284 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   wait_lgkm0();
   tile_barrier();
   if (DIFFP && patch && ps2[0] > ps0[0]) {
-    patch_tile(sB0, ldsP(0), ps0[0], ps1[0], ps2[0]);
+    patch_tile(stB(0), ldsP(0), ps0[0], ps1[0], ps2[0]);
     wait_lgkm0();
     tile_barrier();
   }
 
-  bf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
-  bf16x8 e0 = {}, e1 = {};
-  read_ops(sA0, sB0, 0, a0, b0);
-  if (FUSE && fuse_h) e0 = read_e(sE0, 0);
   // FUSE: the K loop ends with the backbone; the adapter tile (its B_t side is fetched like any tile) follows below
-  const int KT_loop = fuse_h ? KT : kt_end - kt_first;
+  const int KT_loop = fuse_h && !SPLITK ? KT + KT_pad : kt_end - kt_first;
 
-  // Steps 0..2 run from registers read one step ahead; before the last step every wave has read all of this
-  // stage and tile kt+1 has landed (the loads of the NST-2 tiles after it may stay in flight): barrier; then,
-  // under the last step's MFMAs, the first operands of tile kt+1 are read and all loads of tile kt+NST are
-  // issued into the stage just freed.
-  for (int kt2 = 0; kt2 < KT_loop; kt2 += NST) {
+  if constexpr (KS) {
+    // Each wave takes one of the four MFMA steps of every K-tile: every operand is read from LDS once (waves that each own a
+    // quarter of the piece read all of them twice, and FUSE's slab four times), and the four sums meet in LDS once, at the end.
+    // All operands are read one K-tile ahead (there is one wave a SIMD: nothing hides an LDS read but the wave's own
+    // products); one barrier a K-tile, at its start: by then every wave has read this tile into registers (its stage may be
+    // refilled) and the next one has landed.
+    // Bound by the direct-to-LDS loads, about 24 cycles for each 1 KB instruction of a compute unit, whatever their depth
+    // (a stage less changes nothing) and place in the loop: 0.27 us a K-tile of 64 x 128 (the loads alone 0.27, the rest
+    // 0.15), 0.175 of 64 x 64 (0.165 and 0.10), 0.335 of 128 x 128.
+    static_assert(MI == 1, "row groups of 64");
+    constexpr int NSLOT = 4 * MI * NI, RT = 2 * (MI + NI), HW = 2 * MI;
+    f32x16 accf[2 * MI][2 * NI], haccf[FUSE ? HW : 1];
 #pragma unroll
-    for (int u = 0; u < NST; ++u) {
-      const int kt = kt2 + u;
-      if (kt < KT_loop) {
-        bf16_t* cA = stA(u);
-        bf16_t* cB = stB(u);
-        bf16_t* cE = stE(u);
-        prepare();
-        __builtin_amdgcn_sched_barrier(0);
-        fused_step(a0, b0, cA, cB, 1, a1, b1, true, std::false_type{}, nullptr, nullptr, e0, e1, cE, nullptr);
-        fused_step(a1, b1, cA, cB, 2, a0, b0, true, std::false_type{}, nullptr, nullptr, e1, e0, cE, nullptr);
-        fused_step(a0, b0, cA, cB, 3, a1, b1, true, std::false_type{}, nullptr, nullptr, e0, e1, cE, nullptr);
-        wait_vmcnt<(NST - 2) * NLD>();
-        wait_lgkm0();
-        tile_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        if (DIFFP) {
-          // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.  (Waiting for the
-          // tile one step earlier and adding the entries under the MFMAs of the third step was slower.)
-          const int un = (u + 1) % NST;
-          if (patch && ps2[un] > ps0[un]) {
-            patch_tile(stB(un), ldsP(un), ps0[un], ps1[un], ps2[un]);
-            wait_lgkm0();
-            tile_barrier();
-          }
-          // this stage is refilled with tile kt + NST (PRE == NST here): its entries, and the offsets of the tile after
-          ps0[u] = nx0; ps1[u] = nx1; ps2[u] = nx2;
-          bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
+    for (int v = 0; v < 16; ++v) {
+#pragma unroll
+      for (int t = 0; t < 2 * MI; ++t)
+#pragma unroll
+        for (int q = 0; q < 2 * NI; ++q) accf[t][q][v] = 0.f;
+#pragma unroll
+      for (int t = 0; t < (FUSE ? HW : 1); ++t) haccf[t][v] = 0.f;
+    }
+    bf16x8 ra[2][2 * MI], rb[2][2 * NI], re[2] = {};
+#pragma unroll
+    for (int r = 0; r < RT; ++r) read_step(stA(0), stB(0), r, ra[0], rb[0]);
+    if (FUSE) re[0] = read_e(stE(0), wave);            // (a tile that forms no Hs multiplies zeros: no branch in the loop)
+    int su = 0;                                      // stage of tile kt
+    prepare();
+    for (int kt2 = 0; kt2 < KT_loop; kt2 += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int kt = kt2 + u;
+        {
+          const int un = su + 1 == NST ? 0 : su + 1;
+          const int o0 = nx0, o2 = nx2;              // DIFFP: entries of the tile that refills this stage
+          wait_vmcnt<(NST - 2) * NLD>();
+          wait_lgkm0();
+          tile_barrier();
           __builtin_amdgcn_sched_barrier(0);
+          if (DIFFP) {
+            // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.
+            if (patch && ps2[1] > ps0[1]) {
+              patch_tile(stB(un), ldsP(un), ps0[1], ps1[1], ps2[1]);
+              wait_lgkm0();
+              tile_barrier();
+            }
+#pragma unroll
+            for (int q = 0; q + 1 < NST; ++q) { ps0[q] = ps0[q + 1]; ps1[q] = ps1[q + 1]; ps2[q] = ps2[q + 1]; }
+            ps0[NST - 1] = nx0; ps1[NST - 1] = nx1; ps2[NST - 1] = nx2;
+            bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // past the last tile: read, unused
+#pragma unroll
+          for (int i = 0; i < NSLOT; ++i) {
+            const int t = i / (2 * NI), q = i % (2 * NI);
+            accf[t][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rb[u][q], ra[u][t], accf[t][q], 0, 0, 0);
+            if (FUSE && q == 2 * NI - 1)
+              haccf[FUSE ? t : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(re[u], ra[u][t], haccf[FUSE ? t : 0], 0, 0, 0);
+#pragma unroll
+            for (int r = i * RT / NSLOT; r < (i + 1) * RT / NSLOT; ++r) read_step(stA(un), stB(un), r, ra[u ^ 1], rb[u ^ 1]);
+            if (FUSE && i == 0) re[u ^ 1] = read_e(stE(un), wave);
+#pragma unroll
+            for (int d = 2 * i * NLD / NSLOT; d < 2 * (i + 1) * NLD / NSLOT && d < NLD; ++d) issue_one(stA(su), stB(su), stE(su), d, ldsP(su), o0, o2);
+            if (i == NSLOT / 2) { issue_done(); prepare(); }      // all loads are out: what the next tile's need
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          su = un;
         }
-        fused_step(a1, b1, stA((u + 1) % NST), stB((u + 1) % NST), 0, a0, b0, true, std::true_type{}, cA, cB, e1, e0,
-                   stE((u + 1) % NST), cE, ldsP(u), ps0[u], ps2[u]);   // past the last tile: read, unused
-        issue_done();
+      }
+    }
+    // the refills issued past the last tile (zeros) must have landed before the stages are reused below
+    wait_vmcnt<0>();
+    wait_lgkm0();
+    tile_barrier();
+    if (FUSE && fuse_h) {
+      // The adapter tile.  Its W-side operand (rows of B_t) was fetched like any K-tile into the stage after the last
+      // backbone tile's; its A side is Hs = s_t (X A_t) of the tile's rows, of which every wave holds a share in haccf.
+      // The shares meet in two other stages, wave w brings row block w together (lane: row li of it, columns 8 j + 4 lg ..
+      // + 3).  Scaled, masked, rounded to bf16, it goes into the adapter tile's stage in the layout the operand reads expect
+      // (pieces 4..7 of a row, contraction indices 32..63, are zero), and from the tiles of the first column to memory.
+      const int sK = (KT + KT_pad) % NST;
+      static_assert(HW * 4 * 1024 <= 2 * STAGE / 2 && NST >= 4, "the shares of Hs fit two stages");
+      float4* red = (float4*)stA(sK < 2 ? 2 : 0);
+#pragma unroll
+      for (int t = 0; t < HW; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          red[((t * 4 + wave) * 4 + j) * 64 + lane] = make_float4(haccf[FUSE ? t : 0][4 * j], haccf[FUSE ? t : 0][4 * j + 1], haccf[FUSE ? t : 0][4 * j + 2], haccf[FUSE ? t : 0][4 * j + 3]);
+      wait_lgkm0();
+      tile_barrier();
+      bf16_t* hA = stA(sK);
+      if (wave < HW) {
+        const int row_l = wave * 32 + li;
+        const bool keep = row_l < nrows && sRow[row_l] != 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const float4 x = red[((wave * 4 + w) * 4 + j) * 64 + lane];
+            v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+          }
+          const int col = 8 * j + 4 * lg;
+#pragma unroll
+          for (int c4 = 0; c4 < 4; ++c4) v[c4] = (keep && col + c4 < rank) ? tk.scale * v[c4] : 0.f;
+          uint2 pk;
+          pk.x = pack_bf16x2(v[0], v[1]);
+          pk.y = pack_bf16x2(v[2], v[3]);
+          *(uint2*)(hA + row_l * BK + ((j ^ swz) * 8) + 4 * lg) = pk;
+          if (c0 == 0 && p.HsOut != nullptr && row_l < nrows && col < p.RP)
+            *(uint2*)(p.HsOut + (size_t)(row0 + row_l) * p.RP + col) = pk;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          *(uint4*)(hA + row_l * BK + (((4 + 2 * lg + q) ^ swz) * 8)) = make_uint4(0, 0, 0, 0);
+      }
+      wait_lgkm0();
+      tile_barrier();
+      if (wave < ((rank + 15) >> 4)) {               // steps that carry data (rank <= 32: one or two)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) read_step(hA, stB(sK), r, ra[0], rb[0]);
+#pragma unroll
+        for (int i = 0; i < NSLOT; ++i)
+          accf[i / (2 * NI)][i % (2 * NI)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rb[0][i % (2 * NI)], ra[0][i / (2 * NI)], accf[i / (2 * NI)][i % (2 * NI)], 0, 0, 0);
+      }
+      wait_lgkm0();
+      tile_barrier();
+    }
+    // The four sums of every 32x32 block meet in LDS, a row of blocks of each wave's part at a time: added in the order of the
+    // steps, so that an element's sum does not depend on the shape of the piece.
+    static_assert(16 * NI * 4 * 1024 <= NST * STAGE * 2, "the shares of one row of blocks fit the stages");
+    float4* red = (float4*)sm.base;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+      for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const f32x16& x = accf[(o >> 1) * MI + mi][(o & 1) * NI + ni];
+            red[(((o * 4 + wave) * NI + ni) * 4 + j) * 64 + lane] = make_float4(x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]);
+          }
+          __builtin_amdgcn_sched_barrier(0);         // (a block at a time out of the accumulation registers)
+        }
+      wait_lgkm0();
+      tile_barrier();
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float4 s4 = red[((wave * 4 * NI + ni) * 4 + j) * 64 + lane];
+#pragma unroll
+          for (int w = 1; w < 4; ++w) {
+            const float4 x = red[(((wave * 4 + w) * NI + ni) * 4 + j) * 64 + lane];
+            s4.x += x.x; s4.y += x.y; s4.z += x.z; s4.w += x.w;
+          }
+          acc[mi][ni][4 * j] = s4.x; acc[mi][ni][4 * j + 1] = s4.y; acc[mi][ni][4 * j + 2] = s4.z; acc[mi][ni][4 * j + 3] = s4.w;
+        }
+      wait_lgkm0();
+      tile_barrier();
+    }
+  } else if constexpr (PIECE) {
+    // One wave a SIMD: nothing hides an LDS read but the wave's own products, so all operands of the next K-tile are read
+    // under those of this one (read one step of 16 ahead, as the eight-wave loop does, a quarter took 0.367 us a K-tile, 0.335
+    // so; the loads alone take 0.31, see above).  One barrier a K-tile, as above.
+    constexpr int NM = MI * NI, NR = MI + NI, NSLOT = 4 * NM, RT = 4 * NR;
+    bf16x8 ra[2][4][MI], rb[2][4][NI], re[2][4] = {};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      read_ops(stA(0), stB(0), ks, ra[0][ks], rb[0][ks]);
+      if (FUSE) re[0][ks] = read_e(stE(0), ks);
+    }
+    int su = 0;                                      // stage of tile kt
+    prepare();
+    for (int kt2 = 0; kt2 < KT_loop; kt2 += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int kt = kt2 + u;
+        if (FUSE || kt < KT_loop) {
+          const int un = su + 1 == NST ? 0 : su + 1;
+          const int o0 = nx0, o2 = nx2;              // DIFFP: entries of the tile that refills this stage
+          wait_vmcnt<(NST - 2) * NLD>();
+          wait_lgkm0();
+          tile_barrier();
+          __builtin_amdgcn_sched_barrier(0);
+          if (DIFFP) {
+            // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.
+            if (patch && ps2[1] > ps0[1]) {
+              patch_tile(stB(un), ldsP(un), ps0[1], ps1[1], ps2[1]);
+              wait_lgkm0();
+              tile_barrier();
+            }
+#pragma unroll
+            for (int q = 0; q + 1 < NST; ++q) { ps0[q] = ps0[q + 1]; ps1[q] = ps1[q + 1]; ps2[q] = ps2[q + 1]; }
+            ps0[NST - 1] = nx0; ps1[NST - 1] = nx1; ps2[NST - 1] = nx2;
+            bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // past the last tile: read, unused
+#pragma unroll
+          for (int i = 0; i < NSLOT; ++i) {
+            const int ks = i / NM;
+            mma_one(ra[u][ks], rb[u][ks], i % NM);
+#pragma unroll
+            for (int r = i * RT / NSLOT; r < (i + 1) * RT / NSLOT; ++r)
+              read_one(stA(un), stB(un), r / NR, r % NR, ra[u ^ 1][r / NR], rb[u ^ 1][r / NR]);
+            if (FUSE) {
+              if (i % NM == 0) re[u ^ 1][ks] = read_e(stE(un), ks);
+              if (i % NM == NM - 1) mma_h(re[u][ks], ra[u][ks]);
+            }
+#pragma unroll
+            for (int d = 2 * i * NLD / NSLOT; d < 2 * (i + 1) * NLD / NSLOT && d < NLD; ++d) issue_one(stA(su), stB(su), stE(su), d, ldsP(su), o0, o2);
+            if (i == NSLOT / 2) { issue_done(); prepare(); }      // all loads are out: what the next tile's need
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          su = un;
+        }
+      }
+    }
+  } else {
+    bf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
+    read_ops(stA(0), stB(0), 0, a0, b0);
+    // Steps 0..2 run from registers read one step ahead; before the last step every wave has read all of this
+    // stage and tile kt+1 has landed: barrier; then, under the last step's MFMAs, the first operands of tile kt+1 are
+    // read and all loads of tile kt+2 are issued into the stage just freed.
+    for (int kt2 = 0; kt2 < KT_loop; kt2 += NST) {
+#pragma unroll
+      for (int u = 0; u < NST; ++u) {
+        const int kt = kt2 + u;
+        if (kt < KT_loop) {
+          bf16_t* cA = stA(u);
+          bf16_t* cB = stB(u);
+          prepare();
+          __builtin_amdgcn_sched_barrier(0);
+          fused_step(a0, b0, cA, cB, 1, a1, b1, std::false_type{}, nullptr, nullptr);
+          fused_step(a1, b1, cA, cB, 2, a0, b0, std::false_type{}, nullptr, nullptr);
+          fused_step(a0, b0, cA, cB, 3, a1, b1, std::false_type{}, nullptr, nullptr);
+          wait_vmcnt<(NST - 2) * NLD>();
+          wait_lgkm0();
+          tile_barrier();
+          __builtin_amdgcn_sched_barrier(0);
+          if (DIFFP) {
+            // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.  (Waiting for the
+            // tile one step earlier and adding the entries under the MFMAs of the third step was slower.)
+            const int un = (u + 1) % NST;
+            if (patch && ps2[un] > ps0[un]) {
+              patch_tile(stB(un), ldsP(un), ps0[un], ps1[un], ps2[un]);
+              wait_lgkm0();
+              tile_barrier();
+            }
+            // this stage is refilled with tile kt + NST (PRE == NST here): its entries, and the offsets of the tile after
+            ps0[u] = nx0; ps1[u] = nx1; ps2[u] = nx2;
+            bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          fused_step(a1, b1, stA((u + 1) % NST), stB((u + 1) % NST), 0, a0, b0, std::true_type{}, cA, cB, ldsP(u), ps0[u],
+                     ps2[u]);                        // past the last tile: read, unused
+          issue_done();
+        }
       }
     }
   }
-  // the refills issued past the last tile (zeros) must have landed before the stages are reused below
-  wait_vmcnt<0>();
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  if (!KS) {
+    // the refills issued past the last tile (zeros) must have landed before the stages are reused below
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
 
   if (SPLITK) {                                     // 16 bytes a lane, 1 KB a store
     float4* part = (float4*)(p.Part + ((size_t)split * p.quarters + slot) * (BMT * BN)) + wave * (MI * NI * 4 * 64) + lane;
@@ -673,37 +924,49 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           part[((mi * NI + ni) * 4 + j) * 64] = make_float4(acc[mi][ni][4 * j], acc[mi][ni][4 * j + 1], acc[mi][ni][4 * j + 2], acc[mi][ni][4 * j + 3]);
+    if (fuse_h) {                                   // this wave's rows of the share of X A_t, 32 columns a row
+      const int row = (slot < 4 * p.n_m * p.n_n ? 2 * tm + mhalf : 2 * p.n_m + tm) * BMT + (wm * MI + wn) * 32 + li;
+      float* hp = p.PartH + ((size_t)split * (2 * p.n_m + p.n_mh) * BMT + row) * 32 + 4 * lg;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *(float4*)(hp + 8 * j) = make_float4(hacc[0][4 * j], hacc[0][4 * j + 1], hacc[0][4 * j + 2], hacc[0][4 * j + 3]);
+    }
     return;
   }
-  if (FUSE && fuse_h) {
+  if (!KS && FUSE && fuse_h) {
     // The adapter tile.  Its W-side operand (rows of B_t) was fetched like any K-tile into the stage after the last
     // backbone tile's; its A side is Hs = s_t (X A_t) of the tile's rows, which the waves hold in hacc: this lane has
     // row wn*32 + li of the wave's row half and columns 8 j + 4 lg .. + 3.  Scaled, masked beyond the rank, rounded to
     // bf16, it goes into that stage in the layout the operand reads expect (pieces 4..7 of a row, contraction
     // indices 32..63, are zero), and from the tiles of the first column to memory.
-    const int sK = KT % NST;
+    const int sK = (KT + KT_pad) % NST;
     bf16_t* hA = stA(sK);
     const bf16_t* hB = stB(sK);
-    const int row_l = wm * (32 * MI) + wn * 32 + li;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = 8 * j + 4 * lg;
-      float v[4];
+    for (int i = 0; i < HB; ++i) {
+      if (MI == 1 && wn != 0) break;                // (both waves of a row half hold its only block)
+      const int row_l = wm * (32 * MI) + (MI == 1 ? 0 : (wn * HB + i) * 32) + li;
+      const bool keep = row_l < nrows && sRow[row_l] != 0;
 #pragma unroll
-      for (int c4 = 0; c4 < 4; ++c4) v[c4] = (col + c4 < rank) ? tk.scale * hacc[4 * j + c4] : 0.f;
-      uint2 pk;
-      pk.x = pack_bf16x2(v[0], v[1]);
-      pk.y = pack_bf16x2(v[2], v[3]);
-      *(uint2*)(hA + row_l * BK + ((j ^ swz) * 8) + 4 * lg) = pk;
-      if (c0 == 0 && p.HsOut != nullptr && row_l < nrows && col < p.RP)
-        *(uint2*)(p.HsOut + (size_t)(row0 + row_l) * p.RP + col) = pk;
+      for (int j = 0; j < 4; ++j) {
+        const int col = 8 * j + 4 * lg;
+        float v[4];
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) v[c4] = (keep && col + c4 < rank) ? tk.scale * hacc[i][4 * j + c4] : 0.f;
+        uint2 pk;
+        pk.x = pack_bf16x2(v[0], v[1]);
+        pk.y = pack_bf16x2(v[2], v[3]);
+        *(uint2*)(hA + row_l * BK + ((j ^ swz) * 8) + 4 * lg) = pk;
+        if (c0 == 0 && p.HsOut != nullptr && row_l < nrows && col < p.RP)
+          *(uint2*)(p.HsOut + (size_t)(row0 + row_l) * p.RP + col) = pk;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *(uint4*)(hA + row_l * BK + (((4 + 2 * lg + q) ^ swz) * 8)) = make_uint4(0, 0, 0, 0);
     }
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-      *(uint4*)(hA + row_l * BK + (((4 + 2 * lg + q) ^ swz) * 8)) = make_uint4(0, 0, 0, 0);
     wait_lgkm0();
     tile_barrier();
     const int nks = (rank + 15) >> 4;               // steps that carry data (rank <= 32: one or two)
+    bf16x8 a0[MI], b0[NI];
     for (int ks = 0; ks < nks; ++ks) {
       read_ops(hA, hB, ks, a0, b0);
       mma(a0, b0);
@@ -714,8 +977,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
 
   // ---- epilogue: aggregate, mask, store; 32 rows of the wave tile at a time through this wave's own array.
   constexpr int AREA = NI == 2 ? 2560 : 1280;     // elements of a staging area (5 KB or 2.5 KB)
-  constexpr int AREAS = A_ELEMS / AREA;           // staging areas per A stage
-  static_assert(32 * EPW <= AREA && NW <= AREAS * NST, "every wave has its own staging area");
+  constexpr int AREAS = PIECE ? NW : A_ELEMS / AREA;   // staging areas per stage (eight waves: in its A side)
+  static_assert(32 * EPW <= AREA && NW <= AREAS * NST && (!PIECE || NW * AREA <= NST * STAGE), "every wave has its own staging area");
   bf16_t* stage = stA(wave / AREAS) + (wave % AREAS) * AREA;
   constexpr int PPR = WCOLS / 8;                 // 16-byte pieces per staged row
   constexpr int RPI = 64 / PPR;                  // rows one wave instruction moves
@@ -774,54 +1037,65 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   }
 }
 
-// Workgroups 0 .. n_full-1 compute full tiles, slot by slot with the XCD in the low three bits of the index (the
-// hardware deals consecutive workgroups round-robin to the eight XCDs, so one XCD's L2 sees neighbouring tiles).
+// A row group without tokens: CLEAR_N columns of its output rows (d: its number times the slabs of CLEAR_N columns, plus the
+// slab), a wave a row, and with the first of them the rows of Hs.
+template <int NTHR>
+__device__ __forceinline__ void clear_group(const GemmParams& p, int d) {
+  const int slabs = (p.Nc + CLEAR_N - 1) / CLEAR_N;
+  const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + p.n_mh + d / slabs) * DI_WORDS);
+  const int c = (d % slabs) * CLEAR_N + (threadIdx.x & 63) * 8;
+  if (c < p.Nc)
+    for (int m = threadIdx.x >> 6; m < iw.z; m += NTHR / 64) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
+  if (d % slabs == 0 && p.HsOut != nullptr)
+    for (int e = threadIdx.x; e < iw.z * (p.RP / 8); e += NTHR)
+      *(uint4*)(p.HsOut + (size_t)(iw.y + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
+}
+
+// Stamps of the diagnostic counters; the start stamps wait in the buffer itself (words 2, 3), so that nothing stays live
+// across the tile.
+__device__ __forceinline__ void clock_start(const GemmParams& p) {
+  if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) { p.clk[2] = clock64(); p.clk[3] = wall_clock64(); }
+}
+__device__ __forceinline__ void clock_end(const GemmParams& p) {
+  if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
+    atomicAdd(p.clk, (unsigned long long)clock64() - p.clk[2]);
+    atomicAdd(p.clk + 1, (unsigned long long)wall_clock64() - p.clk[3]);
+  }
+}
+
+// Workgroup b's quarter of a tile left over, or (from half0 on) of one whose row group has tokens in its first 128 rows only.
+struct Quarter { int L, half, mhalf; bool hg; };
+__device__ __forceinline__ Quarter quarter_piece(const GemmParams& p, int b) {
+  Quarter q;
+  q.hg = b >= p.half0;
+  const int t = b - (q.hg ? p.half0 : p.n_full);
+  q.half = (t >> 3) & 1;
+  q.mhalf = q.hg ? 0 : (t >> 4) & 1;
+  if (q.hg) {
+    q.L = p.start_h[t & 7] + (t >> 4);
+    if (q.L >= p.start_h[(t & 7) + 1]) q.L = -1;
+  } else {
+    q.L = tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 5));
+  }
+  return q;
+}
+
+// Launches with full tiles.  Workgroups 0 .. n_full-1 compute full tiles, slot by slot with the XCD in the low three bits of
+// the index (the hardware deals consecutive workgroups round-robin to the eight XCDs, so one XCD's L2 sees neighbouring tiles).
 // The workgroups after them compute the remaining tiles in pieces (tail_split = 2: two half-width tiles each;
 // 4: four 128 x 128 quarters each); all pieces of a tile run on the same XCD.  The dispatcher hands out workgroups
 // in index order, so the pieces start as the compute units finish their last full tile.
-// SPLITK: all tiles are quarters, and p.splits workgroups share the contraction of each; the (share, quarter) pairs, share by
-// share, go to the XCDs in eight equal runs (dealt by whole tiles, 10 tiles of 6 quarters left three XCDs idle and gave
-// the others two rounds: 20.8 us, 14.8 so, for 60 quarters of 2560 x 2560 in four shares).
-template <bool NT, bool FUSE, bool DIFFP, bool TAIL, bool SPLITK = false>
+template <bool NT, bool DIFFP, bool TAIL>
 __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
-  constexpr int STAGE_ELEMS = BM * BK;            // 32 KB per operand and stage
-  __shared__ __attribute__((aligned(1024))) bf16_t sA0[STAGE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t sA1[STAGE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t sB0[STAGE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t sB1[STAGE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t sE0[FUSE ? 2048 : 8];   // FUSE: [64][rank <= 32] slabs of A_t, 4 KB a stage
-  __shared__ __attribute__((aligned(1024))) bf16_t sE1[FUSE ? 2048 : 8];
-  __shared__ __attribute__((aligned(1024))) bf16_t sE2[FUSE ? 2048 : 8];
-  __shared__ __attribute__((aligned(1024))) bf16_t sE3[FUSE ? 2048 : 8];
-  __shared__ __attribute__((aligned(1024))) uint32_t sP[DIFFP ? 4 * 256 : 2];   // DIFFP: 256 packed entries a stage
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[4 * (BM * BK + (DIFFP ? kPackElems : 0))];   // two stages of 64 KB, or four of 32 KB
+  static_assert(piece_stages(2, 2, false, DIFFP) == 4, "four stages of a quarter");
   __shared__ int sOff[DIFFP ? 3 * 1024 : 2];                                      // DIFFP: K < 65536, so at most 1023 K-tiles
   __shared__ int sRow[256];
-  const Smem sm = {sA0, sA1, sB0, sB1, sRow, sE0, sE1, sE2, sE3, (uint32_t)(uintptr_t)(lds_void_ptr)sP, sOff};
+  const Smem sm = {smem, sRow, sOff};
   const int b = blockIdx.x;
-  if (b >= p.clear0) {                            // a row group without tokens: CLEAR_N columns of its output rows, a wave a row
-    const int slabs = (p.Nc + CLEAR_N - 1) / CLEAR_N, d = b - p.clear0;
-    const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + p.n_mh + d / slabs) * DI_WORDS);
-    const int c = (d % slabs) * CLEAR_N + (threadIdx.x & 63) * 8;
-    if (c < p.Nc)
-      for (int m = threadIdx.x >> 6; m < iw.z; m += 8) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
-    if (FUSE && d % slabs == 0 && p.HsOut != nullptr)
-      for (int e = threadIdx.x; e < iw.z * (p.RP / 8); e += 512)
-        *(uint4*)(p.HsOut + (size_t)(iw.y + e / (p.RP / 8)) * p.RP + (e % (p.RP / 8)) * 8) = make_uint4(0, 0, 0, 0);
-    return;
-  }
-  // the start stamps wait in the buffer itself (words 2, 3), so that nothing stays live across the tile
-  if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) { p.clk[2] = clock64(); p.clk[3] = wall_clock64(); }
-  if constexpr (SPLITK) {
-    const int id = (b & 7) * (p.clear0 >> 3) + (b >> 3), split = id / p.quarters, q = id % p.quarters;
-    int L, half, mhalf;
-    if (split >= p.splits) return;
-    const bool hg = quarter_of(p, q, L, half, mhalf);
-    if (hg && threadIdx.x >= 256) {
-      if (split == 0) clear_below(p, L, half);
-      return;
-    }
-    gemm_tile<NT, 2, 2, 2, false, false, TAIL, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q);
-  } else if (!FUSE && b < p.n_full) {                    // a launch with the down-projection in the loop has pieces only
+  if (b >= p.clear0) return clear_group<512>(p, b - p.clear0);
+  clock_start(p);
+  if (b < p.n_full) {
     const int L = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 3);
     if (L < 0) return;
     gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, 0, p.n_m, L, 0, 0, sm);
@@ -829,40 +1103,74 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
     const int t = b - p.n_full;                                       // n_full is a multiple of 8
     const int L = tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 4));
     if (L < 0) return;
-    gemm_tile<NT, 4, 4, 1, FUSE, DIFFP, TAIL>(p, 0, p.n_m, L, (t >> 3) & 1, 0, sm);
+    gemm_tile<NT, 4, 4, 1, false, DIFFP, TAIL>(p, 0, p.n_m, L, (t >> 3) & 1, 0, sm);
   } else {
-    // a quarter of a tile left over, or of one whose row group has tokens in its first 128 rows only
-    const bool hg = b >= p.half0;
-    const int t = b - (hg ? p.half0 : p.n_full);
-    const int half = (t >> 3) & 1, mhalf = hg ? 0 : (t >> 4) & 1;
-    int L;
-    if (hg) {
-      L = p.start_h[t & 7] + (t >> 4);
-      if (L >= p.start_h[(t & 7) + 1]) return;
-    } else {
-      L = tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 5));
-      if (L < 0) return;
-    }
-    if (hg && threadIdx.x >= 256) {                // the four waves that a quarter does not need clear the padding below it
-      clear_below(p, L, half);
+    const Quarter q = quarter_piece(p, b);
+    if (q.L < 0) return;
+    if (q.hg && threadIdx.x >= 256) {              // the four waves that a quarter does not need clear the padding below it
+      clear_below(p, q.L, q.half);
       return;
     }
-    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, TAIL>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm);
+    gemm_tile<NT, 2, 2, 2, false, DIFFP, TAIL>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm);
   }
-  if (p.clk != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
-    atomicAdd(p.clk, (unsigned long long)clock64() - p.clk[2]);
-    atomicAdd(p.clk + 1, (unsigned long long)wall_clock64() - p.clk[3]);
+  clock_end(p);
+}
+
+// Launches without full tiles: four waves a workgroup, one a SIMD, with all of its registers.
+//   PIECES_HALF     256 x 128, quarters for the row groups with tokens in their first 128 rows only
+//   PIECES_QUARTER  128 x 128 (or such quarters alone)
+//   PIECES_64X128, PIECES_64X64   of row groups of 64; an XCD takes a run of pieces, the row group running fastest, so that
+//                   the pieces that read the same columns of W do it through one L2
+// SPLITK (quarters): p.splits workgroups share the contraction of each; the (share, quarter) pairs, share by
+// share, go to the XCDs in eight equal runs (dealt by whole tiles, 10 tiles of 6 quarters left three XCDs idle and gave
+// the others two rounds: 20.8 us, 14.8 so, for 60 quarters of 2560 x 2560 in four shares).
+enum : int { PIECES_HALF = 0, PIECES_QUARTER, PIECES_64X128, PIECES_64X64 };
+template <int PIECES, bool NT, bool FUSE, bool DIFFP, bool SPLITK>
+__global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p) {
+  constexpr int MI = PIECES == PIECES_HALF ? 4 : (PIECES == PIECES_QUARTER ? 2 : 1), NI = PIECES == PIECES_64X64 ? 1 : 2;
+  constexpr int ELEMS = piece_stages(MI, NI, FUSE, DIFFP) * piece_elems(MI, NI, FUSE, DIFFP);
+  constexpr int QUART = PIECES == PIECES_HALF ? piece_stages(2, 2, FUSE, DIFFP) * piece_elems(2, 2, FUSE, DIFFP) : 0;
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[ELEMS > QUART ? ELEMS : QUART];
+  __shared__ int sOff[DIFFP ? 3 * 1024 : 2];                                      // DIFFP: K < 65536, so at most 1023 K-tiles
+  __shared__ int sRow[256];
+  const Smem sm = {smem, sRow, sOff};
+  const int b = blockIdx.x;
+  if (b >= p.clear0) return clear_group<256>(p, b - p.clear0);
+  clock_start(p);
+  if constexpr (SPLITK) {
+    const int id = (b & 7) * (p.clear0 >> 3) + (b >> 3), split = id / p.quarters, q = id % p.quarters;
+    int L, half, mhalf;
+    if (split >= p.splits) return;
+    const bool hg = quarter_of(p, q, L, half, mhalf);
+    if (hg && split == 0) clear_below(p, L, half);
+    gemm_tile<NT, 2, 2, 2, FUSE, false, true, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q);
+  } else if constexpr (PIECES >= PIECES_64X128) {
+    const int id = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 3);
+    if (id < 0) return;
+    gemm_tile<NT, 1, 1, NI, FUSE, false, true>(p, 0, p.n_m, id % p.n_m, id / p.n_m, 0, sm);
+  } else if (PIECES == PIECES_HALF && b < p.half0) {
+    const int L = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 4);
+    if (L < 0) return;
+    gemm_tile<NT, 2, 4, 2, FUSE, DIFFP, true>(p, 0, p.n_m, L, (b >> 3) & 1, 0, sm);
+  } else {
+    const Quarter q = quarter_piece(p, b);
+    if (q.L < 0) return;
+    if (q.hg) clear_below(p, q.L, q.half);
+    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, true>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm);
   }
+  clock_end(p);
 }
 
 // The shares of a split contraction, summed in ascending order, then the epilogue of gemm_tile (scale, mask, round, store).
 // Bound by latency: there are few outputs, and a wave's time is its chain of loads.  So a workgroup takes one 32 x 64 block of
 // a wave tile, eight a quarter, a wave a quarter of the block's accumulator registers (1 KB a wave instruction, as the tiles
 // stored them), four shares in flight; the block turns in LDS into rows, one 16-byte piece a thread.
-template <bool NT>
+template <bool NT, bool FUSE>
 __global__ __launch_bounds__(256) void k_gemm_sum(const GemmParams p) {
   constexpr int EPW = 72;
   __shared__ __attribute__((aligned(16))) bf16_t stage[32 * EPW];
+  __shared__ __attribute__((aligned(16))) bf16_t sH[FUSE ? 32 * 40 : 8];      // FUSE: Hs of the block's rows
+  __shared__ __attribute__((aligned(16))) bf16_t sB[FUSE ? 32 * 64 : 8];      //       and the block's columns of B_t
   const int b = blockIdx.x >> 3, wave_t = (blockIdx.x >> 1) & 3, mi = blockIdx.x & 1;    // quarter, its wave tile, row block
   int L, half, mhalf, tm, tn;
   const bool hg = quarter_of(p, b, L, half, mhalf);
@@ -891,6 +1199,41 @@ __global__ __launch_bounds__(256) void k_gemm_sum(const GemmParams p) {
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int i = 0; i < 2; ++i) { s[i].x += v[u][i].x; s[i].y += v[u][i].y; s[i].z += v[u][i].z; s[i].w += v[u][i].w; }
+  }
+  if (FUSE && tk.kind == MUX_ADAPTER_LORA) {
+    // Hs = s_t (X A_t) of the block's rows from the shares, four columns a thread, to memory from the blocks of the first
+    // column; then the adapter's product, on the vector units (rank <= 32): a thread's row times its two runs of columns.
+    const int hr = threadIdx.x >> 3, hc = (threadIdx.x & 7) * 4, hm = m0 + hr;        // row, column of Hs
+    const bool hin = hm < nrows && row_is_valid(p.dtab, row0 + hm);
+    const int qrows = 2 * p.n_m + p.n_mh, prow = (hg ? 2 * p.n_m + tm : 2 * tm + mhalf) * 128 + hm;
+    float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = 0; k < p.splits; k += 4) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        v[u] = k + u < p.splits ? *(const float4*)(p.PartH + ((size_t)(k + u) * qrows * 128 + prow) * 32 + hc) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { h.x += v[u].x; h.y += v[u].y; h.z += v[u].z; h.w += v[u].w; }
+    }
+    const int rank = tk.rank;
+    uint2 pk;
+    pk.x = pack_bf16x2(hin && hc < rank ? tk.scale * h.x : 0.f, hin && hc + 1 < rank ? tk.scale * h.y : 0.f);
+    pk.y = pack_bf16x2(hin && hc + 2 < rank ? tk.scale * h.z : 0.f, hin && hc + 3 < rank ? tk.scale * h.w : 0.f);
+    *(uint2*)(sH + hr * 40 + hc) = pk;
+    if (cw0 == 0 && hm < nrows && hc < p.RP) *(uint2*)(p.HsOut + (size_t)(row0 + hm) * p.RP + hc) = pk;
+    const int bc = cw0 + (int)(threadIdx.x & 7) * 8;
+    *(uint4*)(sB + hr * 64 + (threadIdx.x & 7) * 8) = hr < rank && bc < p.Nc ? *(const uint4*)((const bf16_t*)tk.B + (size_t)hr * p.Nc + bc) : make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    for (int k = 0; k < rank; ++k) {
+      const float hk = bf16_to_f32(sH[li * 40 + k]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = 2 * wave + i;
+        const uint2 w = *(const uint2*)(sB + k * 64 + 32 * (r >> 2) + 8 * (r & 3) + 4 * lg);
+        s[i].x = fmaf(hk, __uint_as_float(w.x << 16), s[i].x); s[i].y = fmaf(hk, __uint_as_float(w.x & 0xffff0000u), s[i].y);
+        s[i].z = fmaf(hk, __uint_as_float(w.y << 16), s[i].z); s[i].w = fmaf(hk, __uint_as_float(w.y & 0xffff0000u), s[i].w);
+      }
+    }
   }
   const int m = m0 + (int)(threadIdx.x >> 3), c = cw0 + (int)(threadIdx.x & 7) * 8;      // the piece this thread stores
   const bool out = m < nrows && c < p.Nc, keep = out && row_is_valid(p.dtab, row0 + m);
@@ -934,7 +1277,7 @@ int compute_units() {
 
 // The tile plan of a launch: whole tiles for the full rounds of workgroups, the rest as halves or quarters, then the
 // quarters of the row groups with tokens in their first 128 rows only, then the clearing of those without any.
-struct TilePlan { int n_m, n_mh, n_n, n_full, tail_split, start_h[9], half0, clear0, grid; };
+struct TilePlan { int n_m, n_mh, n_n, n_full, tail_split, start_h[9], half0, clear0, grid, pieces; };
 TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   TilePlan t{};
   t.n_m = st->n_gemm[0];
@@ -981,32 +1324,51 @@ TilePlan plan_tiles(const mux_segtab* st, int Nc) {
   t.half0 = t.n_full + 8 * t.tail_split * tail_slots;
   t.clear0 = t.half0 + 16 * slots_h;
   t.grid = t.clear0 + st->n_gemm[2] * ((Nc + CLEAR_N - 1) / CLEAR_N);
+  t.pieces = t.tail_split == 4 ? PIECES_QUARTER : PIECES_HALF;
   return t;
 }
 
-// How many workgroups share the contraction of a quarter.  Launches whose quarters leave half of the compute units or
-// more without one spend their time walking all of K on the rest; with S shares the walk is 1 / S as long.  Estimate, in us,
-// from launches of 16 to 256 workgroups: 0.46 a K-tile (0.57 with the down-projection in the loop, which a split launch
-// leaves to a launch of its own: 9), 12 for the second launch and the shares' stores, 0.01 a share of a quarter.  A share
-// keeps eight K-tiles, twice what is in flight.
-// Whole pass, whole contraction -> split, rank 16: 4096 x 4096, 100 tokens, forward 39.3 -> 25.7 us, training 88.4 -> 62.0;
-// 8000 x 1000, 300 tokens, 70.1 -> 30.5 and 109.1 -> 69.4; 11008 x 4096, 64 tokens, 93.6 -> 39.2 and 140.1 -> 79.6; near the
-// line 2048 x 3000, 300 tokens, training 77.8 -> 66.6, and 4096 x 4096, 500 tokens of rank 64, 45.5 -> 44.2 forward.
+// Pieces of a launch that quarters would not fill: of row groups of 64, where all of them find a compute unit at once.  A
+// unit's loads bound a piece, 16 KB a K-tile for 64 x 64, 24 for 64 x 128, 32 for a quarter, so that smaller pieces on idle
+// units take less time although they read more in all.  4096 x 4096, tasks of 37, 129, 64 and 90 tokens, forward: 160 quarters
+// 41 us, 224 pieces of 64 x 128 27.2, 448 of 64 x 64 40; 512 x 1024, 1000 tokens, 256 pieces of 64 x 64 8.7 us, quarters 10.6; 1000 x 1000, 800
+// tokens, forward and backward 31.6 us, quarters 41.1, 64 x 128 36.7.
+int choose_pieces(const mux_segtab* st, int Nc, int units) {
+  if (st->n_gemm64[0] * ((Nc + 63) / 64) <= units) return PIECES_64X64;
+  if (st->n_gemm64[0] * ((Nc + 127) / 128) <= units) return PIECES_64X128;
+  return PIECES_QUARTER;
+}
+
+// How many workgroups share the contraction of a quarter.  A launch that leaves compute units without a piece spends its
+// time walking all of K on the rest; with S shares the walk of a quarter is 1 / S as long.  Estimate, in us, for weights that
+// come from memory, as they do where a step goes through many layers (60 layers of 4096 x 640, three tasks of 64 to 100 tokens,
+// forward: 26.4 us a call whole, 20.3 in eight shares; one layer over and over, its W in the last-level cache, 20.0 and 18.7): a
+// K-tile 0.45 of a quarter, 0.40 of 64 x 128, 0.30 of 64 x 64, with the down-projection in the loop 0.04 more; 9 for the second
+// launch and the shares' stores, 0.01 a share of a quarter.  A share keeps eight K-tiles, twice what is in flight.
+// Weights from memory, whole -> shared: 640 x 4096, three tasks, forward and backward 31.2 -> 25.6 us a call, with a fourth of
+// 440 tokens 33.8 -> 31.6; 4096 x 4096, 100 tokens, forward 28.8 -> 23.5.  From the cache: 8000 x 1000, 300 tokens, 34.5 -> 23.6,
+// 11008 x 4096, 64 tokens, 47.0 -> 28.2; near the line 2048 x 512, 64 tokens, 13.5 -> 14.4.
 // Arithmetic on the host alone: sizes are asked for in processes without a device too.
 int count_quarters(const mux_segtab* st, int Nc) {
   return (4 * st->n_gemm[0] + 2 * st->n_gemm[1]) * ((Nc + TILE_N - 1) / TILE_N);
 }
+// Bytes of one share: its quarters' partial tiles, and where the forward forms Hs, its part of X A_t
+size_t share_bytes(const mux_segtab* st, int Nc, bool nt) {
+  const size_t q = (size_t)count_quarters(st, Nc) * (128 * 128 * 4);
+  return q + (nt ? 0 : (size_t)(2 * st->n_gemm[0] + st->n_gemm[1]) * (128 * 32 * 4));
+}
 int plan_splits(const mux_segtab* st, int Kc, int Nc, bool nt, size_t room, int units) {
   const int quarters = count_quarters(st, Nc), kt = (Kc + BK - 1) / BK;
   if (quarters == 0 || st->n_diff > 0) return 1;
-  const bool fused = !nt && st->n_lora > 0 && st->n_tuning == 0 && st->r_max <= 32;
-  const size_t share = (size_t)quarters * (128 * 128 * 4);
+  const double fused = !nt && st->n_lora > 0 && st->n_tuning == 0 && st->r_max <= 32 ? 0.04 : 0.0;
+  const size_t share = share_bytes(st, Nc, nt);
   int most = units / quarters < kt / 8 ? units / quarters : kt / 8;
   if ((size_t)most * share > room) most = (int)(room / share);
+  const int pieces = choose_pieces(st, Nc, units);
   int best = 1;
-  double best_us = kt * (fused ? 0.57 : 0.46);
+  double best_us = kt * (fused + (pieces == PIECES_64X64 ? 0.30 : (pieces == PIECES_64X128 ? 0.40 : 0.45)));
   for (int s = 2; s <= most; ++s) {
-    const double us = (kt + s - 1) / s * 0.46 + 0.01 * s * quarters + 12.0 + (fused ? 9.0 : 0.0);
+    const double us = (kt + s - 1) / s * (0.45 + fused) + 0.01 * s * quarters + 9.0;
     if (us < best_us) { best_us = us; best = s; }
   }
   return best;
@@ -1020,7 +1382,34 @@ int launch_splits(const CallCtx& c, int Kc, int Nc, bool nt) {
 }
 size_t split_bytes(const mux_segtab* st, int Kc, int Nc, bool nt) {
   const int s = plan_splits(st, Kc, Nc, nt, ~(size_t)0, kComputeUnits);
-  return s > 1 ? (size_t)s * count_quarters(st, Nc) * (128 * 128 * 4) : 0;
+  return s > 1 ? (size_t)s * share_bytes(st, Nc, nt) : 0;
+}
+
+// The plan of a launch of pieces of row groups of 64.
+TilePlan plan_rows64(const mux_segtab* st, int Nc, int pieces) {
+  TilePlan t{};
+  t.pieces = pieces;
+  t.n_m = st->n_gemm64[0];
+  t.n_n = (Nc + (pieces == PIECES_64X64 ? 63 : 127)) / (pieces == PIECES_64X64 ? 64 : 128);
+  t.half0 = t.clear0 = (t.n_m * t.n_n + 7) / 8 * 8;
+  t.grid = t.clear0 + st->n_gemm64[1] * ((Nc + CLEAR_N - 1) / CLEAR_N);
+  return t;
+}
+template <int PIECES, bool NT>
+void launch_pieces(const char* name, dim3 grid, hipStream_t stream, const GemmParams& p) {
+  if constexpr (PIECES <= PIECES_QUARTER) {
+    if (p.DiffPack != nullptr) {
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, false, true, false>), grid, dim3(256), 0, stream, p);
+      return;
+    }
+  }
+  if constexpr (!NT) {
+    if (p.HsOut != nullptr) {
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, true, false, false>), grid, dim3(256), 0, stream, p);
+      return;
+    }
+  }
+  MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, false, false, false>), grid, dim3(256), 0, stream, p);
 }
 
 template <bool NT>
@@ -1030,18 +1419,26 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.dtab = c.dtab; p.tasks = *c.tref; p.Ain = Ain; p.W = (const bf16_t*)c.W; p.ldw = c.ldw; p.Ext = Ext; p.Out = Out;
   p.Zsave = Zsave; p.Kc = Kc; p.Nc = Nc; p.RP = c.RP;
   p.HsOut = fuse_down ? (bf16_t*)Ext : nullptr;
-  const TilePlan t = plan_tiles(c.st, Nc);
+  p.DiffPack = (const uint32_t*)c.diffPack;
+  p.splits = launch_splits(c, Kc, Nc, NT);
+  TilePlan t = plan_tiles(c.st, Nc);
   p.items_off = c.st->dev_image[DH_OFF_GEMM_ITEMS];
+  if (p.splits == 1) {
+    // (masked entries are listed by buckets of 128 lines)
+    if (t.n_full == 0 && t.tail_split == 4 && p.DiffPack == nullptr) t.pieces = choose_pieces(c.st, Nc, compute_units());
+    if (t.pieces >= PIECES_64X128) {
+      t = plan_rows64(c.st, Nc, t.pieces);
+      p.items_off = c.st->dev_image[DH_OFF_GEMM_ITEMS64];
+    }
+  }
   p.n_m = t.n_m; p.n_n = t.n_n; p.n_full = t.n_full; p.tail_split = t.tail_split;
   p.n_mh = t.n_mh; p.half0 = t.half0; p.clear0 = t.clear0;
   for (int x = 0; x < 9; ++x) p.start_h[x] = t.start_h[x];
   p.AinScaled = (const bf16_t*)c.dYs;
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
-  p.DiffPack = (const uint32_t*)c.diffPack;
   p.clk = diag_clock_buffer();
   if (t.grid == 0) return MUX_OK;
   p.Part = (float*)c.split;
-  p.splits = launch_splits(c, Kc, Nc, NT);
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
   const char* name = NT ? "gemm_nt" : "gemm_nn";
@@ -1050,18 +1447,28 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   if (p.splits > 1) {
     p.quarters = count_quarters(c.st, Nc);
     p.clear0 = (p.splits * p.quarters + 7) / 8 * 8;
-    const dim3 sgrid(t.grid - t.clear0 + p.clear0);
-    if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true, true>), sgrid, block, 0, c.stream, p);
-    else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, false, true>), sgrid, block, 0, c.stream, p);
-    prof_note_bytes(((double)p.splits * 4 + 2) * c.st->valid_total * Nc);
-    MUX_LAUNCH("gemm_sum", k_gemm_sum<NT>, dim3(8 * p.quarters), dim3(256), 0, c.stream, p);
+    p.PartH = p.Part + (size_t)p.splits * p.quarters * (128 * 128);
+    const dim3 sgrid(t.grid - t.clear0 + p.clear0), sums(8 * p.quarters);
+    const double moved = ((double)p.splits * 4 + 2) * c.st->valid_total * Nc;
+    if (!NT && fuse_down) {
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES_QUARTER, false, true, false, true>), sgrid, dim3(256), 0, c.stream, p);
+      prof_note_bytes(moved);
+      MUX_LAUNCH("gemm_sum", (k_gemm_sum<false, true>), sums, dim3(256), 0, c.stream, p);
+    } else {
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES_QUARTER, NT, false, false, true>), sgrid, dim3(256), 0, c.stream, p);
+      prof_note_bytes(moved);
+      MUX_LAUNCH("gemm_sum", (k_gemm_sum<NT, false>), sums, dim3(256), 0, c.stream, p);
+    }
     return MUX_OK;
   }
-  if (!NT && fuse_down && tail) MUX_LAUNCH(name, (k_gemm_dma<false, true, false, true>), grid, block, 0, c.stream, p);
-  else if (!NT && fuse_down) MUX_LAUNCH(name, (k_gemm_dma<false, true, false, false>), grid, block, 0, c.stream, p);
-  else if (p.DiffPack != nullptr) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true, false>), grid, block, 0, c.stream, p);
-  else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true>), grid, block, 0, c.stream, p);
-  else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, false>), grid, block, 0, c.stream, p);
+  if (t.n_full == 0) {
+    if (t.pieces == PIECES_HALF) launch_pieces<PIECES_HALF, NT>(name, grid, c.stream, p);
+    else if (t.pieces == PIECES_QUARTER) launch_pieces<PIECES_QUARTER, NT>(name, grid, c.stream, p);
+    else if (t.pieces == PIECES_64X128) launch_pieces<PIECES_64X128, NT>(name, grid, c.stream, p);
+    else launch_pieces<PIECES_64X64, NT>(name, grid, c.stream, p);
+  } else if (p.DiffPack != nullptr) MUX_LAUNCH(name, (k_gemm_dma<NT, true, false>), grid, block, 0, c.stream, p);
+  else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true>), grid, block, 0, c.stream, p);
+  else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false>), grid, block, 0, c.stream, p);
   return MUX_OK;
 }
 
@@ -1090,7 +1497,6 @@ bool gemm_dma_fuses_down(const CallCtx& c) {
   static const int mode = [] { const char* e = getenv("MUX_GEMM_FUSE_DOWN"); return e == nullptr ? 1 : atoi(e); }();
   if (mode == 0) return false;
   if (c.st->n_lora == 0 || c.st->n_tuning > 0 || c.st->r_max > 32 || c.diffPack != nullptr) return false;
-  if (launch_splits(c, c.K, c.N, false) > 1) return false;
   const TilePlan t = plan_tiles(c.st, c.N);
   if (t.n_full != 0 || (t.n_m + t.n_mh) * t.n_n == 0) return false;
   return t.tail_split == 4 || mode == 2;

@@ -23,6 +23,7 @@ enum : int {
   DH_OFF_ITEM_BITS,      // per 64-row work item: two words, bit r = row row0 + r of the item is a real token
   DH_OFF_GEMM_ITEMS,     // the 256-row work items ordered for the backbone product (see mux_segtab::n_gemm), DI_WORDS each,
                          // with the rows up to the last real token in the place of DI_NVALID
+  DH_OFF_GEMM_ITEMS64,   // the same of the 64-row work items (see mux_segtab::n_gemm64)
   DH_HDR_WORDS = 32
 };
 constexpr int kNumTileSizes = 4;
@@ -99,6 +100,7 @@ struct mux_segtab {
   // 256-row work items by what the backbone product has to compute of them: those with a real token past their first
   // 128 rows, those with real tokens in the first 128 rows only, those without any
   int32_t n_gemm[3] = {0, 0, 0};
+  int32_t n_gemm64[2] = {0, 0};     // 64-row work items with a real token, and those without any
 };
 
 namespace mux {

@@ -248,7 +248,7 @@ extern "C" mux_status mux_segtab_build(const mux_task_desc* tasks, int32_t n_tas
         dv.push_back((int32_t)w[1]);
       }
     }
-    // the 256-row items in the order of n_gemm, inside a class as they lie in the batch
+    // the 256-row items in the order of n_gemm, the 64-row items in that of n_gemm64, inside a class as they lie in the batch
     {
       while (dv.size() % 4) dv.push_back(0);
       dv[DH_OFF_GEMM_ITEMS] = (int32_t)dv.size();
@@ -258,6 +258,16 @@ extern "C" mux_status mux_segtab_build(const mux_task_desc* tasks, int32_t n_tas
           while (live > 0 && st->row_task[it.row0 + live - 1] < 0) --live;
           if ((live > 128 ? 0 : live > 0 ? 1 : 2) != cls) continue;
           st->n_gemm[cls]++;
+          const int32_t w[DI_WORDS] = {it.task, it.row0, it.nrows, live};
+          dv.insert(dv.end(), w, w + DI_WORDS);
+        }
+      dv[DH_OFF_GEMM_ITEMS64] = (int32_t)dv.size();
+      for (int cls = 0; cls < 2; ++cls)
+        for (const Item& it : st->items[0]) {
+          int32_t live = it.task >= 0 ? it.nrows : 0;
+          while (live > 0 && st->row_task[it.row0 + live - 1] < 0) --live;
+          if ((live > 0 ? 0 : 1) != cls) continue;
+          st->n_gemm64[cls]++;
           const int32_t w[DI_WORDS] = {it.task, it.row0, it.nrows, live};
           dv.insert(dv.end(), w, w + DI_WORDS);
         }

@@ -245,6 +245,79 @@ def test_every_tile_of_random_row_groups(env, seed):
             assert torch.equal(got, want), (case, (got != want).nonzero()[:4].tolist())
 
 
+@pytest.mark.parametrize("K,N,lens,shared", [
+    (64, 64, [1], False), (136, 72, [64, 1, 65, 200], False), (320, 1096, [37, 129, 64, 90], False),       # 64 x 64
+    (136, 4104, [37, 129, 64, 90], False), (520, 5000, [63, 128, 1], False),                               # 64 x 128
+    (72, 5000, [200, 130, 90], False), (192, 2304, [256, 700, 1000], False),                               # quarters, halves
+    (4096, 640, [100, 70, 64], True), (4168, 712, [64, 300, 1], True), (11008, 520, [40], True)])          # shared contraction
+@pytest.mark.parametrize("ranks", [(16, 8), (32, 1), (12, 31)])
+def test_small_launches_form_hs(env, K, N, lens, shared, ranks):
+    """Launches without full tiles, whose forward forms Hs in the tile loop, in every shape of piece: contractions of an even
+    and an odd number of K-tiles and with tails, columns that leave the last piece ragged, ranks from 1 to 32, a task without
+    an adapter between two LoRA tasks, NaN on the padding rows of X.  Integers so small that every sum, Hs and the products are
+    exact in any order, so Y, dX and the saved Hs have to be the very values; the first task's B holds an infinity, which must
+    reach that column of that task alone."""
+    mx, torch = env
+    dev = "cuda:0"
+    kinds = [(wlm.KIND_LORA, ranks[0]) if i == 0 else (wlm.KIND_NONE, 0) if i == 1 else (wlm.KIND_LORA, ranks[1]) for i in range(len(lens))]
+    st = mx.mux_segtab_build([mx.TaskDesc(k, r, 2.0, [n]) for (k, r), n in zip(kinds, lens)], 64)
+    nb, T = mx.mux_segtab_device_bytes(st), mx.mux_segtab_rows(st)
+    dtab = torch.empty(nb, dtype=torch.uint8, device=dev)
+    mx.mux_segtab_upload(st, dtab, nb)
+    gen = torch.Generator(device=dev).manual_seed(K + N)
+    ints = lambda *shape: torch.randint(-1, 2, shape, device=dev, generator=gen).to(torch.bfloat16)          # noqa: E731
+    row_task = torch.from_numpy(np.ascontiguousarray(mx.mux_segtab_row_task(st))).to(dev)
+    X, W, dY = ints(T, K), ints(K, N), ints(T, N)
+    X[row_task < 0] = float("nan")
+    dY[row_task < 0] = float("nan")
+    A, B = [], []
+    for k, r in kinds:
+        a = b = None
+        if k == wlm.KIND_LORA:
+            a, b = torch.zeros(K, r, dtype=torch.bfloat16, device=dev), ints(r, N)
+            a[torch.randperm(K, device=dev, generator=gen)[:40]] = ints(40, r)         # |X A| <= 40, |s X A| <= 80
+        A.append(a), B.append(b)
+    layer = mx.LayerDesc(K, N, mx.MUX_DT_BF16, W, len(lens), A, B, [None] * len(lens))
+    ws_bytes = mx.mux_lora_workspace_bytes(layer, st)
+    ws = torch.full((max(ws_bytes, 256),), 0xFF, dtype=torch.uint8, device=dev)
+    saved = torch.full((mx.mux_lora_saved_bytes(layer, st),), 0xFF, dtype=torch.uint8, device=dev)
+    Y, dX = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device=dev), torch.full((T, K), float("nan"), dtype=torch.bfloat16, device=dev)
+    grads = [[None if m is None else torch.empty(m.shape, device=dev) for m in ms] for ms in (A, B)]
+    stream = torch.cuda.current_stream()
+    print(f"K={K} N={N} lens={lens} ranks={ranks}", flush=True)
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    mx.mux_lora_forward(layer, st, dtab, X, Y, saved, ws, ws_bytes, stream)
+    torch.cuda.synchronize()
+    names = [e["name"] for e in mx.mux_profile_collect()]
+    mx.mux_profile_enable(0)
+    mx.mux_lora_backward(layer, st, dtab, X, dY, saved, dX, grads[0], grads[1], [None] * len(lens), 0, ws, ws_bytes, stream)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert ("gemm_sum" in names) == shared and (N == 2304 or "down_x" not in names), names
+    rp = (max(r for _, r in kinds) + 15) // 16 * 16
+    Hs = saved[:T * rp * 2].view(torch.bfloat16).view(T, rp)
+    valid = (row_task >= 0)[:, None]
+    zero = torch.zeros((), device=dev)
+    Xf, dYf = torch.where(valid, X.float(), zero), torch.where(valid, dY.float(), zero)
+    want_y, want_dx = Xf @ W.float(), dYf @ W.float().t().contiguous()
+    for t, (k, r) in enumerate(kinds):
+        rows = row_task == t
+        if k != wlm.KIND_LORA:
+            continue
+        h, g = 2.0 * (Xf[rows] @ A[t].float()), (2.0 * (dYf[rows] @ B[t].float().t().contiguous())).to(torch.bfloat16).float()
+        assert torch.equal(Hs[rows][:, :r].float(), h) and not Hs[rows][:, r:].any(), t
+        want_y[rows] += h @ B[t].float()
+        want_dx[rows] += g @ A[t].float().t().contiguous()
+    assert torch.equal(Y, want_y.to(torch.bfloat16)), (Y != want_y.to(torch.bfloat16)).nonzero()[:4].tolist()
+    assert torch.equal(dX, want_dx.to(torch.bfloat16)), (dX != want_dx.to(torch.bfloat16)).nonzero()[:4].tolist()
+    B[0][0, N - 1] = float("inf")
+    Y2 = torch.full_like(Y, float("nan"))
+    mx.mux_lora_forward(layer, st, dtab, X, Y2, saved, ws, ws_bytes, stream)
+    hit = torch.zeros(T, N, dtype=torch.bool, device=dev)
+    hit[row_task == 0, N - 1] = True
+    assert torch.equal(Y2[~hit], Y[~hit]) and not torch.isfinite(Y2[hit]).any()
+
+
 def test_mfma_probe_runs(env):
     """The diagnostic MFMA loop: launches, reports its FLOP count, leaves finite sums (operands 1 and 0.5: every
     accumulator element of a loop turn grows by 8 products of 16 terms of 0.5), rejects bad arguments."""
