@@ -219,12 +219,13 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 template <bool NT, int WAVES_N, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int L,
                                           const int half, const int mhalf, const Smem sm, const int split = 0,
-                                          const int slot = 0) {
+                                          const int slot = 0, const bool clear = false) {
   static_assert(!SPLITK || (!DIFFP && MI == 2 && NI == 2), "SPLITK: quarters, the plain loop");
   static_assert(WAVES_N == 4 || WAVES_N == 2 || WAVES_N == 1, "eight waves or four");
   static_assert(!FUSE || (!NT && WAVES_N <= 2), "FUSE: forward, pieces");
   constexpr bool KS = WAVES_N == 1;               // the waves share out the contraction in the loop, the tile after it
   constexpr int WNW = KS ? 2 : WAVES_N;
+  static_assert(!DIFFP || !KS, "DIFFP: tiles and their halves and quarters");
   static_assert(!DIFFP || !FUSE, "DIFFP: not with FUSE");
   constexpr int BN = WNW * NI * 32;
   constexpr int BMT = 2 * MI * 32;
@@ -632,6 +633,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     issue(stA(s0), stB(s0), stE(s0), ldsP(s0), ps0[s0], ps2[s0]);
   }
   if (DIFFP) bucket_offsets(PRE, nx0, nx1, nx2);
+  // (here, its stores wait for nothing and, younger than the loads, nothing waits for them: before the loads or behind the tile
+  // they cost a launch of short contractions 2 us of 11, 448 x 10496 with three tasks)
+  if (clear) clear_below(p, L, half);
   wait_vmcnt<(PRE - 1) * NLD>();
   wait_lgkm0();
   tile_barrier();
@@ -674,27 +678,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     for (int kt2 = 0; kt2 < KT_loop; kt2 += 2) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int kt = kt2 + u;
         {
           const int un = su + 1 == NST ? 0 : su + 1;
-          const int o0 = nx0, o2 = nx2;              // DIFFP: entries of the tile that refills this stage
           wait_vmcnt<(NST - 2) * NLD>();
           wait_lgkm0();
           tile_barrier();
           __builtin_amdgcn_sched_barrier(0);
-          if (DIFFP) {
-            // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.
-            if (patch && ps2[1] > ps0[1]) {
-              patch_tile(stB(un), ldsP(un), ps0[1], ps1[1], ps2[1]);
-              wait_lgkm0();
-              tile_barrier();
-            }
-#pragma unroll
-            for (int q = 0; q + 1 < NST; ++q) { ps0[q] = ps0[q + 1]; ps1[q] = ps1[q + 1]; ps2[q] = ps2[q + 1]; }
-            ps0[NST - 1] = nx0; ps1[NST - 1] = nx1; ps2[NST - 1] = nx2;
-            bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
-            __builtin_amdgcn_sched_barrier(0);
-          }
           // past the last tile: read, unused
 #pragma unroll
           for (int i = 0; i < NSLOT; ++i) {
@@ -706,7 +695,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
             for (int r = i * RT / NSLOT; r < (i + 1) * RT / NSLOT; ++r) read_step(stA(un), stB(un), r, ra[u ^ 1], rb[u ^ 1]);
             if (FUSE && i == 0) re[u ^ 1] = read_e(stE(un), wave);
 #pragma unroll
-            for (int d = 2 * i * NLD / NSLOT; d < 2 * (i + 1) * NLD / NSLOT && d < NLD; ++d) issue_one(stA(su), stB(su), stE(su), d, ldsP(su), o0, o2);
+            for (int d = 2 * i * NLD / NSLOT; d < 2 * (i + 1) * NLD / NSLOT && d < NLD; ++d) issue_one(stA(su), stB(su), stE(su), d);
             if (i == NSLOT / 2) { issue_done(); prepare(); }      // all loads are out: what the next tile's need
             __builtin_amdgcn_sched_barrier(0);
           }
@@ -806,7 +795,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
       wait_lgkm0();
       tile_barrier();
     }
-  } else if constexpr (PIECE) {
+  } else if constexpr (PIECE && !DIFFP) {
     // One wave a SIMD: nothing hides an LDS read but the wave's own products, so all operands of the next K-tile are read
     // under those of this one (read one step of 16 ahead, as the eight-wave loop does, a quarter took 0.367 us a K-tile, 0.335
     // so; the loads alone take 0.31, see above).  One barrier a K-tile, as above.
@@ -825,24 +814,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
         const int kt = kt2 + u;
         if (FUSE || kt < KT_loop) {
           const int un = su + 1 == NST ? 0 : su + 1;
-          const int o0 = nx0, o2 = nx2;              // DIFFP: entries of the tile that refills this stage
           wait_vmcnt<(NST - 2) * NLD>();
           wait_lgkm0();
           tile_barrier();
           __builtin_amdgcn_sched_barrier(0);
-          if (DIFFP) {
-            // Tile kt + 1 has landed: its masked entries, then a second barrier, then it may be read.
-            if (patch && ps2[1] > ps0[1]) {
-              patch_tile(stB(un), ldsP(un), ps0[1], ps1[1], ps2[1]);
-              wait_lgkm0();
-              tile_barrier();
-            }
-#pragma unroll
-            for (int q = 0; q + 1 < NST; ++q) { ps0[q] = ps0[q + 1]; ps1[q] = ps1[q + 1]; ps2[q] = ps2[q + 1]; }
-            ps0[NST - 1] = nx0; ps1[NST - 1] = nx1; ps2[NST - 1] = nx2;
-            bucket_offsets(kt + NST + 1, nx0, nx1, nx2);
-            __builtin_amdgcn_sched_barrier(0);
-          }
           // past the last tile: read, unused
 #pragma unroll
           for (int i = 0; i < NSLOT; ++i) {
@@ -856,7 +831,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
               if (i % NM == NM - 1) mma_h(re[u][ks], ra[u][ks]);
             }
 #pragma unroll
-            for (int d = 2 * i * NLD / NSLOT; d < 2 * (i + 1) * NLD / NSLOT && d < NLD; ++d) issue_one(stA(su), stB(su), stE(su), d, ldsP(su), o0, o2);
+            for (int d = 2 * i * NLD / NSLOT; d < 2 * (i + 1) * NLD / NSLOT && d < NLD; ++d) issue_one(stA(su), stB(su), stE(su), d);
             if (i == NSLOT / 2) { issue_done(); prepare(); }      // all loads are out: what the next tile's need
             __builtin_amdgcn_sched_barrier(0);
           }
@@ -868,8 +843,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     bf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
     read_ops(stA(0), stB(0), 0, a0, b0);
     // Steps 0..2 run from registers read one step ahead; before the last step every wave has read all of this
-    // stage and tile kt+1 has landed: barrier; then, under the last step's MFMAs, the first operands of tile kt+1 are
-    // read and all loads of tile kt+2 are issued into the stage just freed.
+    // stage and tile kt+1 has landed (the loads of the NST-2 tiles after it may stay in flight): barrier; then, under the
+    // last step's MFMAs, the first operands of tile kt+1 are read and all loads of tile kt+NST are issued into the stage just
+    // freed.
     for (int kt2 = 0; kt2 < KT_loop; kt2 += NST) {
 #pragma unroll
       for (int u = 0; u < NST; ++u) {
@@ -990,22 +966,25 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     const bool to_z = z_only || pass + 1 < passes;
     bf16_t* dst = to_z ? p.Zsave + (size_t)(tk.zrow0 - tk.row_begin) * p.Nc : p.Out;   // indexed by the row in the batch
     if (scale_out && !to_z) {
+      // (all loads before the first product: a column past the end reads the first ones and is not stored)
+      float lv[NI][4][4];
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int c = c0 + wn * WCOLS + ni * 32 + 8 * j + 4 * lg;
-          const bool in = c < p.Nc;                           // Nc is a multiple of 8: the four columns together
-          const float l0 = in ? bf16_to_f32(Lvec[c]) : 0.f, l1 = in ? bf16_to_f32(Lvec[c + 1]) : 0.f;
-          const float l2 = in ? bf16_to_f32(Lvec[c + 2]) : 0.f, l3 = in ? bf16_to_f32(Lvec[c + 3]) : 0.f;
+          const bf16_t* l = Lvec + (c < p.Nc ? c : 0);        // Nc is a multiple of 8: the four columns together
 #pragma unroll
-          for (int mi = 0; mi < MI; ++mi) {
-            acc[mi][ni][4 * j + 0] *= l0;
-            acc[mi][ni][4 * j + 1] *= l1;
-            acc[mi][ni][4 * j + 2] *= l2;
-            acc[mi][ni][4 * j + 3] *= l3;
-          }
+          for (int e = 0; e < 4; ++e) lv[ni][j][e] = bf16_to_f32(l[e]);
         }
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[mi][ni][4 * j + e] *= lv[ni][j][e];
     }
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
@@ -1080,7 +1059,7 @@ __device__ __forceinline__ Quarter quarter_piece(const GemmParams& p, int b) {
   return q;
 }
 
-// Launches with full tiles.  Workgroups 0 .. n_full-1 compute full tiles, slot by slot with the XCD in the low three bits of
+// Launches with full tiles, and those that add masked entries.  Workgroups 0 .. n_full-1 compute full tiles, slot by slot with the XCD in the low three bits of
 // the index (the hardware deals consecutive workgroups round-robin to the eight XCDs, so one XCD's L2 sees neighbouring tiles).
 // The workgroups after them compute the remaining tiles in pieces (tail_split = 2: two half-width tiles each;
 // 4: four 128 x 128 quarters each); all pieces of a tile run on the same XCD.  The dispatcher hands out workgroups
@@ -1116,7 +1095,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   clock_end(p);
 }
 
-// Launches without full tiles: four waves a workgroup, one a SIMD, with all of its registers.
+// The other launches: four waves a workgroup, one a SIMD, with all of its registers.
 //   PIECES_HALF     256 x 128, quarters for the row groups with tokens in their first 128 rows only
 //   PIECES_QUARTER  128 x 128 (or such quarters alone)
 //   PIECES_64X128, PIECES_64X64   of row groups of 64; an XCD takes a run of pieces, the row group running fastest, so that
@@ -1125,15 +1104,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
 // share, go to the XCDs in eight equal runs (dealt by whole tiles, 10 tiles of 6 quarters left three XCDs idle and gave
 // the others two rounds: 20.8 us, 14.8 so, for 60 quarters of 2560 x 2560 in four shares).
 enum : int { PIECES_HALF = 0, PIECES_QUARTER, PIECES_64X128, PIECES_64X64 };
-template <int PIECES, bool NT, bool FUSE, bool DIFFP, bool SPLITK>
+template <int PIECES, bool NT, bool FUSE, bool SPLITK>
 __global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p) {
   constexpr int MI = PIECES == PIECES_HALF ? 4 : (PIECES == PIECES_QUARTER ? 2 : 1), NI = PIECES == PIECES_64X64 ? 1 : 2;
-  constexpr int ELEMS = piece_stages(MI, NI, FUSE, DIFFP) * piece_elems(MI, NI, FUSE, DIFFP);
-  constexpr int QUART = PIECES == PIECES_HALF ? piece_stages(2, 2, FUSE, DIFFP) * piece_elems(2, 2, FUSE, DIFFP) : 0;
+  constexpr int ELEMS = piece_stages(MI, NI, FUSE, false) * piece_elems(MI, NI, FUSE, false);
+  constexpr int QUART = PIECES == PIECES_HALF ? piece_stages(2, 2, FUSE, false) * piece_elems(2, 2, FUSE, false) : 0;
   __shared__ __attribute__((aligned(1024))) bf16_t smem[ELEMS > QUART ? ELEMS : QUART];
-  __shared__ int sOff[DIFFP ? 3 * 1024 : 2];                                      // DIFFP: K < 65536, so at most 1023 K-tiles
   __shared__ int sRow[256];
-  const Smem sm = {smem, sRow, sOff};
+  const Smem sm = {smem, sRow, nullptr};
   const int b = blockIdx.x;
   if (b >= p.clear0) return clear_group<256>(p, b - p.clear0);
   clock_start(p);
@@ -1142,8 +1120,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p) {
     int L, half, mhalf;
     if (split >= p.splits) return;
     const bool hg = quarter_of(p, q, L, half, mhalf);
-    if (hg && split == 0) clear_below(p, L, half);
-    gemm_tile<NT, 2, 2, 2, FUSE, false, true, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q);
+    gemm_tile<NT, 2, 2, 2, FUSE, false, true, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q, hg && split == 0);
   } else if constexpr (PIECES >= PIECES_64X128) {
     const int id = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 3);
     if (id < 0) return;
@@ -1151,12 +1128,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p) {
   } else if (PIECES == PIECES_HALF && b < p.half0) {
     const int L = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 4);
     if (L < 0) return;
-    gemm_tile<NT, 2, 4, 2, FUSE, DIFFP, true>(p, 0, p.n_m, L, (b >> 3) & 1, 0, sm);
+    gemm_tile<NT, 2, 4, 2, FUSE, false, true>(p, 0, p.n_m, L, (b >> 3) & 1, 0, sm);
   } else {
     const Quarter q = quarter_piece(p, b);
     if (q.L < 0) return;
-    if (q.hg) clear_below(p, q.L, q.half);
-    gemm_tile<NT, 2, 2, 2, FUSE, DIFFP, true>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm);
+    gemm_tile<NT, 2, 2, 2, FUSE, false, true>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm, 0, 0, q.hg);
   }
   clock_end(p);
 }
@@ -1397,19 +1373,13 @@ TilePlan plan_rows64(const mux_segtab* st, int Nc, int pieces) {
 }
 template <int PIECES, bool NT>
 void launch_pieces(const char* name, dim3 grid, hipStream_t stream, const GemmParams& p) {
-  if constexpr (PIECES <= PIECES_QUARTER) {
-    if (p.DiffPack != nullptr) {
-      MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, false, true, false>), grid, dim3(256), 0, stream, p);
-      return;
-    }
-  }
   if constexpr (!NT) {
     if (p.HsOut != nullptr) {
-      MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, true, false, false>), grid, dim3(256), 0, stream, p);
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, true, false>), grid, dim3(256), 0, stream, p);
       return;
     }
   }
-  MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, false, false, false>), grid, dim3(256), 0, stream, p);
+  MUX_LAUNCH(name, (k_gemm_pieces<PIECES, NT, false, false>), grid, dim3(256), 0, stream, p);
 }
 
 template <bool NT>
@@ -1451,23 +1421,24 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
     const dim3 sgrid(t.grid - t.clear0 + p.clear0), sums(8 * p.quarters);
     const double moved = ((double)p.splits * 4 + 2) * c.st->valid_total * Nc;
     if (!NT && fuse_down) {
-      MUX_LAUNCH(name, (k_gemm_pieces<PIECES_QUARTER, false, true, false, true>), sgrid, dim3(256), 0, c.stream, p);
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES_QUARTER, false, true, true>), sgrid, dim3(256), 0, c.stream, p);
       prof_note_bytes(moved);
       MUX_LAUNCH("gemm_sum", (k_gemm_sum<false, true>), sums, dim3(256), 0, c.stream, p);
     } else {
-      MUX_LAUNCH(name, (k_gemm_pieces<PIECES_QUARTER, NT, false, false, true>), sgrid, dim3(256), 0, c.stream, p);
+      MUX_LAUNCH(name, (k_gemm_pieces<PIECES_QUARTER, NT, false, true>), sgrid, dim3(256), 0, c.stream, p);
       prof_note_bytes(moved);
       MUX_LAUNCH("gemm_sum", (k_gemm_sum<NT, false>), sums, dim3(256), 0, c.stream, p);
     }
     return MUX_OK;
   }
-  if (t.n_full == 0) {
+  if (p.DiffPack != nullptr) {
+    MUX_LAUNCH(name, (k_gemm_dma<NT, true, false>), grid, block, 0, c.stream, p);
+  } else if (t.n_full == 0) {
     if (t.pieces == PIECES_HALF) launch_pieces<PIECES_HALF, NT>(name, grid, c.stream, p);
     else if (t.pieces == PIECES_QUARTER) launch_pieces<PIECES_QUARTER, NT>(name, grid, c.stream, p);
     else if (t.pieces == PIECES_64X128) launch_pieces<PIECES_64X128, NT>(name, grid, c.stream, p);
     else launch_pieces<PIECES_64X64, NT>(name, grid, c.stream, p);
-  } else if (p.DiffPack != nullptr) MUX_LAUNCH(name, (k_gemm_dma<NT, true, false>), grid, block, 0, c.stream, p);
-  else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true>), grid, block, 0, c.stream, p);
+  } else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true>), grid, block, 0, c.stream, p);
   else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false>), grid, block, 0, c.stream, p);
   return MUX_OK;
 }
