@@ -1,5 +1,5 @@
 // bf16 matrix-core path: sequences the MFMA kernels of one layer call.
-#include "mux_device_utils.h"
+#include "mux_grad_device.h"
 
 namespace mux {
 
@@ -45,14 +45,21 @@ mux_status fast_forward(const CallCtx& c, const void* X, void* Y, void* H, void*
 mux_status fast_backward(const CallCtx& c, const void* X, const void* dY, const void* H, const void* Z, void* G, void* dX,
                          int accumulate, void* part) {
   // one pass over dY: Gs and the partial sums of dB_t
-  if (mux_status s = adapter_dy_pass(c, dY, H, G, part)) return s;
+  if (mux_status s = adapter_dy_pass(c, dY, H, G, part, accumulate)) return s;
   // Adapter-Tuning rows enter the backbone backward as dY + Gs D_t^T
   if (mux_status s = adapter_tune_add(c, dY, G, c.dYs, 1)) return s;
-  if (mux_status s = adapter_grads(c, X, dY, H, G, Z, part, accumulate)) return s;
-  if (!dX) return MUX_OK;
-  if (c.diffPack) diff_pack(c, true); else diff_merge(c, c.diffW_slots);
-  // IA3_OUT rows read dY * l_t, written by the dl kernel above
-  return gemm_dma_backward(c, dY, G, dX);
+  adapter_dl(c, dY, Z, part);
+  // dA_t: in the launch of the backbone product where that leaves compute units idle
+  const adapter::GradParams job = adapter_grad_job(c, X, G, Z, part, accumulate);
+  const bool ride = dX && job.n_items > 0 && gemm_dma_takes_grads(c);
+  if (!ride) adapter_grad_da(c, job);
+  if (dX) {
+    if (c.diffPack) diff_pack(c, true); else diff_merge(c, c.diffW_slots);
+    // IA3_OUT rows read dY * l_t, written by the dl kernel above
+    if (mux_status s = gemm_dma_backward(c, dY, G, dX, ride ? &job : nullptr)) return s;
+  }
+  adapter_reduce(c, part, accumulate);
+  return MUX_OK;
 }
 
 }  // namespace mux

@@ -187,21 +187,26 @@ void diff_merge(const CallCtx& c, int slots);                                   
 void diff_forward(const CallCtx& c, int dtype, const void* X, void* Y);                                       // Y += x (M_t * delta_t)
 void diff_backward(const CallCtx& c, int dtype, const void* X, const void* dY, void* dX, int accumulate);     // dX, d delta_t
 
+namespace adapter { struct GradParams; }
+
 // matrix-core backbone GEMM (bf16)
 bool gemm_dma_supported(const CallCtx& c);
 bool fast_gemm_patches_diff(const CallCtx& c, bool backward);   // the backbone product of this call can add masked entries in LDS
 bool gemm_dma_fuses_down(const CallCtx& c);   // the forward launch would be half / quarter tiles only: Hs is formed in its K loop
 size_t gemm_split_bytes(int K, int N, const mux_segtab* st);   // what CallCtx::split can use
 mux_status gemm_dma_forward(const CallCtx& c, const void* X, const void* Hs, void* Y, void* Z, bool fuse_down);
-mux_status gemm_dma_backward(const CallCtx& c, const void* dY, const void* Gs, void* dX);
+bool gemm_dma_takes_grads(const CallCtx& c);  // the backward launch has compute units to spare for the gradient dA_t
+mux_status gemm_dma_backward(const CallCtx& c, const void* dY, const void* Gs, void* dX, const adapter::GradParams* job);
 
 // matrix-core adapter kernels (bf16): down-projections and per-task gradient reductions
 mux_status adapter_down_x(const CallCtx& c, const void* X, void* Hs);                       // S1
-mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, void* Gs, void* part);   // S4: Gs, dB partials
+mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, void* Gs, void* part, int accumulate);   // S4: Gs, dB (partials)
 mux_status adapter_down_tune(const CallCtx& c, const void* Z, void* Hs);                    // Adapter-Tuning forward
 mux_status adapter_tune_add(const CallCtx& c, const void* In, const void* Small, void* Out, int backward);
-mux_status adapter_grads(const CallCtx& c, const void* X, const void* dY, const void* Hs, const void* Gs, const void* Z,
-                         void* part, int accumulate);                                       // S6, and the sums of S4
+adapter::GradParams adapter_grad_job(const CallCtx& c, const void* X, const void* Gs, const void* Z, void* part, int accumulate);   // S6
+void adapter_grad_da(const CallCtx& c, const adapter::GradParams& job);
+void adapter_dl(const CallCtx& c, const void* dY, const void* Z, void* part);
+void adapter_reduce(const CallCtx& c, void* part, int accumulate);                          // the sums of S4, S6 and of IA3
 size_t adapter_partial_bytes(int K, int N, const mux_segtab* st);
 
 // matrix-core (MFMA) kernels, bf16 storage

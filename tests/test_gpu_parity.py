@@ -119,6 +119,39 @@ def test_contraction_tails_and_odd_ranks(env, K, N):
         assert torch.equal(g.Y, y) and torch.equal(g.dX, dx)
 
 
+@pytest.mark.parametrize("K,N,lens", [
+    (264, 512, [100, 256, 1, 129, 64]),      # one column slab, every task one row group: no partials at all
+    (264, 520, [100, 256, 1, 129, 64]),      # two column slabs
+    (264, 72, [700, 30, 1030, 257, 5]),      # one column slab, several row groups
+    (1032, 512, [300, 3, 40, 90, 256])])
+@pytest.mark.parametrize("ranks", [(16, 3, 8), (32, 20, 16), (64, 33, 12)])
+def test_gradients_without_partials(env, K, N, lens, ranks):
+    """The pass over dY where one column slab is all of it (Gs leaves it scaled, masked and rounded) and where a task is one
+    row group (its sums are the gradients), beside the general case; ranks of one, two and four pieces, Adapter-Tuning, a
+    scratch memory and padding rows of NaN, row groups without tokens, gradients overwritten and added to."""
+    mx, torch = env
+    kinds = [(wlm.KIND_LORA, ranks[0]), (wlm.KIND_ADAPTER, ranks[1]), (wlm.KIND_LORA, ranks[2]), (wlm.KIND_IA3, 0), (wlm.KIND_LORA, ranks[1])]
+    wl = wlm.Workload(name="direct", layers=[("w", K, N)], chunk=512, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(k, r, 2.0, [n]) for (k, r), n in zip(kinds, lens)])
+    g, got, ref, errs = run_case(env, wl, seed=K + N)
+    first = {k: [None if t is None else t.clone() for t in getattr(g, k)] for k in ("dA", "dB", "dL")}
+    dx = g.dX.clone()
+    pad = torch.from_numpy(np.nonzero(oracle_table(wl).row_task < 0)[0]).to("cuda:0")
+    g.X[pad] = float("nan"); g.dY[pad] = float("nan")
+    g.ws.view(torch.uint8).fill_(0xFF)
+    g.forward(); g.backward()
+    torch.cuda.synchronize()
+    assert torch.equal(g.dX, dx)
+    for k in first:
+        for a, b in zip(first[k], getattr(g, k)):
+            assert a is None or torch.equal(a, b), k
+    g.backward(accumulate=1)
+    torch.cuda.synchronize()
+    for k in first:
+        for a, b in zip(first[k], getattr(g, k)):
+            assert a is None or torch.equal(b, a + a), k
+
+
 @pytest.mark.parametrize("K,N", [(264, 136), (1032, 520)])
 def test_gradient_reduction_blocks(env, K, N):
     """The blocks that bring the partial gradients together: as many columns of dA_t as a rank leaves room for (ranks 1 to
