@@ -52,6 +52,7 @@ struct AttnParams {
   int short_map;      // forward: the pairs are dealt to the XCDs as in the kernel of the short sequences
   int list_off;       // word offset of the launch's block list in dtab
   int block0, n_blocks;   // the launch covers the entries block0 .. block0 + n_blocks - 1 of its list
+  int n_blocks64, grid128;   // one-kernel backward: then as many of at most 64 tokens, from workgroup grid128 on
   float scale;
 };
 
@@ -108,8 +109,8 @@ __host__ __device__ __forceinline__ bool short_deals_blocks(int D, int n_blocks)
 // and 200 x 10, 427 and 317; 53 heads of 96, 128 x 128, dealt in turn 380, the block fastest 404.)
 // false = nothing to do.
 template <int D>
-__device__ __forceinline__ bool short_item(int n_blocks, int n_heads, int& block, int& head) {
-  const unsigned xcd = blockIdx.x & 7, j = blockIdx.x >> 3, nb = (unsigned)n_blocks, nh = (unsigned)n_heads;
+__device__ __forceinline__ bool short_item(unsigned id, int n_blocks, int n_heads, int& block, int& head) {
+  const unsigned xcd = id & 7, j = id >> 3, nb = (unsigned)n_blocks, nh = (unsigned)n_heads;
   if ((n_heads & 7) == 0) {
     const unsigned hx = nh >> 3;
     block = (int)(j / hx);
@@ -118,8 +119,8 @@ __device__ __forceinline__ bool short_item(int n_blocks, int n_heads, int& block
     block = (int)(xcd + 8 * (j / nh));
     head = (int)(j % nh);
   } else {
-    block = (int)(blockIdx.x % nb);
-    head = (int)(blockIdx.x / nb);
+    block = (int)(id % nb);
+    head = (int)(id / nb);
   }
   return block < n_blocks && head < n_heads;
 }
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd(AttnParams p) {
   __shared__ __align__(16) bf16_t sK[TILE * KP];
   __shared__ __align__(16) bf16_t sV[TILE * TP];
   int wi_block, wi_head;
-  if (p.short_map) { if (!short_item<D>(p.n_blocks, p.H, wi_block, wi_head)) return; }
+  if (p.short_map) { if (!short_item<D>(blockIdx.x, p.n_blocks, p.H, wi_block, wi_head)) return; }
   else work_item(p.n_blocks, p.H, wi_block, wi_head);
   const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN], q0 = blk[DA_BLOCK0];
@@ -606,23 +607,30 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_kv(AttnParams p) {
 // workgroups a compute unit.  Measured, forward and backward of a call: 32 heads of 80, sequences of 64 and 128 tokens
 // (2944 in all) 94 -> 71 us; 46 sequences of 64 and 32 heads of 128, 113 -> 82 us; 160 sequences of 128, 64 heads of 64,
 // 931 -> 574 us.
+// A workgroup of four waves takes one such sequence of up to 128 tokens and a key/value head, or two heads of one of up to
+// 64 tokens (two waves each; `tid`, `stored`: the thread inside its head's waves, and false where there is no second head).
 template <int D, int R>
-__global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
+struct ShortLds {
+  static constexpr int TP = Dim<D>::TP, QT = 32, SP = QT + 16;        // SP: pitch of the dS tile
+  __align__(16) bf16_t K[R * TP];
+  __align__(16) bf16_t Q[QT * TP];
+  __align__(16) bf16_t dO[QT * TP];
+  __align__(16) bf16_t S[R * SP];
+  float lse[R], delta[R];
+};
+template <int D, int R>
+__device__ __forceinline__ void attn_bwd_short(const AttnParams& p, const int wi_block, const int wi_head, const bool stored,
+                                               const int tid, ShortLds<D, R>& lds) {
   constexpr int KS = Dim<D>::KS, DT = Dim<D>::DT, DP = Dim<D>::DP, TP = Dim<D>::TP;
-  constexpr int NW = R / 32, NTHR = 64 * NW, QT = 32, SP = QT + 16;   // SP: pitch of the dS tile
+  constexpr int NW = R / 32, NTHR = 64 * NW, QT = 32, SP = ShortLds<D, R>::SP;
   constexpr bool LATE = D > 96;                // loads of the next tile behind the products: their registers are not free before
-  __shared__ __align__(16) bf16_t sK[R * TP];
-  __shared__ __align__(16) bf16_t sQ[QT * TP];
-  __shared__ __align__(16) bf16_t sD[QT * TP];
-  __shared__ __align__(16) bf16_t sS[R * SP];
-  __shared__ float sLse[R], sDelta[R];
-  int wi_block, wi_head;                       // wi_head: a key/value head
-  if (!short_item<D>(p.n_blocks, p.Hkv, wi_block, wi_head)) return;
+  bf16_t *const sK = lds.K, *const sQ = lds.Q, *const sD = lds.dO, *const sS = lds.S;
+  float *const sLse = lds.lse, *const sDelta = lds.delta;
   const int32_t* blk = p.dtab + p.list_off + (p.block0 + wi_block) * DA_WORDS;
   const int first = blk[DA_FIRST_ROW], len = blk[DA_LEN];
   const int hc = wi_head * D;
   const int group = p.H / p.Hkv;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, half = lane >> 5;
+  const int wave = tid >> 6, lane = tid & 63, li = lane & 31, half = lane >> 5;
   const int kl = 32 * wave + li;               // this lane's key (and, for the statistics, its query) in the sequence
   const bool kok = kl < len;
   // dO . O (the two half-waves take alternate 16-byte pieces of the rows of query kl) and the log-sum-exp, into LDS
@@ -742,7 +750,7 @@ __global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
         for (int j = 0; j < 16; ++j) dq[j] = 0.f;
         for (int k16 = 0; k16 < qb + QT; k16 += 16)
           dq = mma(read_across<TP>(sK, k16, 32 * dt, lane), read_across<SP>(sS, k16, 0, lane), dq);
-        if (qb + li < len) {
+        if (stored && qb + li < len) {
           bf16_t* orow = p.dQ + (size_t)(first + qb + li) * p.ldq + hcq + 32 * dt + 4 * half;
 #pragma unroll
           for (int jg = 0; jg < 4; ++jg) {
@@ -756,7 +764,7 @@ __global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
       }
     }
   }                                             // next query head of the group
-  if (kok) {
+  if (stored && kok) {
     bf16_t* krow = p.dK + (size_t)(first + kl) * p.ldk + hc;
     bf16_t* vrow = p.dV + (size_t)(first + kl) * p.ldv + hc;
 #pragma unroll
@@ -773,6 +781,37 @@ __global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short(AttnParams p) {
         *(uint2*)(vrow + 32 * dt + 8 * jg + 4 * half) = b;
       }
   }
+}
+
+// Blocks block0 .. + n_blocks of the list, sequences of 65 to 128 tokens, and the n_blocks64 of at most 64 tokens behind them,
+// in one launch: a workgroup loads, computes and stores, and in a launch of one kind all of them do so at the same time; two
+// kinds fill each other's gaps.  Two heads a workgroup: the heads of a sequence lie side by side, and half as many workgroups
+// pass through the dispatcher.  Forward and backward, a launch for each kind, one head a workgroup -> so: 32 heads of 80, 14
+// sequences of 128 tokens and 18 of 64, 62.3 -> 54.4 us; 160 of 64, 224 -> 192; 53 heads of 96, 20 each of 128, 100, 60 and 33
+// tokens, 259 -> 245; 40 heads of 64, the same, 131.8 -> 122.
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_attn_bwd_short(AttnParams p) {
+  typedef ShortLds<D, 128> Wide;
+  typedef ShortLds<D, 64> Narrow;
+  static_assert(4 * sizeof(Narrow) <= 160 * 1024, "two workgroups a compute unit");
+  __shared__ __align__(16) unsigned char mem[sizeof(Wide) > 2 * sizeof(Narrow) ? sizeof(Wide) : 2 * sizeof(Narrow)];
+  int block, head;
+  if (blockIdx.x < (unsigned)p.grid128) {
+    if (short_item<D>(blockIdx.x, p.n_blocks, p.Hkv, block, head))
+      attn_bwd_short<D, 128>(p, block, head, true, threadIdx.x, *(Wide*)mem);
+  } else if (short_item<D>(blockIdx.x - p.grid128, p.n_blocks64, (p.Hkv + 1) / 2, block, head)) {
+    const int unit = threadIdx.x >> 7, h = 2 * head + unit;
+    attn_bwd_short<D, 64>(p, p.n_blocks + block, h < p.Hkv ? h : p.Hkv - 1, h < p.Hkv, threadIdx.x & 127, ((Narrow*)mem)[unit]);
+  }
+}
+// One head a workgroup: D = 128 (two heads of 64 tokens would take 87 KB of LDS, one workgroup a unit; a launch for each kind), and
+// launches of few heads.
+template <int D, int R>
+__global__ __launch_bounds__(2 * R, 2) void k_attn_bwd_short_one(AttnParams p) {
+  __shared__ ShortLds<D, R> lds;
+  int block, head;
+  if (short_item<D>(blockIdx.x, R == 128 ? p.n_blocks : p.n_blocks64, p.Hkv, block, head))
+    attn_bwd_short<D, R>(p, (R == 128 ? 0 : p.n_blocks) + block, head, true, threadIdx.x, lds);
 }
 
 mux_status check(const char* fn, const mux_attn_desc* d, const mux_segtab* st) {
@@ -805,14 +844,6 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
     else if ((D) == 80) MUX_LAUNCH(name, K<80>, grid, dim3(256), 0, stream, p);            \
     else MUX_LAUNCH(name, K<64>, grid, dim3(256), 0, stream, p);                           \
   } while (0)
-#define ATTN_LAUNCH_SHORT(name, R, D, grid, stream, p)                                                     \
-  do {                                                                                                     \
-    if ((D) == 128) MUX_LAUNCH(name, (k_attn_bwd_short<128, R>), grid, dim3(2 * R), 0, stream, p);          \
-    else if ((D) == 96) MUX_LAUNCH(name, (k_attn_bwd_short<96, R>), grid, dim3(2 * R), 0, stream, p);       \
-    else if ((D) == 80) MUX_LAUNCH(name, (k_attn_bwd_short<80, R>), grid, dim3(2 * R), 0, stream, p);       \
-    else MUX_LAUNCH(name, (k_attn_bwd_short<64, R>), grid, dim3(2 * R), 0, stream, p);                      \
-  } while (0)
-
 // Workgroups of a launch whose pairs short_item hands out
 unsigned short_grid(int n_blocks, int n_heads, int D) {
   const bool dealt = n_heads % 8 != 0 && short_deals_blocks(D, n_blocks);
@@ -953,15 +984,27 @@ extern "C" mux_status mux_attn_backward(const mux_attn_desc* desc, const mux_seg
     q.list_off = st->dev_image[DH_ATT_OFF_FWD];
     ATTN_LAUNCH("attn_bwd_q", k_attn_bwd_q, D, dim3((unsigned)n_long * (unsigned)desc->n_heads), stream, q);
   }
-  if (n128 > 0) {
+  if (n128 + n64 > 0) {
     p.block0 = n_long;
-    p.n_blocks = n128;
-    ATTN_LAUNCH_SHORT("attn_bwd_128", 128, D, dim3(short_grid(n128, desc->n_kv_heads, D)), stream, p);
-  }
-  if (n64 > 0) {
-    p.block0 = n_long + n128;
-    p.n_blocks = n64;
-    ATTN_LAUNCH_SHORT("attn_bwd_64", 64, D, dim3(short_grid(n64, desc->n_kv_heads, D)), stream, p);
+    p.n_blocks = n128; p.n_blocks64 = n64;
+    const unsigned one64 = n64 > 0 ? short_grid(n64, desc->n_kv_heads, D) : 0;
+    if (D == 128) {
+      if (n128 > 0) MUX_LAUNCH("attn_bwd_128", (k_attn_bwd_short_one<128, 128>), dim3(short_grid(n128, desc->n_kv_heads, D)), dim3(256), 0, stream, p);
+      if (n64 > 0) MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<128, 64>), dim3(one64), dim3(128), 0, stream, p);
+    } else if (n128 == 0 && (int64_t)n64 * desc->n_kv_heads < 2 * kComputeUnits) {
+      // so few that two heads a workgroup would leave compute units idle (15 heads of 64, two sequences, forward and backward
+      // 30.4 us so, 32.4 in pairs; 36 heads of 96, twelve, 41.6 and 42.4)
+      if (D == 96) MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<96, 64>), dim3(one64), dim3(128), 0, stream, p);
+      else if (D == 80) MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<80, 64>), dim3(one64), dim3(128), 0, stream, p);
+      else MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<64, 64>), dim3(one64), dim3(128), 0, stream, p);
+    } else {
+      p.grid128 = n128 > 0 ? (int)short_grid(n128, desc->n_kv_heads, D) : 0;
+      const char* name = n64 == 0 ? "attn_bwd_128" : (n128 == 0 ? "attn_bwd_64" : "attn_bwd_128_64");
+      const dim3 grid((unsigned)p.grid128 + (n64 > 0 ? short_grid(n64, (desc->n_kv_heads + 1) / 2, D) : 0));
+      if (D == 96) MUX_LAUNCH(name, k_attn_bwd_short<96>, grid, dim3(256), 0, stream, p);
+      else if (D == 80) MUX_LAUNCH(name, k_attn_bwd_short<80>, grid, dim3(256), 0, stream, p);
+      else MUX_LAUNCH(name, k_attn_bwd_short<64>, grid, dim3(256), 0, stream, p);
+    }
   }
   return last_hip(fn);
 }

@@ -169,6 +169,21 @@ def test_which_kernels_take_the_backward_of_short_sequences(env, lens, H, Hkv, d
     assert {n[len("attn_bwd_"):] for n in names if n.startswith("attn_bwd_")} - {"q"} == kernels, names
 
 
+@pytest.mark.parametrize("H,d", [(5, 80), (7, 64), (3, 96), (8, 80)])
+def test_both_kinds_of_short_sequences_in_one_launch(env, H, d):
+    """Sequences of 65 to 128 and of at most 64 tokens, enough of both for the one-kernel backward of both widths: one launch,
+    two heads of a short sequence a workgroup, the last one alone where the heads are odd; ragged lengths, one token."""
+    mx, _ = env
+    n64 = 512 // H + 3
+    lens = [[128] * 20 + [65, 100, 127], [1, 64, 33, 32] + [64 - i % 40 for i in range(n64)], [128, 2, 90]]
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    run(env, lens, chunk=64, H=H, seed=70 + H + d, d=d)
+    names = {e["name"] for e in mx.mux_profile_collect()}
+    mx.mux_profile_enable(0)
+    assert "attn_bwd_128_64" in names, names
+
+
 @pytest.mark.parametrize("H,Hkv,d", [(5, 5, 80), (7, 7, 64), (3, 1, 96), (8, 8, 80), (24, 8, 64)])
 def test_short_sequences_over_the_xcds(env, H, Hkv, d):
     """The ways in which (block, head) pairs of short sequences are dealt to the XCDs, forward and backward: numbers of heads
