@@ -52,7 +52,7 @@ __device__ __forceinline__ float gelu_slope_f(float u) {
   return 0.5f * (1.f + erff(u * 0.70710678f)) + u * __expf(-0.5f * u * u) * 0.39894228f;
 }
 
-template <int NJM, int NWV, int DEPTH>
+template <int NJM, int NWV, int DEPTH, bool STREAM>
 __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
   constexpr int ROWS = 32, NTHR = 64 * NWV;
   constexpr int PP = NJM * 16 + 8;                              // LDS pitch of the [64][r] slab of A_t (elements)
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(64 * NWV) void k_down(const DownParams p) {
     const uint32_t kx = (c + b_pc < cend) ? (uint32_t)c * 2u : OOB;     // OOB + OOB wraps into range: mask on k only
     const uint32_t kp = in ? (uint32_t)c * (uint32_t)ppr * 16u : OOB;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) gx[buf][q] = buf_load16(rIn, (x_off[q] == OOB || kx == OOB) ? OOB : x_off[q] + kx);
+    for (int q = 0; q < 4; ++q) gx[buf][q] = buf_load16_once<STREAM>(rIn, (x_off[q] == OOB || kx == OOB) ? OOB : x_off[q] + kx);
 #pragma unroll
     for (int q = 0; q < 2 * NJM; ++q) {
       const bool ok = p_off[q] != OOB && kp != OOB;
@@ -215,10 +215,15 @@ void launch_down(const CallCtx& c, const char* name, DownParams p) {
   // leave room for one workgroup a compute unit, four for two.  So they take eight where a unit has one workgroup or none
   // (84 items at 4096: 18.6 -> 15.1 us) and four beyond (324 items: 61.7 us, eight waves 63.6).
   const dim3 grid(items * 2);
-  if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2>), grid, dim3(512), 0, c.stream, p);
-  else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2>), grid, dim3(512), 0, c.stream, p);
-  else if (items * 2 <= (unsigned)kComputeUnits) MUX_LAUNCH(name, (k_down<4, 8, 2>), grid, dim3(512), 0, c.stream, p);
-  else MUX_LAUNCH(name, (k_down<4, 4, 2>), grid, dim3(256), 0, c.stream, p);
+  const bool stream = (size_t)c.st->T * p.C * 2 > kStreamBytes;
+  auto launch = [&](auto STREAM) {
+    constexpr bool S = decltype(STREAM)::value;
+    if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2, S>), grid, dim3(512), 0, c.stream, p);
+    else if (c.st->r_max <= 32) MUX_LAUNCH(name, (k_down<2, 8, 2, S>), grid, dim3(512), 0, c.stream, p);
+    else if (items * 2 <= (unsigned)kComputeUnits) MUX_LAUNCH(name, (k_down<4, 8, 2, S>), grid, dim3(512), 0, c.stream, p);
+    else MUX_LAUNCH(name, (k_down<4, 4, 2, S>), grid, dim3(256), 0, c.stream, p);
+  };
+  if (stream) launch(std::true_type{}); else launch(std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -259,7 +264,7 @@ __device__ __forceinline__ void lds_barrier() {     // LDS traffic of every wave
   asm volatile("" ::: "memory");
 }
 
-template <int NJM, int BATCH, int DEPTH, bool ONE>
+template <int NJM, int BATCH, int DEPTH, bool ONE, bool STREAM>
 __global__ __launch_bounds__(512) void k_s4(const S4Params p) {
   constexpr int NWV = 8, NTHR = 512, BROWS = BATCH * 32, RPITCH = BROWS + 4;   // RPITCH: floats between two columns of a staged share
   constexpr int UNR = BATCH > DEPTH ? BATCH : DEPTH;
@@ -317,7 +322,7 @@ __global__ __launch_bounds__(512) void k_s4(const S4Params p) {
     for (int q = 0; q < 4; ++q) {
       const int m = base + b_row + 8 * q;
       const bool ok = b_col_ok && m < it.nrows && ((vbits >> (b_row + 8 * q)) & 1u);
-      gb[buf][q] = buf_load16(rB, ok ? (uint32_t)(((size_t)m * p.N + cw0 + b_pc) * 2) : OOB);
+      gb[buf][q] = buf_load16_once<STREAM>(rB, ok ? (uint32_t)(((size_t)m * p.N + cw0 + b_pc) * 2) : OOB);
     }
 #pragma unroll
     for (int q = 0; q < NJM; ++q) {
@@ -495,10 +500,10 @@ __global__ __launch_bounds__(256) void k_gs_reduce(const int32_t* __restrict__ d
 
 // ------------------------------------------------------------------------------------------------
 // The gradient partials of dA_t (dD_t), a workgroup of four waves a (row group, 256 columns), in a launch of their own.
-template <int NJM, int DEPTH>
+template <int NJM, int DEPTH, bool STREAM>
 __global__ __launch_bounds__(256) void k_grad(const GradParams p, const TaskRef tasks) {
   __shared__ __attribute__((aligned(16))) bf16_t lds[kGradLdsElems];
-  grad_rows<NJM, DEPTH>(p, tasks, blockIdx.x, blockIdx.y, lds);
+  grad_rows<NJM, DEPTH, STREAM>(p, tasks, blockIdx.x, blockIdx.y, lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -857,14 +862,18 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, voi
   const dim3 grid((unsigned)c.st->items[ts].size(), (unsigned)slabs);
   // (rank pieces, steps between two meetings of the waves, steps of loads in flight)
   if (slabs == 1) {
-    if (c.st->r_max <= 16) MUX_LAUNCH("s4_dy_pass", (k_s4<1, 2, 2, true>), grid, dim3(512), 0, c.stream, p);
-    else if (c.st->r_max <= 32) MUX_LAUNCH("s4_dy_pass", (k_s4<2, 2, 1, true>), grid, dim3(512), 0, c.stream, p);
-    else MUX_LAUNCH("s4_dy_pass", (k_s4<4, 1, 1, true>), grid, dim3(512), 0, c.stream, p);
+    if (c.st->r_max <= 16) MUX_LAUNCH("s4_dy_pass", (k_s4<1, 2, 2, true, false>), grid, dim3(512), 0, c.stream, p);
+    else if (c.st->r_max <= 32) MUX_LAUNCH("s4_dy_pass", (k_s4<2, 2, 1, true, false>), grid, dim3(512), 0, c.stream, p);
+    else MUX_LAUNCH("s4_dy_pass", (k_s4<4, 1, 1, true, false>), grid, dim3(512), 0, c.stream, p);
     return MUX_OK;
   }
-  if (c.st->r_max <= 16) MUX_LAUNCH("s4_dy_pass", (k_s4<1, 2, 2, false>), grid, dim3(512), 0, c.stream, p);
-  else if (c.st->r_max <= 32) MUX_LAUNCH("s4_dy_pass", (k_s4<2, 2, 1, false>), grid, dim3(512), 0, c.stream, p);
-  else MUX_LAUNCH("s4_dy_pass", (k_s4<4, 1, 1, false>), grid, dim3(512), 0, c.stream, p);
+  auto launch = [&](auto STREAM) {
+    constexpr bool S = decltype(STREAM)::value;
+    if (c.st->r_max <= 16) MUX_LAUNCH("s4_dy_pass", (k_s4<1, 2, 2, false, S>), grid, dim3(512), 0, c.stream, p);
+    else if (c.st->r_max <= 32) MUX_LAUNCH("s4_dy_pass", (k_s4<2, 2, 1, false, S>), grid, dim3(512), 0, c.stream, p);
+    else MUX_LAUNCH("s4_dy_pass", (k_s4<4, 1, 1, false, S>), grid, dim3(512), 0, c.stream, p);
+  };
+  if ((size_t)c.st->T * c.N * 2 > kStreamBytes) launch(std::true_type{}); else launch(std::false_type{});
   // moved: the partials of every slab once in (a task's real tokens, its rank rounded up to four columns), Gs once out
   double moved = (double)c.st->T * c.RP * 2;
   for (const HostTask& ht : c.st->tasks)
@@ -920,9 +929,13 @@ void adapter_grad_da(const CallCtx& c, const GradParams& p) {
   if (p.n_items == 0) return;
   const dim3 grid((unsigned)p.n_items, (unsigned)p.col_blocks);
   // two steps of loads in flight where the registers still allow four waves a SIMD
-  if (p.pieces == 1) MUX_LAUNCH("grad_da", (k_grad<1, 2>), grid, dim3(256), 0, c.stream, p, *c.tref);
-  else if (p.pieces == 2) MUX_LAUNCH("grad_da", (k_grad<2, 2>), grid, dim3(256), 0, c.stream, p, *c.tref);
-  else MUX_LAUNCH("grad_da", (k_grad<4, 1>), grid, dim3(256), 0, c.stream, p, *c.tref);
+  auto launch = [&](auto STREAM) {
+    constexpr bool S = decltype(STREAM)::value;
+    if (p.pieces == 1) MUX_LAUNCH("grad_da", (k_grad<1, 2, S>), grid, dim3(256), 0, c.stream, p, *c.tref);
+    else if (p.pieces == 2) MUX_LAUNCH("grad_da", (k_grad<2, 2, S>), grid, dim3(256), 0, c.stream, p, *c.tref);
+    else MUX_LAUNCH("grad_da", (k_grad<4, 1, S>), grid, dim3(256), 0, c.stream, p, *c.tref);
+  };
+  if ((size_t)c.st->T * c.K * 2 > kStreamBytes) launch(std::true_type{}); else launch(std::false_type{});
 }
 
 // IA3_OUT: the partial sums of dl_t and the scaled rows the backbone backward reads.

@@ -8,6 +8,7 @@
 namespace mux {
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 constexpr int kBatch = 32;      // task pointers per launch (kernel arguments)
 
 struct DispatchParams {
@@ -22,7 +23,9 @@ struct DispatchParams {
 
 // grid = (64-row items, slabs of 256 vectors across the width), four waves: wave w moves the rows w, w + 4, ...
 // `first` launch of a gather also zeroes the rows of no task and the padding rows of every task.
-template <class V>
+// STREAM: the rows are read past the caches (see kStreamBytes; 16-byte vectors: 18 k tokens of 5120 bf16 values, gather and
+// scatter, 159.5 -> 127.7 us).
+template <class V, bool STREAM>
 __global__ __launch_bounds__(256) void k_dispatch(DispatchParams p, int first) {
   const ItemView it = load_item(p.dtab, 0, blockIdx.x);
   const bool mine = it.task >= p.task_base && it.task < p.task_base + p.task_count;
@@ -61,7 +64,10 @@ __global__ __launch_bounds__(256) void k_dispatch(DispatchParams p, int first) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const int o = slab + k * 64 * (int)sizeof(V);
-          if (o < p.width_bytes) v[u][k] = *(const V*)(src + o);
+          if (o < p.width_bytes) {
+            if constexpr (STREAM) v[u][k] = __builtin_bit_cast(V, __builtin_nontemporal_load((const u32x4*)(src + o)));
+            else v[u][k] = *(const V*)(src + o);
+          }
         }
       } else if (p.to_aligned && first) {
         dst[u] = arow;
@@ -97,6 +103,7 @@ mux_status run(const char* fn, const mux_segtab* st, const void* dev_segtab, voi
   hipStream_t stream = (hipStream_t)hip_stream;
   const unsigned n_items = (unsigned)st->items[0].size();
   bool first = true;
+  const bool past_caches = (size_t)st->T * (size_t)width * elem_bytes > kStreamBytes;
   for (int base = 0; base < st->n_tasks || first; base += kBatch) {
     DispatchParams p{};
     p.dtab = (const int32_t*)dev_segtab;
@@ -110,9 +117,10 @@ mux_status run(const char* fn, const mux_segtab* st, const void* dev_segtab, voi
     p.to_aligned = to_aligned;
     const char* name = to_aligned ? "dispatch_gather" : "dispatch_scatter";
     const unsigned wb = (unsigned)p.width_bytes;
-    if (vec) MUX_LAUNCH(name, k_dispatch<uint4>, dim3(n_items, (wb + 4095) / 4096), dim3(256), 0, stream, p, first ? 1 : 0);
-    else if (elem_bytes == 4) MUX_LAUNCH(name, k_dispatch<uint32_t>, dim3(n_items, (wb + 1023) / 1024), dim3(256), 0, stream, p, first ? 1 : 0);
-    else MUX_LAUNCH(name, k_dispatch<uint16_t>, dim3(n_items, (wb + 511) / 512), dim3(256), 0, stream, p, first ? 1 : 0);
+    if (vec && past_caches) MUX_LAUNCH(name, (k_dispatch<uint4, true>), dim3(n_items, (wb + 4095) / 4096), dim3(256), 0, stream, p, first ? 1 : 0);
+    else if (vec) MUX_LAUNCH(name, (k_dispatch<uint4, false>), dim3(n_items, (wb + 4095) / 4096), dim3(256), 0, stream, p, first ? 1 : 0);
+    else if (elem_bytes == 4) MUX_LAUNCH(name, (k_dispatch<uint32_t, false>), dim3(n_items, (wb + 1023) / 1024), dim3(256), 0, stream, p, first ? 1 : 0);
+    else MUX_LAUNCH(name, (k_dispatch<uint16_t, false>), dim3(n_items, (wb + 511) / 512), dim3(256), 0, stream, p, first ? 1 : 0);
     first = false;
   }
   hipError_t e = hipGetLastError();

@@ -43,6 +43,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
 constexpr int BM = 256;
@@ -53,6 +54,7 @@ constexpr int TILE_N = 256;                     // width of a tile in the launch
 // now).
 constexpr int CLEAR_N = 512;
 constexpr uint32_t OOB = 0x80000000u;
+constexpr size_t kStreamOut = (size_t)64 << 20;      // bytes of an output from which on it is written past the caches
 
 // A workgroup reads these one after the other as it finds out what it computes, from lines of 64 bytes that are cold at the
 // start of a launch: what it needs first lies in the first line, what comes next in the second.  (Spread over three lines,
@@ -217,7 +219,9 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 // (256 a tile; a bucket pair with more reads the rest from memory when the tile is patched).
 // SPLITK (quarters): the tile's `split`-th share of its K-tiles only; the accumulators go to p.Part as they lie in the
 // registers (slot: the quarter's number), for k_gemm_sum.
-template <bool NT, int WAVES_N, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false>
+// STREAM: the output is written past the caches.
+template <bool NT, int WAVES_N, int MI, int NI, bool FUSE = false, bool DIFFP = false, bool TAIL = false, bool SPLITK = false,
+          bool STREAM = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, const int n_m, const int L,
                                           const int half, const int mhalf, const Smem sm, const int split = 0,
                                           const int slot = 0, const bool clear = false) {
@@ -558,7 +562,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   // the products of this step's slab fragment with the X fragments of this wave's row blocks, picked by selects on the
   // (uniform) wn: an index would send the fragments through scratch memory, and a branch per row block makes the compiler
   // copy the accumulator behind each MFMA
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   auto mma_h = [&](const bf16x8& e, const bf16x8 (&a)[MI]) {
 #pragma unroll
     for (int i = 0; i < HB; ++i) {
@@ -1008,7 +1011,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
         if (m < nrows && c < p.Nc) {
           uint4 v = *(const uint4*)(stage + ml * EPW + e_pc);
           if (sRow[m] == 0) v = make_uint4(0, 0, 0, 0);
-          *(uint4*)(dst + (size_t)(row0 + m) * p.Nc + c) = v;
+          uint4* d = (uint4*)(dst + (size_t)(row0 + m) * p.Nc + c);
+          if (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4*)d);
+          else *d = v;
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1065,7 +1070,7 @@ __device__ __forceinline__ Quarter quarter_piece(const GemmParams& p, int b) {
 // The workgroups after them compute the remaining tiles in pieces (tail_split = 2: two half-width tiles each;
 // 4: four 128 x 128 quarters each); all pieces of a tile run on the same XCD.  The dispatcher hands out workgroups
 // in index order, so the pieces start as the compute units finish their last full tile.
-template <bool NT, bool DIFFP, bool TAIL>
+template <bool NT, bool DIFFP, bool TAIL, bool STREAM>
 __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   __shared__ __attribute__((aligned(1024))) bf16_t smem[4 * (BM * BK + (DIFFP ? kPackElems : 0))];   // two stages of 64 KB, or four of 32 KB
   static_assert(piece_stages(2, 2, false, DIFFP) == 4, "four stages of a quarter");
@@ -1078,12 +1083,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
   if (b < p.n_full) {
     const int L = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 3);
     if (L < 0) return;
-    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL>(p, 0, p.n_m, L, 0, 0, sm);
+    gemm_tile<NT, 4, 4, 2, false, DIFFP, TAIL, false, STREAM>(p, 0, p.n_m, L, 0, 0, sm);
   } else if (b < p.half0 && p.tail_split == 2) {
     const int t = b - p.n_full;                                       // n_full is a multiple of 8
     const int L = tile_of_slot(p.n_m * p.n_n, t & 7, (p.n_full >> 3) + (t >> 4));
     if (L < 0) return;
-    gemm_tile<NT, 4, 4, 1, false, DIFFP, TAIL>(p, 0, p.n_m, L, (t >> 3) & 1, 0, sm);
+    gemm_tile<NT, 4, 4, 1, false, DIFFP, TAIL, false, STREAM>(p, 0, p.n_m, L, (t >> 3) & 1, 0, sm);
   } else {
     const Quarter q = quarter_piece(p, b);
     if (q.L < 0) return;
@@ -1091,7 +1096,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_dma(const GemmParams p) {
       clear_below(p, q.L, q.half);
       return;
     }
-    gemm_tile<NT, 2, 2, 2, false, DIFFP, TAIL>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm);
+    gemm_tile<NT, 2, 2, 2, false, DIFFP, TAIL, false, STREAM>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm);
   }
   clock_end(p);
 }
@@ -1120,9 +1125,9 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p, cons
     static_assert(sizeof(smem) >= adapter::kGradLdsElems * sizeof(bf16_t), "the gradient's slabs");
     if (b >= p.grad0) {
       const int g = b - p.grad0, item = g % job.n_items, cols = g / job.n_items;
-      if (job.pieces == 1) adapter::grad_rows<1, 2>(job, p.tasks, item, cols, smem);
-      else if (job.pieces == 2) adapter::grad_rows<2, 2>(job, p.tasks, item, cols, smem);
-      else adapter::grad_rows<4, 1>(job, p.tasks, item, cols, smem);
+      if (job.pieces == 1) adapter::grad_rows<1, 2, false>(job, p.tasks, item, cols, smem);
+      else if (job.pieces == 2) adapter::grad_rows<2, 2, false>(job, p.tasks, item, cols, smem);
+      else adapter::grad_rows<4, 1, false>(job, p.tasks, item, cols, smem);
       return;
     }
   }
@@ -1421,6 +1426,12 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
   p.clk = diag_clock_buffer();
   if (t.grid == 0) return MUX_OK;
+  // An output of whole cache lines that would push the operands of the tiles to come out of the last-level cache goes past it:
+  // LoRA, forward and backward, through the caches and past them: 4096 x 4096, 12000 tokens (98 MB) 698 and 683 us, 8000 (65 MB)
+  // 459 and 458; 32 tasks of about 1024 tokens, 8192 x 1024 and 1024 x 8192 (84 and 671 MB, with the loads of kStreamBytes) 2593 and 2480;
+  // 18 k tokens, 5120-wide, 5797 and 5686; 5120 tokens, 11008 columns (113 MB), 1894 and 1900.  Smaller outputs the next kernel may
+  // still find there, and lines that tiles share (6424 columns) would be written twice.
+  const bool stream = (size_t)c.st->T * Nc * 2 >= kStreamOut && Nc % 64 == 0;
   p.Part = (float*)c.split;
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
@@ -1450,14 +1461,16 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
     return MUX_OK;
   }
   if (p.DiffPack != nullptr) {
-    MUX_LAUNCH(name, (k_gemm_dma<NT, true, false>), grid, block, 0, c.stream, p);
+    MUX_LAUNCH(name, (k_gemm_dma<NT, true, false, false>), grid, block, 0, c.stream, p);
   } else if (t.n_full == 0) {
     if (t.pieces == PIECES_HALF) launch_pieces<PIECES_HALF, NT>(name, grid, c.stream, p, job);
     else if (t.pieces == PIECES_QUARTER) launch_pieces<PIECES_QUARTER, NT>(name, grid, c.stream, p, job);
     else if (t.pieces == PIECES_64X128) launch_pieces<PIECES_64X128, NT>(name, grid, c.stream, p, job);
     else launch_pieces<PIECES_64X64, NT>(name, grid, c.stream, p, job);
-  } else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true>), grid, block, 0, c.stream, p);
-  else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false>), grid, block, 0, c.stream, p);
+  } else if (stream && tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true, true>), grid, block, 0, c.stream, p);
+  else if (stream) MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, true>), grid, block, 0, c.stream, p);
+  else if (tail) MUX_LAUNCH(name, (k_gemm_dma<NT, false, true, false>), grid, block, 0, c.stream, p);
+  else MUX_LAUNCH(name, (k_gemm_dma<NT, false, false, false>), grid, block, 0, c.stream, p);
   return MUX_OK;
 }
 

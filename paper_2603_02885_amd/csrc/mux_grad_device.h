@@ -19,6 +19,11 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
 __device__ __forceinline__ u32x4 buf_load16(rsrc_t r, uint32_t byte_off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, 0);
 }
+// The same past the caches (see kStreamBytes)
+template <bool STREAM>
+__device__ __forceinline__ u32x4 buf_load16_once(rsrc_t r, uint32_t byte_off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, STREAM ? 2 : 0);
+}
 __device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)p);
 }
@@ -67,7 +72,7 @@ constexpr int kGradLdsElems = 4 * 2 * 32 * GP;
 
 // DEPTH steps of loads in flight; the loop body has no branch and a fixed number of loads per step (what does not
 // exist gets an out-of-range offset), so that the wait for one step's data leaves the younger loads in flight.
-template <int NJM, int DEPTH>
+template <int NJM, int DEPTH, bool STREAM>
 __device__ __forceinline__ void grad_rows(const GradParams& p, const TaskRef& tasks, const int item, const int cols, bf16_t* lds) {
   const int4 iw = *(const int4*)(p.dtab + p.items_off + item * DI_WORDS);
   const ItemView it = {iw.x, iw.y, iw.z, iw.w};
@@ -106,7 +111,7 @@ __device__ __forceinline__ void grad_rows(const GradParams& p, const TaskRef& ta
     for (int q = 0; q < 4; ++q) {
       const int m = base + b_row + 8 * q;
       const bool ok = b_col_ok && m < it.nrows && ((vbits >> (b_row + 8 * q)) & 1u);
-      gb[buf][q] = buf_load16(rB, ok ? (uint32_t)(((size_t)m * C + cw0 + b_pc) * 2) : OOB);
+      gb[buf][q] = buf_load16_once<STREAM>(rB, ok ? (uint32_t)(((size_t)m * C + cw0 + b_pc) * 2) : OOB);
     }
 #pragma unroll
     for (int q = 0; q < NJM; ++q) {
