@@ -451,13 +451,139 @@ __global__ __launch_bounds__(512) void k_s4(const S4Params p) {
   else put(std::false_type{});
 }
 
+// ------------------------------------------------------------------------------------------------
+// IA3_OUT: part[item][n] = sum_{rows} g[i][n] * z[i][n], and dYs[i][n] = g[i][n] * l_t[n] (the operand of the
+// backbone backward for these rows).  grid = (64-row items, ceil(N/1024)), 512 threads: 128 column threads of 8
+// columns, times four quarters of the item's rows (16 rows each, all 32 loads of a thread issued before the first
+// sum), the quarters' sums added through LDS in the order of the rows.
+constexpr int kDlCols = 1024;
+struct DlParams {
+  const bf16_t *dY, *Z;
+  float* part;
+  bf16_t* dYs;
+  int N, items_off, bits_off;
+};
+__device__ __forceinline__ void dl_rows(const int32_t* dtab, const TaskRef& tasks, const DlParams& q, int item, int block,
+                                        float (*sq)[128][9]) {
+  const bf16_t* const dY = q.dY;
+  const bf16_t* const Z = q.Z;
+  const int N = q.N;
+  const int4 iw = *(const int4*)(dtab + q.items_off + item * DI_WORDS);
+  const int task = iw.x, row0 = iw.y, nrows = iw.z;
+  if (task < 0 || iw.w == 0) return;
+  if (get_task_kind(tasks, task) != MUX_ADAPTER_IA3_OUT) return;
+  const DevTask tk = get_task(tasks, task);
+  const uint32_t* bw = (const uint32_t*)(dtab + q.bits_off) + 2 * item;
+  const int ct = threadIdx.x & 127, rq = threadIdx.x >> 7;
+  const uint32_t bits = (rq < 2 ? bw[0] : bw[1]) >> (16 * (rq & 1)) & 0xffffu;    // validity of this quarter's 16 rows
+  const int n0 = (block * 128 + ct) * 8;
+  const bool cols = n0 < N;
+  constexpr int RQ = 16;
+  float s[8], lv[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) { s[e] = 0.f; lv[e] = 0.f; }
+  if (cols) {
+    const uint4 l4 = *(const uint4*)((const bf16_t*)tk.L + n0);
+    const uint32_t* pl = (const uint32_t*)&l4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { lv[2 * e] = __uint_as_float(pl[e] << 16); lv[2 * e + 1] = __uint_as_float(pl[e] & 0xffff0000u); }
+    // every thread issues the same 2 RQ loads (a row that does not count reads the item's first row instead and is
+    // dropped afterwards)
+    uint4 gv[RQ], zv[RQ];
+#pragma unroll
+    for (int u = 0; u < RQ; ++u) {
+      const int m = rq * RQ + u;
+      const int row = row0 + (m < nrows ? m : 0);
+      gv[u] = *(const uint4*)(dY + (size_t)row * N + n0);
+      zv[u] = *(const uint4*)(Z + (size_t)(tk.zrow0 + row - tk.row_begin) * N + n0);
+    }
+#pragma unroll
+    for (int u = 0; u < RQ; ++u) {
+      const int m = rq * RQ + u;
+      if (!(m < nrows && ((bits >> u) & 1u))) continue;
+      const uint32_t* pg = (const uint32_t*)&gv[u];
+      const uint32_t* pz = (const uint32_t*)&zv[u];
+      uint4 sv;
+      uint32_t* ps = (uint32_t*)&sv;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g0 = __uint_as_float(pg[e] << 16), g1 = __uint_as_float(pg[e] & 0xffff0000u);
+        s[2 * e] = fmaf(g0, __uint_as_float(pz[e] << 16), s[2 * e]);
+        s[2 * e + 1] = fmaf(g1, __uint_as_float(pz[e] & 0xffff0000u), s[2 * e + 1]);
+        ps[e] = pack_bf16x2(g0 * lv[2 * e], g1 * lv[2 * e + 1]);
+      }
+      *(uint4*)(q.dYs + (size_t)(tk.zrow0 + row0 + m - tk.row_begin) * N + n0) = sv;
+    }
+  }
+  if (rq > 0) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sq[rq - 1][ct][e] = s[e];
+  }
+  __syncthreads();
+  if (rq == 0 && cols) {
+    float* dst = q.part + (size_t)item * N + n0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dst[e] = ((s[e] + sq[0][ct][e]) + sq[1][ct][e]) + sq[2][ct][e];
+  }
+}
+
+__global__ __launch_bounds__(512) void k_dl(const int32_t* __restrict__ dtab, const TaskRef tasks, const DlParams q) {
+  __shared__ float sq[3][128][9];
+  dl_rows(dtab, tasks, q, blockIdx.x, blockIdx.y, sq);
+}
+
+// Ranks that are not multiples of 8: A_t [K, r] (Adapter-Tuning: D_t [N, r]) once more with its rows padded to
+// round_up(r, 8) elements (zeros), so that every kernel of the matrix-core path reads rows of whole 16-byte pieces.
+// tk.L is the caller's matrix, tk.A the padded copy in the workspace; piece e of the copy by one thread.  A copy of a few
+// hundred KB, bound by its launch (4 us at 1608 x 12); before it, such ranks sent the whole backward product to a
+// register-staged GEMM at a third of the pipelined one's rate.
+__device__ __forceinline__ void pad_rank_piece(const TaskRef& tasks, int task, int e, int K, int N) {
+  const DevTask tk = get_task(tasks, task);
+  if ((tk.kind != MUX_ADAPTER_LORA && tk.kind != MUX_ADAPTER_TUNING) || tk.L == nullptr) return;
+  const int rows = tk.kind == MUX_ADAPTER_LORA ? K : N;
+  const int pieces = rank_pieces(tk.rank);
+  if (e >= rows * pieces) return;
+  const int row = e / pieces, j0 = (e % pieces) * 8;
+  const uint16_t* src = (const uint16_t*)tk.L + (size_t)row * tk.rank;
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int j = j0 + 2 * i;
+    w[i] = (j < tk.rank ? (uint32_t)src[j] : 0u) | (j + 1 < tk.rank ? (uint32_t)src[j + 1] << 16 : 0u);
+  }
+  *(uint4*)((uint16_t*)tk.A + (size_t)e * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+__global__ __launch_bounds__(256) void k_pad_rank(const TaskRef tasks, int K, int N) {
+  pad_rank_piece(tasks, blockIdx.x, blockIdx.y * 256 + threadIdx.x, K, N);
+}
+
 // Gs[T,RP] = s_t * (sum over the column slabs of the shares k_s4 left, ascending), times gelu'(u) for the TUNING rows;
-// zero on padding rows, beyond the rank and on the rows of the other kinds.  One workgroup per 64-row item.
-__global__ __launch_bounds__(256) void k_gs_reduce(const int32_t* __restrict__ dtab, const TaskRef tasks,
+// zero on padding rows, beyond the rank and on the rows of the other kinds.  One workgroup per 64-row item.  Behind these
+// the launch has the workgroups of two small jobs that need nothing of it and that the next launches wait for, as
+// launches of their own 4-9 us each: the padded copies of A_t (n_pad a task) and, in the build with DL, the IA3 rows
+// (1608 x 6424, ranks 4 and 12, two micro-batches forward and backward: 391 us, 384 with the copies, 376 with both).
+template <bool DL>
+__global__ __launch_bounds__(DL ? 512 : 256) void k_gs_reduce(const int32_t* __restrict__ dtab, const TaskRef tasks,
                                                   const float* __restrict__ gpart, int n_slabs, int T, int RP,
                                                   const bf16_t* __restrict__ U2, bf16_t* __restrict__ Gs, int items_off,
-                                                  int bits_off) {
-  const int item = blockIdx.x;
+                                                  int bits_off, int n_items, int n_dl, int n_pad, int K, const DlParams q) {
+  constexpr int NTHR = DL ? 512 : 256;
+  int b = blockIdx.x;
+  if constexpr (DL) {                  // the longest first: n_dl column blocks an item
+    __shared__ float sq[3][128][9];
+    if (b < n_items * n_dl) {
+      dl_rows(dtab, tasks, q, b / n_dl, b % n_dl, sq);
+      return;
+    }
+    b -= n_items * n_dl;
+  }
+  if (b >= n_items) {
+    b -= n_items;
+    pad_rank_piece(tasks, b / n_pad, (b % n_pad) * NTHR + threadIdx.x, K, q.N);
+    return;
+  }
+  const int item = b;
   const int4 iw = *(const int4*)(dtab + items_off + item * DI_WORDS);
   const uint32_t* bw = (const uint32_t*)(dtab + bits_off) + 2 * item;
   const uint32_t bits0 = bw[0], bits1 = bw[1];
@@ -468,7 +594,7 @@ __global__ __launch_bounds__(256) void k_gs_reduce(const int32_t* __restrict__ d
   int rank = 0;
   if (mine) { const DevTask tk = get_task(tasks, task); scale = tk.scale; rank = tk.rank; }
   const int q4 = RP >> 2;                        // groups of four columns a row
-  for (int e = threadIdx.x; e < nrows * q4; e += 256) {
+  for (int e = threadIdx.x; e < nrows * q4; e += NTHR) {
     const int m = e / q4, j = (e % q4) * 4;
     const size_t o = (size_t)(row0 + m) * RP + j;
     const bool valid = mine && (((m < 32 ? bits0 >> m : bits1 >> (m - 32)) & 1u) != 0u) && j < rank;
@@ -636,75 +762,6 @@ __global__ __launch_bounds__(256) void k_tune_add(const TuneAddParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// IA3_OUT: part[item][n] = sum_{rows} g[i][n] * z[i][n], and dYs[i][n] = g[i][n] * l_t[n] (the operand of the
-// backbone backward for these rows).  grid = (64-row items, ceil(N/1024)), 512 threads: 128 column threads of 8
-// columns, times four quarters of the item's rows (16 rows each, all 32 loads of a thread issued before the first
-// sum), the quarters' sums added through LDS in the order of the rows.
-__global__ __launch_bounds__(512) void k_dl(const int32_t* __restrict__ dtab, const TaskRef tasks,
-                                           const bf16_t* __restrict__ dY, const bf16_t* __restrict__ Z, float* __restrict__ part,
-                                           bf16_t* __restrict__ dYs, int N, int items_off, int bits_off) {
-  __shared__ float sq[3][128][9];
-  const int item = blockIdx.x;
-  const int4 iw = *(const int4*)(dtab + items_off + item * DI_WORDS);
-  const int task = iw.x, row0 = iw.y, nrows = iw.z;
-  if (task < 0 || iw.w == 0) return;
-  if (get_task_kind(tasks, task) != MUX_ADAPTER_IA3_OUT) return;
-  const DevTask tk = get_task(tasks, task);
-  const uint32_t* bw = (const uint32_t*)(dtab + bits_off) + 2 * item;
-  const int ct = threadIdx.x & 127, rq = threadIdx.x >> 7;
-  const uint32_t bits = (rq < 2 ? bw[0] : bw[1]) >> (16 * (rq & 1)) & 0xffffu;    // validity of this quarter's 16 rows
-  const int n0 = (blockIdx.y * 128 + ct) * 8;
-  const bool cols = n0 < N;
-  constexpr int RQ = 16;
-  float s[8], lv[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) { s[e] = 0.f; lv[e] = 0.f; }
-  if (cols) {
-    const uint4 l4 = *(const uint4*)((const bf16_t*)tk.L + n0);
-    const uint32_t* pl = (const uint32_t*)&l4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { lv[2 * e] = __uint_as_float(pl[e] << 16); lv[2 * e + 1] = __uint_as_float(pl[e] & 0xffff0000u); }
-    // every thread issues the same 2 RQ loads (a row that does not count reads the item's first row instead and is
-    // dropped afterwards)
-    uint4 gv[RQ], zv[RQ];
-#pragma unroll
-    for (int u = 0; u < RQ; ++u) {
-      const int m = rq * RQ + u;
-      const int row = row0 + (m < nrows ? m : 0);
-      gv[u] = *(const uint4*)(dY + (size_t)row * N + n0);
-      zv[u] = *(const uint4*)(Z + (size_t)(tk.zrow0 + row - tk.row_begin) * N + n0);
-    }
-#pragma unroll
-    for (int u = 0; u < RQ; ++u) {
-      const int m = rq * RQ + u;
-      if (!(m < nrows && ((bits >> u) & 1u))) continue;
-      const uint32_t* pg = (const uint32_t*)&gv[u];
-      const uint32_t* pz = (const uint32_t*)&zv[u];
-      uint4 sv;
-      uint32_t* ps = (uint32_t*)&sv;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float g0 = __uint_as_float(pg[e] << 16), g1 = __uint_as_float(pg[e] & 0xffff0000u);
-        s[2 * e] = fmaf(g0, __uint_as_float(pz[e] << 16), s[2 * e]);
-        s[2 * e + 1] = fmaf(g1, __uint_as_float(pz[e] & 0xffff0000u), s[2 * e + 1]);
-        ps[e] = pack_bf16x2(g0 * lv[2 * e], g1 * lv[2 * e + 1]);
-      }
-      *(uint4*)(dYs + (size_t)(tk.zrow0 + row0 + m - tk.row_begin) * N + n0) = sv;
-    }
-  }
-  if (rq > 0) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sq[rq - 1][ct][e] = s[e];
-  }
-  __syncthreads();
-  if (rq == 0 && cols) {
-    float* dst = part + (size_t)item * N + n0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dst[e] = ((s[e] + sq[0][ct][e]) + sq[1][ct][e]) + sq[2][ct][e];
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
 // out_t = (accumulate ? out_t : 0) + sum over the task's items, ascending.  grid = (tasks, blocks).
 // LoRA and Adapter-Tuning tasks: the first blocks take 1024 elements of dB_t [r][N] each, from part0; the blocks after
 // them dA_t, whose partials in part1 are [r][K] and which is stored [K][r]: such a block takes all r of
@@ -818,6 +875,27 @@ bool single_groups(const mux_segtab* st, int ts_b, int ts_a) {
   return true;
 }
 
+// 16-byte pieces of the largest padded copy of an A_t (D_t); 0: no rank needs one
+size_t padded_pieces(const CallCtx& c) {
+  size_t most = 0;
+  for (const HostTask& ht : c.st->tasks)
+    if (rank_is_padded(ht)) {
+      const size_t n = (size_t)rank_pieces(ht.rank) * (ht.kind == MUX_ADAPTER_LORA ? c.K : c.N);
+      if (n > most) most = n;
+    }
+  return most;
+}
+
+int dl_blocks(int N) { return (N + kDlCols - 1) / kDlCols; }
+// The IA3 rows ride in the launch of gs_reduce where they have no more than a few rounds of workgroups.  Forward and
+// backward, a launch of their own against riding: 512 rows of 2048 x 2048 81.4 -> 79.6 us (64 workgroups), 3072 of
+// 4096 x 4096 396 -> 392 (384), 4096 of 4096 x 4096 326.5 -> 323 (288); 4096 of 4096 x 8192, 1280 workgroups,
+// 1147 and 1148: the 174 registers of that build then cost the reduction what the launch gains.
+bool dl_rides_along(const CallCtx& c) {
+  return c.st->n_ia3 > 0 && c.st->n_lora + c.st->n_tuning > 0 && s4_slabs(c.N) > 1 &&
+         c.st->items[TS64].size() * (size_t)dl_blocks(c.N) <= 4 * (size_t)kComputeUnits;
+}
+
 struct PartLayout { size_t gpart, part0, part1, ia3, total; };
 PartLayout part_layout(int K, int N, const mux_segtab* st) {
   PartLayout o{};
@@ -837,6 +915,21 @@ PartLayout part_layout(int K, int N, const mux_segtab* st) {
 
 size_t adapter_partial_bytes(int K, int N, const mux_segtab* st) { return part_layout(K, N, st).total; }
 
+namespace {
+DlParams dl_params(const CallCtx& c, const void* dY, const void* Z, void* part) {
+  const PartLayout pl = part_layout(c.K, c.N, c.st);
+  return DlParams{(const bf16_t*)dY, (const bf16_t*)Z, (float*)((char*)part + pl.gpart + pl.part0 + pl.part1), (bf16_t*)c.dYs,
+                  c.N, c.st->dev_image[DH_NITEMS0 + 3 * TS64 + 1], c.st->dev_image[DH_OFF_ITEM_BITS]};
+}
+}  // namespace
+
+void adapter_pad_ranks(const CallCtx& c) {
+  const size_t most = padded_pieces(c);
+  if (most > 0)
+    MUX_LAUNCH("pad_rank", k_pad_rank, dim3((unsigned)c.st->n_tasks, (unsigned)((most + 255) / 256)), dim3(256), 0, c.stream,
+               *c.tref, c.K, c.N);
+}
+
 mux_status adapter_down_x(const CallCtx& c, const void* X, void* Hs) {
   if (c.st->n_lora == 0) return MUX_OK;
   DownParams p{c.dtab, (const bf16_t*)X, (bf16_t*)Hs, nullptr, c.K, c.RP, DOWN_X};
@@ -846,7 +939,7 @@ mux_status adapter_down_x(const CallCtx& c, const void* X, void* Hs) {
 
 // The pass over dY: Gs (LoRA: s_t dY B_t^T; Adapter-Tuning: s_t (dY U_t^T) * gelu'(u)) and the partial sums of
 // dB_t = Hs^T dY (dU_t), which adapter_reduce brings together.
-mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, void* Gs, void* part, int accumulate) {
+mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, const void* Z, void* Gs, void* part, int accumulate) {
   if (c.st->n_lora + c.st->n_tuning == 0) return MUX_OK;
   const PartLayout pl = part_layout(c.K, c.N, c.st);
   float* gpart = (float*)part;
@@ -862,6 +955,7 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, voi
   const dim3 grid((unsigned)c.st->items[ts].size(), (unsigned)slabs);
   // (rank pieces, steps between two meetings of the waves, steps of loads in flight)
   if (slabs == 1) {
+    adapter_pad_ranks(c);
     if (c.st->r_max <= 16) MUX_LAUNCH("s4_dy_pass", (k_s4<1, 2, 2, true, false>), grid, dim3(512), 0, c.stream, p);
     else if (c.st->r_max <= 32) MUX_LAUNCH("s4_dy_pass", (k_s4<2, 2, 1, true, false>), grid, dim3(512), 0, c.stream, p);
     else MUX_LAUNCH("s4_dy_pass", (k_s4<4, 1, 1, true, false>), grid, dim3(512), 0, c.stream, p);
@@ -879,9 +973,16 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, voi
   for (const HostTask& ht : c.st->tasks)
     if (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) moved += (double)slabs * ht.valid * round_up(ht.rank, 4) * 4;
   prof_note_bytes(moved);
-  MUX_LAUNCH("gs_reduce", k_gs_reduce, dim3((unsigned)c.st->items[TS64].size()), dim3(256), 0, c.stream, c.dtab, *c.tref,
-             (const float*)gpart, slabs, c.st->T, c.RP, (const bf16_t*)c.U2, (bf16_t*)Gs,
-             c.st->dev_image[DH_NITEMS0 + 3 * TS64 + 1], c.st->dev_image[DH_OFF_ITEM_BITS]);
+  const bool dl = dl_rides_along(c);
+  const unsigned items = (unsigned)c.st->items[TS64].size(), threads = dl ? 512 : 256;
+  const unsigned n_pad = (unsigned)((padded_pieces(c) + threads - 1) / threads), n_dl = dl ? (unsigned)dl_blocks(c.N) : 0;
+  auto reduce = [&](auto DL) {
+    MUX_LAUNCH("gs_reduce", (k_gs_reduce<decltype(DL)::value>), dim3(items * (1 + n_dl) + (unsigned)c.st->n_tasks * n_pad),
+               dim3(threads), 0, c.stream, c.dtab, *c.tref, (const float*)gpart, slabs, c.st->T, c.RP, (const bf16_t*)c.U2,
+               (bf16_t*)Gs, c.st->dev_image[DH_NITEMS0 + 3 * TS64 + 1], c.st->dev_image[DH_OFF_ITEM_BITS], (int)items,
+               (int)n_dl, (int)n_pad, c.K, dl_params(c, dY, Z, part));
+  };
+  if (dl) reduce(std::true_type{}); else reduce(std::false_type{});
   return MUX_OK;
 }
 
@@ -940,11 +1041,9 @@ void adapter_grad_da(const CallCtx& c, const GradParams& p) {
 
 // IA3_OUT: the partial sums of dl_t and the scaled rows the backbone backward reads.
 void adapter_dl(const CallCtx& c, const void* dY, const void* Z, void* part) {
-  if (c.st->n_ia3 == 0) return;
-  const PartLayout pl = part_layout(c.K, c.N, c.st);
-  MUX_LAUNCH("grad_dl", k_dl, dim3((unsigned)c.st->items[TS64].size(), (c.N + 1023) / 1024), dim3(512), 0, c.stream,
-             c.dtab, *c.tref, (const bf16_t*)dY, (const bf16_t*)Z, (float*)((char*)part + pl.gpart + pl.part0 + pl.part1),
-             (bf16_t*)c.dYs, c.N, c.st->dev_image[DH_NITEMS0 + 3 * TS64 + 1], c.st->dev_image[DH_OFF_ITEM_BITS]);
+  if (c.st->n_ia3 == 0 || dl_rides_along(c)) return;
+  MUX_LAUNCH("grad_dl", k_dl, dim3((unsigned)c.st->items[TS64].size(), (unsigned)dl_blocks(c.N)), dim3(512), 0, c.stream,
+             c.dtab, *c.tref, dl_params(c, dY, Z, part));
 }
 
 // The partial sums of every gradient brought together, after all of the above.

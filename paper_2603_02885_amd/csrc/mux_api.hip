@@ -14,29 +14,6 @@ __global__ __launch_bounds__(64) void k_write_tasks(DevTask* __restrict__ out, c
   if (i < count) out[base + i] = tb.t[i];
 }
 
-// Ranks that are not multiples of 8: A_t [K, r] (Adapter-Tuning: D_t [N, r]) once more with its rows padded to
-// round_up(r, 8) elements (zeros), so that every kernel of the matrix-core path reads rows of whole 16-byte pieces.
-// tk.L is the caller's matrix, tk.A the padded copy in the workspace; one thread per 16-byte piece.  A copy of a few
-// hundred KB, bound by its launch (4 us at 1608 x 12); before it, such ranks sent the whole backward product to a
-// register-staged GEMM at a third of the pipelined one's rate.
-__global__ __launch_bounds__(256) void k_pad_rank(const TaskRef tasks, int K, int N) {
-  const DevTask tk = get_task(tasks, blockIdx.x);
-  if ((tk.kind != MUX_ADAPTER_LORA && tk.kind != MUX_ADAPTER_TUNING) || tk.L == nullptr) return;
-  const int rows = tk.kind == MUX_ADAPTER_LORA ? K : N;
-  const int pieces = rank_pieces(tk.rank);
-  const int e = blockIdx.y * 256 + threadIdx.x;
-  if (e >= rows * pieces) return;
-  const int row = e / pieces, j0 = (e % pieces) * 8;
-  const uint16_t* src = (const uint16_t*)tk.L + (size_t)row * tk.rank;
-  uint32_t w[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int j = j0 + 2 * i;
-    w[i] = (j < tk.rank ? (uint32_t)src[j] : 0u) | (j + 1 < tk.rank ? (uint32_t)src[j + 1] << 16 : 0u);
-  }
-  *(uint4*)((uint16_t*)tk.A + (size_t)e * 8) = make_uint4(w[0], w[1], w[2], w[3]);
-}
-
 // A table without rows: every task's gradient is zero.  grid = (tasks, blocks over the largest gradient).
 __global__ __launch_bounds__(256) void k_zero_grads(const TaskRef tasks, int K, int N) {
   const DevTask tk = get_task(tasks, blockIdx.x);
@@ -52,11 +29,6 @@ __global__ __launch_bounds__(256) void k_zero_grads(const TaskRef tasks, int K, 
 }
 
 namespace {
-
-// A ranked task whose A_t (D_t) has rows that are no whole number of 16-byte pieces
-inline bool rank_is_padded(const HostTask& ht) {
-  return (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) && (ht.rank & 7) != 0;
-}
 
 struct Layout {
   size_t esz;          // bytes per stored element
@@ -185,7 +157,7 @@ void build_tasks(const mux_layer_desc* L, const mux_segtab* st, void* const* dA,
     d.scale = ht.scale; d.kind = kind; d.rank = ht.rank;
     d.row_begin = ht.row_begin; d.row_count = ht.row_count; d.zrow0 = ht.zrow0;
     if (padded && rank_is_padded(ht)) {
-      d.L = d.A;                                  // the caller's matrix; k_pad_rank lays its copy out
+      d.L = d.A;                                  // the caller's matrix; adapter_pad_ranks lays its copy out
       d.A = padded;
       padded += (size_t)round_up(ht.rank, 8) * (kind == MUX_ADAPTER_LORA ? L->K : L->N);
     }
@@ -208,10 +180,9 @@ void build_tasks(const mux_layer_desc* L, const mux_segtab* st, void* const* dA,
 }
 
 // Makes the tasks visible to the kernels of the call: by value in `ref` when they fit and no kernel of the call needs
-// the table in memory, else written into the workspace by a small kernel; and pads the rows of the A_t that need it
-// (matrix-core path).
+// the table in memory, else written into the workspace by a small kernel.
 void publish_tasks(const mux_layer_desc* L, const mux_segtab* st, const std::vector<DevTask>& tasks, bool need_table,
-                   DevTask* dtasks, TaskRef& ref, bool fast, hipStream_t stream) {
+                   DevTask* dtasks, TaskRef& ref, hipStream_t stream) {
   std::memset(&ref, 0, sizeof(ref));
   if (!need_table && st->n_tasks <= kArgTasks) {
     for (int t = 0; t < st->n_tasks; ++t) ref.arg.t[t] = tasks[t];
@@ -225,16 +196,6 @@ void publish_tasks(const mux_layer_desc* L, const mux_segtab* st, const std::vec
     }
     ref.mem = dtasks;
   }
-  size_t most = 0;                    // 16-byte pieces of the largest padded copy
-  if (fast)
-    for (const HostTask& ht : st->tasks)
-      if (rank_is_padded(ht)) {
-        const size_t n = (size_t)rank_pieces(ht.rank) * (ht.kind == MUX_ADAPTER_LORA ? L->K : L->N);
-        if (n > most) most = n;
-      }
-  if (most > 0)
-    MUX_LAUNCH("pad_rank", k_pad_rank, dim3((unsigned)st->n_tasks, (unsigned)((most + 255) / 256)), dim3(256), 0, stream,
-               ref, L->K, L->N);
 }
 
 }  // namespace
@@ -303,7 +264,7 @@ extern "C" mux_status mux_lora_forward(const mux_layer_desc* layer, const mux_se
   uint16_t* const padded = fast ? (uint16_t*)((char*)ws + lo.tasks_bytes + lo.g_bytes) : nullptr;
   build_tasks(layer, st, nullptr, nullptr, nullptr, padded, c.diffPack ? 2 : (c.diffW ? 1 : 0), false, tasks);
   TaskRef tref;
-  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, fast && st->T > 0, stream);
+  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, stream);
   c.tref = &tref;
   c.dtasks = tref.mem;
   mux_status s;
@@ -342,7 +303,7 @@ static mux_status backward_impl(const char* fn, const mux_layer_desc* layer, con
   uint16_t* const padded = fast ? (uint16_t*)((char*)ws + lo.tasks_bytes + lo.g_bytes) : nullptr;
   build_tasks(layer, st, dA, dB, dL, padded, c.diffPack ? 2 : (c.diffW ? 1 : 0), true, tasks);
   TaskRef tref;
-  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, fast && st->T > 0, stream);
+  publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, stream);
   c.tref = &tref;
   c.dtasks = tref.mem;
   if (st->T == 0) {                 // no rows at all: zero gradients (or leave the accumulators as they are)

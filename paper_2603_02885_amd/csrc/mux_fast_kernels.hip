@@ -27,6 +27,7 @@ bool fast_gemm_patches_diff(const CallCtx& c, bool backward) {
 
 // The caller has checked fast_supported for the shapes and pointers of this call.
 mux_status fast_forward(const CallCtx& c, const void* X, void* Y, void* H, void* Z, void*) {
+  adapter_pad_ranks(c);
   // small launches form Hs = s_t X A_t inside the backbone tile loop; the others stream X once more for it
   const bool fuse_down = gemm_dma_fuses_down(c);
   if (!fuse_down)
@@ -45,7 +46,7 @@ mux_status fast_forward(const CallCtx& c, const void* X, void* Y, void* H, void*
 mux_status fast_backward(const CallCtx& c, const void* X, const void* dY, const void* H, const void* Z, void* G, void* dX,
                          int accumulate, void* part) {
   // one pass over dY: Gs and the partial sums of dB_t
-  if (mux_status s = adapter_dy_pass(c, dY, H, G, part, accumulate)) return s;
+  if (mux_status s = adapter_dy_pass(c, dY, H, Z, G, part, accumulate)) return s;
   // Adapter-Tuning rows enter the backbone backward as dY + Gs D_t^T
   if (mux_status s = adapter_tune_add(c, dY, G, c.dYs, 1)) return s;
   adapter_dl(c, dY, Z, part);
@@ -55,7 +56,7 @@ mux_status fast_backward(const CallCtx& c, const void* X, const void* dY, const 
   if (!ride) adapter_grad_da(c, job);
   if (dX) {
     if (c.diffPack) diff_pack(c, true); else diff_merge(c, c.diffW_slots);
-    // IA3_OUT rows read dY * l_t, written by the dl kernel above
+    // IA3_OUT rows read dY * l_t, written above
     if (mux_status s = gemm_dma_backward(c, dY, G, dX, ride ? &job : nullptr)) return s;
   }
   adapter_reduce(c, part, accumulate);

@@ -137,6 +137,10 @@ constexpr size_t kStreamBytes = (size_t)112 << 20;
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 // 16-byte pieces in a row of A_t (D_t) as the matrix-core kernels read it
 __host__ __device__ inline int rank_pieces(int rank) { return (rank + 7) >> 3; }
+// A ranked task whose A_t (D_t) has rows that are no whole number of 16-byte pieces
+inline bool rank_is_padded(const HostTask& ht) {
+  return (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) && (ht.rank & 7) != 0;
+}
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Everything a kernel launcher needs about one call.
@@ -206,12 +210,14 @@ mux_status gemm_dma_backward(const CallCtx& c, const void* dY, const void* Gs, v
 
 // matrix-core adapter kernels (bf16): down-projections and per-task gradient reductions
 mux_status adapter_down_x(const CallCtx& c, const void* X, void* Hs);                       // S1
-mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, void* Gs, void* part, int accumulate);   // S4: Gs, dB (partials)
+void adapter_pad_ranks(const CallCtx& c);                                                   // the padded copies of A_t, in a launch of their own
+// S4: Gs, dB (partials); also lays the padded copies of A_t out and, where dl_rides_along, does the work of adapter_dl
+mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, const void* Z, void* Gs, void* part, int accumulate);
 mux_status adapter_down_tune(const CallCtx& c, const void* Z, void* Hs);                    // Adapter-Tuning forward
 mux_status adapter_tune_add(const CallCtx& c, const void* In, const void* Small, void* Out, int backward);
 adapter::GradParams adapter_grad_job(const CallCtx& c, const void* X, const void* Gs, const void* Z, void* part, int accumulate);   // S6
 void adapter_grad_da(const CallCtx& c, const adapter::GradParams& job);
-void adapter_dl(const CallCtx& c, const void* dY, const void* Z, void* part);
+void adapter_dl(const CallCtx& c, const void* dY, const void* Z, void* part);               // nothing where adapter_dy_pass did it
 void adapter_reduce(const CallCtx& c, void* part, int accumulate);                          // the sums of S4, S6 and of IA3
 size_t adapter_partial_bytes(int K, int N, const mux_segtab* st);
 

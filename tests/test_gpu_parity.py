@@ -152,6 +152,26 @@ def test_gradients_without_partials(env, K, N, lens, ranks):
             assert a is None or torch.equal(b, a + a), k
 
 
+@pytest.mark.parametrize("K,N,ia3", [(264, 512, 70), (264, 520, 70), (1032, 1032, 513), (72, 8200, 7200)])
+def test_small_jobs_in_the_launch_of_the_gs_sums(env, K, N, ia3):
+    """The padded copies of A_t and D_t (ranks 12, 7 and 1) and the IA3 rows behind the sums of Gs, or in launches of their own
+    (one column slab; more IA3 rows than ride along): the backward finds nothing of the forward in its scratch memory."""
+    mx, torch = env
+    kinds = [(wlm.KIND_LORA, 12, 200), (wlm.KIND_IA3, 0, ia3), (wlm.KIND_ADAPTER, 7, 129), (wlm.KIND_LORA, 1, 65), (wlm.KIND_LORA, 16, 64)]
+    wl = wlm.Workload(name="jobs", layers=[("w", K, N)], chunk=64, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(k, r, 2.0, [n]) for k, r, n in kinds])
+    g, got, ref, errs = run_case(env, wl, seed=K + N)
+    first = {k: [None if t is None else t.clone() for t in getattr(g, k)] for k in ("dA", "dB", "dL")}
+    dx = g.dX.clone()
+    g.ws.view(torch.uint8).fill_(0xFF)
+    g.backward()
+    torch.cuda.synchronize()
+    assert torch.equal(g.dX, dx)
+    for k in first:
+        for a, b in zip(first[k], getattr(g, k)):
+            assert a is None or torch.equal(a, b), k
+
+
 @pytest.mark.parametrize("K,N", [(264, 136), (1032, 520)])
 def test_gradient_reduction_blocks(env, K, N):
     """The blocks that bring the partial gradients together: as many columns of dA_t as a rank leaves room for (ranks 1 to
