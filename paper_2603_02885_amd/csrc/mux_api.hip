@@ -295,6 +295,8 @@ static mux_status backward_impl(const char* fn, const mux_layer_desc* layer, con
   const void* H = saved;
   const void* Z = (saved && st->z_rows > 0) ? (const char*)saved + lo.h_bytes : nullptr;
   void* G = (char*)ws + lo.tasks_bytes;
+  const size_t x_bytes = (size_t)st->T * layer->K * lo.esz;
+  c.dx_apart = !overlap(dX, x_bytes, X, x_bytes) && !overlap(dX, x_bytes, saved, lo.saved_bytes);
   const bool fast = layer->dtype == MUX_DT_BF16 && !(layer->flags & MUX_LAYER_REFERENCE_KERNELS) &&
                     fast_supported(c, X, dY, dX, G, H, Z);
   if (fast && lo.dp_bytes > 0 && dX && fast_gemm_patches_diff(c, true)) c.diffPack = (char*)ws + lo.ws_bytes - lo.dp_bytes;

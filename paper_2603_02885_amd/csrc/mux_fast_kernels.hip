@@ -50,9 +50,10 @@ mux_status fast_backward(const CallCtx& c, const void* X, const void* dY, const 
   // Adapter-Tuning rows enter the backbone backward as dY + Gs D_t^T
   if (mux_status s = adapter_tune_add(c, dY, G, c.dYs, 1)) return s;
   adapter_dl(c, dY, Z, part);
-  // dA_t: in the launch of the backbone product where that leaves compute units idle
+  // dA_t: in the launch of the backbone product where that leaves compute units idle.  It reads X (Adapter-Tuning: the saved
+  // x W), so not where dX goes over them.
   const adapter::GradParams job = adapter_grad_job(c, X, G, Z, part, accumulate);
-  const bool ride = dX && job.n_items > 0 && gemm_dma_takes_grads(c);
+  const bool ride = dX && c.dx_apart && job.n_items > 0 && gemm_dma_takes_grads(c);
   if (!ride) adapter_grad_da(c, job);
   if (dX) {
     if (c.diffPack) diff_pack(c, true); else diff_merge(c, c.diffW_slots);

@@ -141,6 +141,9 @@ __host__ __device__ inline int rank_pieces(int rank) { return (rank + 7) >> 3; }
 inline bool rank_is_padded(const HostTask& ht) {
   return (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) && (ht.rank & 7) != 0;
 }
+inline bool overlap(const void* p, size_t n, const void* q, size_t m) {
+  return p && q && (uintptr_t)p < (uintptr_t)q + m && (uintptr_t)q < (uintptr_t)p + n;
+}
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Everything a kernel launcher needs about one call.
@@ -167,6 +170,7 @@ struct CallCtx {
                            // them to the tiles of W in LDS (index << 16 | bf16 value; null: another route is taken)
   void* split;             // workspace: `split_room` bytes for the partial tiles of backbone products whose contraction is split
   size_t split_room;
+  bool dx_apart;           // backward: dX shares no memory with X or with what the forward saved
 };
 
 // H / G row pitch in elements

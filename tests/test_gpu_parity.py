@@ -152,6 +152,40 @@ def test_gradients_without_partials(env, K, N, lens, ranks):
             assert a is None or torch.equal(b, a + a), k
 
 
+@pytest.mark.parametrize("K,N,lens", [(256, 256, [100, 150, 40]), (2056, 192, [256, 700, 100]), (640, 4096, [100, 70, 64]),
+                                      (264, 1032, [300, 500, 260])])
+def test_input_gradient_over_the_inputs(env, K, N, lens):
+    """dX in the memory of X, and in that of what the forward saved: launches whose workgroups could take dA_t along would read
+    there what others write, so dA_t comes before them; the same bits as with buffers apart (pieces of 64, halves, a shared
+    contraction; Adapter-Tuning reads the saved x W)."""
+    mx, torch = env
+    kinds = [(wlm.KIND_LORA, 16), (wlm.KIND_ADAPTER, 12), (wlm.KIND_IA3, 0)]
+    wl = wlm.Workload(name="over", layers=[("w", K, N)], chunk=64, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(k, r, 2.0, [n]) for (k, r), n in zip(kinds, lens)])
+    g, got, ref, errs = run_case(env, wl, seed=K)
+    outs = lambda: [g.dX] + [t for k in ("dA", "dB", "dL") for t in getattr(g, k) if t is not None]          # noqa: E731
+    want = [t.clone() for t in outs()]
+    places = [g.X]
+    if g.dX.numel() * 2 <= g.saved.numel():
+        places.append(g.saved[:g.dX.numel() * 2].view(torch.bfloat16).view(g.dX.shape))
+    for place in places:
+        g.forward()
+        g.dX = place
+        print(f"K={K} N={N} dX over {'X' if place is g.X else 'saved'}", flush=True)
+        mx.mux_profile_enable(1)
+        mx.mux_profile_collect()
+        x = g.X.clone()
+        g.backward()
+        torch.cuda.synchronize()
+        names = {e["name"] for e in mx.mux_profile_collect()}
+        mx.mux_profile_enable(0)
+        assert "grad_da" in names, names
+        for a, b in zip(want, outs()):
+            assert torch.equal(a, b)
+        g.X.copy_(x)
+    assert len(places) == 2 or N <= K
+
+
 @pytest.mark.parametrize("K,N,ia3", [(264, 512, 70), (264, 520, 70), (1032, 1032, 513), (72, 8200, 7200)])
 def test_small_jobs_in_the_launch_of_the_gs_sums(env, K, N, ia3):
     """The padded copies of A_t and D_t (ranks 12, 7 and 1) and the IA3 rows behind the sums of Gs, or in launches of their own
