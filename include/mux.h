@@ -221,8 +221,8 @@ mux_status mux_lora_forward(const mux_layer_desc* layer, const mux_segtab* st,
  * dA, dB, dL: host arrays of n_tasks device pointers to fp32 buffers ([K,r_t], [r_t,N], [N]);
  * an entry may be NULL to skip that gradient.  accumulate = 0 overwrites, 1 adds to what the
  * buffers hold (micro-batch accumulation).  dX may be NULL to skip the input gradient.
- * `saved` must be the buffer the matching forward filled with the same layer and table.  dX may take the memory of X or of
- * `saved` where no task is DIFF: it is written after their last read then. */
+ * `saved` must be the buffer the matching forward filled with the same layer and table.  Where no task is DIFF, dX,
+ * dA_t, dB_t and dl_t may take the memory of X or of `saved`: they are written after their last read then. */
 mux_status mux_lora_backward(const mux_layer_desc* layer, const mux_segtab* st,
                              const void* dev_segtab, const void* X, const void* dY,
                              const void* saved, void* dX, void* const* dA, void* const* dB,

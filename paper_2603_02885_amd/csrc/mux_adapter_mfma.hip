@@ -866,8 +866,11 @@ int grad_width(const CallCtx& c) { return (c.st->n_tuning > 0 && c.N > c.K) ? c.
 
 // Is every LoRA and Adapter-Tuning task one row group, of size `ts_b` in the pass over dY and `ts_a` in the one over X?  Then
 // their sums are the gradients, and no partials and no reduction are needed (256 x 256, two tasks of 100 and 150 tokens, 4 us
-// of 34).
-bool single_groups(const mux_segtab* st, int ts_b, int ts_a) {
+// of 34).  Not where a gradient goes over an input: the reduction writes after the last read of X, dY and the saved activations,
+// the passes themselves do not.
+bool single_groups(const CallCtx& c, int ts_b, int ts_a) {
+  const mux_segtab* const st = c.st;
+  if (!c.grads_apart) return false;
   for (int t = 0; t < st->n_tasks; ++t) {
     if (st->tasks[t].kind != MUX_ADAPTER_LORA && st->tasks[t].kind != MUX_ADAPTER_TUNING) continue;
     if (st->tasks[t].valid == 0 || st->task_item_count[ts_b][t] != 1 || st->task_item_count[ts_a][t] != 1) return false;
@@ -948,7 +951,7 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, con
   S4Params p{c.dtab, (const bf16_t*)dY, (const bf16_t*)Hs, gpart, part0, c.N, c.RP, ts, c.st->T,
              c.st->dev_image[DH_NITEMS0 + 3 * ts + 1], c.st->dev_image[DH_OFF_ROWBITS]};
   p.tasks = *c.tref;
-  p.direct = single_groups(c.st, ts, da_group(c.st, grad_width(c))) ? 1 : 0;
+  p.direct = single_groups(c, ts, da_group(c.st, grad_width(c))) ? 1 : 0;
   p.accumulate = accumulate;
   p.U2 = (const bf16_t*)c.U2;
   p.Gs = (bf16_t*)Gs;
@@ -1018,7 +1021,7 @@ GradParams adapter_grad_job(const CallCtx& c, const void* X, const void* Gs, con
   p.K = c.K; p.N = c.N; p.RP = c.RP; p.T = c.st->T;
   p.items_off = c.st->dev_image[DH_NITEMS0 + 3 * ts + 1];
   p.rowbits_off = c.st->dev_image[DH_OFF_ROWBITS];
-  p.direct = single_groups(c.st, s4_group(c.st, c.N), ts) ? 1 : 0;
+  p.direct = single_groups(c, s4_group(c.st, c.N), ts) ? 1 : 0;
   p.accumulate = accumulate;
   p.n_items = (int)c.st->items[ts].size();
   p.col_blocks = (K1 + 255) / 256;
@@ -1052,7 +1055,7 @@ void adapter_reduce(const CallCtx& c, void* part, int accumulate) {
   const PartLayout pl = part_layout(c.K, c.N, c.st);
   const int K1 = grad_width(c);
   const int ts_b = s4_group(c.st, c.N), ts_a = da_group(c.st, K1);
-  const bool ranked = c.st->n_lora + c.st->n_tuning > 0 && !single_groups(c.st, ts_b, ts_a);
+  const bool ranked = c.st->n_lora + c.st->n_tuning > 0 && !single_groups(c, ts_b, ts_a);
   float* part0 = (float*)((char*)part + pl.gpart);
   float* part1 = (float*)((char*)part + pl.gpart + pl.part0);
   float* part_ia3 = (float*)((char*)part + pl.gpart + pl.part0 + pl.part1);

@@ -304,6 +304,14 @@ static mux_status backward_impl(const char* fn, const mux_layer_desc* layer, con
   std::vector<DevTask> tasks;
   uint16_t* const padded = fast ? (uint16_t*)((char*)ws + lo.tasks_bytes + lo.g_bytes) : nullptr;
   build_tasks(layer, st, dA, dB, dL, padded, c.diffPack ? 2 : (c.diffW ? 1 : 0), true, tasks);
+  c.grads_apart = true;
+  for (int t = 0; t < st->n_tasks && fast; ++t) {
+    const HostTask& ht = st->tasks[t];
+    if (ht.kind != MUX_ADAPTER_LORA && ht.kind != MUX_ADAPTER_TUNING) continue;
+    const size_t a = (size_t)(ht.kind == MUX_ADAPTER_LORA ? layer->K : layer->N) * ht.rank * 4, b = (size_t)ht.rank * layer->N * 4;
+    const auto apart = [&](const void* in, size_t n) { return !overlap(tasks[t].dA, a, in, n) && !overlap(tasks[t].dB, b, in, n); };
+    c.grads_apart = c.grads_apart && apart(X, x_bytes) && apart(dY, (size_t)st->T * layer->N * lo.esz) && apart(saved, lo.saved_bytes);
+  }
   TaskRef tref;
   publish_tasks(layer, st, tasks, !fast, (DevTask*)ws, tref, stream);
   c.tref = &tref;

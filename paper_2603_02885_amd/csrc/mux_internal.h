@@ -171,6 +171,7 @@ struct CallCtx {
   void* split;             // workspace: `split_room` bytes for the partial tiles of backbone products whose contraction is split
   size_t split_room;
   bool dx_apart;           // backward: dX shares no memory with X or with what the forward saved
+  bool grads_apart;        //           nor does any dA_t or dB_t, or with dY
 };
 
 // H / G row pitch in elements

@@ -186,6 +186,37 @@ def test_input_gradient_over_the_inputs(env, K, N, lens):
     assert len(places) == 2 or N <= K
 
 
+@pytest.mark.parametrize("N", [264, 776])
+@pytest.mark.parametrize("place", ["X", "saved"])
+def test_adapter_gradients_over_the_inputs(env, N, place):
+    """dA_t and dB_t in the memory of X or of what the forward saved: tasks of one row group, whose gradients the passes over dY
+    and X would write straight while others still read, take the reduction instead; the same bits."""
+    mx, torch = env
+    wl = wlm.Workload(name="over", layers=[("w", 256, N)], chunk=64, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(wlm.KIND_LORA, 8, 2.0, [100]), wlm.Task(wlm.KIND_LORA, 3, 2.0, [250])])
+    g, got, ref, errs = run_case(env, wl, seed=N)
+    outs = lambda: [g.dX] + [t for k in ("dA", "dB") for t in getattr(g, k)]          # noqa: E731
+    want = [t.clone() for t in outs()]
+    mem = (g.X.view(torch.uint8) if place == "X" else g.saved).view(-1)
+    at = 0
+    for grads in ((g.dA, 0), (g.dB, 1)) if place == "X" else ((g.dB, 1),):
+        t, n = grads[1], grads[0][grads[1]].numel() * 4
+        grads[0][t] = mem[at:at + n].view(torch.float32).view(grads[0][t].shape)
+        at += n
+    assert at <= mem.numel()
+    print(f"N={N} gradients over {place}", flush=True)
+    g.forward()
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    g.backward()
+    torch.cuda.synchronize()
+    names = {e["name"] for e in mx.mux_profile_collect()}
+    mx.mux_profile_enable(0)
+    assert "reduce_grads" in names, names
+    for a, b in zip(want, outs()):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("K,N,ia3", [(264, 512, 70), (264, 520, 70), (1032, 1032, 513), (72, 8200, 7200)])
 def test_small_jobs_in_the_launch_of_the_gs_sums(env, K, N, ia3):
     """The padded copies of A_t and D_t (ranks 12, 7 and 1) and the IA3 rows behind the sums of Gs, or in launches of their own
