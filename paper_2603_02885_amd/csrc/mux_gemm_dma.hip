@@ -1508,12 +1508,15 @@ mux_status gemm_dma_forward(const CallCtx& c, const void* X, const void* Hs, voi
   return launch<false>(c, (const bf16_t*)X, (const bf16_t*)Hs, (bf16_t*)Y, (bf16_t*)Z, c.K, c.N, fuse_down);
 }
 
-// Launches of pieces only: their workgroups have four waves, and most of them compute units to spare.  Forward and backward, a
-// launch of its own -> riding: 256 x 256, 250 tokens, 29.0 -> 25.1 us; 2048 x 3000, 300 tokens, 58.9 -> 50.8; 2560 x 2560, 900
-// tokens, 81 -> 77.2; 1608 x 6424, 2400 tokens in two micro-batches, 402 -> 393; none of 70 drawn training calls slower by more than 1 %.
+// Launches of pieces only (their workgroups have four waves), of at most two rounds of them: those have compute units to spare,
+// or nearly so.  Behind more rounds the gradient runs at the end, one workgroup a unit with the pieces' LDS, where a launch of its
+// own has four.  Forward and backward, a launch of its own -> riding: 256 x 256, 250 tokens, 29.0 -> 25.1 us; 2048 x 3000, 300
+// tokens, 58.9 -> 50.8; 2560 x 2560, 900 tokens, 81 -> 77.2; 1608 x 6424, 2400 tokens in two micro-batches, 402 -> 393; tasks of 40
+// to 128 tokens, N = 1024, 512 pieces: 4096, 16 tasks 82.6 -> 80.7, 8192, 8 tasks of rank 64 114.5 -> 112.0; 768 and more: 4096, 24
+// tasks 103.0 -> 104.9, 8192, 32 tasks 208.3 -> 213.1, 2048, 64 tasks of rank 64 159.6 -> 160.8.
 bool gemm_dma_takes_grads(const CallCtx& c) {
   const TilePlan t = plan_tiles(c.st, c.K);
-  return t.n_full == 0 && t.grid > 0 && c.diffPack == nullptr;
+  return t.n_full == 0 && t.grid > 0 && t.clear0 <= 2 * compute_units() && c.diffPack == nullptr;
 }
 
 mux_status gemm_dma_backward(const CallCtx& c, const void* dY, const void* Gs, void* dX, const adapter::GradParams* job) {

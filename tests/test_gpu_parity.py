@@ -217,6 +217,24 @@ def test_adapter_gradients_over_the_inputs(env, N, place):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("n,rides", [(16, True), (20, False)])
+def test_gradients_ride_where_units_idle(env, n, rides):
+    """Tasks of at most 128 tokens, whose row groups make pieces only: dA_t rides in the backward product of up to two rounds of
+    them (16 tasks at 4096 columns: 512 pieces), and has a launch of its own behind more."""
+    mx, torch = env
+    wl = wlm.Workload(name="short", layers=[("w", 4096, 72)], chunk=64, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(wlm.KIND_LORA, 8, 2.0, [128 - 7 * t % 90]) for t in range(n)])
+    g, got, ref, errs = run_case(env, wl, seed=n)
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    g.backward()
+    torch.cuda.synchronize()
+    names = {e["name"] for e in mx.mux_profile_collect()}
+    mx.mux_profile_enable(0)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert ("grad_da" not in names) == rides, names
+
+
 @pytest.mark.parametrize("K,N,ia3", [(264, 512, 70), (264, 520, 70), (1032, 1032, 513), (72, 8200, 7200)])
 def test_small_jobs_in_the_launch_of_the_gs_sums(env, K, N, ia3):
     """The padded copies of A_t and D_t (ranks 12, 7 and 1) and the IA3 rows behind the sums of Gs, or in launches of their own
