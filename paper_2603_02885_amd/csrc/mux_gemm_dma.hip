@@ -294,10 +294,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const int KT_ext = lora && !(FUSE && SPLITK) ? (rank + BK - 1) / BK : 0;
   // this tile forms Hs of its rows in the K loop (SPLITK: only those of the first column, whose share k_gemm_sum adds up)
   const bool fuse_h = FUSE && lora && (!SPLITK || c0 == 0);
-  // The loops of pieces take two K-tiles a turn, and where a second way out between the two would make the compiler copy all
-  // accumulators at every turn (FUSE, and the pieces of 64 rows) an odd number of tiles is followed by one of zeros.
-  const int KT_pad = fuse_h && !SPLITK ? KT & 1 : 0;
-  const int KT_total = KT + KT_pad + KT_ext;
+  const int KT_total = KT + KT_ext;
   const int kt_first = SPLITK ? (int)((unsigned)(split * KT_total) / (unsigned)p.splits) : 0;
   const int kt_end = SPLITK ? (int)((unsigned)((split + 1) * KT_total) / (unsigned)p.splits) : KT_total;
   // DIFFP: the bucket offsets of this task's listing for this direction, the buckets of this tile in a K-tile's row
@@ -393,7 +390,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   const int special = SPLITK && kt_end < odd_tile ? kt_end : odd_tile;
   auto prepare = [&]() {
     if (next_tile < special) return;
-    if (PIECE && (next_tile >= kt_end || (fuse_h && next_tile == KT && KT_pad))) {
+    if (PIECE && next_tile >= kt_end) {
       curA[2] = 0; curB[2] = 0;                               // past the end, or the next share's: zeros, whatever the offset
       if (FUSE) kE = OOB;
     } else if (TAIL && next_tile == KT - 1) {                                // the last backbone tile is not full: pieces past the end
@@ -410,7 +407,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
       if (next_tile >= KT_total) {
         kA = OOB; kB = OOB;
       } else {
-        const int j0 = (next_tile - KT - KT_pad) * BK;        // first contraction index of this adapter tile
+        const int j0 = (next_tile - KT) * BK;        // first contraction index of this adapter tile
         curB = rP; kB = 0; stepA = 0; stepB = 0;
         if (FUSE) {
           curA[2] = 0;                                        // the A side of the adapter tile comes from the accumulators
@@ -650,7 +647,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   }
 
   // FUSE: the K loop ends with the backbone; the adapter tile (its B_t side is fetched like any tile) follows below
-  const int KT_loop = fuse_h && !SPLITK ? KT + KT_pad : kt_end - kt_first;
+  // The loops of pieces take two K-tiles a turn.  The last of an odd number follows the loop, as products alone: a way out in the
+  // middle of a turn made the compiler copy all accumulators at every turn, and a K-tile of zeros in its place took as long as any
+  // (448 x 10496, three tasks of 95, 92 and 29 tokens, forward 12.3 us so, 11.3 now; 832 x 4096, the same, 12.0 and 10.9).
+  const int KT_loop = fuse_h && !SPLITK ? KT : kt_end - kt_first;
 
   if constexpr (KS) {
     // Each wave takes one of the four MFMA steps of every K-tile: every operand is read from LDS once (waves that each own a
@@ -679,7 +679,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     if (FUSE) re[0] = read_e(stE(0), wave);            // (a tile that forms no Hs multiplies zeros: no branch in the loop)
     int su = 0;                                      // stage of tile kt
     prepare();
-    for (int kt2 = 0; kt2 < KT_loop; kt2 += 2) {
+    for (int kt2 = 0; kt2 + 1 < KT_loop; kt2 += 2) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         {
@@ -707,6 +707,15 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
         }
       }
     }
+    if (KT_loop & 1) {                               // its operands are there: products alone
+#pragma unroll
+      for (int i = 0; i < NSLOT; ++i) {
+        const int t = i / (2 * NI), q = i % (2 * NI);
+        accf[t][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rb[0][q], ra[0][t], accf[t][q], 0, 0, 0);
+        if (FUSE && q == 2 * NI - 1)
+          haccf[FUSE ? t : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(re[0], ra[0][t], haccf[FUSE ? t : 0], 0, 0, 0);
+      }
+    }
     // the refills issued past the last tile (zeros) must have landed before the stages are reused below
     wait_vmcnt<0>();
     wait_lgkm0();
@@ -717,7 +726,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
       // The shares meet in two other stages, wave w brings row block w together (lane: row li of it, columns 8 j + 4 lg ..
       // + 3).  Scaled, masked, rounded to bf16, it goes into the adapter tile's stage in the layout the operand reads expect
       // (pieces 4..7 of a row, contraction indices 32..63, are zero), and from the tiles of the first column to memory.
-      const int sK = (KT + KT_pad) % NST;
+      const int sK = KT % NST;
       static_assert(HW * 4 * 1024 <= 2 * STAGE / 2 && NST >= 4, "the shares of Hs fit two stages");
       float4* red = (float4*)stA(sK < 2 ? 2 : 0);
 #pragma unroll
@@ -812,11 +821,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     }
     int su = 0;                                      // stage of tile kt
     prepare();
-    for (int kt2 = 0; kt2 < KT_loop; kt2 += 2) {
+    for (int kt2 = 0; kt2 + 1 < KT_loop; kt2 += 2) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int kt = kt2 + u;
-        if (FUSE || kt < KT_loop) {
+        {
           const int un = su + 1 == NST ? 0 : su + 1;
           wait_vmcnt<(NST - 2) * NLD>();
           wait_lgkm0();
@@ -841,6 +849,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
           }
           su = un;
         }
+      }
+    }
+    if (KT_loop & 1) {                               // its operands are there: products alone
+#pragma unroll
+      for (int i = 0; i < NSLOT; ++i) {
+        mma_one(ra[0][i / NM], rb[0][i / NM], i % NM);
+        if (FUSE && i % NM == NM - 1) mma_h(re[0][i / NM], ra[0][i / NM]);
       }
     }
   } else {
@@ -918,7 +933,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     // row wn*32 + li of the wave's row half and columns 8 j + 4 lg .. + 3.  Scaled, masked beyond the rank, rounded to
     // bf16, it goes into that stage in the layout the operand reads expect (pieces 4..7 of a row, contraction
     // indices 32..63, are zero), and from the tiles of the first column to memory.
-    const int sK = (KT + KT_pad) % NST;
+    const int sK = KT % NST;
     bf16_t* hA = stA(sK);
     const bf16_t* hB = stB(sK);
 #pragma unroll
