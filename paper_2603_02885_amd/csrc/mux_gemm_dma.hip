@@ -54,7 +54,8 @@ constexpr int TILE_N = 256;                     // width of a tile in the launch
 // now).
 constexpr int CLEAR_N = 512;
 constexpr uint32_t OOB = 0x80000000u;
-constexpr size_t kStreamOut = (size_t)64 << 20;      // bytes of an output from which on it is written past the caches
+// Bytes of an output, and of it and the activations that it is formed from, beyond which it is written past the caches
+constexpr size_t kStreamOut = (size_t)64 << 20, kStreamBoth = (size_t)144 << 20;
 
 // A workgroup reads these one after the other as it finds out what it computes, from lines of 64 bytes that are cold at the
 // start of a launch: what it needs first lies in the first line, what comes next in the second.  (Spread over three lines,
@@ -1443,12 +1444,14 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.Wdiff = (const bf16_t*)c.diffW; p.wdiff_stride = c.diffW_stride;
   p.clk = diag_clock_buffer();
   if (t.grid == 0) return MUX_OK;
-  // An output of whole cache lines that would push the operands of the tiles to come out of the last-level cache goes past it:
-  // LoRA, forward and backward, through the caches and past them: 4096 x 4096, 12000 tokens (98 MB) 698 and 683 us, 8000 (65 MB)
-  // 459 and 458; 32 tasks of about 1024 tokens, 8192 x 1024 and 1024 x 8192 (84 and 671 MB, with the loads of kStreamBytes) 2593 and 2480;
-  // 18 k tokens, 5120-wide, 5797 and 5686; 5120 tokens, 11008 columns (113 MB), 1894 and 1900.  Smaller outputs the next kernel may
-  // still find there, and lines that tiles share (6424 columns) would be written twice.
-  const bool stream = (size_t)c.st->T * Nc * 2 >= kStreamOut && Nc % 64 == 0;
+  // An output of whole cache lines goes past the last-level cache where that would not hold it for its reader beside the
+  // activations: it would push them, and the operands of the tiles to come, out.  Two projections, each one's output the next one's input, LoRA,
+  // forward and backward, through the caches and past them (MB of the two activations): 4096 and 11008 columns (32, 86) 1259 and
+  // 1271 us, 2048 and 5504 (32, 85) 720 and 731, 4096 and 4096 (64, 64) 1101 and 1106, (70, 70) 1134 and 1143; 3072 and 3072
+  // (80, 80) 1062 and 1053, 4096 and 2048 (102, 51) 917 and 903, 2560 and 2560 (88, 88) 991 and 970, 4096 and 4096 (125, 125)
+  // 1949 and 1921, 5120 and 5120 (176, 176) 3346 and 3288.  Lines that tiles share (6424 columns) would be written twice.
+  const size_t out_bytes = (size_t)c.st->T * Nc * 2, in_bytes = (size_t)c.st->T * Kc * 2;
+  const bool stream = out_bytes >= kStreamOut && out_bytes + in_bytes > kStreamBoth && Nc % 64 == 0;
   p.Part = (float*)c.split;
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
