@@ -1449,9 +1449,13 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   // forward and backward, through the caches and past them (MB of the two activations): 4096 and 11008 columns (32, 86) 1259 and
   // 1271 us, 2048 and 5504 (32, 85) 720 and 731, 4096 and 4096 (64, 64) 1101 and 1106, (70, 70) 1134 and 1143; 3072 and 3072
   // (80, 80) 1062 and 1053, 4096 and 2048 (102, 51) 917 and 903, 2560 and 2560 (88, 88) 991 and 970, 4096 and 4096 (125, 125)
-  // 1949 and 1921, 5120 and 5120 (176, 176) 3346 and 3288.  Lines that tiles share (6424 columns) would be written twice.
+  // 1949 and 1921, 5120 and 5120 (176, 176) 3346 and 3288.  Lines that tiles share (6424 columns) would be written twice.  Not the
+  // forward of a batch of Adapter-Tuning for the most part: it writes x W, which the next two launches read (9000 tokens of rank
+  // 64, 4096 x 4096, tune_down 40.3 us past the caches, 31.5 through them).
   const size_t out_bytes = (size_t)c.st->T * Nc * 2, in_bytes = (size_t)c.st->T * Kc * 2;
-  const bool stream = out_bytes >= kStreamOut && out_bytes + in_bytes > kStreamBoth && Nc % 64 == 0;
+  int64_t tuning = 0;
+  for (const HostTask& ht : c.st->tasks) tuning += !NT && ht.kind == MUX_ADAPTER_TUNING ? ht.row_count : 0;
+  const bool stream = out_bytes >= kStreamOut && out_bytes + in_bytes > kStreamBoth && 2 * tuning <= c.st->T && Nc % 64 == 0;
   p.Part = (float*)c.split;
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
