@@ -128,9 +128,9 @@ unsigned long long* diag_clock_buffer();
   } while (0)
 
 constexpr int kComputeUnits = 256;  // of the part the kernels are made for (MI355X)
-// A tensor of more bytes than this is read past the caches (non-temporal loads) by the kernels that read it once from end to
-// end: the 256 MB last-level cache would not hold it until somebody reads it again, and has to throw out what somebody will.  A
-// smaller one is still there for the backbone product that reads it next.  LoRA, 4096 x 4096, forward and backward, through the
+// Rows of more bytes than this are read past the caches (non-temporal loads) by the kernels that read them once from end to
+// end: the 256 MB last-level cache would not hold them until somebody reads them again, and has to throw out what somebody will.
+// Fewer are still there for the backbone product that reads them next.  LoRA, 4096 x 4096, forward and backward, through the
 // caches and past them: 6000 tokens (49 MB) 390 and 395 us, 12000 (98 MB) 730 and 734, 16000 (131 MB) 994 and 975, 24000 1419
 // and 1393; Dispatch of 4096 bf16 values, 8000 tokens 51.3 and 56.9 us, 12000 73.8 and 74.5, 16000 97.6 and 90.6, 20000 136.6 and 111.8.
 constexpr size_t kStreamBytes = (size_t)112 << 20;
