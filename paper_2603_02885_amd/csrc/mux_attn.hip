@@ -713,7 +713,8 @@ __device__ __forceinline__ void attn_bwd_short(const AttnParams& p, const int wi
         for (int st = 0; st < KS; ++st) {
           s = mma(*(const bf16x8*)(sQ + li * TP + 16 * st + 8 * half), *(const bf16x8*)(kfrag + 16 * st), s);
           dp = mma(*(const bf16x8*)(sD + li * TP + 16 * st + 8 * half), vf[st], dp);
-          if (D > 96 && st % 2 == 1) __builtin_amdgcn_sched_barrier(0);     // (the operand reads would pile up in registers)
+          // (the operand reads would pile up in registers, and beyond them: 53 heads of 96, 30 x 120 and 10 x 50 tokens 166.2 us, 163.8 so)
+          if ((D > 96 || (D == 96 && R == 64)) && st % 2 == 1) __builtin_amdgcn_sched_barrier(0);
         }
         // P (keys past the sequence come after every query: the mask takes them)
 #pragma unroll
