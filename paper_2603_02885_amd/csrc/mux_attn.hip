@@ -881,9 +881,10 @@ void plan_backward(const mux_segtab* st, const mux_attn_desc* desc, int& n_long,
     n_long += n64 + n128;
     n64 = n128 = 0;
   }
-  // The launch of narrower workgroups for at most 64 tokens fills the chip, and so does what it leaves to the other
-  // (128 x 64 tokens and 128, 8 groups of 4 heads: 263 us in two launches, 185 in one; 51 x 64 tokens and 12 x 128, 20 heads of 64:
-  // 53 and 65).
+  // Narrower workgroups for at most 64 tokens where they fill the chip, and so does what they leave to the others (128 x 64
+  // tokens and 128, 8 groups of 4 heads of 128: 263 us in two launches, 185 in one; 51 x 64 tokens and 12 x 128, 20 heads of 64:
+  // 53 and 65).  D < 128, where both kinds share a launch, all in the wide ones, two kinds: 32 heads of 80, 14 x 120 and 6 x 50
+  // tokens 62.5 us, 66.0, 30 and 10 96.9, 100.4; 24 of 96, 30 and 10 84.1, 85.5; 20 of 64, 14 and 12 43.9, 44.7, but 14 and 18 58.1, 49.5.
   if (n128 > 0 && (n64 * hkv < fill || !pays(n128, 128))) { n128 += n64; n64 = 0; }
   if ((n128 > 0 && !pays(n128, 128)) || (n64 > 0 && !pays(n64, 64))) { n_long += n64 + n128; n64 = n128 = 0; }
 }
@@ -992,9 +993,13 @@ extern "C" mux_status mux_attn_backward(const mux_attn_desc* desc, const mux_seg
     if (D == 128) {
       if (n128 > 0) MUX_LAUNCH("attn_bwd_128", (k_attn_bwd_short_one<128, 128>), dim3(short_grid(n128, desc->n_kv_heads, D)), dim3(256), 0, stream, p);
       if (n64 > 0) MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<128, 64>), dim3(one64), dim3(128), 0, stream, p);
-    } else if (n128 == 0 && (int64_t)n64 * desc->n_kv_heads < 2 * kComputeUnits) {
-      // so few that two heads a workgroup would leave compute units idle (15 heads of 64, two sequences, forward and backward
-      // 30.4 us so, 32.4 in pairs; 36 heads of 96, twelve, 41.6 and 42.4)
+    } else if (n128 == 0 && (int64_t)n64 * desc->n_kv_heads * D < (D == 64 ? 2048 : 1536) * (int64_t)kComputeUnits) {
+      // Nothing but sequences of at most 64 tokens: two heads a workgroup move whole lines where there is enough to move
+      // (48 MB a tensor of full sequences; 64 MB of heads of 64, whose rows are whole lines); below, a workgroup of twice the
+      // waves finds its place later.  Forward and backward,
+      // one head, two: 16 heads of 96, 40 x 50 tokens 45.2 us, 47.7; 40 of 96, 80 x 50 110.4, 115.2; 24 of 96, 160 x 50 119.7,
+      // 119.3; 53 of 96, 80 x 50 153.1, 150.5, 160 x 64 358.7, 336.5; 33 of 80, 80 x 64 79.1, 82.6, 160 x 64 190.8, 183.3; 32 of 80, 160 x
+      // 64 229.9, 195.9; 40 of 64, 80 x 50 81.9, 86.0, 160 x 50 133.8, 144.8, 300 x 64 362.6, 333.3; 8 groups of 4 heads of 64, 160 x 64 85.7, 92.1.
       if (D == 96) MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<96, 64>), dim3(one64), dim3(128), 0, stream, p);
       else if (D == 80) MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<80, 64>), dim3(one64), dim3(128), 0, stream, p);
       else MUX_LAUNCH("attn_bwd_64", (k_attn_bwd_short_one<64, 64>), dim3(one64), dim3(128), 0, stream, p);

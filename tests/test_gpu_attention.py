@@ -184,6 +184,19 @@ def test_both_kinds_of_short_sequences_in_one_launch(env, H, d):
     assert "attn_bwd_128_64" in names, names
 
 
+@pytest.mark.parametrize("H,d,n", [(9, 96, 454), (9, 96, 456), (11, 80, 446), (11, 80, 447), (8, 64, 1023), (8, 64, 1024)])
+def test_short_sequences_alone(env, H, d, n):
+    """Nothing but sequences of at most 64 tokens: one head a workgroup up to 4095 heads of 96, 4915 of 80, 8191 of 64, two from
+    there on, the last one alone where the heads are odd."""
+    mx, _ = env
+    mx.mux_profile_enable(1)
+    mx.mux_profile_collect()
+    run(env, [[64, 33, 1] + [1 + i % 12 for i in range(n - 3)]], chunk=64, H=H, seed=90 + n, d=d)
+    names = {e["name"] for e in mx.mux_profile_collect()}
+    mx.mux_profile_enable(0)
+    assert "attn_bwd_64" in names and "attn_bwd_kv" not in names, names
+
+
 @pytest.mark.parametrize("H,Hkv,d", [(5, 5, 80), (7, 7, 64), (3, 1, 96), (8, 8, 80), (24, 8, 64)])
 def test_short_sequences_over_the_xcds(env, H, Hkv, d):
     """The ways in which (block, head) pairs of short sequences are dealt to the XCDs, forward and backward: numbers of heads
