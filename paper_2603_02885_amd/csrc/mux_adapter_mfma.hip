@@ -225,7 +225,7 @@ void launch_down(const CallCtx& c, const char* name, DownParams p) {
   // leave room for one workgroup a compute unit, four for two.  So they take eight where a unit has one workgroup or none
   // (84 items at 4096: 18.6 -> 15.1 us) and four beyond (324 items: 61.7 us, eight waves 63.6).
   const dim3 grid(items * 2);
-  const bool stream = p.mode == DOWN_X && ranked_bytes(c.st, p.C, 0) > kStreamBytes;     // (k_tune_add reads the x W of DOWN_TUNE again)
+  const bool stream = p.mode == DOWN_X && past_caches(c, ranked_bytes(c.st, p.C, 0));     // (k_tune_add reads the x W of DOWN_TUNE again)
   auto launch = [&](auto STREAM) {
     constexpr bool S = decltype(STREAM)::value;
     if (c.st->r_max <= 16) MUX_LAUNCH(name, (k_down<1, 8, 2, S>), grid, dim3(512), 0, c.stream, p);
@@ -980,7 +980,7 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, con
     else if (c.st->r_max <= 32) MUX_LAUNCH("s4_dy_pass", (k_s4<2, 2, 1, false, S>), grid, dim3(512), 0, c.stream, p);
     else MUX_LAUNCH("s4_dy_pass", (k_s4<4, 1, 1, false, S>), grid, dim3(512), 0, c.stream, p);
   };
-  if (ranked_bytes(c.st, c.N, c.N) > kStreamBytes) launch(std::true_type{}); else launch(std::false_type{});
+  if (past_caches(c, ranked_bytes(c.st, c.N, c.N))) launch(std::true_type{}); else launch(std::false_type{});
   // moved: the partials of every slab once in (a task's real tokens, its rank rounded up to four columns), Gs once out
   double moved = (double)c.st->T * c.RP * 2;
   for (const HostTask& ht : c.st->tasks)
@@ -1049,7 +1049,7 @@ void adapter_grad_da(const CallCtx& c, const GradParams& p) {
     else if (p.pieces == 2) MUX_LAUNCH("grad_da", (k_grad<2, 2, S>), grid, dim3(256), 0, c.stream, p, *c.tref);
     else MUX_LAUNCH("grad_da", (k_grad<4, 1, S>), grid, dim3(256), 0, c.stream, p, *c.tref);
   };
-  if (ranked_bytes(c.st, c.K, c.N) > kStreamBytes) launch(std::true_type{}); else launch(std::false_type{});
+  if (past_caches(c, ranked_bytes(c.st, c.K, c.N))) launch(std::true_type{}); else launch(std::false_type{});
 }
 
 // IA3_OUT: the partial sums of dl_t and the scaled rows the backbone backward reads.

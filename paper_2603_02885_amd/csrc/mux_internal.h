@@ -174,6 +174,16 @@ struct CallCtx {
   bool grads_apart;        //           nor does any dA_t or dB_t, or with dY
 };
 
+// The adapter kernels read `bytes` bytes of rows past the caches where they are many (see kStreamBytes) and the last-level
+// cache could not hold the layer's two activations anyway.  Where it can, the products find there what these kernels have
+// read: LoRA, three tasks, past the caches and through them: 8280 x 1128, 11000 tokens (173 and 23 MB) forward 292 and 254 us,
+// forward and backward 618 and 586, 8192 x 512, 9000 (140 and 8 MB) 304 and 277, 4096 x 1024, 24000 (187 and 46 MB) 514 and 505; 32000 (250 and
+// 62 MB) 644 and 664, 4096 x 4096, 28000 (218 and 218 MB) 1718 and 1740, 1024 x 8192, 20000 (39 and 312 MB) 764 and 774.
+constexpr size_t kStreamActs = (size_t)240 << 20;
+inline bool past_caches(const CallCtx& c, size_t bytes) {
+  return bytes > kStreamBytes && (size_t)c.st->T * ((size_t)c.K + c.N) * 2 > kStreamActs;
+}
+
 // H / G row pitch in elements
 inline int rank_pitch(const mux_segtab* st) { return (st->n_lora + st->n_tuning) > 0 ? round_up(st->r_max, 16) : 0; }
 
