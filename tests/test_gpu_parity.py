@@ -384,7 +384,7 @@ def test_every_tile_of_random_row_groups(env, seed):
 @pytest.mark.parametrize("K,N,lens,shared", [
     (64, 64, [1], False), (136, 72, [64, 1, 65, 200], False), (320, 1096, [37, 129, 64, 90], False),       # 64 x 64
     (136, 4104, [37, 129, 64, 90], False), (520, 5000, [63, 128, 1], False),                               # 64 x 128
-    (72, 5000, [200, 130, 90], False), (192, 2304, [256, 700, 1000], False),                               # quarters, halves
+    (72, 5000, [200, 130, 90], False), (192, 2304, [256, 700, 1000], False), (1096, 2304, [256, 700, 1000], False),      # quarters, halves
     (4096, 640, [100, 70, 64], True), (4168, 712, [64, 300, 1], True), (11008, 520, [40], True)])          # shared contraction
 @pytest.mark.parametrize("ranks", [(16, 8), (32, 1), (12, 31)])
 def test_small_launches_form_hs(env, K, N, lens, shared, ranks):
