@@ -68,6 +68,7 @@ struct GemmParams {
   int n_m;                 // row groups with tokens past their first 128 rows
   int n_mh;                // those with tokens in their first 128 rows only
   int half0, clear0;       // first workgroups of the pieces of the latter, and of those that clear the groups without tokens
+  int below;               // and, before these, the rows past the first 128 of the n_mh groups
   int n_n;                 // column tiles
   int items_off;           // word offset in dtab of the row groups' list (DH_OFF_GEMM_ITEMS)
   int Kc, Nc, RP;
@@ -1038,11 +1039,15 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
 }
 
 // A row group without tokens: CLEAR_N columns of its output rows (d: its number times the slabs of CLEAR_N columns, plus the
-// slab), a wave a row, and with the first of them the rows of Hs.
+// slab), a wave a row, and with the first of them the rows of Hs.  With `below`, first the same of the rows past the first 128
+// of the groups that have tokens in those only.
 template <int NTHR>
 __device__ __forceinline__ void clear_group(const GemmParams& p, int d) {
   const int slabs = (p.Nc + CLEAR_N - 1) / CLEAR_N;
-  const int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + p.n_mh + d / slabs) * DI_WORDS);
+  const int g = d / slabs + (p.below ? 0 : p.n_mh), m0 = g < p.n_mh ? 128 : 0;
+  int4 iw = *(const int4*)(p.dtab + p.items_off + (p.n_m + g) * DI_WORDS);
+  iw.y += m0;
+  iw.z -= m0;
   const int c = (d % slabs) * CLEAR_N + (threadIdx.x & 63) * 8;
   if (c < p.Nc)
     for (int m = threadIdx.x >> 6; m < iw.z; m += NTHR / 64) *(uint4*)(p.Out + (size_t)(iw.y + m) * p.Nc + c) = make_uint4(0, 0, 0, 0);
@@ -1156,7 +1161,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p, cons
     int L, half, mhalf;
     if (split >= p.splits) return;
     const bool hg = quarter_of(p, q, L, half, mhalf);
-    gemm_tile<NT, 2, 2, 2, FUSE, false, true, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q, hg && split == 0);
+    gemm_tile<NT, 2, 2, 2, FUSE, false, true, true>(p, hg ? p.n_m : 0, hg ? p.n_mh : p.n_m, L, half, mhalf, sm, split, q, hg && split == 0 && !p.below);
   } else if constexpr (PIECES >= PIECES_64X128) {
     const int id = tile_of_slot(p.n_m * p.n_n, b & 7, b >> 3);
     if (id < 0) return;
@@ -1168,7 +1173,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pieces(const GemmParams p, cons
   } else {
     const Quarter q = quarter_piece(p, b);
     if (q.L < 0) return;
-    gemm_tile<NT, 2, 2, 2, FUSE, false, true>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm, 0, 0, q.hg);
+    gemm_tile<NT, 2, 2, 2, FUSE, false, true>(p, q.hg ? p.n_m : 0, q.hg ? p.n_mh : p.n_m, q.L, q.half, q.mhalf, sm, 0, 0, q.hg && !p.below);
   }
   clock_end(p);
 }
@@ -1459,17 +1464,24 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   p.Part = (float*)c.split;
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");
-  const char* name = NT ? "gemm_nt" : "gemm_nn";
   const adapter::GradParams job = take ? *take : adapter::GradParams{};
   const int n_grads = job.n_items * job.col_blocks;
-  if (n_grads > 0 && (t.n_full != 0 || p.DiffPack != nullptr)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot take the gradients along");
-  const dim3 grid(t.grid + n_grads), block(512);
-  p.grad0 = t.grid;
   const bool tail = Kc % BK != 0;                 // (masked entries are added only where there is none)
   // Halves of a short contraction that carry nothing else: eight waves bring the outputs out in half the time, four walk a long
   // contraction faster.  Forward, eight waves, four: 1024 columns, 4616 tokens, IA3, K = 320 12.1 us, 14.3, 768 17.2, 19.0, 1024 19.8,
   // 21.1, 1536 26.6, 26.2, 2048 31.3, 30.5; LoRA of rank 16 with its down_x, 320 14.6, 16.4, 1024 23.8, 23.8, 1280 28.7, 28.3, 2048 37.1, 34.8.
   const bool eight_waves = t.pieces == PIECES_HALF && Kc <= 1024 && !fuse_down && n_grads == 0;
+  const bool four_waves = t.n_full == 0 && p.DiffPack == nullptr && !eight_waves;
+  // The rows past the first 128 of a group with tokens in those only: where there are units left for it, workgroups of their own
+  // clear them; else the quarters do, behind their first loads.  Thirteen tasks of 41 to 176 tokens aligned to 256, forward,
+  // quarters, own workgroups: 768 x 1280 14.2 us, 13.4, 2048 x 1280 23.5, 22.8; 448 x 10496, three tasks, 246 quarters, 12.2 and 13.3.
+  const int below = t.n_mh * ((Nc + CLEAR_N - 1) / CLEAR_N), pieces = p.splits > 1 ? p.splits * count_quarters(c.st, Nc) : t.clear0;
+  p.below = four_waves && c.st->n_gemm_below > 0 && below > 0 && pieces + below <= compute_units();
+  if (p.below) t.grid += below;
+  const char* name = NT ? "gemm_nt" : "gemm_nn";
+  if (n_grads > 0 && (t.n_full != 0 || p.DiffPack != nullptr)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot take the gradients along");
+  const dim3 grid(t.grid + n_grads), block(512);
+  p.grad0 = t.grid;
   if (p.splits > 1) {
     p.quarters = count_quarters(c.st, Nc);
     p.clear0 = (p.splits * p.quarters + 7) / 8 * 8;
@@ -1490,7 +1502,7 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   }
   if (p.DiffPack != nullptr) {
     MUX_LAUNCH(name, (k_gemm_dma<NT, true, false, false>), grid, block, 0, c.stream, p);
-  } else if (t.n_full == 0 && !eight_waves) {
+  } else if (four_waves) {
     if (t.pieces == PIECES_HALF) launch_pieces<PIECES_HALF, NT>(name, grid, c.stream, p, job);
     else if (t.pieces == PIECES_QUARTER) launch_pieces<PIECES_QUARTER, NT>(name, grid, c.stream, p, job);
     else if (t.pieces == PIECES_64X128) launch_pieces<PIECES_64X128, NT>(name, grid, c.stream, p, job);

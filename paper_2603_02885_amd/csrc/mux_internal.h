@@ -100,6 +100,7 @@ struct mux_segtab {
   // 256-row work items by what the backbone product has to compute of them: those with a real token past their first
   // 128 rows, those with real tokens in the first 128 rows only, those without any
   int32_t n_gemm[3] = {0, 0, 0};
+  int32_t n_gemm_below = 0;         // of the second kind, those of more than 128 rows
   int32_t n_gemm64[2] = {0, 0};     // 64-row work items with a real token, and those without any
 };
 

@@ -258,6 +258,7 @@ extern "C" mux_status mux_segtab_build(const mux_task_desc* tasks, int32_t n_tas
           while (live > 0 && st->row_task[it.row0 + live - 1] < 0) --live;
           if ((live > 128 ? 0 : live > 0 ? 1 : 2) != cls) continue;
           st->n_gemm[cls]++;
+          if (cls == 1 && it.nrows > 128) st->n_gemm_below++;
           const int32_t w[DI_WORDS] = {it.task, it.row0, it.nrows, live};
           dv.insert(dv.end(), w, w + DI_WORDS);
         }

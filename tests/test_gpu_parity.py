@@ -235,6 +235,21 @@ def test_gradients_ride_where_units_idle(env, n, rides):
         assert ("grad_da" not in names) == rides, names
 
 
+@pytest.mark.parametrize("K,N,n", [(136, 1304, 13), (136, 1304, 25), (4168, 264, 5), (2056, 136, 30)])
+@pytest.mark.parametrize("kind", [wlm.KIND_LORA, wlm.KIND_IA3])
+def test_rows_below_few_tokens(env, K, N, n, kind):
+    """Row groups of 256 with tokens in their first 128 rows only, and groups without any: the rows without tokens are cleared by
+    workgroups of their own where units are left, else by the quarters above them, in whole and in shared contractions, with
+    the rows of the saved Hs; every buffer starts out as NaN."""
+    mx, torch = env
+    wl = wlm.Workload(name="below", layers=[("w", K, N)], chunk=512, sigma_w=0.05, sigma_ab=0.05,
+                      tasks=[wlm.Task(kind, 8 if kind == wlm.KIND_LORA else 0, 2.0, [1 + 37 * t % 180]) for t in range(n)])
+    g, got, ref, errs = run_case(env, wl, seed=K + n, pad_fill=float("nan"))
+    if kind == wlm.KIND_LORA:
+        Hs = g.saved[:g.T * 32].view(torch.bfloat16).view(g.T, 16)
+        assert torch.isfinite(Hs).all()
+
+
 @pytest.mark.parametrize("K,N,ia3", [(264, 512, 70), (264, 520, 70), (1032, 1032, 513), (72, 8200, 7200)])
 def test_small_jobs_in_the_launch_of_the_gs_sums(env, K, N, ia3):
     """The padded copies of A_t and D_t (ranks 12, 7 and 1) and the IA3 rows behind the sums of Gs, or in launches of their own
