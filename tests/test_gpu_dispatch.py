@@ -63,6 +63,35 @@ def test_gather_scatter_bit_exact(env, width, elem, flags):
             assert torch.isnan(t[:s.shape[0], width:]).all()
 
 
+def test_rows_past_the_caches(env):
+    """More bytes than are read through the caches (112 MB), odd sequence lengths and padding rows: a gather and a scatter,
+    bit by bit against the rows that the table gives."""
+    mx, torch = env
+    width, chunk, dev = 3080, 64, "cuda:0"
+    lens = [[4099, 77, 1], [6001, 333], [2050] * 3, [3001]]
+    st = mx.mux_segtab_build([mx.TaskDesc(mx.MUX_ADAPTER_NONE, 0, 1.0, l) for l in lens], chunk, 0, 0)
+    T = mx.mux_segtab_rows(st)
+    assert T * width * 2 > 112 << 20
+    nb = mx.mux_segtab_device_bytes(st)
+    dtab = torch.zeros(nb, dtype=torch.uint8, device=dev)
+    mx.mux_segtab_upload(st, dtab, nb)
+    gen = torch.Generator(device=dev).manual_seed(5)
+    src = [torch.randint(-2 ** 15, 2 ** 15 - 1, (sum(l), width), device=dev, generator=gen, dtype=torch.int32).to(torch.int16) for l in lens]
+    aligned = torch.full((T, width), -1, dtype=torch.int16, device=dev)
+    print(f"dispatch case: T={T} width={width}", flush=True)
+    mx.mux_dispatch_gather(st, dtab, src, width, aligned, width, width, 2, torch.cuda.current_stream())
+    row_task = torch.from_numpy(np.ascontiguousarray(mx.mux_segtab_row_task(st))).to(dev)
+    torch.cuda.synchronize()
+    for t, s in enumerate(src):
+        assert torch.equal(aligned[row_task == t], s), t
+    assert not aligned[row_task < 0].any()
+    back = [torch.full_like(s, -1) for s in src]
+    mx.mux_dispatch_scatter(st, dtab, aligned, width, back, width, width, 2, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for t, s in enumerate(src):
+        assert torch.equal(back[t], s), t
+
+
 def test_argument_checks(env):
     mx, torch = env
     st = mx.mux_segtab_build([mx.TaskDesc(mx.MUX_ADAPTER_NONE, 0, 1.0, [5])], 16, 0, 0)
