@@ -18,8 +18,10 @@
  *     synchronises.  Argument checks happen on the host before anything is launched; a call
  *     that returns an error has launched nothing.
  *   - Same inputs give bit-identical outputs (no floating-point atomics anywhere): the same layer, table and tensors, on the
- *     same kind of device, with a workspace of at least the size asked for.  How many workgroups share a sum, and so the
- *     order of its terms, follows from the whole batch: a task's results may differ in their last bits between two tables.
+ *     same kind of device, with a workspace of at least the size asked for.  How many workgroups share a sum, and into which
+ *     pieces a backbone product is cut (those of a few small row groups add four interleaved parts of the contraction), follow
+ *     from the whole batch, and with them the order of a sum's terms: a task's results may differ in their last bits between two
+ *     tables.
  *   - Tensors are row-major and dense unless a leading dimension is given.
  *     X[T,K], W[K,N] (Y = X W, the orientation of Eq. 1), Y[T,N], dY[T,N], dX[T,K],
  *     A_t[K,r_t], B_t[r_t,N], l_t[N].  T = mux_segtab_rows().

@@ -5,12 +5,12 @@
  *
  * Environment variables, all read once per process, for measurement and testing only:
  *   MUX_GEMM_NO_HALF_TILES     the backbone product (Eq. 1, Eq. 2) keeps the tiles of the last round whole;
- *   MUX_GEMM_NO_QUARTER_TILES  it splits them into halves where it would take quarters;
+ *   MUX_GEMM_NO_QUARTER_TILES  it splits them into halves where it would take quarters or pieces of row groups of 64;
  *   MUX_GEMM_NO_SPLIT          it never shares the contraction of a few tiles out to several workgroups (nor does it with
  *                              the two above, which leave no launch of nothing but quarters);
  *   MUX_GEMM_FUSE_DOWN=0       the forward never forms Hs = s_t X A_t inside the backbone tile loop (by default it
- *                              does in launches of quarter tiles, LoRA ranks up to 32, no Adapter-Tuning task);
- *                              =2: in launches of half tiles as well.
+ *                              does in launches of quarter tiles and of pieces of row groups of 64, LoRA ranks up to 32, no
+ *                              Adapter-Tuning task); =2: in launches of half tiles as well.
  */
 #ifndef MUX_DIAG_H_
 #define MUX_DIAG_H_

@@ -119,37 +119,51 @@ def test_contraction_tails_and_odd_ranks(env, K, N):
         assert torch.equal(g.Y, y) and torch.equal(g.dX, dx)
 
 
-@pytest.mark.parametrize("K,N,lens", [
-    (264, 512, [100, 256, 1, 129, 64]),      # one column slab, every task one row group: no partials at all
-    (264, 520, [100, 256, 1, 129, 64]),      # two column slabs
-    (264, 72, [700, 30, 1030, 257, 5]),      # one column slab, several row groups
-    (1032, 512, [300, 3, 40, 90, 256])])
+@pytest.mark.parametrize("K,N,chunk,lens,direct", [
+    (264, 512, 64, [100, 256, 1, 129, 64], True),      # one column slab, every task one row group: no partials at all
+    (264, 520, 64, [100, 256, 1, 129, 64], True),      # two column slabs
+    (264, 512, 512, [100, 256, 1, 129, 64], False),    # one column slab, two row groups a task, one of them without tokens
+    (264, 72, 512, [700, 30, 1030, 257, 5], False),    # one column slab, several row groups
+    (1032, 512, 64, [300, 3, 40, 90, 256], False)])    # one task of two row groups
 @pytest.mark.parametrize("ranks", [(16, 3, 8), (32, 20, 16), (64, 33, 12)])
-def test_gradients_without_partials(env, K, N, lens, ranks):
+def test_gradients_without_partials(env, K, N, chunk, lens, direct, ranks):
     """The pass over dY where one column slab is all of it (Gs leaves it scaled, masked and rounded) and where a task is one
     row group (its sums are the gradients), beside the general case; ranks of one, two and four pieces, Adapter-Tuning, a
     scratch memory and padding rows of NaN, row groups without tokens, gradients overwritten and added to."""
     mx, torch = env
     kinds = [(wlm.KIND_LORA, ranks[0]), (wlm.KIND_ADAPTER, ranks[1]), (wlm.KIND_LORA, ranks[2]), (wlm.KIND_IA3, 0), (wlm.KIND_LORA, ranks[1])]
-    wl = wlm.Workload(name="direct", layers=[("w", K, N)], chunk=512, sigma_w=0.05, sigma_ab=0.05,
+    wl = wlm.Workload(name="direct", layers=[("w", K, N)], chunk=chunk, sigma_w=0.05, sigma_ab=0.05,
                       tasks=[wlm.Task(k, r, 2.0, [n]) for (k, r), n in zip(kinds, lens)])
+    wl.tasks = [t for t in wl.tasks if not direct or t.kind != wlm.KIND_IA3]       # (whose sums take the reduction)
     g, got, ref, errs = run_case(env, wl, seed=K + N)
     first = {k: [None if t is None else t.clone() for t in getattr(g, k)] for k in ("dA", "dB", "dL")}
     dx = g.dX.clone()
     pad = torch.from_numpy(np.nonzero(oracle_table(wl).row_task < 0)[0]).to("cuda:0")
     g.X[pad] = float("nan"); g.dY[pad] = float("nan")
     g.ws.view(torch.uint8).fill_(0xFF)
-    g.forward(); g.backward()
-    torch.cuda.synchronize()
-    assert torch.equal(g.dX, dx)
-    for k in first:
-        for a, b in zip(first[k], getattr(g, k)):
-            assert a is None or torch.equal(a, b), k
-    g.backward(accumulate=1)
-    torch.cuda.synchronize()
-    for k in first:
-        for a, b in zip(first[k], getattr(g, k)):
-            assert a is None or torch.equal(b, a + a), k
+    # gradient buffers as allocated, then such that are only 4-byte aligned
+    for off in (0, 1):
+        for k in first:
+            for t, v in enumerate(first[k]):
+                if v is not None and off:
+                    getattr(g, k)[t] = torch.full((v.numel() + 1,), float("nan"), device="cuda:0")[1:].view(v.shape)
+        g.forward()
+        mx.mux_profile_enable(1)
+        mx.mux_profile_collect()
+        g.backward()
+        torch.cuda.synchronize()
+        names = {e["name"] for e in mx.mux_profile_collect()}
+        mx.mux_profile_enable(0)
+        assert ("reduce_grads" not in names) == direct and ("gs_reduce" not in names) == (N <= 512), names
+        assert torch.equal(g.dX, dx)
+        for k in first:
+            for a, b in zip(first[k], getattr(g, k)):
+                assert a is None or torch.equal(a, b), k
+        g.backward(accumulate=1)
+        torch.cuda.synchronize()
+        for k in first:
+            for a, b in zip(first[k], getattr(g, k)):
+                assert a is None or torch.equal(b, a + a), k
 
 
 @pytest.mark.parametrize("K,N,lens", [(256, 256, [100, 150, 40]), (2056, 192, [256, 700, 100]), (640, 4096, [100, 70, 64]),
@@ -457,6 +471,10 @@ def test_small_launches_form_hs(env, K, N, lens, shared, ranks):
             continue
         h, g = 2.0 * (Xf[rows] @ A[t].float()), (2.0 * (dYf[rows] @ B[t].float().t().contiguous())).to(torch.bfloat16).float()
         assert torch.equal(Hs[rows][:, :r].float(), h) and not Hs[rows][:, r:].any(), t
+        # (integers below 2^24: exact sums; products of Gs, rounded, in 64 bits)
+        assert torch.equal(grads[1][t], h.t().contiguous() @ dYf[rows]), t
+        da = X[rows].double().t().contiguous() @ g.double()
+        assert torch.allclose(grads[0][t].double(), da, rtol=0, atol=1e-6 * float(da.abs().max())), t
         want_y[rows] += h @ B[t].float()
         want_dx[rows] += g @ A[t].float().t().contiguous()
     assert torch.equal(Y, want_y.to(torch.bfloat16)), (Y != want_y.to(torch.bfloat16)).nonzero()[:4].tolist()
@@ -657,8 +675,17 @@ def test_nan_isolation(env, which):
 
 def test_dynamic_task_attach(env):
     """A task arriving between calls (section 3.1, register_tasks): a new table and a longer layer
-    description; where no sum is shared out differently the tasks already there get bit-identical results."""
+    description; where the backbone products keep their kind of pieces and share no sum out differently, the tasks already there
+    get bit-identical results."""
     check_attach(env, mixed_workload(), wlm.Task(wlm.KIND_LORA, 12, 1.0, [40, 40]), same_bits=True)
+
+
+def test_dynamic_task_attach_other_pieces(env):
+    """The same where the new task takes a launch from pieces of row groups of 64 (165 of 64 x 128) to quarters (238): the four
+    waves of the former sum a quarter of the contraction each.  The other tasks' results stay the same to rounding."""
+    tasks = [wlm.Task(wlm.KIND_NONE, 0, 1.0, [100]), wlm.Task(wlm.KIND_IA3, 0, 1.0, [70]), wlm.Task(wlm.KIND_LORA, 16, 2.0, [64])]
+    wl = wlm.Workload(name="attach64", layers=[("w", 136, 4104)], tasks=tasks, chunk=64, sigma_w=0.05, sigma_ab=0.05)
+    check_attach(env, wl, wlm.Task(wlm.KIND_LORA, 16, 1.0, [300, 140]), same_bits=False)
 
 
 def test_dynamic_task_attach_shared_contraction(env):
