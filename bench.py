@@ -743,6 +743,12 @@ def main():
         step(mx, st, dtab, layers, ws, ws_bytes, stream)
     torch.cuda.synchronize()
     prof_all = mx.mux_profile_collect()
+    # and every projection once by itself: which kernels it launches (small jobs ride in other launches where that pays)
+    layer_kernels = []
+    for L in layers:
+        step(mx, st, dtab, [L], ws, ws_bytes, stream)
+        torch.cuda.synchronize()
+        layer_kernels.append({e["name"] for e in mx.mux_profile_collect()})
     mx.mux_profile_enable(0)
 
     ms_per_step = (t1 - t0) * 1e3 / args.steps
@@ -768,10 +774,14 @@ def main():
     done_tr = sum(done[t] * wl.tasks[t].rank for t in range(M) if wl.tasks[t].kind == 1)
     flops_backbone = 4.0 * T_done * sumKN
     flops_adapter = 6.0 * sum_tr * sum(K + N for _, K, N in wl.layers) + 12.0 * sum_tune * sum(N for _, K, N in wl.layers)
-    gemm_flops = {  # per step, per kernel family (all layers): 2TKN + 2 sum T_t r_t N (fwd) / K (bwd) over those rows
-        "gemm_nn": 2.0 * T_done * sumKN + 2.0 * done_tr * sum(N for _, K, N in wl.layers),
-        "gemm_nt": 2.0 * T_done * sumKN + 2.0 * done_tr * sum(K for _, K, N in wl.layers),
-    }
+    # per step, per kernel family: 2TKN + 2 sum T_t r_t N (fwd) / K (bwd) over those rows, of the layers that launch it; the
+    # backward product with dA_t in its launch has that gradient's products besides (over the real tokens)
+    grad_flops = [sum(2.0 * int(img[16 + 8 * t + 2]) * wl.tasks[t].rank * (K if wl.tasks[t].kind == 1 else N)
+                      for t in range(M) if wl.tasks[t].kind in (1, 3)) for _, K, N in wl.layers]
+    gemm_flops = {"gemm_nn": 2.0 * T_done * sumKN + 2.0 * done_tr * sum(N for _, K, N in wl.layers)}
+    for name in ("gemm_nt", "gemm_nt_da"):
+        gemm_flops[name] = sum(2.0 * T_done * K * N + 2.0 * done_tr * K + (f if name == "gemm_nt_da" else 0.0)
+                               for (_, K, N), f, ks in zip(wl.layers, grad_flops, layer_kernels) if name in ks)
     kernels = {}
     for e in prof_all:      # every kernel, from the extra steps after the timed region
         kernels[e["name"]] = {"launches": e["launches"], "avg_us": e["total_ms"] * 1e3 / max(e["launches"], 1),
@@ -800,8 +810,9 @@ def main():
         # one pass over dY: Gs and dB_t together (reads Hs, writes Gs and the fp32 dB_t)
         "s4_dy_pass": sum(2.0 * v_rank * N + 2.0 * N * sum_r13 + 2.0 * v_rank * RP + 2.0 * T * RP + 4.0 * N * sum_r13 for K, N in dims),
         "grad_dbda": sum(2.0 * v_rank * (N + K) + 4.0 * v_rank * RP + 4.0 * (N + K) * sum_r13 for K, N in dims),
-        "grad_da": sum(2.0 * v_rank * K + 2.0 * v_rank * RP + 4.0 * K * sum_r13 for K, N in dims),
-        "grad_dl": sum(4.0 * v_ia3 * N + 4.0 * N * sum(1 for k in kinds if k == 2) for K, N in dims),
+        # (of the layers where they have launches of their own)
+        "grad_da": sum(2.0 * v_rank * K + 2.0 * v_rank * RP + 4.0 * K * sum_r13 for (K, N), ks in zip(dims, layer_kernels) if "grad_da" in ks),
+        "grad_dl": sum(4.0 * v_ia3 * N + 4.0 * N * sum(1 for k in kinds if k == 2) for (K, N), ks in zip(dims, layer_kernels) if "grad_dl" in ks),
         # Adapter-Tuning steps: each streams the task's rows of z, dY or both once
         "tune_down": sum(2.0 * v_tune * N for K, N in dims),
         "tune_up": sum(4.0 * v_tune * N for K, N in dims),
@@ -863,7 +874,9 @@ def main():
             f = line.split()
             if len(f) == 3 and f[0] == "traffic_bytes_per_launch" and f[1] == dom:
                 roofline["traffic"] = float(f[2])
-                roofline["algorithmic_bytes_per_launch"] = sum(2.0 * (T * K + K * N + T * N) for _, K, N in wl.layers) / len(wl.layers)
+                roofline["algorithmic_bytes_per_launch"] = sum(
+                    2.0 * (T * K + K * N + T * N) for (_, K, N), ks in zip(wl.layers, layer_kernels) if dom in ks) / max(
+                        1, sum(dom in ks for ks in layer_kernels))
     for n in gemm_names:
         kernels[n]["tflops"] = gemm_flops[n] / (kernels[n]["total_ms_per_step"] * 1e-3) / 1e12
         kernels[n]["frac_of_bf16_mfma_peak"] = kernels[n]["tflops"] / PEAK_BF16_MFMA

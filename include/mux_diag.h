@@ -28,7 +28,8 @@ extern "C" {
  * mux_profile_collect waits for the recorded events, fills up to `cap` entries with one line
  * per kernel (name, number of launches, summed duration in milliseconds; for the kernels that only bring partial
  * sums together or write the task table -- the method itself asks for none of their bytes -- the bytes they moved
- * as the library counts them at the launch, else 0), returns the number
+ * as the library counts them at the launch, with those of the small jobs that ride along, else 0; a backbone product with
+ * dA_t in its launch goes under a name of its own, gemm_nt_da), returns the number
  * of distinct kernels in *n, and clears the record.  Process-wide, not thread-safe; leave it
  * disabled under HIP graph capture. */
 typedef struct {

@@ -985,8 +985,13 @@ mux_status adapter_dy_pass(const CallCtx& c, const void* dY, const void* Hs, con
   double moved = (double)c.st->T * c.RP * 2;
   for (const HostTask& ht : c.st->tasks)
     if (ht.kind == MUX_ADAPTER_LORA || ht.kind == MUX_ADAPTER_TUNING) moved += (double)slabs * ht.valid * round_up(ht.rank, 4) * 4;
-  prof_note_bytes(moved);
   const bool dl = dl_rides_along(c);
+  // and what rides along: the IA3 rows of dY and of the saved x W in, their scaled copies and the partial sums out; A_t in, its copy out
+  for (const HostTask& ht : c.st->tasks) {
+    if (dl && ht.kind == MUX_ADAPTER_IA3_OUT) moved += 6.0 * ht.valid * c.N + 4.0 * c.N * ((ht.row_count + 63) / 64);
+    if (rank_is_padded(ht)) moved += 2.0 * (ht.rank + round_up(ht.rank, 8)) * (ht.kind == MUX_ADAPTER_LORA ? c.K : c.N);
+  }
+  prof_note_bytes(moved);
   const unsigned items = (unsigned)c.st->items[TS64].size(), threads = dl ? 512 : 256;
   const unsigned n_pad = (unsigned)((padded_pieces(c) + threads - 1) / threads), n_dl = dl ? (unsigned)dl_blocks(c.N) : 0;
   auto reduce = [&](auto DL) {

@@ -1478,7 +1478,7 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   const int below = t.n_mh * ((Nc + CLEAR_N - 1) / CLEAR_N), pieces = p.splits > 1 ? p.splits * count_quarters(c.st, Nc) : t.clear0;
   p.below = four_waves && c.st->n_gemm_below > 0 && below > 0 && pieces + below <= compute_units();
   if (p.below) t.grid += below;
-  const char* name = NT ? "gemm_nt" : "gemm_nn";
+  const char* name = NT ? (n_grads > 0 ? "gemm_nt_da" : "gemm_nt") : "gemm_nn";
   if (n_grads > 0 && (t.n_full != 0 || p.DiffPack != nullptr)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot take the gradients along");
   const dim3 grid(t.grid + n_grads), block(512);
   p.grad0 = t.grid;
