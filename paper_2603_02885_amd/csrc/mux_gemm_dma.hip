@@ -40,10 +40,12 @@
 namespace mux {
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+using adapter::bf16x4;
+using adapter::bf16x8;
+using adapter::lds_read_tr;
+using adapter::OOB;
+using adapter::u32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
 constexpr int BM = 256;
@@ -53,7 +55,6 @@ constexpr int TILE_N = 256;                     // width of a tile in the launch
 // them: 2048 columns, 1 MB a workgroup, did (704 x 2496, two tasks of 88 and 62 tokens aligned to 512, forward 13.0 us so, 12.7
 // now).
 constexpr int CLEAR_N = 512;
-constexpr uint32_t OOB = 0x80000000u;
 // Bytes of an output, and of it and the activations that it is formed from, beyond which it is written past the caches
 constexpr size_t kStreamOut = (size_t)64 << 20, kStreamBoth = (size_t)144 << 20;
 
@@ -116,9 +117,6 @@ __device__ __forceinline__ void dma4(rsrc_t r, uint32_t lds_addr, uint32_t byte_
                :
                : "s"(lds_addr), "v"(byte_off), "s"(r)
                : "m0");
-}
-__device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)p);
 }
 // s_waitcnt vmcnt(n) only (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14])
 template <int N>
@@ -206,7 +204,7 @@ __device__ __forceinline__ bool quarter_of(const GemmParams& p, int q, int& L, i
 // the column piece.
 // FUSE (forward, pieces): the down-projection Hs = s_t X A_t of the tile's rows is
 // computed in the same K loop -- the [64][rank] slab of A_t of every K-tile is staged beside the tile of W, the two waves
-// of a row half multiply it with the X fragments of half of its row blocks each (of the one it has, both) -- and goes, scaled and
+// of a row half multiply it with the X fragments of half of its row blocks each (MI = 1: each wave its step) -- and goes, scaled and
 // rounded to bf16, straight into the A side of the adapter K-tile (and, from the tiles of the first column, to
 // memory for the backward): no separate pass over X, no launch for it.  Every column tile redoes the product for
 // its rows, which is why this is for launches that do not fill the compute units anyway.
@@ -235,6 +233,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
   constexpr int BN = WNW * NI * 32;
   constexpr int BMT = 2 * MI * 32;
   constexpr bool PIECE = WNW == 2, ROW64 = MI == 1;
+  static_assert(KS == ROW64, "row groups of 64: one wave a step");
   // LDS stages.  A stage of a full or half tile takes 64 or 48 KB: two of 64 KB fit.  A piece's takes less and has less
   // MFMA time, which is below the latency of the loads: as many stages as there is room for, so many tiles less one in flight.
   constexpr int NST = PIECE ? piece_stages(MI, NI, FUSE, DIFFP) : 2;
@@ -662,7 +661,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     // Bound by the direct-to-LDS loads, about 24 cycles for each 1 KB instruction of a compute unit, whatever their depth
     // (a stage less changes nothing) and place in the loop: 0.27 us a K-tile of 64 x 128 (the loads alone 0.27, the rest
     // 0.15), 0.175 of 64 x 64 (0.165 and 0.10), 0.335 of 128 x 128.
-    static_assert(MI == 1, "row groups of 64");
     constexpr int NSLOT = 4 * MI * NI, RT = 2 * (MI + NI), HW = 2 * MI;
     f32x16 accf[2 * MI][2 * NI], haccf[FUSE ? HW : 1];
 #pragma unroll
@@ -939,8 +937,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, const int item0, 
     const bf16_t* hB = stB(sK);
 #pragma unroll
     for (int i = 0; i < HB; ++i) {
-      if (MI == 1 && wn != 0) break;                // (both waves of a row half hold its only block)
-      const int row_l = wm * (32 * MI) + (MI == 1 ? 0 : (wn * HB + i) * 32) + li;
+      const int row_l = wm * (32 * MI) + (wn * HB + i) * 32 + li;
       const bool keep = row_l < nrows && sRow[row_l] != 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
