@@ -1528,10 +1528,14 @@ bool gemm_dma_supported(const CallCtx& c) {
 }
 
 // Can the forward of this call form Hs = s_t X A_t inside the backbone tile loop?  The kernel can when the launch is
-// made of half or quarter tiles only, with LoRA ranks up to 32 and no Adapter-Tuning task.  It is chosen for launches of quarter tiles (at most a quarter of the compute
-// units' worth of 256 x 256 tiles): there the loop waits on loads, the extra product per step costs about 0.13 us per
-// 64 of K, and the launch it saves costs 9 to 25 us; in launches of half tiles the extra product costs more than the
-// launch (measured 4 to 13 % slower).  MUX_GEMM_FUSE_DOWN (read once): 0 never, 2 in launches of half tiles as well.
+// made of pieces only, with LoRA ranks up to 32 and no Adapter-Tuning task.  It is chosen for launches of quarters and of pieces of
+// row groups of 64 (at most a quarter of the compute units' worth of 256 x 256 tiles): there the loop waits on loads, and the launch
+// that it saves costs more than the extra product; not in launches of halves.  Forward, four LoRA tasks of rank 16, separate and
+// fused, six layers in turn (their weights come from memory): 4096 x 4096, 128 tokens 29.5 us, 23.3, 512 40.8, 36.9, 1024 51.3, 51.7;
+// 2560 x 2560, 512 25.6, 20.5; 11008 x 4096, 512 89.0, 72.5, 1024 130.2, 119.3; 8192 x 1024, 2048 68.8, 58.6; halves: 4096 x 4096, 1536
+// 64.3, 73.5; 2560 x 2560, 1536 32.3, 33.0; 11008 x 4096, 2048 170.8, 195.8.  One layer over and over, its weights in the last-level cache,
+// loses where the quarters fill the units: 4096 x 4096, 1024 44.0, 48.8; 11008 x 4096, 1024 98.2, 114.7.
+// MUX_GEMM_FUSE_DOWN (read once): 0 never, 2 in launches of halves as well.
 bool gemm_dma_fuses_down(const CallCtx& c) {
   static const int mode = [] { const char* e = getenv("MUX_GEMM_FUSE_DOWN"); return e == nullptr ? 1 : atoi(e); }();
   if (mode == 0) return false;
