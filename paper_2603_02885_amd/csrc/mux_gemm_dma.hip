@@ -57,6 +57,7 @@ constexpr int TILE_N = 256;                     // width of a tile in the launch
 constexpr int CLEAR_N = 512;
 // Bytes of an output, and of it and the activations that it is formed from, beyond which it is written past the caches
 constexpr size_t kStreamOut = (size_t)64 << 20, kStreamBoth = (size_t)144 << 20;
+constexpr int kStreamDepth = 512;               // contraction up to which the former alone decides
 
 // A workgroup reads these one after the other as it finds out what it computes, from lines of 64 bytes that are cold at the
 // start of a launch: what it needs first lies in the first line, what comes next in the second.  (Spread over three lines,
@@ -1451,13 +1452,17 @@ mux_status launch(const CallCtx& c, const bf16_t* Ain, const bf16_t* Ext, bf16_t
   // forward and backward, through the caches and past them (MB of the two activations): 4096 and 11008 columns (32, 86) 1259 and
   // 1271 us, 2048 and 5504 (32, 85) 720 and 731, 4096 and 4096 (64, 64) 1101 and 1106, (70, 70) 1134 and 1143; 3072 and 3072
   // (80, 80) 1062 and 1053, 4096 and 2048 (102, 51) 917 and 903, 2560 and 2560 (88, 88) 991 and 970, 4096 and 4096 (125, 125)
-  // 1949 and 1921, 5120 and 5120 (176, 176) 3346 and 3288.  Lines that tiles share (6424 columns) would be written twice.  Not the
+  // 1949 and 1921, 5120 and 5120 (176, 176) 3346 and 3288.  Behind a contraction of up to 512 an output goes past them from kStreamOut on:
+  // such a launch is bound by what it writes, and crowds its operands out of the L2s.  Six projections in a row, 448 and 8384 columns, 4096
+  // tokens (4, 69), forward and backward, through the caches and past them: LoRA 879 and 861 us, IA3 919 and 855, no adapter 589 and 554;
+  // 256 and 8384 714 and 689, 755 and 706, 456 and 416; 640 and 8384, 6144 tokens, 1450 and 1461, 1490 and 1471, 1095 and 1137; 1280 and
+  // 8384, 4096, 1456 and 1474, 1431 and 1449, 1146 and 1219.  Lines that tiles share (6424 columns) would be written twice.  Not the
   // forward of a batch of Adapter-Tuning for the most part: it writes x W, which the next two launches read (9000 tokens of rank
   // 64, 4096 x 4096, tune_down 40.3 us past the caches, 31.5 through them).
   const size_t out_bytes = (size_t)c.st->T * Nc * 2, in_bytes = (size_t)c.st->T * Kc * 2;
   int64_t tuning = 0;
   for (const HostTask& ht : c.st->tasks) tuning += !NT && ht.kind == MUX_ADAPTER_TUNING ? ht.row_count : 0;
-  const bool stream = out_bytes >= kStreamOut && out_bytes + in_bytes > kStreamBoth && 2 * tuning <= c.st->T && Nc % 64 == 0;
+  const bool stream = out_bytes >= kStreamOut && (Kc <= kStreamDepth || out_bytes + in_bytes > kStreamBoth) && 2 * tuning <= c.st->T && Nc % 64 == 0;
   p.Part = (float*)c.split;
   if (fuse_down && (NT || t.n_full != 0)) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot carry the down-projection");
   if (p.DiffPack != nullptr && fuse_down) return fail(MUX_ERR_UNSUPPORTED, "gemm: this launch cannot add masked entries in the tile loop");

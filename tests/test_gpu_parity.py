@@ -410,6 +410,57 @@ def test_every_tile_of_random_row_groups(env, seed):
             assert torch.equal(got, want), (case, (got != want).nonzero()[:4].tolist())
 
 
+@pytest.mark.parametrize("K,N,rows", [(512, 8192, 4096), (512, 8192, 4032), (456, 8192, 4096), (576, 8192, 4096), (576, 8192, 9216),
+                                      (8192, 448, 4096), (8192, 520, 4160)])
+def test_outputs_past_the_caches(env, K, N, rows):
+    """Outputs around 64 MB, from which on they are written past the caches behind a contraction of up to 512 (with a tail and
+    without) and, with the input, beyond 144 MB behind a longer one; forward and backward, a LoRA, an IA3 and a plain task, padding rows
+    of NaN.  Small integers: exact in any order."""
+    mx, torch = env
+    dev = "cuda:0"
+    kinds = [(wlm.KIND_LORA, 16), (wlm.KIND_IA3, 0), (wlm.KIND_NONE, 0)]
+    lens = [rows // 2 - 1, rows // 4, rows // 4 - 3]
+    st = mx.mux_segtab_build([mx.TaskDesc(k, r, 2.0, [n]) for (k, r), n in zip(kinds, lens)], 16)
+    nb, T = mx.mux_segtab_device_bytes(st), mx.mux_segtab_rows(st)
+    assert T == rows
+    dtab = torch.empty(nb, dtype=torch.uint8, device=dev)
+    mx.mux_segtab_upload(st, dtab, nb)
+    gen = torch.Generator(device=dev).manual_seed(K + N + rows)
+    ints = lambda *shape: torch.randint(-1, 2, shape, device=dev, generator=gen).to(torch.bfloat16)          # noqa: E731
+    row_task = torch.from_numpy(np.ascontiguousarray(mx.mux_segtab_row_task(st))).to(dev)
+    X, W, dY, l = ints(T, K), ints(K, N), ints(T, N), 1 + ints(N).abs()
+    X[row_task < 0] = float("nan")
+    dY[row_task < 0] = float("nan")
+    a, b = torch.zeros(K, 16, dtype=torch.bfloat16, device=dev), ints(16, N)
+    a[torch.randperm(K, device=dev, generator=gen)[:40]] = ints(40, 16)                # |s X A| <= 80
+    layer = mx.LayerDesc(K, N, mx.MUX_DT_BF16, W, 3, [a, None, None], [b, None, None], [None, l, None])
+    ws_bytes = mx.mux_lora_workspace_bytes(layer, st)
+    ws = torch.full((max(ws_bytes, 256),), 0xFF, dtype=torch.uint8, device=dev)
+    saved = torch.full((mx.mux_lora_saved_bytes(layer, st),), 0xFF, dtype=torch.uint8, device=dev)
+    Y, dX = (torch.full((T, w), float("nan"), dtype=torch.bfloat16, device=dev) for w in (N, K))
+    dA, dB, dL = torch.empty(K, 16, device=dev), torch.empty(16, N, device=dev), torch.empty(N, device=dev)
+    print(f"K={K} N={N} rows={rows}", flush=True)
+    stream = torch.cuda.current_stream()
+    mx.mux_lora_forward(layer, st, dtab, X, Y, saved, ws, ws_bytes, stream)
+    mx.mux_lora_backward(layer, st, dtab, X, dY, saved, dX, [dA, None, None], [dB, None, None], [None, dL, None], 0, ws, ws_bytes, stream)
+    valid = (row_task >= 0)[:, None]
+    zero = torch.zeros((), device=dev)
+    Xf, dYf = torch.where(valid, X.float(), zero), torch.where(valid, dY.float(), zero)
+    r0, r1 = row_task == 0, row_task == 1
+    z = Xf @ W.float()
+    want_y = z.clone()
+    want_y[r1] *= l.float()
+    want_y[r0] += 2.0 * (Xf[r0] @ a.float()) @ b.float()
+    assert torch.equal(Y, want_y.to(torch.bfloat16))
+    gs = (2.0 * (dYf[r0] @ b.float().t().contiguous())).to(torch.bfloat16).float()
+    dYf[r1] *= l.float()
+    want_dx = dYf @ W.float().t().contiguous()
+    want_dx[r0] += gs @ a.float().t().contiguous()
+    assert torch.equal(dX, want_dx.to(torch.bfloat16))
+    want_dl = (torch.where(valid, dY.double(), zero.double())[r1] * z[r1].to(torch.bfloat16).double()).sum(0)
+    assert torch.equal(dL.double(), want_dl)                  # integers, the saved x W rounded to bf16: sums below 2^24
+
+
 @pytest.mark.parametrize("K,N,lens,shared", [
     (64, 64, [1], False), (136, 72, [64, 1, 65, 200], False), (320, 1096, [37, 129, 64, 90], False),       # 64 x 64
     (136, 4104, [37, 129, 64, 90], False), (520, 5000, [63, 128, 1], False),                               # 64 x 128
